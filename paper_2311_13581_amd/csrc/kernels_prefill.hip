@@ -4,25 +4,18 @@
 // of tokens pushed through them re-reads the model dozens of times and leaves the matrix cores
 // idle.  Here up to 2048 prompt rows go through each layer in one pass:
 //
-//   gemm_tile_kernel   a workgroup of 4 wavefronts computes 256 (or 128, 64) output features x 64
-//                      rows.  The activation tile of a k-step (rows x 32 features, as (hi, lo)
-//                      pairs) is staged once in LDS and read by all wavefronts; every
-//                      wavefront streams the weight tiles of its own strips straight into
-//                      registers, three k-steps ahead.  Accumulators (128 registers per lane)
-//                      stay in the register file for the whole K loop: no split of K, one fixed
-//                      summation order.  Same operand formats and the same fused epilogues as the
-//                      decode GEMM (RMSNorm scale, rotary embedding and K/V page writes, SiLU * up,
-//                      residual add with (hi, lo) of the next norm's input).
+//   gemm_tile_kernel   a workgroup of eight wavefronts computes 256 x 128 (or 256 x 256, 384 x 128) output features x
+//                      rows; both operands stream from memory straight into a ring of LDS stages.  Accumulators
+//                      stay in the register file for the whole K loop, one fixed summation order.  Same operand
+//                      formats and the same fused epilogues as the decode GEMM (RMSNorm scale, rotary embedding and
+//                      K/V page writes, SiLU * up, residual add with (hi, lo) of the next norm's input).  Where the
+//                      tiles would leave compute units idle, K is cut into slices whose sums tile_reduce_kernel adds.
 //   attn_prefill_kernel causal attention of a block of 32 (or 16) query rows of one head over the
 //                      paged cache, without a split of the keys across workgroups: the four
 //                      wavefronts take alternate 32-key steps and merge once at the end.  K and V
 //                      tiles are used for all row groups of the block.
 //   attn_prefill_shared_kernel  the same for passes of more than 512 rows: 128 rows per workgroup,
 //                      the K and V tiles of a step fetched once into LDS for all four wavefronts.
-//
-// Workgroup -> tile mapping: consecutive workgroup ids go to different dies (XCDs), each with its
-// own L2.  The 64 workgroups a die holds at a time are given a block of 8 x 8 tiles, so a weight
-// tile and an activation tile fetched into that L2 are each used by 8 workgroups.
 #include "pass_internal.h"
 
 namespace pass {
@@ -42,65 +35,187 @@ __device__ __forceinline__ float other_half(float v) { return dpp_mov<0x128>(v);
 
 template <int I> struct ic { static constexpr int value = I; };
 
-enum { TILE_QKV = 0, TILE_RESID = 1, TILE_GATEUP = 2 };
+enum { TILE_QKV = 0, TILE_RESID = 1, TILE_GATEUP = 2, TILE_PART = 3 };
 
 struct TileArgs {
   const u32x4 *W;             // packed weight tiles [strip][K/32][64 lanes]
-  const uint16_t *X;          // activation rows as (hi, lo) tiles [ceil(M/8)][K/32][64 lanes][8]
+  const u32x4 *X;             // activation rows as (hi, lo) tiles [ceil(M/8)][K/32][64 lanes][8]
   int M, K, n_strips;
   int layer;
   const uint16_t *gain_next;  // RESID: gain of the norm that follows
   PrefillSegs segs;           // QKV: whose rows these are (K/V go to that sequence's pages)
   int tiles_m, tiles_n;
-  int blk_n, blk_m, blocks_m, n_blocks;  // blocks of tiles, one per die at a time
+  int panel;                  // row tiles of a panel: tiles are walked panel by panel, features outside, rows inside
+  int slices, kt_slice;       // PART: slices of K and k-steps of each
+  float *part;                // PART: [slice][M][16 * n_strips] sums over a slice of K
 };
 
-constexpr int kTileStrips = 4;  // strips of 16 features per wavefront (fewer when the tiles would not fill the chip)
+// Copy of 64 x 16 bytes from memory (one address per lane) to 1 KB of LDS (wavefront-uniform), past the register
+// file: a compute unit draws 59 B per clock out of its die's L2 this way, through registers it draws 36 (measured
+// with all units on a 1 MB buffer).  In assembly because the compiler, which cannot tell the stages of a ring of
+// buffers apart, would wait for every copy in flight before each LDS read; it has no register result.  The copies
+// of a wavefront complete in order; wait_copies<N> leaves the youngest N in flight.
+__device__ __forceinline__ void copy_to_lds(const u32x4 *src, u32x4 *dst) {
+  const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+__device__ __forceinline__ void wait_lds_reads() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+// the workgroup meets; neither the compiler nor the instruction scheduler moves memory accesses across
+__device__ __forceinline__ void meet() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
 
-// MG = 8-row groups per workgroup tile (rows = 8 * MG).
-// Two wavefronts per SIMD (256 registers each): above that budget the compiler moves the
-// accumulators to AGPRs and, the MFMA then not being tied to its accumulator, permutes them
-// every trip with hundreds of register copies.
-// SW = strips of 16 features per wavefront: the tile is 64 * SW features x 8 * MG rows.
-template <int EPI, int MG, int SW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tile_kernel(Params p, PrefillWs w, TileArgs a) {
-  constexpr int NT = 256;
-  constexpr int ROWS = MG * 8;
-  constexpr bool NORM = (EPI != TILE_RESID);
-  constexpr int BL = MG / 4;  // 16-byte chunks of the activation tile each thread stages per k-step
-  __shared__ u32x4 sB[2][MG][64];
-  __shared__ float s_inv[ROWS];
-  __shared__ float s_part[NT];
+// What becomes of four consecutive output features n .. n + 3 (n % 4 == 0) of row m, `inv` = 1 / rms of the row.
+__device__ __forceinline__ void finish_qkv(const Params &p, const PrefillWs &w, const TileArgs &a, int m, int n, floatx4 v) {
+  const int which = n / p.D;        // 0 q, 1 k, 2 v
+  const int c = n - which * p.D;    // column inside the projection
+  const int head = c / p.hd, dim = c - head * p.hd;
+  if (which < 2) {
+    const int half = p.hd / 2;
+    const float *cs = p.rope_cos + (size_t)m * half + dim / 2;
+    const float *sn = p.rope_sin + (size_t)m * half + dim / 2;
+    const float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
+    v[0] = x0 * cs[0] - x1 * sn[0];
+    v[1] = x0 * sn[0] + x1 * cs[0];
+    v[2] = x2 * cs[1] - x3 * sn[1];
+    v[3] = x2 * sn[1] + x3 * cs[1];
+  }
+  if (which == 0) {
+    *(floatx4 *)(w.q + (size_t)m * p.D + c) = v;
+    return;
+  }
+  // K rows [page][head][pos][dim], V pages transposed [page][head][dim][pos]; bf16 storage
+  // (the rows of a 16-row group share a block: the index is uniform over the wavefront)
+  const int sb = __builtin_amdgcn_readfirstlane(m / kPrefillBlockRows), sr = m % kPrefillBlockRows;
+  if (sr >= a.segs.rows[sb]) return;  // a padding row: nothing to cache
+  const int pos = a.segs.pos[sb] + sr;
+  const int page = p.block_table[(size_t)a.segs.slot[sb] * p.pages_per_seq + (pos >> p.page_shift)];
+  const size_t hbase = ((size_t)a.layer * p.n_pages + page) * p.H + head;
+  const int off = pos & (p.page_size - 1);
+  if (which == 1) {
+    uint2 pk;
+    pk.x = pack2_bf16(v[0], v[1]);
+    pk.y = pack2_bf16(v[2], v[3]);
+    *(uint2 *)((uint16_t *)p.k_pool + (hbase * p.page_size + off) * p.hd + dim) = pk;
+  } else {
+    uint16_t *vp = (uint16_t *)p.v_pool + (hbase * p.hd + dim) * p.page_size + off;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) vp[(size_t)r * p.page_size] = f32_to_bf16(v[r]);
+  }
+}
+// residual add, (hi, lo) of h * gain of the next norm; returns the four features' share of sum h^2
+__device__ __forceinline__ float finish_resid(const Params &p, const uint16_t *gain_next, int m, int n, floatx4 y) {
+  float *hp = p.h + (size_t)m * p.d + n;
+  const floatx4 hv = *(floatx4 *)hp + y;
+  *(floatx4 *)hp = hv;
+  float tv[4], ss = 0.f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    tv[r] = hv[r] * bf16_to_f32(gain_next[n + r]);
+    ss += hv[r] * hv[r];
+  }
+  store_split4(p.xg, m, p.d, n, tv);
+  return ss;
+}
+// silu(gate) * up of FFN features f .. f + 3
+__device__ __forceinline__ void finish_gateup(const Params &p, int m, int f, floatx4 yg, floatx4 yu, float inv) {
+  float tv[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float gt = yg[r] * inv, up = yu[r] * inv;
+    tv[r] = gt / (1.0f + __expf(-gt)) * up;
+  }
+  store_split4(p.act_x, m, p.F, f, tv);
+}
 
-  // tile of this workgroup (see the note on dies at the top): the `per` workgroups that one die
-  // holds at a time form a block of blk_n x blk_m tiles
-  const int per = a.blk_n * a.blk_m;
-  const int loc = blockIdx.x >> 3;
-  const int block = (loc / per) * 8 + (blockIdx.x & 7), within = loc % per;
-  if (block >= a.n_blocks) return;
-  const int tn = (block / a.blocks_m) * a.blk_n + within / a.blk_m;
-  const int tm = (block % a.blocks_m) * a.blk_m + within % a.blk_m;
-  if (tn >= a.tiles_n || tm >= a.tiles_m) return;
+// The tiled GEMM.  Y[rows][features] += W . X over k-steps of 32; a workgroup of eight wavefronts owns 16 * WF * SW
+// features x 16 * WR * RG rows, a wavefront SW strips of 16 features x RG groups of 16 rows.
+// Both operands of a k-step go straight from memory to LDS, into a ring of three stages, two steps ahead of their
+// use.  The (hi, lo) halves of an activation row are two B operands of one accumulator (a weight fragment is read
+// once for both), so a k-step is 2 * SW * RG MFMAs per wavefront.
+// The wavefronts form two groups, one wavefront of each group per SIMD, that alternate: while one group reads the
+// fragments of its next k-step out of LDS and requests a later stage, the other keeps the matrix cores busy; the
+// workgroup meets after every half step.  Timeline of half steps: group 0 reads step t in 2t and multiplies in
+// 2t + 1, group 1 reads it in 2t + 1 and multiplies in 2t + 2.  A stage is overwritten by requests issued two half
+// steps after group 0's reads (one after group 1's) have returned; its copies have landed, in every wavefront, at
+// the meeting before group 0 reads it (each group waits for its own at the end of half step 2t - 1).
+// Bound by power: at 2047 x 12288 x 4096 the matrix cores are busy 76 % of the cycles at the 1.8 GHz the chip then
+// holds.  Against a form that kept weight fragments in registers, staged the activations through registers and gave
+// hi and lo columns accumulators of their own (4 wavefronts, 256 x 64 tiles): QKV 363 -> 283 us, Wo 124 -> 97,
+// gate/up 633 -> 590, down 326 -> 247 (7B shapes, 2047 rows).
+template <int EPI, int WF, int WR, int SW, int RG>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tile_kernel(Params p, PrefillWs w, TileArgs a) {
+  constexpr int TS = WF * SW, TG = WR * RG;         // strips and 16-row groups of the tile
+  constexpr int NA = TS / 8, NB = TG * 2 / 8;       // 1 KB copies of a wavefront per step
+  constexpr int ROWS = TG * 16;
+  constexpr bool NORM = (EPI == TILE_QKV || EPI == TILE_GATEUP);
+  static_assert(WF * WR == 8 && TS % 8 == 0 && TG % 4 == 0, "eight wavefronts share the copies evenly");
+  static_assert(EPI != TILE_GATEUP || SW % 2 == 0, "a wavefront needs a gate strip and its up strip");
+  __shared__ u32x4 sA0[TS][64], sA1[TS][64], sA2[TS][64], sB0[TG * 2][64], sB1[TG * 2][64], sB2[TG * 2][64];
+  __shared__ float s_inv[ROWS], s_part[512];
+
+  // tile of this workgroup: consecutive workgroup ids go to different dies (XCDs), each with its own L2; every die
+  // gets a contiguous eighth of the tiles in panel order, so its workgroups share weight and activation tiles
+  const int n_tiles = a.tiles_m * a.tiles_n * a.slices;
+  const int die = blockIdx.x & 7, rem = n_tiles & 7;
+  int t = die * (n_tiles >> 3) + min(die, rem) + (int)(blockIdx.x >> 3);
+  const int slice = t / (a.tiles_m * a.tiles_n);
+  t -= slice * a.tiles_m * a.tiles_n;
+  const int pnl = t / (a.panel * a.tiles_n);
+  t -= pnl * a.panel * a.tiles_n;
+  const int gm = min(a.panel, a.tiles_m - pnl * a.panel);
+  const int tn = t / gm, tm = pnl * a.panel + t % gm;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ml = lane & 15, g4 = lane >> 4;
-  const int KT = a.K >> 5;
+  const int grp = wave >> 2, wf = wave % WF, wr = wave / WF;
+  const int c = lane & 15, kq = lane >> 4;
+  const int KT = a.K >> 5, n_groups = (a.M + 7) >> 3;
+  const int kt0 = slice * a.kt_slice, kt1 = min(KT, kt0 + a.kt_slice);
   const int m0 = tm * ROWS;
-  const int strip0 = (tn * 4 + wave) * SW;
+
+  // sources of this wavefront's copies.  Strips past the end repeat the last one, row groups past the end the last
+  // one (in bounds; their results are dropped).  Fragment (16-row group, half): lane (c, kq) takes the slot of row
+  // c & 7 of 8-row group c >> 3.
+  const u32x4 *ap[NA], *bp[NB];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) ap[i] = a.W + ((size_t)min(tn * TS + wave * NA + i, a.n_strips - 1) * KT) * 64 + lane;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int f = wave * NB + i, rg = f >> 1, half = f & 1;
+    const int g8 = min(tm * TG * 2 + 2 * rg + (c >> 3), n_groups - 1);
+    bp[i] = a.X + (size_t)g8 * KT * 64 + kq * 16 + half * 8 + (c & 7);
+  }
+  auto issue = [&](u32x4 (*dA)[64], u32x4 (*dB)[64], int kt) __attribute__((always_inline)) {
+    const size_t off = (size_t)min(kt, kt1 - 1) * 64;  // steps past the end repeat the last one (never read)
+#pragma unroll
+    for (int i = 0; i < NA; ++i) copy_to_lds(ap[i] + off, &dA[wave * NA + i][0]);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) copy_to_lds(bp[i] + off, &dB[wave * NB + i][0]);
+  };
+  issue(sA0, sB0, kt0);
+  issue(sA1, sB1, kt0 + 1);
 
   // 1 / rms of the tile's rows from the producer's partial sums of h^2
   if constexpr (NORM) {
-    constexpr int TG = NT / ROWS;
-    const int row = tid % ROWS, tg = tid / ROWS;
+    constexpr int TH = 512 / ROWS;
+    const int row = tid % ROWS, th = tid / ROWS;
     float ss = 0.f;
     if (m0 + row < a.M) {
       // eight requests at a time (indices past the end repeat the last partial and are dropped)
-      for (int i0 = tg; i0 < w.np; i0 += 8 * TG) {
+      for (int i0 = th; i0 < w.np; i0 += 8 * TH) {
         float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = p.ssq[(size_t)min(i0 + u * TG, w.np - 1) * w.rows + m0 + row];
+        for (int u = 0; u < 8; ++u) v[u] = p.ssq[(size_t)min(i0 + u * TH, w.np - 1) * w.rows + m0 + row];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) ss += (i0 + u * TG < w.np) ? v[u] : 0.f;
+        for (int u = 0; u < 8; ++u) ss += (i0 + u * TH < w.np) ? v[u] : 0.f;
       }
     }
     s_part[tid] = ss;
@@ -108,251 +223,210 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (tid < ROWS) {
       float tot = 0.f;
 #pragma unroll
-      for (int j = 0; j < TG; ++j) tot += s_part[j * ROWS + tid];
+      for (int j = 0; j < TH; ++j) tot += s_part[j * ROWS + tid];
       s_inv[tid] = 1.0f / sqrtf(tot / (float)p.d + p.eps);
     }
-    // published by the barriers of the main loop
+    // published by the meetings of the main loop
   }
 
-  floatx4 acc[SW][MG];
+  floatx4 acc[SW][RG];
 #pragma unroll
   for (int s = 0; s < SW; ++s)
 #pragma unroll
-    for (int g = 0; g < MG; ++g) acc[s][g] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int g = 0; g < RG; ++g) acc[s][g] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // activation tile: thread (wave, lane) stages lane slot `lane` of groups j * 4 + wave.  Loads go
-  // through a buffer descriptor; slots of rows >= M get an out-of-range offset and read as zero.
-  const int n_groups = (a.M + 7) >> 3;
-  const __amdgpu_buffer_rsrc_t xr =
-      __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, n_groups * 16 * a.K * 2, 0x00020000);
-  int boff[BL];
+  auto step = [&](const u32x4 (*dA)[64], const u32x4 (*dB)[64], u32x4 (*nA)[64], u32x4 (*nB)[64], int kt) __attribute__((always_inline)) {
+    bf16x8 av[SW], bv[RG][2];
 #pragma unroll
-  for (int j = 0; j < BL; ++j) {
-    const int grp = tm * MG + j * 4 + wave;
-    boff[j] = (grp * 8 + (lane & 7) < a.M) ? (grp * KT * 64 + lane) * 16 : 0x40000000;
-  }
-  // weight tiles of this wavefront's strips (strips past the end repeat the last one; their
-  // results are dropped)
-  const u32x4 *wp[SW];
+    for (int s = 0; s < SW; ++s) av[s] = __builtin_bit_cast(bf16x8, dA[wf * SW + s][lane]);
 #pragma unroll
-  for (int s = 0; s < SW; ++s) wp[s] = a.W + (size_t)min(strip0 + s, a.n_strips - 1) * KT * 64 + lane;
-
-  constexpr int AD = 3;  // k-steps both operands are requested ahead
-  u32x4 aR[AD + 1][SW], bR[AD + 1][BL];
-  auto load_a = [&](u32x4 (&dst)[SW], int kt) {
+    for (int g = 0; g < RG; ++g)
 #pragma unroll
-    for (int s = 0; s < SW; ++s) dst[s] = wp[s][(size_t)kt * 64];
-  };
-  auto load_b = [&](u32x4 (&dst)[BL], int kt) {
-#pragma unroll
-    for (int j = 0; j < BL; ++j) dst[j] = __builtin_amdgcn_raw_buffer_load_b128(xr, boff[j] + kt * 1024, 0, 0);
-  };
-  auto store_b = [&](int buf, const u32x4 (&src)[BL]) {
-#pragma unroll
-    for (int j = 0; j < BL; ++j) sB[buf][j * 4 + wave][lane] = src[j];
-  };
-  auto compute = [&](const u32x4 (&av)[SW], int buf) {
-    // four activation fragments in flight: the fragment of group g + 4 is requested from LDS as
-    // soon as group g has been issued
-    u32x4 b[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) b[g] = sB[buf][g][lane];
-#pragma unroll
-    for (int g = 0; g < MG; ++g) {
-#pragma unroll
-      for (int s = 0; s < SW; ++s)
-        acc[s][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[s]),
-                                                            __builtin_bit_cast(bf16x8, b[g & 3]), acc[s][g], 0, 0, 0);
-      if (g + 4 < MG) b[g & 3] = sB[buf][g + 4][lane];
-    }
-    // the order above is the order wanted: left alone, the scheduler moves every LDS read down to
-    // its first use to save registers, and the wavefront then waits out the LDS latency once per
-    // group.  (0x100 = LDS read, 0x008 = MFMA.)
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-    for (int g = 0; g < MG; ++g) {
-      __builtin_amdgcn_sched_group_barrier(0x008, SW, 0);
-      if (g + 4 < MG) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-  };
-  // k-step kt: request both operands of step kt+3 (indices past the end repeat the last step: in
-  // bounds, never used), hand the activation tile of step kt+1 (requested two steps ago) over to
-  // LDS buffer (kt+1) & 1, compute from buffer kt & 1.  Loads return in order, so a wait for any
-  // request also waits for everything requested before it: every wait here is for requests at
-  // least two steps old, and a step costs its MFMAs, not a trip to memory.  One barrier per step:
-  // a buffer is rewritten only after the barrier that follows its last reader, and read only
-  // after the barrier that follows its writers.
-  auto step = [&](auto I, int kt) {
-    constexpr int i = decltype(I)::value;
-    load_b(bR[(i + AD) % (AD + 1)], min(kt + AD, KT - 1));
-    load_a(aR[(i + AD) % (AD + 1)], min(kt + AD, KT - 1));
-    // the requests leave before the step computes (left alone, the instruction scheduler sinks
-    // them to the point of use and the step pays their whole latency), and no instruction moves
-    // from one step into the next
+      for (int h = 0; h < 2; ++h) bv[g][h] = __builtin_bit_cast(bf16x8, dB[(wr * RG + g) * 2 + h][lane]);
+    issue(nA, nB, kt + 2);
     __builtin_amdgcn_sched_barrier(0);
-    store_b((kt + 1) & 1, bR[(i + 1) % (AD + 1)]);
-    compute(aR[i], kt & 1);
-    __syncthreads();
+    wait_lds_reads();
+    if (grp) wait_copies<NA + NB>();
+    meet();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int s = 0; s < SW; ++s) acc[s][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[s], bv[g][h], acc[s][g], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
+    if (!grp) wait_copies<NA + NB>();
+    meet();
   };
-#pragma unroll
-  for (int j = 0; j < AD; ++j) load_b(bR[j], min(j, KT - 1));
-#pragma unroll
-  for (int j = 0; j < AD; ++j) load_a(aR[j], min(j, KT - 1));
-  store_b(0, bR[0]);
-  __syncthreads();
-  int kt = 0;
-  for (; kt + AD < KT; kt += AD + 1) {
-    step(ic<0>{}, kt);
-    step(ic<1>{}, kt + 1);
-    step(ic<2>{}, kt + 2);
-    if constexpr (AD == 3) step(ic<3>{}, kt + 3);
+  wait_copies<NA + NB>();
+  wait_lds_reads();
+  meet();
+  if (grp) meet();
+  int kt = kt0;
+  for (; kt + 2 < kt1; kt += 3) {
+    step(sA0, sB0, sA2, sB2, kt);
+    step(sA1, sB1, sA0, sB0, kt + 1);
+    step(sA2, sB2, sA1, sB1, kt + 2);
   }
-  if (kt < KT) {
-    step(ic<0>{}, kt);
-    if (kt + 1 < KT) step(ic<1>{}, kt + 1);
-    if (AD == 3 && kt + 2 < KT) step(ic<2>{}, kt + 2);
-  }
+  if (kt < kt1) step(sA0, sB0, sA2, sB2, kt);
+  if (kt + 1 < kt1) step(sA1, sB1, sA0, sB0, kt + 1);
+  if (!grp) meet();
+  wait_copies<0>();  // no copy may land in LDS that the next workgroup already owns
 
-  // Epilogue.  After adding the lo columns to the hi columns, lane (ml < 8, g4) holds
-  // Y[m0 + 8g + ml][16 strip + 4 g4 .. + 3].
-  float ss_row[MG];  // RESID: this wavefront's sum of h^2 per row
+  // lane (c, kq) holds Y[row 16 g + c][features 16 strip + 4 kq .. + 3]
+  const int strip0 = tn * TS + wf * SW;
 #pragma unroll
-  for (int g = 0; g < MG; ++g) {
-    const int m = m0 + g * 8 + (ml & 7);
-    const bool row_live = m < a.M && ml < 8;
+  for (int g = 0; g < RG; ++g) {
+    const int lr = (wr * RG + g) * 16 + c, m = m0 + lr;
+    const bool row_live = m < a.M;
     float inv = 1.f;
-    if constexpr (NORM) inv = s_inv[g * 8 + (ml & 7)];
+    if constexpr (NORM) inv = s_inv[lr];
     float ss = 0.f;
     if constexpr (EPI == TILE_GATEUP) {
 #pragma unroll
-      for (int s = 0; s < SW; s += 2) {
-        floatx4 yg = acc[s][g], yu = acc[s + 1][g];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          yg[r] += other_half(yg[r]);
-          yu[r] += other_half(yu[r]);
-        }
-        if (row_live && strip0 + s + 1 < a.n_strips) {
-          const int f0 = ((strip0 + s) >> 1) * 16 + 4 * g4;
-          float tv[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            float gt = yg[r] * inv, up = yu[r] * inv;
-            tv[r] = gt / (1.0f + __expf(-gt)) * up;
-          }
-          store_split4(p.act_x, m, p.F, f0, tv);
-        }
-      }
+      for (int s = 0; s < SW; s += 2)
+        if (row_live && strip0 + s + 1 < a.n_strips)
+          finish_gateup(p, m, ((strip0 + s) >> 1) * 16 + 4 * kq, acc[s][g], acc[s + 1][g], inv);
     } else {
 #pragma unroll
       for (int s = 0; s < SW; ++s) {
-        floatx4 y = acc[s][g];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) y[r] += other_half(y[r]);
-        const int strip = strip0 + s;
-        const bool live = row_live && strip < a.n_strips;
-        const int n = strip * 16 + 4 * g4;
-        if constexpr (EPI == TILE_RESID) {
-          if (live) {
-            float *hp = p.h + (size_t)m * p.d + n;
-            floatx4 hv = *(floatx4 *)hp + y;
-            *(floatx4 *)hp = hv;
-            float tv[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              tv[r] = hv[r] * bf16_to_f32(a.gain_next[n + r]);
-              ss += hv[r] * hv[r];
-            }
-            store_split4(p.xg, m, p.d, n, tv);
-          }
-        } else {  // TILE_QKV
-          if (live) {
-            const int which = n / p.D;        // 0 q, 1 k, 2 v
-            const int c = n - which * p.D;    // column inside the projection
-            const int head = c / p.hd, dim = c - head * p.hd;
-            floatx4 v = y * inv;
-            if (which < 2) {
-              const int half = p.hd / 2;
-              const float *cs = p.rope_cos + (size_t)m * half + dim / 2;
-              const float *sn = p.rope_sin + (size_t)m * half + dim / 2;
-              const float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
-              v[0] = x0 * cs[0] - x1 * sn[0];
-              v[1] = x0 * sn[0] + x1 * cs[0];
-              v[2] = x2 * cs[1] - x3 * sn[1];
-              v[3] = x2 * sn[1] + x3 * cs[1];
-            }
-            if (which == 0) {
-              *(floatx4 *)(w.q + (size_t)m * p.D + c) = v;
-            } else {
-              // K rows [page][head][pos][dim], V pages transposed [page][head][dim][pos]; bf16 storage
-              // (the eight rows of a group share a block: the index is uniform over the wavefront)
-              const int sb = __builtin_amdgcn_readfirstlane(m / kPrefillBlockRows), sr = m % kPrefillBlockRows;
-              if (sr >= a.segs.rows[sb]) continue;  // a padding row: nothing to cache
-              const int pos = a.segs.pos[sb] + sr;
-              const int page = p.block_table[(size_t)a.segs.slot[sb] * p.pages_per_seq + (pos >> p.page_shift)];
-              const size_t hbase = ((size_t)a.layer * p.n_pages + page) * p.H + head;
-              const int off = pos & (p.page_size - 1);
-              if (which == 1) {
-                uint2 pk;
-                pk.x = pack2_bf16(v[0], v[1]);
-                pk.y = pack2_bf16(v[2], v[3]);
-                *(uint2 *)((uint16_t *)p.k_pool + (hbase * p.page_size + off) * p.hd + dim) = pk;
-              } else {
-                uint16_t *vp = (uint16_t *)p.v_pool + (hbase * p.hd + dim) * p.page_size + off;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) vp[(size_t)r * p.page_size] = f32_to_bf16(v[r]);
-              }
-            }
-          }
+        const int n = (strip0 + s) * 16 + 4 * kq;
+        if (row_live && strip0 + s < a.n_strips) {
+          if constexpr (EPI == TILE_RESID)
+            ss += finish_resid(p, a.gain_next, m, n, acc[s][g]);
+          else if constexpr (EPI == TILE_QKV)
+            finish_qkv(p, w, a, m, n, acc[s][g] * inv);
+          else
+            *(floatx4 *)(a.part + ((size_t)slice * a.M + m) * (a.n_strips * 16) + n) = acc[s][g];
         }
       }
     }
-    ss_row[g] = ss;
-  }
-  if constexpr (EPI == TILE_RESID) {
-    // partial sum of h^2 over this wavefront's 16 * SW features, one per row: partial index =
-    // wavefront strip group, rows past M get 0
-    const int part = tn * 4 + wave;
-    if (part < w.np) {
-#pragma unroll
-      for (int g = 0; g < MG; ++g) {
-        float ss = ss_row[g];
-        ss += __shfl_xor(ss, 16);
-        ss += __shfl_xor(ss, 32);
-        if (lane < 8) p.ssq[(size_t)part * w.rows + m0 + g * 8 + lane] = ss;
-      }
+    if constexpr (EPI == TILE_RESID) {
+      // partial sum of h^2 over this wavefront's 16 * SW features, one per row
+      const int part = tn * WF + wf;
+      ss += __shfl_xor(ss, 16);
+      ss += __shfl_xor(ss, 32);
+      if (lane < 16 && row_live && strip0 < a.n_strips) p.ssq[(size_t)part * w.rows + m] = ss;
     }
   }
 }
 
+// Adds the slices of a product that was split along K (in slice order) and finishes it as the fused epilogues do.
+// One workgroup: 16 rows x 64 features (a gate strip, its up strip, twice); thread = (row, four features), so that
+// the (hi, lo) tiles and the transposed V pages are written as whole runs of rows.
 template <int EPI>
-void launch_tile(const Params &p, const PrefillWs &w, TileArgs a, int sw, hipStream_t s) {
-  a.tiles_n = (a.n_strips + 4 * sw - 1) / (4 * sw);
-  a.tiles_m = (a.M + 63) / 64;
-  // a die (32 compute units, two workgroups each) holds 64 workgroups: a block of 8 x 8 tiles
-  // re-reads the least per multiply-add (2048 features and 512 rows per die at a time)
-  a.blk_n = w.blk_n ? w.blk_n : 8;
-  a.blk_m = w.blk_m ? w.blk_m : 8;
-  a.blocks_m = (a.tiles_m + a.blk_m - 1) / a.blk_m;
-  a.n_blocks = a.blocks_m * ((a.tiles_n + a.blk_n - 1) / a.blk_n);
-  const int grid = ((a.n_blocks + 7) / 8) * 8 * a.blk_n * a.blk_m;
-  if constexpr (EPI != TILE_GATEUP) {  // (a gate/up wavefront needs a gate strip and its up strip)
-    if (sw == 1) { gemm_tile_kernel<EPI, 8, 1><<<grid, 256, 0, s>>>(p, w, a); return; }
+__global__ __launch_bounds__(256) void tile_reduce_kernel(Params p, PrefillWs w, TileArgs a) {
+  __shared__ float s_part[16][17];
+  const int r = threadIdx.x & 15, qd = threadIdx.x >> 4;
+  const int m = blockIdx.y * 16 + r, n = blockIdx.x * 64 + qd * 4, N = a.n_strips * 16;
+  const bool live = m < a.M && n < N;
+  const size_t stride = (size_t)a.M * N, at = (size_t)min(m, a.M - 1) * N + min(n, N - 4);
+  constexpr int MAXS = 8;
+  floatx4 v[MAXS];
+#pragma unroll
+  for (int i = 0; i < MAXS; ++i)  // all slices requested at once (index clamped, surplus dropped)
+    v[i] = *(const floatx4 *)(a.part + min(i, a.slices - 1) * stride + at);
+  float inv = 1.f;
+  if constexpr (EPI != TILE_RESID) {
+    float ss = 0.f;
+    if (m < a.M)
+      for (int i = qd; i < w.np; i += 16) ss += p.ssq[(size_t)i * w.rows + m];
+    s_part[qd][r] = ss;
+    __syncthreads();
+    float tot = 0.f;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) tot += s_part[j][r];
+    inv = 1.0f / sqrtf(tot / (float)p.d + p.eps);
   }
-  if (sw == 2) { gemm_tile_kernel<EPI, 8, 2><<<grid, 256, 0, s>>>(p, w, a); return; }
-  gemm_tile_kernel<EPI, 8, kTileStrips><<<grid, 256, 0, s>>>(p, w, a);
+  floatx4 y = v[0];
+#pragma unroll
+  for (int i = 1; i < MAXS; ++i)
+    if (i < a.slices) y += v[i];
+  if constexpr (EPI == TILE_QKV) {
+    if (live) finish_qkv(p, w, a, m, n, y * inv);
+  } else if constexpr (EPI == TILE_GATEUP) {
+    // quads 0..3 gate, 4..7 up of one strip pair, 8..11 gate, 12..15 up of the next: the up quad is four quads on
+    __shared__ floatx4 s_up[8][16];
+    if (qd & 4) s_up[(qd >> 3) * 4 + (qd & 3)][r] = y;
+    __syncthreads();
+    if (!(qd & 4) && live) finish_gateup(p, m, (n >> 5) * 16 + (n & 15), y, s_up[(qd >> 3) * 4 + (qd & 3)][r], inv);
+  } else {
+    float ss = live ? finish_resid(p, a.gain_next, m, n, y) : 0.f;
+    s_part[qd][r] = ss;
+    __syncthreads();
+    if (threadIdx.x < 16 && m < a.M) {
+      float tot = 0.f;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) tot += s_part[j][threadIdx.x];
+      p.ssq[(size_t)blockIdx.x * w.rows + m] = tot;
+    }
+  }
 }
 
-// Strips per wavefront for a GEMM of n_strips strips on M rows: halved (down to `least`) until
-// there are at least 384 tiles for the chip's 512 workgroup slots (measured on 7B shapes: 384 wide
-// tiles beat 768 narrow ones, 256 do not beat 512).  Narrow tiles pull more operand bytes per
-// multiply-add, but a pass with few rows is bound by how many workgroups walk K side by side.
-int tile_strips(int n_strips, int M, int least) {
-  int sw = kTileStrips;
-  const int tiles_m = (M + 63) / 64;
-  while (sw > least && tiles_m * ((n_strips + 4 * sw - 1) / (4 * sw)) < 384) sw >>= 1;
-  return sw;
+// Shapes of the tiled GEMM: features x rows of a tile, and what a k-step of it takes when every compute unit has one.
+struct TileShape { int ts, rows, strips_per_wave; float step_us; };
+constexpr TileShape kTileShapes[3] = {{16, 128, 4, 0.74f}, {16, 256, 8, 1.40f}, {24, 128, 12, 1.10f}};
+struct TilePlan { int shape, slices; };
+
+// Which tile and how many slices of K.  The tiles run in rounds of one per compute unit (256), a round takes the
+// steps of a tile; what a shape leaves idle in its last round decides, as long as the weights do not have to be
+// waited for.  Slices fill the chip when there are fewer tiles than units; their sums cost a write, a read and a
+// launch.
+TilePlan plan_tiles(int n_strips, int K, int M, size_t part_floats, int want) {
+  const int KT = K / 32;
+  TilePlan best{0, 1};
+  float best_us = 1e30f;
+  for (int s = 0; s < 3; ++s) {
+    const TileShape &t = kTileShapes[s];
+    if (want == 2 && s != 0) continue;
+    if (want == 4 && s != 1) continue;
+    if (want == 3 && s != 2) continue;
+    const int tiles = ((n_strips + t.ts - 1) / t.ts) * ((M + t.rows - 1) / t.rows);
+    for (int ks = 1; ks <= 8; ++ks) {
+      const int kts = (KT + ks - 1) / ks;
+      if ((kts < 8 && want != 1 && ks > 1) || (KT + kts - 1) / kts != ks) continue;  // every slice has steps
+      if (ks > 1 && (want > 1 || (size_t)ks * M * n_strips * 16 > part_floats)) continue;
+      if (want == 1 && ks == 1 && KT > 1) continue;
+      const float rounds = (float)((tiles * ks + 255) / 256);
+      float us = rounds * (kts * t.step_us + 4.f);
+      const float stream = (float)n_strips * K * 32 / 5.0e6f;  // the weights at 5 TB/s
+      if (us < stream) us = stream;
+      if (ks > 1) us += 4.f + (float)ks * M * n_strips * 16 * 8 / 4.0e6f;
+      if (us < best_us) { best_us = us; best = TilePlan{s, ks}; }
+    }
+  }
+  return best;
+}
+
+// Launches a product with its epilogue; returns the number of partial sums of h^2 per row that RESID leaves.
+template <int EPI>
+int launch_tile(const Params &p, const PrefillWs &w, TileArgs a, hipStream_t s) {
+  const TilePlan pl = plan_tiles(a.n_strips, a.K, a.M, w.part_floats, w.strips_opt);
+  const TileShape &t = kTileShapes[pl.shape];
+  a.tiles_n = (a.n_strips + t.ts - 1) / t.ts;
+  a.tiles_m = (a.M + t.rows - 1) / t.rows;
+  // a die works on 32 tiles at a time: about 1024 rows x 1024 features re-read the least per multiply-add
+  a.panel = w.panel ? w.panel : 1024 / t.rows;
+  const int KT = a.K / 32;
+  a.kt_slice = (KT + pl.slices - 1) / pl.slices;
+  a.slices = (KT + a.kt_slice - 1) / a.kt_slice;
+  a.part = w.part;
+  const int grid = a.tiles_n * a.tiles_m * a.slices;
+  auto go = [&](auto E) {
+    constexpr int e = decltype(E)::value;
+    if (pl.shape == 1) gemm_tile_kernel<e, 2, 4, 8, 4><<<grid, 512, 0, s>>>(p, w, a);
+    else if (pl.shape == 2) gemm_tile_kernel<e, 2, 4, 12, 2><<<grid, 512, 0, s>>>(p, w, a);
+    else gemm_tile_kernel<e, 4, 2, 4, 4><<<grid, 512, 0, s>>>(p, w, a);
+  };
+  if (a.slices == 1) {
+    go(ic<EPI>{});
+    return (a.n_strips + t.strips_per_wave - 1) / t.strips_per_wave;
+  }
+  go(ic<TILE_PART>{});
+  tile_reduce_kernel<EPI><<<dim3((a.n_strips + 3) / 4, (a.M + 15) / 16), 256, 0, s>>>(p, w, a);
+  return (a.n_strips + 3) / 4;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -765,24 +839,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 }  // namespace
 
-// Strips per wavefront of the residual projections for a pass of M rows.  Fixes the number of
-// partial sums of h^2 per row (one per wavefront strip group), which the producer of the rows
-// must know.
-int prefill_resid_strips(const Params &p, int M) { return tile_strips(p.d / 16, M, 1); }
-
 void launch_prefill_qkv(const Params &p, const PrefillWs &w, const void *W, int layer, const PrefillSegs &segs, int M,
                         hipStream_t s) {
-  TileArgs a{(const u32x4 *)W, p.xg, M, p.d, 3 * p.D / 16, layer, nullptr, segs, 0, 0, 0, 0, 0, 0};
-  launch_tile<TILE_QKV>(p, w, a, w.resid_strips_opt ? w.resid_strips_opt : tile_strips(a.n_strips, M, 1), s);
+  TileArgs a{(const u32x4 *)W, (const u32x4 *)p.xg, M, p.d, 3 * p.D / 16, layer, nullptr, segs, 0, 0, 0, 1, 0, nullptr};
+  launch_tile<TILE_QKV>(p, w, a, s);
 }
-void launch_prefill_resid(const Params &p, const PrefillWs &w, const void *W, const uint16_t *X, int K,
-                          const void *gain_next, int M, hipStream_t s) {
-  TileArgs a{(const u32x4 *)W, X, M, K, p.d / 16, 0, (const uint16_t *)gain_next, PrefillSegs{}, 0, 0, 0, 0, 0, 0};
-  launch_tile<TILE_RESID>(p, w, a, w.resid_strips, s);
+int launch_prefill_resid(const Params &p, const PrefillWs &w, const void *W, const uint16_t *X, int K, const void *gain_next, int M,
+                         hipStream_t s) {
+  TileArgs a{(const u32x4 *)W, (const u32x4 *)X, M, K, p.d / 16, 0, (const uint16_t *)gain_next, PrefillSegs{}, 0, 0, 0, 1, 0, nullptr};
+  return launch_tile<TILE_RESID>(p, w, a, s);
 }
 void launch_prefill_gateup(const Params &p, const PrefillWs &w, const void *W, int M, hipStream_t s) {
-  TileArgs a{(const u32x4 *)W, p.xg, M, p.d, 2 * p.F / 16, 0, nullptr, PrefillSegs{}, 0, 0, 0, 0, 0, 0};
-  launch_tile<TILE_GATEUP>(p, w, a, w.resid_strips_opt > 1 ? w.resid_strips_opt : tile_strips(a.n_strips, M, 2), s);
+  TileArgs a{(const u32x4 *)W, (const u32x4 *)p.xg, M, p.d, 2 * p.F / 16, 0, nullptr, PrefillSegs{}, 0, 0, 0, 1, 0, nullptr};
+  launch_tile<TILE_GATEUP>(p, w, a, s);
 }
 void launch_prefill_attention(const Params &p, const PrefillWs &w, int layer, int slot, int pos0, int R,
                               hipStream_t s) {

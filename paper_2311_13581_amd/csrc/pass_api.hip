@@ -233,7 +233,10 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   W.rows = std::min(kPrefillRows, (c.max_seq_len + 127) / 128 * 128);
   W.np = (int)(d / 16);  // most partial sums of h^2 a row can have (one per strip)
   const size_t R = W.rows;
-  const size_t ws_bytes = R * 4 * (d + d + D + D + F + W.np + c.head_dim) + 8 * 256;
+  // sums over slices of K of the GEMMs that are split: at most one tile of 384 x 128 per compute unit, and never more
+  // than eight slices of the widest product
+  W.part_floats = std::min<size_t>((size_t)256 * 384 * 128, 8 * R * std::max(3 * D, std::max(2 * F, d)));
+  const size_t ws_bytes = R * 4 * (d + d + D + D + F + W.np + c.head_dim) + W.part_floats * 4 + 9 * 256;
   if (ws_bytes > stage_bytes) stage_bytes = ws_bytes;
   void *staging = A.take<char>(stage_bytes);
   if (ctx) {
@@ -246,6 +249,7 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
     W.q = S2.take<float>(R * D); PP.attn_x = S2.take<uint16_t>(2 * R * D); PP.act_x = S2.take<uint16_t>(2 * R * F);
     PP.ssq = S2.take<float>(R * W.np);
     PP.rope_cos = S2.take<float>(R * c.head_dim / 2); PP.rope_sin = S2.take<float>(R * c.head_dim / 2);
+    W.part = S2.take<float>(W.part_floats);
     ctx->PP = PP; ctx->pws = W;
   }
   return (A.off + 255) & ~(size_t)255;
@@ -454,8 +458,7 @@ int run_prefill_pass(pass_ctx *c, const std::vector<PassSeg> &parts, int M, cons
   P.rope_cos = B.rope_cos; P.rope_sin = B.rope_sin;
   P.prefill_ids = const_cast<int32_t *>(ids);
   PrefillWs W = c->pws;
-  W.resid_strips = W.resid_strips_opt ? W.resid_strips_opt : prefill_resid_strips(P, M);
-  W.np = (P.d / 16 + W.resid_strips - 1) / W.resid_strips;
+  W.np = 1;  // the assembled rows carry their sum of h^2 in one piece
   PrefillSegs segs;
   memset(&segs, 0, sizeof segs);
   segs.n_blocks = (M + kPrefillBlockRows - 1) / kPrefillBlockRows;
@@ -478,9 +481,9 @@ int run_prefill_pass(pass_ctx *c, const std::vector<PassSeg> &parts, int M, cons
       Wg.q = W.q + (size_t)g.row_base * P.D;
       launch_prefill_attention(Pg, Wg, l, g.slot, g.pos0, g.rows, s);
     }
-    launch_prefill_resid(P, W, w.wo, P.attn_x, P.D, w.ffn_norm, M, s);
+    W.np = launch_prefill_resid(P, W, w.wo, P.attn_x, P.D, w.ffn_norm, M, s);
     launch_prefill_gateup(P, W, w.wgu, M, s);
-    launch_prefill_resid(P, W, w.wdown, P.act_x, P.F, l + 1 < P.L ? c->layers[l + 1].attn_norm : c->final_norm, M, s);
+    W.np = launch_prefill_resid(P, W, w.wdown, P.act_x, P.F, l + 1 < P.L ? c->layers[l + 1].attn_norm : c->final_norm, M, s);
   }
   HIP_TRY(c, hipGetLastError());
   return PASS_OK;
@@ -1546,9 +1549,9 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   //                       2000000 + K slices of the split residual GEMM (0 = never split)
   //   tune.prefill_rows   prompt rows per pass of the tiled prompt pass (a multiple of 128)
   //   tune.prefill_tile   query rows per attention workgroup of the tiled prompt pass (0, 16, 32, 128)
-  //   tune.prefill_block  tiles along the features * 100 + tiles along the rows of the block of GEMM tiles one die
-  //                       works on at a time (0 = default 8 x 8)
-  //   tune.prefill_strips strips of 16 features per wavefront in the tiled GEMMs (0 = by row count, 1, 2, 4)
+  //   tune.prefill_block  (1 .. 64) * 100 + row tiles of a panel of the tiled GEMMs' tile order (0 = 1024 rows)
+  //   tune.prefill_strips tile of the tiled GEMMs: 0 = by shape, 1 = 256 x 128 features x rows with K in slices,
+  //                       2 = 256 x 128, 3 = 384 x 128, 4 = 256 x 256
   if (!strcmp(name, "tune.gemm_cfg")) {
     if (value >= 2000000) {
       if (c->tuning.set_split(value - 2000000)) return fail(c, PASS_EINVAL, "tune.gemm_cfg (split residual GEMM): 0 .. 8 slices of K");
@@ -1597,15 +1600,14 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
     return PASS_OK;
   }
   if (!strcmp(name, "tune.prefill_strips")) {
-    if (value != 0 && value != 1 && value != 2 && value != 4) return fail(c, PASS_EINVAL, "tune.prefill_strips: 0 (by row count), 1, 2 or 4");
-    c->pws.resid_strips_opt = value;
+    if (value < 0 || value > 4) return fail(c, PASS_EINVAL, "tune.prefill_strips: 0 (by shape) .. 4");
+    c->pws.strips_opt = value;
     return PASS_OK;
   }
   if (!strcmp(name, "tune.prefill_block")) {
     const int bn = value / 100, bm = value % 100;
-    if (value < 0 || bn > 64 || bm > 64 || (bn == 0) != (bm == 0)) return fail(c, PASS_EINVAL, "tune.prefill_block: tiles along the features * 100 + tiles along the rows (1 .. 64 each), or 0");
-    c->pws.blk_n = bn;
-    c->pws.blk_m = bm;
+    if (value < 0 || bn > 64 || bm > 64 || (bn == 0) != (bm == 0)) return fail(c, PASS_EINVAL, "tune.prefill_block: (1 .. 64) * 100 + row tiles of a panel (1 .. 64), or 0");
+    c->pws.panel = bm;
     return PASS_OK;
   }
   if (!strcmp(name, "kernel_timing")) {

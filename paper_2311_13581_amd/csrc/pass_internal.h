@@ -211,10 +211,11 @@ __device__ __forceinline__ void store_split4(uint16_t *xs, int m, int K, int k, 
 // rope_cos, rope_sin, attn_x and act_x point at buffers of that many rows; the rest is here.
 struct PrefillWs {
   int rows;       // capacity in rows (multiple of 128); also the row stride of the partial sums of h^2
-  int np;         // partial sums of h^2 per row of this pass: one per resid_strips strips of 16 features
-  int resid_strips;  // strips per wavefront of the residual projections in this pass (prefill_resid_strips)
-  int resid_strips_opt;  // 1, 2 or 4: strips per wavefront of every GEMM fixed by the caller (gate/up: at least 2); 0 = by row count
-  int blk_n, blk_m;  // tiles (along the features, along the rows) of the block one die works on at a time; 0 = default
+  int np;         // partial sums of h^2 per row that the last producer of rows has left
+  int strips_opt; // GEMM tiles: 0 = by shape; 1 = split along K, 2 = 256 x 128, 4 = 256 x 256, 3 = 384 x 128 features x rows
+  int panel;      // row tiles of a panel of the GEMMs' tile order; 0 = 1024 rows
+  float *part;    // sums over slices of K: part_floats floats
+  size_t part_floats;
   int attn_rows;  // query rows of an attention workgroup: 16, 32 or 128 (0 = 128 for passes of more than 512 rows, else 32)
   float *q;       // [rows][D] rotated queries
 };
@@ -233,10 +234,10 @@ void launch_prefill_qkv(const Params &p, const PrefillWs &w, const void *W, int 
                         hipStream_t s);
 void launch_prefill_attention(const Params &p, const PrefillWs &w, int layer, int slot, int pos0, int R,
                               hipStream_t s);
-void launch_prefill_resid(const Params &p, const PrefillWs &w, const void *W, const uint16_t *X, int K,
-                          const void *gain_next, int M, hipStream_t s);
+// returns the number of partial sums of h^2 per row it leaves (PrefillWs::np of the next launches)
+int launch_prefill_resid(const Params &p, const PrefillWs &w, const void *W, const uint16_t *X, int K,
+                         const void *gain_next, int M, hipStream_t s);
 void launch_prefill_gateup(const Params &p, const PrefillWs &w, const void *W, int M, hipStream_t s);
-int prefill_resid_strips(const Params &p, int M);
 
 void launch_gemm_logits(const Params &p, const GemmTuning &tn, const void *W, float *logits, int M, hipStream_t s);
 

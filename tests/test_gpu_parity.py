@@ -355,6 +355,25 @@ def test_tiled_prompt_pass(plen, attn_rows, rows, strips, block):
     g.close()
 
 
+@pytest.mark.parametrize("strips", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("d,ffn,plen", [(32, 32, 18), (64, 96, 130), (96, 160, 258), (544, 1184, 140)])
+def test_tiled_gemm_shapes(d, ffn, plen, strips):
+    """Every tile of the prompt pass's GEMM where its ring of stages, its remainders and its slices can go wrong: one,
+    two, three, five, 17 and 37 k-steps (fewer than the ring's three stages, and every remainder of them), row tiles with
+    one row left (129, 257) or a fraction of a 16-row group, strips that end inside a tile (2 .. 74 against 16 or 24), and
+    K in as many slices as have steps (strips = 1: up to eight, the last one shorter).  The calls on top of the prompt are
+    compared with the oracle, which prefills row by row."""
+    shape = synth.ModelShape(2, d, 1, 128, ffn, 1008, dtype=synth.BF16)
+    W = synth.make_weights(shape, 5, 2, 6.0)
+    m = O.Model(shape, W, 2)
+    prompt = np.random.default_rng(plen).integers(0, shape.vocab, plen).astype(np.int32)
+    g = _gpu(shape, W, 2, max_seq_len=320, page_size=64, options={"prefill_tiled": 1, "tune.prefill_strips": strips})
+    st = parity.stepwise_parity(g, m, 0, 2, prompt, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=320)
+    print(st)
+    parity.check_stats(st, 2, parity.ERR_BF16_SMALL)
+    g.close()
+
+
 @pytest.mark.parametrize("rows,lens", [(384, (37, 300, 129, 2, 1, 260)), (128, (200, 5, 131)), (256, (129, 128, 127, 1, 64, 65))])
 def test_prompt_pass_over_several_slots(rows, lens):
     """pass_prefill_batch: ragged prompts of several sequences share tiled passes over the weights (every
