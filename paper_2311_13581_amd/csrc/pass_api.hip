@@ -432,6 +432,12 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
 // No LM head: the last prompt token stays pending and goes through the first draft call.
 struct PassSeg { int slot, pos0, rows, row_base; };
 
+// Rows above which a prompt (or a batch of prompts, whose every prompt starts on a block of 128 rows) takes the tiled
+// pass.  Measured per 7B layer: 32 rows 123 us through the decode kernels, 151 tiled; 48 rows 160 and 159; 64 rows
+// 194 and 165; 100 rows (two chunks) 318 and 184; 384 rows 1140 and 340.  A further prompt of a batch adds about 70 us
+// to a tiled pass and at least 100 us as a call of its own.
+constexpr int kTiledMinRows = 48;
+
 // How pass_prefill_batch packs prompts into tiled passes of at most `cap` rows (a multiple of 128): prompt b has
 // lens[b] - 1 rows to cache; its rows start on a block of 128 rows of a pass; what does not fit goes on in the next
 // pass.  Segments come out in launch order: rows [pos0, pos0 + rows) of `prompt` at rows row_base .. of pass `pass`.
@@ -810,12 +816,10 @@ int pass_prefill(pass_ctx *c, int slot, uint32_t seq_id, const int32_t *prompt, 
   if ((rc = poke(c, ptrs, vals))) return rc;
   if (n > 1) {
     HIP_TRY(c, hipMemcpyAsync(c->prompt_buf, prompt, sizeof(int32_t) * (n - 1), hipMemcpyHostToDevice, c->stream));
-    // long prompts on the matrix-core path: tiled kernels, up to pws.rows rows per pass over the
-    // weights; otherwise the decode kernels, prefill_chunk rows per pass.  A tiled pass costs about
-    // as much as two passes of the decode kernels however few rows it carries (a workgroup walks
-    // all of K whatever the row count), so it takes over above two chunks.
+    // longer prompts on the matrix-core path: tiled kernels, up to pws.rows rows per pass over the
+    // weights; otherwise the decode kernels, prefill_chunk rows per pass
     const bool tiled = c->use_mfma && c->P.v_transposed &&
-                       (c->opt_prefill_tiled == 1 || (c->opt_prefill_tiled < 0 && n - 1 > 2 * kMaxRows));
+                       (c->opt_prefill_tiled == 1 || (c->opt_prefill_tiled < 0 && n - 1 > kTiledMinRows));
     const int chunk = tiled ? c->pws.rows : c->opt_prefill_chunk;
     for (int done = 0; done < n - 1; done += chunk) {
       int R = std::min(chunk, n - 1 - done);
@@ -849,10 +853,10 @@ int pass_prefill_batch(pass_ctx *c, const int32_t *slots, const uint32_t *seq_id
     total += lens[b] - 1;
   }
   // the tiled kernels take rows of several sequences through one pass over the weights; where they do not
-  // apply (generic path, untransposed V pages, switched off, or too few rows to pay for a tiled pass) the
+  // apply (generic path, untransposed V pages, switched off, or too few rows: kTiledMinRows) the
   // prompts go one by one
   const bool tiled = c->use_mfma && c->P.v_transposed &&
-                     (c->opt_prefill_tiled == 1 || (c->opt_prefill_tiled < 0 && total > 2 * kMaxRows));
+                     (c->opt_prefill_tiled == 1 || (c->opt_prefill_tiled < 0 && total > kTiledMinRows));
   int rc;
   if (!tiled) {
     const int32_t *pr = prompts;

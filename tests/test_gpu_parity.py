@@ -374,6 +374,24 @@ def test_tiled_gemm_shapes(d, ffn, plen, strips):
     g.close()
 
 
+@pytest.mark.parametrize("lens", [(48,), (49,), (50,), (65,), (20, 29), (20, 30), (1, 49, 2)])
+def test_prompt_pass_by_length(lens):
+    """Default options on both sides of the row count at which a prompt, or a batch of prompts, changes from the decode
+    kernels to the tiled pass (47, 48, 49, 64 rows; 47 and 48 rows in two prompts, 49 in three), against the oracle."""
+    w = MFMA_HD128
+    W = synth.make_weights(w.shape, w.seed, w.k, w.lm_head_scale)
+    m = O.Model(w.shape, W, w.k)
+    rng = np.random.default_rng(sum(lens))
+    prompts = [rng.integers(0, w.shape.vocab, n).astype(np.int32) for n in lens]
+    slots = list(range(len(lens)))
+    g = _gpu(w.shape, W, w.k, max_slots=len(lens), max_seq_len=128, page_size=64)
+    stats = parity.batch_parity(g, m, slots, [7 + i for i in slots], prompts, slots, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=128,
+                                one_call=True)
+    for sl in slots:
+        parity.check_stats(stats[sl], 2, parity.ERR_BF16_SMALL)
+    g.close()
+
+
 @pytest.mark.parametrize("rows,lens", [(384, (37, 300, 129, 2, 1, 260)), (128, (200, 5, 131)), (256, (129, 128, 127, 1, 64, 65))])
 def test_prompt_pass_over_several_slots(rows, lens):
     """pass_prefill_batch: ragged prompts of several sequences share tiled passes over the weights (every
