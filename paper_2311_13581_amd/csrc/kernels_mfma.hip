@@ -7,9 +7,9 @@
 // adjacent 16-byte loads (1 KB, fully coalesced) and a strip of 16 output features is one
 // contiguous run of K/32 KB.  The M <= 64 activation rows are the B operand (rows padded to 16
 // per MFMA).  A workgroup of 4 to 16 wavefronts owns one strip (a gate and an up strip for
-// gate/up; up to four strips for calls with more than 8 rows) and splits K among its wavefronts;
-// the next trip's weight tiles are requested before the current trip computes; partial tiles are
-// reduced through LDS in a fixed order (deterministic).  No workgroup shares weights with another,
+// gate/up; up to eight strips for calls with more than 8 rows) and splits K among its wavefronts;
+// the next trip's weight tiles are requested before the current trip computes (calls with more than
+// 8 rows: through rings of LDS stages); partial tiles are reduced through LDS in a fixed order (deterministic).  No workgroup shares weights with another,
 // and the activation rows (tens of KB) sit in every XCD's L2, so the block-to-XCD mapping needs
 // no special order.
 //
@@ -33,7 +33,10 @@
 //   LOGITS  : RMSNorm scale, fp32 logits into the slot's logits rows
 // RMSNorm has no kernel: the producer stores (hi, lo) of h * gain and partial sums of h^2; the
 // consumer multiplies its accumulators by rsqrt(mean(h^2) + eps), which commutes with the GEMM.
+#include <limits.h>
+
 #include <algorithm>
+#include <cstdlib>
 
 #include "pass_internal.h"
 
@@ -155,6 +158,8 @@ void launch_assemble_mfma(const Params &p, const void *tok_emb, const void *look
 // ---------------------------------------------------------------------------------------------
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_GATEUP = 2, EPI_LOGITS = 3, EPI_PARTIAL = 4, EPI_GATEUP_SAVE = 5 };
 
+template <int I> struct nb_c { static constexpr int value = I; };
+
 struct GemmArgs {
   const u32x4 *W;             // packed weight tiles
   const uint16_t *X;          // activation rows as (hi, lo) tiles [ceil(M/8)][K/32][64 lanes][8]
@@ -169,119 +174,19 @@ struct GemmArgs {
   float *gu_save;             // GATEUP_SAVE: [M][2F] gate | up before the activation (what its derivative needs)
 };
 
-// MT = number of 8-row groups (one MFMA column block each); NB = output blocks per workgroup (a
-// block is one strip of 16 features, or the gate strip and the up strip of 16 FFN features).
-// Every activation tile a wavefront loads is used for all NB blocks, so the activation traffic
-// out of L2 per weight byte falls as 1/NB: that traffic, not HBM, bounds the calls with many rows.
-template <int MT, int EPI, int WAVES, int U, int NB>
-__global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArgs a) {
+// What follows the K loop, for the register and the LDS-ring form alike.  acc: this wavefront's sums over its k-tiles;
+// red: [WAVES] areas of `red_stride` 16-byte words, one of each wavefront's own, for the partial tiles of MB row groups; strip0: first strip
+// of the workgroup.
+template <int MT, int EPI, int WAVES, int NB, int NS, int MB>
+__device__ __forceinline__ void gemm_finish(const Params &p, const GemmArgs &a, floatx4 (&acc)[NS][MT], floatx4 *red, int red_stride,
+                                            float (*red_ss)[MT][8], int strip0) {
   constexpr int kGemmWaves = WAVES;
   constexpr bool GU = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE);
   constexpr int PER = GU ? 2 : 1;  // strips per block
-  constexpr int NS = NB * PER;
   constexpr bool NORM = (EPI != EPI_RESID && EPI != EPI_PARTIAL);
-  static_assert(WAVES * NS <= 32 && NB <= WAVES, "reduction buffer must fit the static LDS limit");
-  __shared__ floatx4 red[kGemmWaves][NS][64];  // one 8-row group at a time
-  __shared__ float red_ss[kGemmWaves][MT][8];
-
+  static_assert(NS == NB * PER, "strips of a workgroup");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ml = lane & 15, g = lane >> 4;  // ml: MFMA column = pseudo-row; g: k-group of 8
-  const int KT = a.K >> 5;                                        // k-tiles of the whole K (strip stride)
-  const int KTl = (EPI == EPI_PARTIAL) ? a.kt_split : KT;         // k-tiles this workgroup walks
-  const int kbase = (EPI == EPI_PARTIAL) ? blockIdx.y * KTl : 0;  // first of them
-  const int strip0 = blockIdx.x * NS;
-
-  floatx4 acc[NS][MT];
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[s][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  // Activation loads go through a buffer descriptor: a lane whose pseudo-row belongs to a row
-  // >= M gets an out-of-range offset and the hardware returns zeros without touching memory.
-  // All loads are unconditional instructions, so outstanding requests are counted exactly and a
-  // trip can wait for its activations while the next trip's weight tiles stay in flight.
-  const int n_groups = (a.M + 7) >> 3;
-  const __amdgpu_buffer_rsrc_t xr =
-      __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, n_groups * 16 * a.K * 2, 0x00020000);
-  int xoff[MT];  // byte offset of this lane's 16 bytes in k-tile 0
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    int m = mt * 8 + (ml & 7);
-    xoff[mt] = (m < a.M) ? ((mt * KT + kbase) * 64 + lane) * 16 : 0x40000000;
-  }
-  const u32x4 *wp = a.W + ((size_t)strip0 * KT + kbase) * 64 + lane;
-  // strip s of this workgroup, relative to strip0.  NB = 3 does not divide every matrix: strips
-  // past the end repeat the last one (in bounds; their results are dropped in the epilogue)
-  int soff[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) soff[s] = (NB == 3) ? min(s, a.n_strips - 1 - strip0) : s;
-
-  auto load_a = [&](u32x4 (&dst)[U][NS], int kt0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-        dst[u][s] = __builtin_nontemporal_load(wp + ((size_t)soff[s] * KT + kt0 + u * kGemmWaves) * 64);
-  };
-  auto load_b = [&](u32x4 (&dst)[U][MT], int kt0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        dst[u][mt] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff[mt] + (kt0 + u * kGemmWaves) * 1024, 0, 0);
-  };
-  auto mma = [&](const u32x4 (&av)[U][NS], const u32x4 (&bv)[U][MT]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[u][s]),
-                                                               __builtin_bit_cast(bf16x8, bv[u][mt]), acc[s][mt], 0, 0, 0);
-  };
-
-  // full trips: k-tiles kt0 + u * WAVES, u < U, with kt0 = wave + trip * WAVES * U (interleaved
-  // over the wavefronts, so the workgroup walks its strip front to back)
-  const int trip_tiles = kGemmWaves * U;
-  const int n_trips = KTl / trip_tiles;
-  if (n_trips > 0) {
-    // Both operands of trip t+1 are requested during trip t, activations first, so a trip only
-    // ever waits for requests that have had a whole trip to complete.
-    u32x4 a_cur[U][NS], a_nxt[U][NS], b_cur[U][MT], b_nxt[U][MT];
-    load_b(b_cur, wave);
-    load_a(a_cur, wave);
-    for (int t = 0; t < n_trips - 1; ++t) {
-      const int kt1 = wave + (t + 1) * trip_tiles;
-      load_b(b_nxt, kt1);
-      load_a(a_nxt, kt1);
-      mma(a_cur, b_cur);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) a_cur[u][s] = a_nxt[u][s];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) b_cur[u][mt] = b_nxt[u][mt];
-      }
-    }
-    mma(a_cur, b_cur);
-  }
-  // tail: the k-tiles that do not fill a trip, one per wavefront and step (wavefront-uniform bound)
-  for (int kt = n_trips * trip_tiles + wave; kt < KTl; kt += kGemmWaves) {
-    u32x4 bv[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) bv[mt] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff[mt] + kt * 1024, 0, 0);
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      u32x4 av = __builtin_nontemporal_load(wp + ((size_t)soff[s] * KT + kt) * 64);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
-                                                             __builtin_bit_cast(bf16x8, bv[mt]), acc[s][mt], 0, 0, 0);
-    }
-  }
-
+  const int ml = lane & 15, g = lane >> 4;
   // partial sums of h^2 (written by the producer of X) -> this wavefront's share.
   // Lane (ml & 7) covers row mt*8 + (ml & 7); the two halves of the columns take alternate partials.
   if constexpr (NORM) {
@@ -306,25 +211,28 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
       if (lane < 8) red_ss[wave][mt][lane] = ss;
     }
   }
-  // Per 8-row group: every wavefront posts its partial tiles, wavefront j < NB reduces those of
-  // block j in a fixed order, adds the lo columns to the hi columns and runs the fused epilogue.
-  // Lanes with ml < 8 hold Y[m = mt*8 + ml][n0 + 4g .. 4g+3].
+  // Per batch of 8-row groups (as many as the areas take): every wavefront posts its partial tiles, then the
+  // (row group, block) pairs are shared out: a wavefront reduces a pair's tiles in a fixed order, adds the lo columns to
+  // the hi columns and runs the fused epilogue.  Lanes with ml < 8 hold Y[m = mt*8 + ml][n0 + 4g .. 4g+3].
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    if (mt > 0) __syncthreads();  // the previous group has been read
+  for (int mt0 = 0; mt0 < MT; mt0 += MB) {
+   if (mt0 > 0) __syncthreads();  // the previous batch has been read
 #pragma unroll
-    for (int s = 0; s < NS; ++s) red[wave][s][lane] = acc[s][mt];
-    __syncthreads();
-    if (wave >= NB) continue;
-    const int blk = wave;
+   for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (mt0 + mb < MT) red[(size_t)wave * red_stride + (mb * NS + s) * 64 + lane] = acc[s][mt0 + mb < MT ? mt0 + mb : 0];
+   __syncthreads();
+   for (int u = wave; u < MB * NB; u += kGemmWaves) {
+    const int mb = u / NB, blk = u - mb * NB, mt = mt0 + mb;
     const int strip = strip0 + blk * PER;
-    if (NB == 3 && strip >= a.n_strips) continue;  // this workgroup's last block does not exist
+    if (mt >= MT || strip >= a.n_strips) continue;  // past the rows, or a block that does not exist
     floatx4 y[PER];
 #pragma unroll
     for (int s = 0; s < PER; ++s) {
-      y[s] = red[0][blk * PER + s][lane];
+      y[s] = red[(mb * NS + blk * PER + s) * 64 + lane];
 #pragma unroll
-      for (int w = 1; w < kGemmWaves; ++w) y[s] += red[w][blk * PER + s][lane];
+      for (int w = 1; w < kGemmWaves; ++w) y[s] += red[(size_t)w * red_stride + (mb * NS + blk * PER + s) * 64 + lane];
 #pragma unroll
       for (int r = 0; r < 4; ++r) y[s][r] += __shfl_xor(y[s][r], 8);
     }
@@ -421,7 +329,215 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
         }
       }
     }
+   }
   }
+}
+
+// Calls of up to 8 rows: one MFMA column block, one output block per workgroup (a block is one strip of 16 features, or
+// the gate strip and the up strip of 16 FFN features), operands through registers.
+template <int EPI, int WAVES, int U>
+__global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArgs a) {
+  constexpr int MT = 1, NB = 1, kGemmWaves = WAVES;
+  constexpr int NS = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;  // strips
+  static_assert(WAVES * NS <= 32, "reduction buffer must fit the static LDS limit");
+  __shared__ floatx4 red[kGemmWaves * NS * 64];
+  __shared__ float red_ss[kGemmWaves][MT][8];
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ml = lane & 15;  // MFMA column = pseudo-row
+  const int KT = a.K >> 5;  // k-tiles of K (strip stride)
+  const int strip0 = blockIdx.x * NS;
+
+  floatx4 acc[NS][MT];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[s][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  // Activation loads go through a buffer descriptor: a lane whose pseudo-row belongs to a row
+  // >= M gets an out-of-range offset and the hardware returns zeros without touching memory.
+  // All loads are unconditional instructions, so outstanding requests are counted exactly and a
+  // trip can wait for its activations while the next trip's weight tiles stay in flight.
+  const int n_groups = (a.M + 7) >> 3;
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, n_groups * 16 * a.K * 2, 0x00020000);
+  int xoff[MT];  // byte offset of this lane's 16 bytes in k-tile 0
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    int m = mt * 8 + (ml & 7);
+    xoff[mt] = (m < a.M) ? (mt * KT * 64 + lane) * 16 : 0x40000000;
+  }
+  const u32x4 *wp = a.W + (size_t)strip0 * KT * 64 + lane;
+
+  auto load_a = [&](u32x4 (&dst)[U][NS], int kt0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        dst[u][s] = __builtin_nontemporal_load(wp + ((size_t)s * KT + kt0 + u * kGemmWaves) * 64);
+  };
+  auto load_b = [&](u32x4 (&dst)[U][MT], int kt0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        dst[u][mt] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff[mt] + (kt0 + u * kGemmWaves) * 1024, 0, 0);
+  };
+  auto mma = [&](const u32x4 (&av)[U][NS], const u32x4 (&bv)[U][MT]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[u][s]),
+                                                               __builtin_bit_cast(bf16x8, bv[u][mt]), acc[s][mt], 0, 0, 0);
+  };
+
+  // full trips: k-tiles kt0 + u * WAVES, u < U, with kt0 = wave + trip * WAVES * U (interleaved
+  // over the wavefronts, so the workgroup walks its strip front to back)
+  const int trip_tiles = kGemmWaves * U;
+  const int n_trips = KT / trip_tiles;
+  if (n_trips > 0) {
+    // Both operands of trip t+1 are requested during trip t, activations first, so a trip only
+    // ever waits for requests that have had a whole trip to complete.
+    u32x4 a_cur[U][NS], a_nxt[U][NS], b_cur[U][MT], b_nxt[U][MT];
+    load_b(b_cur, wave);
+    load_a(a_cur, wave);
+    for (int t = 0; t < n_trips - 1; ++t) {
+      const int kt1 = wave + (t + 1) * trip_tiles;
+      load_b(b_nxt, kt1);
+      load_a(a_nxt, kt1);
+      mma(a_cur, b_cur);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) a_cur[u][s] = a_nxt[u][s];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) b_cur[u][mt] = b_nxt[u][mt];
+      }
+    }
+    mma(a_cur, b_cur);
+  }
+  // tail: the k-tiles that do not fill a trip, one per wavefront and step (wavefront-uniform bound)
+  for (int kt = n_trips * trip_tiles + wave; kt < KT; kt += kGemmWaves) {
+    u32x4 bv[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) bv[mt] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff[mt] + kt * 1024, 0, 0);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      u32x4 av = __builtin_nontemporal_load(wp + ((size_t)s * KT + kt) * 64);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
+                                                             __builtin_bit_cast(bf16x8, bv[mt]), acc[s][mt], 0, 0, 0);
+    }
+  }
+
+  gemm_finish<MT, EPI, WAVES, NB, NS, 1>(p, a, acc, red, NS * 64, red_ss, strip0);
+}
+
+// Calls with more than 8 rows: the same product with both operands in LDS rings.  Such a call pulls two to three times
+// the weights' bytes out of L2 as activation rows, every workgroup all of its rows once, and through registers a compute
+// unit draws no more than 36 B per clock whatever is in flight (measured); copies from memory to LDS run at 59.
+// Every wavefront owns a ring of D stages of one k-tile (its NS weight tiles and MT activation groups, 1 KB each), fills
+// it by itself and reads it by itself: no barrier before the final reduction, and the wavefronts' rings together keep
+// up to 150 KB of requests in flight per compute unit with no registers spent on them, so that more strips fit a
+// workgroup.  The areas of the reduction are the rings themselves, the accumulators live in the accumulation registers.
+// Measured on 7B shapes (operands through registers -> rings), 40 rows: QKV 31.1 -> 28.5 us, gate/up 39.3 -> 36.9, Wo and
+// down slices 17.7 -> 16.2 on average, LM head 63 -> 49; 64 rows: QKV 40.4 -> 37.4, gate/up 78.9 -> 46.1.  Bound by the unit's
+// vector memory path all the same: every further 8 rows (128 KB per unit at K = 4096) cost 3.3 us, 40 GB/s per unit, a
+// third of what the path delivers when nothing comes from HBM (its returns are in order, so a row out of L2 waits for
+// the weights requested before it).
+template <bool NT>
+__device__ __forceinline__ void copy_to_lds(const void *src, u32x4 *dst) {
+  // in assembly: the compiler, which cannot tell the stages apart, would wait for every copy in flight before each LDS
+  // read.  No register result; the copies of a wavefront complete in order (wait_copies leaves the youngest N in flight)
+  const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(src), "s"(off) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+  static_assert(N >= 0 && N < 64, "six bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+  asm volatile("" ::: "memory");
+}
+
+constexpr int kRingWaves = 4;  // (eight wavefronts with two stages each: 3 to 5 % slower in every product)
+constexpr int ring_stages(int waves, int tiles) { return waves * tiles * 3 <= 156 ? 3 : (waves * tiles * 2 <= 156 ? 2 : 1); }
+
+template <int MT, int EPI, int WAVES, int NB>
+__global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArgs a) {
+  constexpr int PER = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;
+  constexpr int NS = NB * PER, T = NS + MT, D = ring_stages(WAVES, T);
+  __shared__ u32x4 ring[WAVES * D * T * 64];
+  __shared__ float red_ss[WAVES][MT][8];
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KT = a.K >> 5;                                        // k-tiles of the whole K (strip stride)
+  const int KTl = (EPI == EPI_PARTIAL) ? a.kt_split : KT;         // k-tiles this workgroup walks
+  const int kbase = (EPI == EPI_PARTIAL) ? blockIdx.y * KTl : 0;  // first of them
+  const int strip0 = blockIdx.x * NS;
+
+  // strips past the end repeat the last one (in bounds; their results are dropped).  Rows >= M of the last group hold
+  // whatever the buffer holds: a column of the product depends on its own row only, and those columns are dropped.
+  const u32x4 *wp[NS], *xp[MT];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) wp[s] = a.W + ((size_t)min(strip0 + s, a.n_strips - 1) * KT + kbase + wave) * 64 + lane;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) xp[mt] = (const u32x4 *)a.X + ((size_t)mt * KT + kbase + wave) * 64 + lane;
+  u32x4 *mine = ring + wave * (D * T * 64);
+
+  floatx4 acc[NS][MT];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[s][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  // this wavefront's k-tiles: wave, wave + WAVES, ...  (the workgroup walks its strips front to back)
+  const int n = (KTl - wave + WAVES - 1) / WAVES;
+  auto issue = [&](int i, u32x4 *st) __attribute__((always_inline)) {
+    const size_t off = (size_t)i * WAVES * 64;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) copy_to_lds<false>(xp[mt] + off, st + (NS + mt) * 64);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) copy_to_lds<true>(wp[s] + off, st + s * 64);
+  };
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < n) issue(d, mine + d * T * 64);
+  int at = 0;
+  for (int i = 0; i < n; ++i) {
+    u32x4 *st = mine + at * T * 64;
+    const int left = n - 1 - i;  // stages requested after this one: min(left, D - 1)
+    if (left >= D - 1) wait_copies<(D - 1) * T>();
+    else if (D > 2 && left == 1) wait_copies<(D > 2 ? T : 0)>();
+    else wait_copies<0>();
+    u32x4 av[NS], bv[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) bv[mt] = st[(NS + mt) * 64 + lane];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) av[s] = st[s * 64 + lane];
+    if (i + D < n) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // the stage has been read: it can be filled again
+      issue(i + D, st);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[s]),
+                                                             __builtin_bit_cast(bf16x8, bv[mt]), acc[s][mt], 0, 0, 0);
+    at = at + 1 == D ? 0 : at + 1;
+  }
+  constexpr int MB = D * T / NS < MT ? D * T / NS : MT;  // row groups whose partial tiles fit a wavefront's ring
+  gemm_finish<MT, EPI, WAVES, NB, NS, MB>(p, a, acc, (floatx4 *)ring, D * T * 64, red_ss, strip0);
 }
 
 // Launch shape of the decode-sized GEMMs: GemmTuning (a member of the context, so two contexts
@@ -429,12 +545,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
 GemmTuning::GemmTuning()
     : waves{0, 0, 4, 16, 0},       // QKV, Wo, gate/up, LM head, down; 0 = by strip count (launch_gemm_epi)
       unroll{1, 1, 1, 2, 1},
-      // Calls with more than 8 rows are bound by what one compute unit can pull through its vector
-      // memory path, and every workgroup pulls all M activation rows whatever it owns of the
-      // weights: best is one workgroup per compute unit with as many blocks as that leaves it
-      // (QKV: 768 strips = 256 x 3; gate/up: 688 pairs = 230 x 3).
-      big_waves{8, 16, 4, 8, 16},
-      big_blocks{0, 1, 0, 4, 1},   // 0 = as many as leave one workgroup per compute unit
+      big_blocks{0, 0, 0, 0, 0},   // 0 = by the count of blocks (ring_blocks)
       split_ks(4) {}
 
 int GemmTuning::set(int kind, int w, int u) {
@@ -446,11 +557,10 @@ int GemmTuning::set(int kind, int w, int u) {
   return 0;
 }
 
-int GemmTuning::set_big(int kind, int w, int blocks) {
+int GemmTuning::set_big(int kind, int w, int blocks) {  // (the wavefronts are fixed: kRingWaves)
   if (kind < 0 || kind > 4) return -1;
   if (w != 4 && w != 8 && w != 16) return -1;
-  if (blocks < 0 || blocks > 4) return -1;
-  big_waves[kind] = w;
+  if (blocks < 0 || blocks > 8) return -1;
   big_blocks[kind] = blocks;
   return 0;
 }
@@ -463,27 +573,55 @@ int GemmTuning::set_split(int ks) {
 
 template <int EPI, int W, int U>
 static void launch_one(const Params &p, const GemmArgs &a, int grid, hipStream_t s) {
-  gemm_mfma_kernel<1, EPI, W, U, 1><<<grid, W * 64, 0, s>>>(p, a);
+  gemm_mfma_kernel<EPI, W, U><<<grid, W * 64, 0, s>>>(p, a);
 }
 
-template <int EPI, int W, int NB>
-static void launch_big(const Params &p, const GemmArgs &a, int n_blocks, int mt, hipStream_t s) {
+// Blocks a workgroup of the ring form may own: its accumulators (in the accumulation registers; one wavefront per SIMD)
+// and two stages of its ring must fit.
+constexpr bool ring_fits(int strips, int mt) { return strips * mt <= 64 && kRingWaves * 2 * (strips + mt) <= 156; }
+
+template <int MT, int EPI>
+static void launch_rows_mt(const Params &p, const GemmArgs &a, dim3 grid, int nb, hipStream_t s) {
   constexpr int PER = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;
-  if constexpr (W * NB * PER > 32) {
-    launch_big<EPI, 8, 1>(p, a, n_blocks, mt, s);
-  } else {
-    const int grid = (n_blocks + NB - 1) / NB;
-    constexpr int T = W * 64;
-    constexpr int U2 = (NB == 1 && W == 16) ? 2 : 1;  // two k-tiles per trip while registers allow
-    switch (mt) {
-      case 2: gemm_mfma_kernel<2, EPI, W, U2, NB><<<grid, T, 0, s>>>(p, a); break;
-      case 3: gemm_mfma_kernel<3, EPI, W, U2, NB><<<grid, T, 0, s>>>(p, a); break;
-      case 4: gemm_mfma_kernel<4, EPI, W, U2, NB><<<grid, T, 0, s>>>(p, a); break;
-      case 5: gemm_mfma_kernel<5, EPI, W, 1, NB><<<grid, T, 0, s>>>(p, a); break;
-      case 6: gemm_mfma_kernel<6, EPI, W, 1, NB><<<grid, T, 0, s>>>(p, a); break;
-      case 7: gemm_mfma_kernel<7, EPI, W, 1, NB><<<grid, T, 0, s>>>(p, a); break;
-      default: gemm_mfma_kernel<8, EPI, W, 1, NB><<<grid, T, 0, s>>>(p, a); break;
-    }
+  auto go = [&](auto B) {
+    constexpr int NB = decltype(B)::value;
+    if constexpr (ring_fits(NB * PER, MT)) gemm_rows_kernel<MT, EPI, kRingWaves, NB><<<grid, kRingWaves * 64, 0, s>>>(p, a);
+  };
+  switch (nb) {
+    case 1: go(nb_c<1>{}); break;
+    case 2: go(nb_c<2>{}); break;
+    case 3: go(nb_c<3>{}); break;
+    case 4: go(nb_c<4>{}); break;
+    case 5: go(nb_c<5>{}); break;
+    case 6: go(nb_c<6>{}); break;
+    default: go(nb_c<8>{}); break;
+  }
+}
+// Blocks per workgroup (1 .. 6 or 8).  A workgroup pulls all M rows whatever it owns, and a compute unit holds one: the
+// product takes (rounds of 256 workgroups) x (operand tiles per k-tile).  `want` > 0 asks for a number.
+static int ring_blocks(int want, int n_blocks, int per, int mt, int slices) {
+  int best = 1, best_cost = INT_MAX;
+  for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
+    if (!ring_fits(nb * per, mt)) continue;
+    const int cost = want ? std::abs(nb - want) : (((n_blocks + nb - 1) / nb * slices + 255) / 256) * (nb * per + mt);
+    if (cost < best_cost) { best_cost = cost; best = nb; }
+  }
+  return best;
+}
+template <int EPI>
+static void launch_rows(const Params &p, const GemmArgs &a, int n_blocks, int want, int slices, hipStream_t s) {
+  constexpr int PER = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;
+  const int mt = (a.M + 7) / 8, nb = ring_blocks(want, n_blocks, PER, mt, slices);
+  const dim3 grid((n_blocks + nb - 1) / nb, slices);
+  switch (mt) {
+    case 1: if constexpr (EPI == EPI_PARTIAL) launch_rows_mt<1, EPI>(p, a, grid, nb, s); break;
+    case 2: launch_rows_mt<2, EPI>(p, a, grid, nb, s); break;
+    case 3: launch_rows_mt<3, EPI>(p, a, grid, nb, s); break;
+    case 4: launch_rows_mt<4, EPI>(p, a, grid, nb, s); break;
+    case 5: launch_rows_mt<5, EPI>(p, a, grid, nb, s); break;
+    case 6: launch_rows_mt<6, EPI>(p, a, grid, nb, s); break;
+    case 7: launch_rows_mt<7, EPI>(p, a, grid, nb, s); break;
+    default: launch_rows_mt<8, EPI>(p, a, grid, nb, s); break;
   }
 }
 
@@ -514,31 +652,15 @@ static void launch_gemm_epi(const Params &p, const GemmTuning &tn, const GemmArg
     }
     return;
   }
-  int w = tn.big_waves[kind], nb = tn.big_blocks[kind];
-  if (nb == 0) nb = std::min(PER == 2 ? 3 : 4, (n_blocks + 255) / 256);  // 7B: QKV 768 / 256 = 3, gate/up 688 pairs -> 3
-  if (mt == 8 && nb == 4) nb = 2;                 // 64 rows x 4 blocks does not fit the register file
-  if (nb == 3 && mt * PER > 10) nb = 2;           // nor do 3 blocks of more than 40 rows (gate/up) / 80
-  while (nb != 3 && nb > 1 && n_blocks % nb != 0) nb >>= 1;  // a workgroup's blocks must all exist (3: the kernel copes)
-  switch (w * 10 + nb) {
-    case 161: launch_big<EPI, 16, 1>(p, a, n_blocks, mt, s); break;
-    case 162: launch_big<EPI, 16, 2>(p, a, n_blocks, mt, s); break;
-    case 81: launch_big<EPI, 8, 1>(p, a, n_blocks, mt, s); break;
-    case 82: launch_big<EPI, 8, 2>(p, a, n_blocks, mt, s); break;
-    case 84: launch_big<EPI, 8, 4>(p, a, n_blocks, mt, s); break;
-    case 83: launch_big<EPI, 8, 3>(p, a, n_blocks, mt, s); break;
-    case 43: launch_big<EPI, 4, 3>(p, a, n_blocks, mt, s); break;
-    case 41: launch_big<EPI, 4, 1>(p, a, n_blocks, mt, s); break;
-    case 42: launch_big<EPI, 4, 2>(p, a, n_blocks, mt, s); break;
-    case 44: launch_big<EPI, 4, 4>(p, a, n_blocks, mt, s); break;
-    default: launch_big<EPI, 16, 1>(p, a, n_blocks, mt, s); break;
-  }
+  launch_rows<EPI>(p, a, n_blocks, tn.big_blocks[kind], 1, s);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Residual projections (Wo, down) of calls with more than 8 rows.  N = d gives only d/16 strips,
 // one per compute unit at best, and every workgroup would have to pull all M activation rows
 // through its L1: that traffic, not HBM, bounds the kernel.  So K is cut into KS slices across
-// workgroups that each own 4 strips (an activation tile fetched is used 4 times); the slices'
+// workgroups that own that many times the strips (7B: 4 slices, 4 strips; 8 and 8 took 23.2 us for down where
+// these take 22.0, 2 and 2 took 27.7); the slices'
 // sums go to a workspace and this kernel adds them in slice order (deterministic), then does what
 // the fused epilogue does: residual add into h, (hi, lo) of h * gain of the next norm, per-strip
 // partial sums of h^2.  One workgroup per strip of 16 features: thread = (row, 4 features).
@@ -573,28 +695,15 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(Params p, const float
   if ((threadIdx.x & 3) == 0) p.ssq[(size_t)strip * kMaxRows + m] = ss;  // rows >= M get 0
 }
 
-// wavefronts per workgroup and strips per workgroup of the split residual GEMM (K slices: GemmTuning)
-constexpr int kSplitWaves = 8, kSplitBlocks = 4;
-
-static bool launch_resid_split(const Params &p, const GemmTuning &tn, const GemmArgs &a0, int mt, hipStream_t s) {
+static bool launch_resid_split(const Params &p, const GemmTuning &tn, const GemmArgs &a0, int mt, int kind, hipStream_t s) {
   const int n_strips = p.d / 16, KT = a0.K >> 5, KS = tn.split_ks;
-  if (KS < 2 || n_strips % kSplitBlocks != 0 || KT % KS != 0) return false;
+  if (KS < 2 || KT % KS != 0) return false;
   if ((size_t)KS * p.d > (size_t)2 * p.F) return false;  // the slices' sums borrow the generic path's gate/up workspace
   GemmArgs a = a0;
   a.kt_split = KT / KS;
   a.partial = p.gu;
   a.ldy = p.d;
-  dim3 grid(n_strips / kSplitBlocks, KS);
-  constexpr int T = kSplitWaves * 64;
-  switch (mt) {
-    case 2: gemm_mfma_kernel<2, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 3: gemm_mfma_kernel<3, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 4: gemm_mfma_kernel<4, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 5: gemm_mfma_kernel<5, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 6: gemm_mfma_kernel<6, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 7: gemm_mfma_kernel<7, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    default: gemm_mfma_kernel<8, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-  }
+  launch_rows<EPI_PARTIAL>(p, a, n_strips, tn.big_blocks[kind], KS, s);
   resid_reduce_kernel<<<n_strips, 256, 0, s>>>(p, a.partial, KS, a.M, a.gain_next);
   return true;
 }
@@ -606,7 +715,7 @@ void launch_gemm_qkv(const Params &p, const GemmTuning &tn, const void *W, int l
 void launch_gemm_resid(const Params &p, const GemmTuning &tn, const void *W, const uint16_t *X, int K,
                        const void *gain_next, int M, hipStream_t s) {
   GemmArgs a{(const u32x4 *)W, X, M, K, 0, (const uint16_t *)gain_next, nullptr, 0, nullptr, p.d / 16};
-  if (M > 8 && launch_resid_split(p, tn, a, (M + 7) / 8, s)) return;
+  if (M > 8 && launch_resid_split(p, tn, a, (M + 7) / 8, K == p.F ? 4 : 1, s)) return;
   launch_gemm_epi<EPI_RESID>(p, tn, a, p.d / 16, s, K == p.F ? 4 : 1);  // the down projection has its own shape
 }
 void launch_gemm_gateup(const Params &p, const GemmTuning &tn, const void *W, int M, hipStream_t s) {
@@ -628,16 +737,12 @@ void launch_gemm_gateup_save(const Params &p, const void *W, float *gu_save, int
   const int n_blocks = p.F / 16, mt = (M + 7) / 8;
   if (mt == 1)
     launch_one<EPI_GATEUP_SAVE, 4, 1>(p, a, n_blocks, s);
-  else if (mt <= 5)
-    launch_big<EPI_GATEUP_SAVE, 4, 3>(p, a, n_blocks, mt, s);
-  else if (n_blocks % 2 == 0)  // three blocks of more than 40 rows do not fit the register file
-    launch_big<EPI_GATEUP_SAVE, 4, 2>(p, a, n_blocks, mt, s);
   else
-    launch_big<EPI_GATEUP_SAVE, 4, 1>(p, a, n_blocks, mt, s);
+    launch_rows<EPI_GATEUP_SAVE>(p, a, n_blocks, 0, 1, s);
 }
 
 // Plain product Y = X W^T on packed tiles: X as (hi, lo) tiles of K features, W packed [N][K], Y fp32.
-// K is cut into KS slices across workgroups of 8 wavefronts that own 4 strips each; slice ks leaves its
+// K is cut into KS slices across workgroups; slice ks leaves its
 // sums in part[ks][kMaxRows][N] and the consumer adds the slices in order.  Needs N % 64 == 0 and
 // (K / 32) % KS == 0; returns the KS it used (plain_gemm_slices: what the consumer must add up).
 int plain_gemm_slices(int N, int K) {
@@ -653,18 +758,7 @@ int plain_gemm_slices(int N, int K) {
 int launch_gemm_plain(const Params &p, const void *W, const uint16_t *X, int M, int N, int K, float *part, hipStream_t s) {
   const int KS = plain_gemm_slices(N, K);
   GemmArgs a{(const u32x4 *)W, X, M, K, 0, nullptr, nullptr, (K / 32) / KS, part, N / 16, N, nullptr};
-  dim3 grid(N / 64, KS);
-  constexpr int T = kSplitWaves * 64;
-  switch ((M + 7) / 8) {
-    case 1: gemm_mfma_kernel<1, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 2: gemm_mfma_kernel<2, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 3: gemm_mfma_kernel<3, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 4: gemm_mfma_kernel<4, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 5: gemm_mfma_kernel<5, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 6: gemm_mfma_kernel<6, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    case 7: gemm_mfma_kernel<7, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-    default: gemm_mfma_kernel<8, EPI_PARTIAL, kSplitWaves, 1, kSplitBlocks><<<grid, T, 0, s>>>(p, a); break;
-  }
+  launch_rows<EPI_PARTIAL>(p, a, N / 16, 0, KS, s);
   return KS;
 }
 

@@ -1549,7 +1549,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   //   tune.gemm_cfg       launch shape of the decode-sized matrix-core GEMMs of this context:
   //                       kind * 10000 + wavefronts * 100 + unroll (kind 0 QKV, 1 Wo, 2 gate/up, 3 LM head, 4 down;
   //                       wavefronts 4/8/16; unroll 1/2/4); calls with more than 8 rows: 1000000 + kind * 10000 +
-  //                       wavefronts * 100 + blocks (strips of 16 output features per workgroup, 0..4);
+  //                       400 + blocks (strips of 16 output features, or gate / up pairs, per workgroup, 0..8);
   //                       2000000 + K slices of the split residual GEMM (0 = never split)
   //   tune.prefill_rows   prompt rows per pass of the tiled prompt pass (a multiple of 128)
   //   tune.prefill_tile   query rows per attention workgroup of the tiled prompt pass (0, 16, 32, 128)
@@ -1562,7 +1562,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
     } else if (value >= 1000000) {
       int v = value - 1000000;
       if (c->tuning.set_big(v / 10000, (v / 100) % 100, v % 100))
-        return fail(c, PASS_EINVAL, "tune.gemm_cfg (more than 8 rows): kind 0..4, wavefronts 4/8/16, blocks 0..4");
+        return fail(c, PASS_EINVAL, "tune.gemm_cfg (more than 8 rows): kind 0..4, wavefronts 4/8/16, blocks 0..8");
     } else if (c->tuning.set(value / 10000, (value / 100) % 100, value % 100))
       return fail(c, PASS_EINVAL, "tune.gemm_cfg: kind 0..4, wavefronts 4/8/16, unroll 1/2/4");
     for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.second);  // captured launches carry the old shape

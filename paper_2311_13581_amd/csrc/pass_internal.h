@@ -176,11 +176,11 @@ void launch_assemble_mfma(const Params &p, const void *tok_emb, const void *look
 // 3 LM head, 4 down.  The "tune.gemm_cfg" option writes it (see pass_set_option in pass_api.hip).
 struct GemmTuning {
   int waves[5], unroll[5];          // calls of up to 8 rows: wavefronts per workgroup (0 = by strip count), k-tiles per trip
-  int big_waves[5], big_blocks[5];  // calls with more than 8 rows: wavefronts and output blocks per workgroup
+  int big_blocks[5];                // calls with more than 8 rows: output blocks per workgroup (0 = by their count)
   int split_ks;                     // K slices of the split residual GEMMs (0 = never split)
   GemmTuning();
   int set(int kind, int w, int u);            // wavefronts 4/8/16, k-tiles per trip 1/2/4; -1 = rejected
-  int set_big(int kind, int w, int blocks);   // wavefronts 4/8/16, blocks 0..4
+  int set_big(int kind, int w, int blocks);   // blocks 0..8 (wavefronts: 4/8/16 accepted, no effect)
   int set_split(int ks);                      // 0..8
 };
 void launch_gemm_qkv(const Params &p, const GemmTuning &tn, const void *W, int layer, int M, hipStream_t s);

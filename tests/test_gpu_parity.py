@@ -374,6 +374,28 @@ def test_tiled_gemm_shapes(d, ffn, plen, strips):
     g.close()
 
 
+@pytest.mark.parametrize("slots,k,blocks", [(2, 4, 1), (3, 5, 2), (4, 7, 3), (8, 4, 4), (6, 7, 5), (7, 7, 6), (8, 7, 8), (5, 2, 0), (8, 7, 0)])
+@pytest.mark.parametrize("d,ffn", [(32, 32), (96, 160), (544, 1184)])
+def test_row_gemm_shapes(d, ffn, slots, k, blocks):
+    """The decode GEMM of calls with more than 8 rows: 10 .. 64 rows (two to eight 8-row groups, the last one full or not),
+    every number of blocks per workgroup (0: by their count; more than a matrix has, and counts that do not divide it), and
+    one, three, four, five, 17 and 37 k-tiles against rings of two or three stages in four wavefronts (wavefronts with no
+    tile, with fewer tiles than stages, with a remainder).  Every slot follows the oracle."""
+    shape = synth.ModelShape(2, d, 1, 128, ffn, 1008, dtype=synth.BF16)
+    W = synth.make_weights(shape, 6, k, 6.0)
+    m = O.Model(shape, W, k)
+    rng = np.random.default_rng(slots * 16 + k)
+    prompts = [rng.integers(0, shape.vocab, int(n)).astype(np.int32) for n in rng.integers(2, 20, slots)]
+    g = _gpu(shape, W, k, max_slots=slots, max_seq_len=64, page_size=32)
+    for kind in range(5):
+        g.set_option("tune.gemm_cfg", 1000000 + kind * 10000 + 400 + blocks)
+    ids = list(range(slots))
+    stats = parity.batch_parity(g, m, ids, [3 + i for i in ids], prompts, ids, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=64)
+    for sl in ids:
+        parity.check_stats(stats[sl], 2, parity.ERR_BF16_SMALL)
+    g.close()
+
+
 @pytest.mark.parametrize("lens", [(48,), (49,), (50,), (65,), (20, 29), (20, 30), (1, 49, 2)])
 def test_prompt_pass_by_length(lens):
     """Default options on both sides of the row count at which a prompt, or a batch of prompts, changes from the decode
