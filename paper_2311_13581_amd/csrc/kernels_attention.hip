@@ -69,23 +69,40 @@ template <typename T, int DPL> struct RawChunk;
 template <int DPL> struct RawChunk<float, DPL> { float4 v[DPL / 4]; };
 template <int DPL> struct RawChunk<bf16_t, DPL> { uint32_t v[DPL / 2]; };
 
-template <typename T, int HD>
-__global__ __launch_bounds__(256) void attn_split_kernel(Params p, int layer, int R) {
+// Where every group of a launch has one split (`direct`), its workgroups write the rows themselves, in the bits the merge
+// kernel would give them (a merge of one triple multiplies by one), and no merge kernel runs.
+__device__ __forceinline__ void store_attn_split(const Params &p, int m, int head_dim_index, float o) {
+  const uint16_t hi = f32_to_bf16(o);
+  const size_t xi = xs_index(m, p.D, head_dim_index);
+  p.attn_x[xi] = hi;
+  p.attn_x[xi + kXsLoOffset] = f32_to_bf16(o - bf16_to_f32(hi));
+}
+
+// RQ: rows carried in registers (rows of a group, rounded up to 4 or 8: a row's arithmetic does not depend on it)
+template <typename T, int HD, int RQ>
+__global__ __launch_bounds__(256) void attn_split_kernel(Params p, int layer, int R, int direct) {
   constexpr int DPL = HD / 16;
-  constexpr int RQ = kAttnRowsPerGroup;
   constexpr int KU = 4;    // keys per 16-lane group and iteration
   constexpr int NG = 16;   // 16-lane groups per workgroup
   __shared__ float s_m[NG][RQ], s_l[NG][RQ];
   __shared__ float s_acc[NG][RQ][HD];
 
   const int split = blockIdx.x, head = blockIdx.y, g = blockIdx.z;
-  const int groups_per_slot = (R + RQ - 1) / RQ;
+  const int groups_per_slot = (R + kAttnRowsPerGroup - 1) / kAttnRowsPerGroup;
   const int b = g / groups_per_slot;
-  const int r0 = (g % groups_per_slot) * RQ;
-  const int nr = min(RQ, R - r0);
+  const int r0 = (g % groups_per_slot) * kAttnRowsPerGroup;
+  const int nr = min(kAttnRowsPerGroup, R - r0);
   const int slot = p.row_slot[b * R + r0];
-  if (slot < 0) return;  // dead rows (beyond the slot's capacity): the merge kernel writes zeros
   const int pos0 = p.row_pos[b * R + r0];  // position of the group's first row
+  if (slot < 0) {  // dead rows (beyond the slot's capacity): zeros, from here or from the merge kernel
+    if (direct)
+      for (int e = threadIdx.x; e < nr * HD; e += 256) {
+        const int m = b * R + r0 + e / HD, c = head * HD + e % HD;
+        if (direct == 2) store_attn_split(p, m, c, 0.f);
+        else p.attn[(size_t)m * p.D + c] = 0.f;
+      }
+    return;
+  }
   const int n_keys = pos0 + nr;
   int n_splits, chunk;
   split_plan(n_keys, n_splits, chunk);
@@ -175,6 +192,12 @@ __global__ __launch_bounds__(256) void attn_split_kernel(Params p, int layer, in
       l_n += s_l[w][r] * f;
       v += s_acc[w][r][dim] * f;
     }
+    if (direct) {
+      const int m = b * R + r0 + r, c = head * HD + dim;
+      if (direct == 2) store_attn_split(p, m, c, v / l_n);
+      else p.attn[(size_t)m * p.D + c] = v / l_n;
+      continue;
+    }
     size_t pi = pbase + (size_t)r * p.H * kMaxSplits + split;
     p.part_acc[pi * HD + dim] = v;
     if (dim == 0) { p.part_m[pi] = m_n; p.part_l[pi] = l_n; }
@@ -199,7 +222,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void attn_split_mfma_kernel(Params p, int layer, int R) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void attn_split_mfma_kernel(Params p, int layer, int R, int direct) {
   constexpr int HD = 128, RQ = kAttnRowsPerGroup;
   __shared__ float s_m[4][RQ], s_l[4][RQ];
   __shared__ float s_acc[4][RQ][HD];
@@ -219,7 +242,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const int n_keys = pos0 + nr;
   int n_splits, chunk;
   split_plan_mfma(n_keys, p.H, n_splits, chunk);
-  if (slot < 0 || split >= n_splits) return;
+  if (slot < 0 || split >= n_splits) {
+    if (direct && slot < 0)
+      for (int e = threadIdx.x; e < nr * HD; e += 256) store_attn_split(p, m0 + e / HD, head * HD + e % HD, 0.f);
+    return;
+  }
   const int k_lo = split * chunk;
   const int k_hi = min(n_keys, k_lo + chunk);
 
@@ -365,6 +392,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       l_n += s_l[w][r] * f;
       v += s_acc[w][r][dim] * f;
     }
+    if (direct) {
+      store_attn_split(p, m0 + r, head * HD + dim, v / l_n);
+      continue;
+    }
     size_t pi = pbase + (size_t)r * p.H * kMaxSplits + split;
     p.part_acc[pi * HD + dim] = v;
     if (dim == 0) { p.part_m[pi] = m_n; p.part_l[pi] = l_n; }
@@ -450,6 +481,8 @@ __global__ __launch_bounds__(HD * Q) void attn_combine_kernel(Params p, int R, i
   }
 }
 
+template <int I> struct hd_c { static constexpr int value = I; };
+
 template <int HD>
 static void launch_combine(const Params &p, dim3 cgrid, int R, int n_splits, int out_split, int mfma_plan,
                            hipStream_t s) {
@@ -470,23 +503,29 @@ void launch_attention(const Params &p, int dtype, int layer, int B, int R, int n
                       hipStream_t s) {
   int groups = B * ((R + kAttnRowsPerGroup - 1) / kAttnRowsPerGroup);
   dim3 grid(n_splits, p.H, groups), cgrid(B * R, p.H);
-  if (p.v_transposed) {  // bf16, head_dim 128, page_size % 32 == 0: matrix-core kernel
-    attn_split_mfma_kernel<<<grid, 256, 0, s>>>(p, layer, R);
-    launch_combine<128>(p, cgrid, R, n_splits, out_split, 1, s);
+  // one split whatever the group: the split kernel finishes the rows (training also wants their ln-sum-exp: the merge kernel)
+  const int direct = n_splits == 1 && p.lse == nullptr ? 1 + out_split : 0;
+  auto merge = [&](auto HD, int mfma_plan) {
+    if (!direct) launch_combine<decltype(HD)::value>(p, cgrid, R, n_splits, out_split, mfma_plan, s);
+  };
+  if (p.v_transposed) {  // bf16, head_dim 128, page_size % 32 == 0: matrix-core kernel (its rows leave as (hi, lo) tiles)
+    attn_split_mfma_kernel<<<grid, 256, 0, s>>>(p, layer, R, direct);
+    merge(hd_c<128>{}, 1);
     return;
   }
+  auto go = [&](auto T, auto HD) {
+    typedef decltype(T) E;
+    constexpr int D = decltype(HD)::value;
+    if (R <= 4) attn_split_kernel<E, D, 4><<<grid, 256, 0, s>>>(p, layer, R, direct);
+    else attn_split_kernel<E, D, kAttnRowsPerGroup><<<grid, 256, 0, s>>>(p, layer, R, direct);
+    merge(HD, 0);
+  };
   if (p.hd == 128) {
-    if (dtype == PASS_F32)
-      attn_split_kernel<float, 128><<<grid, 256, 0, s>>>(p, layer, R);
-    else
-      attn_split_kernel<bf16_t, 128><<<grid, 256, 0, s>>>(p, layer, R);
-    launch_combine<128>(p, cgrid, R, n_splits, out_split, 0, s);
+    if (dtype == PASS_F32) go(0.f, hd_c<128>{});
+    else go(bf16_t{}, hd_c<128>{});
   } else {
-    if (dtype == PASS_F32)
-      attn_split_kernel<float, 64><<<grid, 256, 0, s>>>(p, layer, R);
-    else
-      attn_split_kernel<bf16_t, 64><<<grid, 256, 0, s>>>(p, layer, R);
-    launch_combine<64>(p, cgrid, R, n_splits, out_split, 0, s);
+    if (dtype == PASS_F32) go(0.f, hd_c<64>{});
+    else go(bf16_t{}, hd_c<64>{});
   }
 }
 

@@ -204,6 +204,191 @@ void launch_silu_mul(const Params &p, int M, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// The decode step's GEMMs with everything around them folded in (five kernels per layer instead of ten; a call of the
+// tiny fp32 model is a chain of dependent launches of 2 to 5 us each and nothing else):
+//   QKV     RMSNorm, rotary embedding, q to the workspace, K/V rows into the paged cache
+//   RESID   residual add into h
+//   GATEUP  RMSNorm, silu(gate) * up
+//   LOGITS  RMSNorm, logits of row m into row rowmap[m]
+// One wavefront per pair of output columns (a rotary pair; a gate column and its up column; two neighbours), lanes
+// stride over K in chunks of VEC elements, MB rows at a time.  RMSNorm: the dot product runs over x * gain and is
+// scaled by 1 / rms at the end, the sum of x^2 comes out of the same pass over the row (every wavefront reads all of
+// every row anyway).  A row's arithmetic depends on the shape only, not on what shares its call.  Rows past the last one
+// repeat it and are dropped, so that all loads are unconditional and leave together; what the epilogue needs is
+// requested before the loop.  Measured on the tiny model (d 256, three rows),
+// per call: 25 kernels and 104 us -> 13 and 50 us, with the attention merge of one split gone as well.
+// ---------------------------------------------------------------------------------------------
+enum { ROW_QKV = 0, ROW_RESID = 1, ROW_GATEUP = 2, ROW_LOGITS = 3 };
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, false));
+}
+// sum over the wavefront, in every lane
+__device__ __forceinline__ float wave_total(float v) {
+  v = dpp_add<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
+  v = dpp_add<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
+  v = dpp_add<0x141, 0xF>(v);  // row_half_mirror
+  v = dpp_add<0x140, 0xF>(v);  // row_mirror: every lane has its row of 16
+  v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3: lane 63 has all
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+template <int VEC>
+__device__ __forceinline__ void load_vec(const float *w, float (&o)[VEC]) {
+#pragma unroll
+  for (int i = 0; i < VEC; i += 4) {
+    const float4 a = *(const float4 *)(w + i);
+    o[i] = a.x; o[i + 1] = a.y; o[i + 2] = a.z; o[i + 3] = a.w;
+  }
+}
+template <int VEC>
+__device__ __forceinline__ void load_vec(const bf16_t *w, float (&o)[VEC]) {
+#pragma unroll
+  for (int i = 0; i < VEC; i += 4) {
+    const uint2 a = *(const uint2 *)(w + i);
+    o[i] = __uint_as_float(a.x << 16); o[i + 1] = __uint_as_float(a.x & 0xffff0000u);
+    o[i + 2] = __uint_as_float(a.y << 16); o[i + 3] = __uint_as_float(a.y & 0xffff0000u);
+  }
+}
+
+struct RowGemm {
+  const float *X;       // [M][K]
+  const void *W, *gain; // [N][K], [K] (RESID: unused)
+  float *out;           // RESID: h, GATEUP: act, LOGITS: logits; QKV: the qkv workspace
+  const int32_t *rowmap;
+  int M, N, K, layer;   // N: output columns (GATEUP: gate and up together)
+};
+
+template <typename T, int EPI, int VEC, int MB>
+__global__ __launch_bounds__(256) void row_gemm_kernel(Params p, RowGemm a) {
+  constexpr bool NORM = (EPI != ROW_RESID);
+  const int lane = threadIdx.x & 63;
+  const int pr = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // pair of columns
+  const int c0 = EPI == ROW_GATEUP ? pr : 2 * pr;
+  const int n_pairs = (a.N + 1) / 2;
+  if (pr >= n_pairs) return;
+  const int c1 = EPI == ROW_GATEUP ? a.N / 2 + pr : min(2 * pr + 1, a.N - 1);
+  const T *w0 = (const T *)a.W + (size_t)c0 * a.K, *w1 = (const T *)a.W + (size_t)c1 * a.K, *gn = (const T *)a.gain;
+  for (int m0 = 0; m0 < a.M; m0 += MB) {
+    const int mine = min(m0 + (lane < MB ? lane : 0), a.M - 1);  // the row this lane finishes
+    // what the epilogue of that row needs
+    int slot = 0, pos = 0, page = 0, orow = mine;
+    float cs = 0.f, sn = 0.f, h0 = 0.f, h1 = 0.f;
+    const int proj = EPI == ROW_QKV ? c0 / p.D : 0;       // 0 q, 1 k, 2 v
+    const int col = c0 - proj * p.D;
+    if constexpr (EPI == ROW_QKV) {
+      const int half = p.hd / 2, i = (col % p.hd) >> 1;
+      slot = p.row_slot[mine];
+      pos = p.row_pos[mine];
+      cs = p.rope_cos[(size_t)mine * half + i];
+      sn = p.rope_sin[(size_t)mine * half + i];
+      page = p.block_table[(size_t)max(slot, 0) * p.pages_per_seq + (pos >> p.page_shift)];
+    } else if constexpr (EPI == ROW_RESID) {
+      h0 = a.out[(size_t)mine * a.N + c0];
+      h1 = a.out[(size_t)mine * a.N + c1];
+    } else if constexpr (EPI == ROW_LOGITS) {
+      orow = a.rowmap[mine];
+    }
+    float s0[MB], s1[MB], sq[MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) s0[i] = s1[i] = sq[i] = 0.f;
+    for (int k0 = lane * VEC; k0 < a.K; k0 += 64 * VEC) {
+      float u[VEC], v[VEC], g[VEC], x[MB][VEC];
+      load_vec<VEC>(w0 + k0, u);
+      load_vec<VEC>(w1 + k0, v);
+      if constexpr (NORM) load_vec<VEC>(gn + k0, g);
+#pragma unroll
+      for (int i = 0; i < MB; ++i) load_vec<VEC>(a.X + (size_t)min(m0 + i, a.M - 1) * a.K + k0, x[i]);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          float t = x[i][e];
+          if constexpr (NORM) {
+            sq[i] = fmaf(t, t, sq[i]);
+            t *= g[e];
+          }
+          s0[i] = fmaf(u[e], t, s0[i]);
+          s1[i] = fmaf(v[e], t, s1[i]);
+        }
+    }
+    // lane i < MB ends with the two columns of row m0 + i
+    float y0 = 0.f, y1 = 0.f, ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      const float t0 = wave_total(s0[i]), t1 = wave_total(s1[i]);
+      y0 = lane == i ? t0 : y0;
+      y1 = lane == i ? t1 : y1;
+      if constexpr (NORM) {
+        const float tq = wave_total(sq[i]);
+        ss = lane == i ? tq : ss;
+      }
+    }
+    if (lane >= MB || m0 + lane >= a.M) continue;
+    if constexpr (NORM) {
+      const float inv = 1.0f / sqrtf(ss / (float)a.K + p.eps);
+      y0 *= inv;
+      y1 *= inv;
+    }
+    if constexpr (EPI == ROW_QKV) {
+      float *q = a.out + (size_t)mine * 3 * p.D;
+      const float r0 = proj < 2 ? y0 * cs - y1 * sn : y0, r1 = proj < 2 ? y0 * sn + y1 * cs : y1;
+      if (proj == 0) {
+        *(float2 *)(q + col) = make_float2(r0, r1);
+      } else if (slot >= 0) {  // a dead row (see row_is_dead) has no place in the cache
+        const int head = col / p.hd, dim = col - head * p.hd;
+        T *pool = (T *)(proj == 1 ? p.k_pool : p.v_pool);
+        const size_t off = ((((size_t)a.layer * p.n_pages + page) * p.H + head) * p.page_size + (pos & (p.page_size - 1))) * (size_t)p.hd + dim;
+        store_f(pool, off, r0);
+        store_f(pool, off + 1, r1);
+      }
+    } else if constexpr (EPI == ROW_GATEUP) {
+      a.out[(size_t)mine * (a.N / 2) + pr] = y0 / (1.0f + __expf(-y0)) * y1;
+    } else if constexpr (EPI == ROW_RESID) {
+      a.out[(size_t)mine * a.N + c0] = h0 + y0;
+      if (c1 != c0) a.out[(size_t)mine * a.N + c1] = h1 + y1;
+    } else {
+      a.out[(size_t)orow * a.N + c0] = y0;
+      if (c1 != c0) a.out[(size_t)orow * a.N + c1] = y1;
+    }
+  }
+}
+
+template <typename T, int EPI>
+static void launch_row_gemm(const Params &p, const RowGemm &a, hipStream_t s) {
+  const int grid = ((a.N + 1) / 2 + 3) / 4;
+  // chunks of 4 below K = 512: with 8 half of the lanes would have nothing to do at K = 256.  (The chunk decides the
+  // order of a row's sums: it follows K alone.)
+  if (a.K < 512) {
+    if (a.M <= 2) row_gemm_kernel<T, EPI, 4, 2><<<grid, 256, 0, s>>>(p, a);
+    else if (a.M <= 4) row_gemm_kernel<T, EPI, 4, 4><<<grid, 256, 0, s>>>(p, a);
+    else row_gemm_kernel<T, EPI, 4, 8><<<grid, 256, 0, s>>>(p, a);
+  } else {
+    if (a.M <= 2) row_gemm_kernel<T, EPI, 8, 2><<<grid, 256, 0, s>>>(p, a);
+    else if (a.M <= 4) row_gemm_kernel<T, EPI, 8, 4><<<grid, 256, 0, s>>>(p, a);
+    else row_gemm_kernel<T, EPI, 8, 8><<<grid, 256, 0, s>>>(p, a);
+  }
+}
+template <int EPI>
+static void launch_row_gemm_dt(int dtype, const Params &p, const RowGemm &a, hipStream_t s) {
+  if (dtype == PASS_F32) launch_row_gemm<float, EPI>(p, a, s);
+  else launch_row_gemm<bf16_t, EPI>(p, a, s);
+}
+void launch_row_qkv(const Params &p, int dtype, const void *gain, const void *W, int layer, int M, hipStream_t s) {
+  launch_row_gemm_dt<ROW_QKV>(dtype, p, RowGemm{p.h, W, gain, p.qkv, nullptr, M, 3 * p.D, p.d, layer}, s);
+}
+void launch_row_resid(const Params &p, int dtype, const float *X, const void *W, int K, int M, hipStream_t s) {
+  launch_row_gemm_dt<ROW_RESID>(dtype, p, RowGemm{X, W, nullptr, p.h, nullptr, M, p.d, K, 0}, s);
+}
+void launch_row_gateup(const Params &p, int dtype, const void *gain, const void *W, int M, hipStream_t s) {
+  launch_row_gemm_dt<ROW_GATEUP>(dtype, p, RowGemm{p.h, W, gain, p.act, nullptr, M, 2 * p.F, p.d, 0}, s);
+}
+void launch_row_logits(const Params &p, int dtype, const void *gain, const void *W, float *logits, int M, hipStream_t s) {
+  launch_row_gemm_dt<ROW_LOGITS>(dtype, p, RowGemm{p.h, W, gain, logits, p.row_out, M, p.V, p.d, 0}, s);
+}
+
+// ---------------------------------------------------------------------------------------------
 // small utilities
 // ---------------------------------------------------------------------------------------------
 struct PokeArgs {

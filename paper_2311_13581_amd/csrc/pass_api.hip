@@ -385,23 +385,16 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
     }
     if (logits_base) launch_gemm_logits(P, c->tuning, c->lm_head, logits_base, M, s);
   } else {
-  launch_assemble(P, dt, c->tok_emb, c->lookahead, mode, B, R, s);
-  for (int l = 0; l < P.L; ++l) {
-    const LayerW &w = c->layers[l];
-    launch_rmsnorm(P, dt, P.h, w.attn_norm, P.xn, M, s);
-    launch_gemm_generic(dt, P.xn, w.wqkv, P.qkv, M, 3 * P.D, P.d, 3 * P.D, nullptr, 0, s);
-    launch_rope_kv(P, dt, l, M, s);
-    launch_attention(P, dt, l, B, R, S, 0, s);
-    launch_gemm_generic(dt, P.attn, w.wo, P.h, M, P.d, P.D, P.d, nullptr, 1, s);
-    launch_rmsnorm(P, dt, P.h, w.ffn_norm, P.xn, M, s);
-    launch_gemm_generic(dt, P.xn, w.wgu, P.gu, M, 2 * P.F, P.d, 2 * P.F, nullptr, 0, s);
-    launch_silu_mul(P, M, s);
-    launch_gemm_generic(dt, P.act, w.wdown, P.h, M, P.d, P.F, P.d, nullptr, 1, s);
-  }
-  if (logits_base) {
-    launch_rmsnorm(P, dt, P.h, c->final_norm, P.xn, M, s);
-    launch_gemm_generic(dt, P.xn, c->lm_head, logits_base, M, P.V, P.d, P.V, P.row_out, 0, s);
-  }
+    launch_assemble(P, dt, c->tok_emb, c->lookahead, mode, B, R, s);
+    for (int l = 0; l < P.L; ++l) {
+      const LayerW &w = c->layers[l];
+      launch_row_qkv(P, dt, w.attn_norm, w.wqkv, l, M, s);
+      launch_attention(P, dt, l, B, R, S, 0, s);
+      launch_row_resid(P, dt, P.attn, w.wo, P.D, M, s);
+      launch_row_gateup(P, dt, w.ffn_norm, w.wgu, M, s);
+      launch_row_resid(P, dt, P.act, w.wdown, P.F, M, s);
+    }
+    if (logits_base) launch_row_logits(P, dt, c->final_norm, c->lm_head, logits_base, M, s);
   }
   HIP_TRY(c, hipGetLastError());
   if (timing) {
@@ -413,7 +406,7 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
       if (c->use_mfma)
         launch_gemm_gateup(P, c->tuning, c->layers[l].wgu, M, s);
       else
-        launch_gemm_generic(dt, P.xn, c->layers[l].wgu, P.gu, M, 2 * P.F, P.d, 2 * P.F, nullptr, 0, s);
+        launch_row_gateup(P, dt, c->layers[l].ffn_norm, c->layers[l].wgu, M, s);
     }
     HIP_TRY(c, hipEventRecord(c->kev[1], s));
     HIP_TRY(c, hipGetLastError());

@@ -155,6 +155,11 @@ void launch_gemm_generic(int dtype, const float *X, const void *W, float *out, i
                          const int32_t *rowmap, int accumulate, hipStream_t s);
 void launch_rope_kv(const Params &p, int dtype, int layer, int M, hipStream_t s);
 void launch_silu_mul(const Params &p, int M, hipStream_t s);
+// the decode step's GEMMs on the generic path, with norm, rotary embedding and cache write, activation or residual add
+void launch_row_qkv(const Params &p, int dtype, const void *gain, const void *W, int layer, int M, hipStream_t s);
+void launch_row_resid(const Params &p, int dtype, const float *X, const void *W, int K, int M, hipStream_t s);
+void launch_row_gateup(const Params &p, int dtype, const void *gain, const void *W, int M, hipStream_t s);
+void launch_row_logits(const Params &p, int dtype, const void *gain, const void *W, float *logits, int M, hipStream_t s);
 // attention (both paths).  out_split: 0 = fp32 into p.attn, 1 = (hi, lo) bf16 pairs into p.attn_x
 void launch_attention(const Params &p, int dtype, int layer, int B, int R, int n_splits, int out_split,
                       hipStream_t s);

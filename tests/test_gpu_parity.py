@@ -396,6 +396,42 @@ def test_row_gemm_shapes(d, ffn, slots, k, blocks):
     g.close()
 
 
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("d,heads,hd,ffn,vocab,slots,k", [
+    (8, 1, 64, 8, 3, 1, 0), (72, 3, 64, 40, 257, 1, 1), (256, 4, 64, 504, 130, 1, 3), (504, 2, 128, 520, 77, 2, 3),
+    (512, 8, 64, 1000, 201, 3, 4), (520, 1, 128, 264, 64, 5, 11)])
+def test_generic_row_gemm_shapes(d, heads, hd, ffn, vocab, slots, k, dtype):
+    """The generic path's fused GEMMs: K below, at and above one chunk per lane (8 .. 1000, both chunk sizes, remainders),
+    an odd number of output columns, one to sixty rows (2, 4 or 8 at a time, full and not), both head sizes and both
+    storage types; every slot follows the oracle through two iterations."""
+    shape = synth.ModelShape(2, d, heads, hd, ffn, vocab, dtype=dtype)
+    W = synth.make_weights(shape, 8, k, 4.0)
+    m = O.Model(shape, W, k)
+    rng = np.random.default_rng(d + slots)
+    prompts = [rng.integers(0, vocab, int(n)).astype(np.int32) for n in rng.integers(1, 20, slots)]
+    g = _gpu(shape, W, k, max_slots=slots, max_seq_len=64, page_size=16, options={"path": 1})
+    ids = list(range(slots))
+    stats = parity.batch_parity(g, m, ids, [3 + i for i in ids], prompts, ids, 2, 0.9, 777, parity.LOGIT_TOL[dtype], max_len=64)
+    for sl in ids:
+        parity.check_stats(stats[sl], 2, parity.ERR_F32 if dtype == synth.F32 else parity.ERR_BF16_SMALL)
+    g.close()
+
+
+@pytest.mark.parametrize("path,plen", [(0, 118), (0, 123), (0, 130), (1, 52), (1, 57), (1, 66)])
+def test_attention_with_one_split(path, plen):
+    """Around the key count at which a group's keys no longer fit one split (128 on the matrix-core path, 64 on the generic
+    one): below it the split kernel writes the rows itself, above it the merge kernel does; the sequence crosses the
+    line while it is followed by the oracle."""
+    w = MFMA_HD128
+    W = synth.make_weights(w.shape, w.seed, w.k, w.lm_head_scale)
+    m = O.Model(w.shape, W, w.k)
+    prompt = np.random.default_rng(plen).integers(0, w.shape.vocab, plen).astype(np.int32)
+    g = _gpu(w.shape, W, w.k, max_seq_len=192, page_size=64, options={"path": path})
+    st = parity.stepwise_parity(g, m, 0, 2, prompt, 4, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=192)
+    parity.check_stats(st, 4, parity.ERR_BF16_SMALL)
+    g.close()
+
+
 @pytest.mark.parametrize("lens", [(48,), (49,), (50,), (65,), (20, 29), (20, 30), (1, 49, 2)])
 def test_prompt_pass_by_length(lens):
     """Default options on both sides of the row count at which a prompt, or a batch of prompts, changes from the decode
