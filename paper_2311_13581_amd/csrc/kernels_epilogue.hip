@@ -19,6 +19,8 @@
 // highest index that may still be kept among the logits equal to it.  Entries outside the filter
 // are skipped by every scan (ln-sum-exp, draws, residual) and have probability zero in the accept
 // test.  K = 0 is no filter (key 0, every index allowed).
+#include <type_traits>
+
 #include "pass_internal.h"
 
 namespace pass {
@@ -96,18 +98,30 @@ __device__ Best block_best(Best v, Best *sh) {
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  Best r = sh[0];
-  for (int w = 1; w < kEpiWaves; ++w) r = better(r, sh[w]);
-  return r;
+  v = sh[threadIdx.x & (kEpiWaves - 1)];  // sixteen wavefronts' results in four exchanges
+#pragma unroll
+  for (int o = kEpiWaves / 2; o > 0; o >>= 1) {
+    Best t;
+    t.s = __shfl_xor(v.s, o);
+    t.idx = __shfl_xor(v.idx, o);
+    v = better(v, t);
+  }
+  return v;
 }
 __device__ MaxSum block_ms(MaxSum v, MaxSum *sh) {
   v = wave_ms(v);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  MaxSum r = sh[0];
-  for (int w = 1; w < kEpiWaves; ++w) r = ms_merge(r, sh[w]);
-  return r;
+  v = sh[threadIdx.x & (kEpiWaves - 1)];
+#pragma unroll
+  for (int o = kEpiWaves / 2; o > 0; o >>= 1) {
+    MaxSum t;
+    t.m = __shfl_xor(v.m, o);
+    t.s = __shfl_xor(v.s, o);
+    v = ms_merge(v, t);
+  }
+  return v;
 }
 
 // Walk NR logits rows of V entries in groups of four consecutive entries ("quads", the unit one
@@ -298,6 +312,37 @@ __device__ void sample_row(const float *logits, int V, bool greedy, float inv_t,
   });
 }
 
+// x_{n+1} is accepted unconditionally: it joins the sequence, its predecessor's K/V stay
+__device__ __forceinline__ void commit_first(const Params &p, const SampleArgs &a, int slot, int token) {
+  p.first[slot] = token;
+  int ng = p.n_gen[slot];
+  int frozen = ng >= p.gen_limit[slot];
+  p.frozen[slot] = frozen;
+  if (a.commit && !frozen) {
+    p.kv_len[slot] += 1;
+    p.pending[slot] = token;
+    if (ng < p.gen_cap) p.gen[(size_t)slot * p.gen_cap + ng] = token;
+    p.n_gen[slot] = ng + 1;
+  }
+}
+// the accepted drafts and the final token y join the sequence
+__device__ __forceinline__ void commit_verified(const Params &p, const SampleArgs &a, int slot, int acc, int y) {
+  const int32_t *drafts = p.drafts + slot * kMaxK;
+  int32_t *lo = p.last_out + slot * (kMaxK + 1);
+  for (int t = 0; t < acc; ++t) lo[t] = drafts[t];
+  lo[acc] = y;
+  p.n_acc[slot] = acc;
+  if (a.commit && !p.frozen[slot]) {
+    int ng = p.n_gen[slot];
+    for (int t = 0; t <= acc; ++t)
+      if (ng + t < p.gen_cap) p.gen[(size_t)slot * p.gen_cap + ng + t] = lo[t];
+    p.n_gen[slot] = ng + acc + 1;
+    p.kv_len[slot] += 1 + acc;  // K/V of x_{n+1} and of the accepted drafts are kept
+    p.pending[slot] = y;
+    p.iter[slot] += 1;
+  }
+}
+
 __global__ __launch_bounds__(kEpiThreads) void draft_epilogue_kernel(Params p, SampleArgs a, int R) {
   __shared__ Best sh_b[kEpiWaves];
   __shared__ MaxSum sh_m[kEpiWaves];
@@ -326,17 +371,7 @@ __global__ __launch_bounds__(kEpiThreads) void draft_epilogue_kernel(Params p, S
     } else if (r > 0) {
       p.drafts[slot * kMaxK + (r - 1)] = best.idx;
     } else {
-      p.first[slot] = best.idx;
-      int ng = p.n_gen[slot];
-      int frozen = ng >= p.gen_limit[slot];
-      p.frozen[slot] = frozen;
-      if (a.commit && !frozen) {
-        // x_{n+1} is accepted unconditionally: it joins the sequence, its predecessor's K/V stay
-        p.kv_len[slot] += 1;
-        p.pending[slot] = best.idx;
-        if (ng < p.gen_cap) p.gen[(size_t)slot * p.gen_cap + ng] = best.idx;
-        p.n_gen[slot] = ng + 1;
-      }
+      commit_first(p, a, slot, best.idx);
     }
   }
 }
@@ -462,30 +497,392 @@ __global__ __launch_bounds__(kEpiThreads) void verify_decide_kernel(Params p, Sa
     }
     y = best.idx;
   }
+  if (threadIdx.x == 0) commit_verified(p, a, slot, acc, y);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same epilogues for large vocabularies, every row spread over workgroups.  One workgroup per row is bound by the
+// vector arithmetic of a single compute unit (exp, Philox, two logarithms per entry: 17 to 26 us for 32000 entries),
+// while 250 units idle.  Here a workgroup takes 1024 entries of a row (4096 of very long rows) and leaves (max, sum, best) in a workspace; the kernel that follows merges the parts in order and goes on:
+//   drafting    part, commit
+//   validation  part, commit (greedy); part, draw, commit (sampled): the workgroups of `draw` each find the accept
+//               count for themselves, then take their entries of the residual or bonus draw
+// With top-k sampling a kernel of one workgroup per row finds the rows' filters first.  Every draw is an argmax over the
+// same scores as above, whoever computes them.
+// Measured at 32000 entries, seven rows, one sequence, T = 0.8: drafting 25.0 us -> 4.7 + 4.0, validation
+// 16.4 + 25.3 -> 4.7 + 6.4 + 3.9; one greedy row: 17.2 -> 4.6 + 4.0 and 16.2 -> 4.6 + 4.0.
+// ---------------------------------------------------------------------------------------------
+// quads of four entries per thread of a part: one while that makes no more parts than the workspace holds (32000
+// entries: 32 parts; with four per thread, eight parts, row_part and verify_draw took 8.8 and 13.6 us instead of 4.7 and 6.4), else four
+constexpr int kPartThreads = 256;
+
+// Wavefront reductions through DPP.  OP(v, the other lane's v) is only applied where the other lane exists; lane 63 ends
+// with the result, which is handed to every lane.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {  // masked rows get their own value back
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <typename F>
+__device__ __forceinline__ void dpp_steps(F &&f) {
+  f(std::integral_constant<int, 0xB1>{}, std::integral_constant<int, 0xF>{});   // quad_perm [1,0,3,2]
+  f(std::integral_constant<int, 0x4E>{}, std::integral_constant<int, 0xF>{});   // quad_perm [2,3,0,1]
+  f(std::integral_constant<int, 0x141>{}, std::integral_constant<int, 0xF>{});  // row_half_mirror
+  f(std::integral_constant<int, 0x140>{}, std::integral_constant<int, 0xF>{});  // row_mirror
+  f(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});  // row_bcast:15 into rows 1 and 3
+  f(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});  // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ float lane63(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); }
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  dpp_steps([&](auto C, auto R) { v = fmaxf(v, __uint_as_float(dpp_u32<C.value, R.value>(__float_as_uint(v)))); });
+  return lane63(v);
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  dpp_steps([&](auto C, auto R) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), C.value, R.value, 0xF, false));
+  });
+  return lane63(v);
+}
+// A candidate as an integer that orders like better(): larger score first, then the lower index; 0 = no candidate
+__device__ __forceinline__ uint64_t best_key(float s, int idx) { return (uint64_t)order_key(s) << 32 | (uint32_t)~idx; }
+__device__ __forceinline__ int key_index(uint64_t key) { return key ? (int)~(uint32_t)key : -1; }
+__device__ __forceinline__ uint64_t wave_key_dpp(uint64_t k) {
+  dpp_steps([&](auto C, auto R) {
+    const uint64_t o = (uint64_t)dpp_u32<C.value, R.value>((uint32_t)(k >> 32)) << 32 | dpp_u32<C.value, R.value>((uint32_t)k);
+    k = o > k ? o : k;
+  });
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(k >> 32), 63) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)k, 63);
+}
+// (max, sum of exp) of the wavefront's lanes; a lane with no entry has max -inf and sum 0
+__device__ __forceinline__ MaxSum wave_ms_dpp(float mx, float sum) {
+  const float m = wave_max_dpp(mx);
+  return MaxSum{m, wave_sum_dpp(mx == -INFINITY ? 0.f : sum * expf(mx - m))};
+}
+
+__device__ __forceinline__ RowFilter read_filter(const uint32_t *key, const int32_t *tie, int at, bool filtered, int V) {
+  RowFilter f;
+  f.key = filtered ? key[at] : 0u;
+  f.tie_max = filtered ? tie[at] : V;
+  return f;
+}
+
+__global__ __launch_bounds__(kEpiThreads) void row_filter_kernel(Params p, SampleArgs a, int R, int verify) {
+  __shared__ SelectShared sh_sel;
+  const int m = blockIdx.x, slot = p.step_slots[m / R], r = m % R;
+  if (a.stats_only && r == 0) return;
+  const float *row = (verify ? p.verify_logits : p.draft_logits) + ((size_t)slot * (1 + p.k) + r) * p.V;
+  const RowFilter f = select_top_k(row, p.V, a.top_k, sh_sel);
   if (threadIdx.x == 0) {
-    int32_t *lo = p.last_out + slot * (kMaxK + 1);
-    for (int t = 0; t < acc; ++t) lo[t] = drafts[t];
-    lo[acc] = y;
-    p.n_acc[slot] = acc;
-    if (a.commit && !p.frozen[slot]) {
-      int ng = p.n_gen[slot];
-      for (int t = 0; t <= acc; ++t)
-        if (ng + t < p.gen_cap) p.gen[(size_t)slot * p.gen_cap + ng + t] = lo[t];
-      p.n_gen[slot] = ng + acc + 1;
-      p.kv_len[slot] += 1 + acc;  // K/V of x_{n+1} and of the accepted drafts are kept
-      p.pending[slot] = y;
-      p.iter[slot] = it + 1;
-    }
+    (verify ? p.flt_key_p : p.flt_key_d)[slot * (kMaxK + 1) + r] = f.key;
+    (verify ? p.flt_tie_p : p.flt_tie_d)[slot * (kMaxK + 1) + r] = f.tie_max;
   }
 }
 
+// Part blockIdx.x of row blockIdx.y: (max, sum of exp, best candidate).  Validation rows keep the argmax of the
+// logits as best, drafting rows the draw (also an argmax of the logits when greedy).
+template <int U>
+__global__ __launch_bounds__(kPartThreads) void row_part_kernel(Params p, SampleArgs a, int R, int verify, int filtered) {
+  __shared__ float sh_m[4], sh_s[4];
+  __shared__ uint64_t sh_k[4];
+  const int m = blockIdx.y, slot = p.step_slots[m / R], r = m % R;
+  if (a.stats_only && r == 0) return;
+  const float *row = (verify ? p.verify_logits : p.draft_logits) + ((size_t)slot * (1 + p.k) + r) * p.V;
+  const bool greedy = a.temperature == 0.f;
+  const float inv_t = greedy ? 1.f : 1.f / a.temperature;
+  const bool draw = !greedy && !verify;
+  const int at = slot * (kMaxK + 1) + r;
+  const int V4 = p.V >> 2, lo = blockIdx.x * (U * kPartThreads) + threadIdx.x;
+  float4 v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) v[u] = ((const float4 *)row)[min(lo + u * kPartThreads, V4 - 1)];
+  const RowFilter flt = read_filter(verify ? p.flt_key_p : p.flt_key_d, verify ? p.flt_tie_p : p.flt_tie_d, at, filtered, p.V);
+  const uint32_t it = p.iter[slot], sid = p.seq_id[slot], c2 = (uint32_t)(r + a.row_base) | (PURPOSE_DRAFT << 8);
+  float l[4 * U], mx = -INFINITY;
+  uint32_t keep = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int q = lo + u * kPartThreads;
+    l[4 * u] = v[u].x; l[4 * u + 1] = v[u].y; l[4 * u + 2] = v[u].z; l[4 * u + 3] = v[u].w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (q < V4 && kept(flt, l[4 * u + e], q * 4 + e)) {
+        keep |= 1u << (4 * u + e);
+        mx = fmaxf(mx, l[4 * u + e] * inv_t);
+      }
+  }
+  float sum = 0.f;
+  uint64_t key = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int q = lo + u * kPartThreads;
+    uint32_t rnd[4] = {0, 0, 0, 0};
+    if (draw && (keep >> (4 * u) & 15u)) philox4x32_10((uint32_t)q, it, c2, sid, a.seed_lo, a.seed_hi, rnd);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (keep >> (4 * u + e) & 1u) {
+        const float x = l[4 * u + e], s = x * inv_t;
+        sum += mx == -INFINITY ? 0.f : __expf(s - mx);
+        const uint64_t k = best_key(draw ? s + gumbel(u01(rnd[e])) : x, q * 4 + e);
+        key = k > key ? k : key;
+      }
+  }
+  const MaxSum ms = wave_ms_dpp(mx, sum);
+  key = wave_key_dpp(key);
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { sh_m[wave] = ms.m; sh_s[wave] = ms.s; sh_k[wave] = key; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const float t = fmaxf(fmaxf(sh_m[0], sh_m[1]), fmaxf(sh_m[2], sh_m[3]));
+    float total = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      total += sh_m[w] == -INFINITY ? 0.f : sh_s[w] * expf(sh_m[w] - t);
+      key = sh_k[w] > key ? sh_k[w] : key;
+    }
+    p.row_parts[(size_t)m * kRowParts + blockIdx.x] = make_float4(t, total, __uint_as_float((uint32_t)(key >> 32)), __uint_as_float((uint32_t)key));
+  }
+}
+
+// ln-sum-exp and best index of a row from its parts (lane i holds part i), by one wavefront; every lane gets both
+__device__ __forceinline__ float4 load_part(const Params &p, int m, int parts) {
+  return p.row_parts[(size_t)m * kRowParts + min((int)(threadIdx.x & 63), parts - 1)];
+}
+__device__ __forceinline__ void merge_parts(float4 v, int parts, float &logz, int &idx) {
+  const bool own = (int)(threadIdx.x & 63) < parts;
+  const MaxSum ms = wave_ms_dpp(own ? v.x : -INFINITY, own ? v.y : 0.f);
+  const uint64_t key = wave_key_dpp(own ? (uint64_t)__float_as_uint(v.z) << 32 | __float_as_uint(v.w) : 0);
+  logz = ms.m + logf(ms.s);
+  idx = key_index(key);
+}
+
+__global__ __launch_bounds__(1024) void draft_commit_kernel(Params p, SampleArgs a, int R, int parts, int filtered) {
+  const int b = blockIdx.x, slot = p.step_slots[b], r = threadIdx.x >> 6;  // a wavefront per row (R <= 16)
+  if (r >= R || (a.stats_only && r == 0)) return;
+  float logz;
+  int idx;
+  merge_parts(load_part(p, b * R + r, parts), parts, logz, idx);
+  if ((threadIdx.x & 63) != 0) return;
+  p.logz_d[slot * (kMaxK + 1) + r] = logz;
+  if (!filtered) {  // the validation call evaluates d_t through the same filter
+    p.flt_key_d[slot * (kMaxK + 1) + r] = 0u;
+    p.flt_tie_d[slot * (kMaxK + 1) + r] = p.V;
+  }
+  if (a.stats_only) return;  // the tokens were drafted elsewhere
+  if (r > 0) {
+    p.drafts[slot * kMaxK + (r - 1)] = idx;
+  } else {
+    commit_first(p, a, slot, idx);
+  }
+}
+
+// Accept test of draft t by lane t - 1.  What it needs of memory is requested before the rows' parts are merged.
+struct AcceptOperands {
+  int x;         // the draft
+  float pl, dl;  // its logit in the target and in the draft row
+  RowFilter fp, fd;
+  float zd;
+};
+__device__ __forceinline__ AcceptOperands accept_operands(const Params &p, int slot, bool filtered, bool greedy) {
+  const int t = min((int)(threadIdx.x & 63) + 1, max(p.k_act, 1)), V = p.V, base = slot * (kMaxK + 1);
+  AcceptOperands o;
+  o.x = p.drafts[slot * kMaxK + t - 1];
+  if (greedy || p.k_act == 0) return o;
+  const int x = clamp_token(p, o.x);
+  o.pl = p.verify_logits[((size_t)slot * (1 + p.k) + t - 1) * V + x];
+  o.dl = p.draft_logits[((size_t)slot * (1 + p.k) + t) * V + x];
+  o.fp = read_filter(p.flt_key_p, p.flt_tie_p, base + t - 1, filtered, V);
+  o.fd = read_filter(p.flt_key_d, p.flt_tie_d, base + t, true, V);
+  o.zd = p.logz_d[base + t];
+  return o;
+}
+// How many drafts are accepted, in every lane of the calling wavefront.  zp, argmax: of the validation rows (LDS).
+__device__ __forceinline__ int count_accepted(const Params &p, const SampleArgs &a, int slot, const AcceptOperands &o, const float *zp,
+                                              const int *argmax) {
+  const int lane = threadIdx.x & 63;
+  bool ok = false;
+  if (lane < p.k_act) {
+    const int t = lane + 1;
+    if (a.temperature == 0.f) {
+      ok = o.x == argmax[t - 1];
+    } else {
+      // a token outside a row's filter has probability zero there
+      const float inv_t = 1.f / a.temperature;
+      const float lp = kept(o.fp, o.pl, o.x) ? o.pl * inv_t - zp[t - 1] : -INFINITY;
+      const float ld = kept(o.fd, o.dl, o.x) ? o.dl * inv_t - o.zd : -INFINITY;
+      uint32_t rnd[4];
+      philox4x32_10(0u, p.iter[slot], (uint32_t)t | (PURPOSE_ACCEPT << 8), p.seq_id[slot], a.seed_lo, a.seed_hi, rnd);
+      ok = logf(u01(rnd[0])) + ld < lp;
+    }
+  }
+  return __builtin_ctzll(~__builtin_amdgcn_ballot_w64(ok));  // lanes k .. 63 count as rejected (k < 16)
+}
+
+// the validation rows' ln-sum-exp and argmax into LDS, by a workgroup of four wavefronts (R <= 16: four rows each)
+__device__ __forceinline__ void merge_rows(const Params &p, int b, int R, int parts, float *zp, int *argmax) {
+  const int wave = threadIdx.x >> 6;
+  float4 v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = load_part(p, b * R + min(wave + 4 * i, R - 1), parts);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = wave + 4 * i;
+    if (r >= R) break;
+    float logz;
+    int idx;
+    merge_parts(v[i], parts, logz, idx);
+    if ((threadIdx.x & 63) == 0) { zp[r] = logz; argmax[r] = idx; }
+  }
+  __syncthreads();
+}
+
+// Part blockIdx.x of the draw that follows the accept chain of slot blockIdx.y: the residual (p_t - d_t)_+ of the first
+// rejected draft, or the extra token's row when all were accepted.
+template <int U>
+__global__ __launch_bounds__(kPartThreads) void verify_draw_kernel(Params p, SampleArgs a, int R, int parts, int filtered) {
+  __shared__ uint64_t sh_k[4];
+  __shared__ float zp[kMaxK + 1];
+  __shared__ int argmax[kMaxK + 1], sh_acc;
+  const int b = blockIdx.y, slot = p.step_slots[b], k = p.k_act, V = p.V, base = slot * (kMaxK + 1);
+  const AcceptOperands ops = accept_operands(p, slot, filtered, false);
+  merge_rows(p, b, R, parts, zp, argmax);
+  if (threadIdx.x < 64) {
+    const int n = count_accepted(p, a, slot, ops, zp, argmax);
+    if (threadIdx.x == 0) sh_acc = n;
+    if (blockIdx.x == 0) {
+      if (threadIdx.x == 0) p.n_acc[slot] = n;
+      if ((int)threadIdx.x < R) { p.logz_p[base + threadIdx.x] = zp[threadIdx.x]; p.argmax_p[base + threadIdx.x] = argmax[threadIdx.x]; }
+    }
+  }
+  __syncthreads();
+  const int acc = sh_acc;
+  const bool bonus = acc == k;
+  const float inv_t = 1.f / a.temperature;
+  const float *pr = p.verify_logits + ((size_t)slot * (1 + p.k) + acc) * V;
+  const float *dr = bonus ? pr : p.draft_logits + ((size_t)slot * (1 + p.k) + acc + 1) * V;
+  const int V4 = V >> 2, lo = blockIdx.x * (U * kPartThreads) + threadIdx.x;
+  float4 vp[U], vd[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int q = min(lo + u * kPartThreads, V4 - 1);
+    vp[u] = ((const float4 *)pr)[q];
+    vd[u] = ((const float4 *)dr)[q];
+  }
+  const RowFilter fp = read_filter(p.flt_key_p, p.flt_tie_p, base + acc, filtered, V);
+  const RowFilter fd = bonus ? fp : read_filter(p.flt_key_d, p.flt_tie_d, base + acc + 1, true, V);
+  const float z_p = zp[acc], z_d = bonus ? 0.f : p.logz_d[base + acc + 1];
+  const uint32_t it = p.iter[slot], sid = p.seq_id[slot], c2 = (uint32_t)(acc + 1) | ((bonus ? PURPOSE_BONUS : PURPOSE_RESIDUAL) << 8);
+  uint64_t key = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int q = lo + u * kPartThreads;
+    if (q >= V4) continue;
+    const float xp[4] = {vp[u].x, vp[u].y, vp[u].z, vp[u].w}, xd[4] = {vd[u].x, vd[u].y, vd[u].z, vd[u].w};
+    uint32_t rnd[4];
+    philox4x32_10((uint32_t)q, it, c2, sid, a.seed_lo, a.seed_hi, rnd);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = q * 4 + e;
+      uint64_t c = 0;
+      if (bonus) {
+        if (kept(fp, xp[e], j)) c = best_key(xp[e] * inv_t + gumbel(u01(rnd[e])), j);
+      } else {
+        const float w = (kept(fp, xp[e], j) ? __expf(xp[e] * inv_t - z_p) : 0.f) - (kept(fd, xd[e], j) ? __expf(xd[e] * inv_t - z_d) : 0.f);
+        if (w > 0.f) c = best_key(__logf(w) + gumbel(u01(rnd[e])), j);
+      }
+      key = c > key ? c : key;
+    }
+  }
+  key = wave_key_dpp(key);
+  if ((threadIdx.x & 63) == 0) sh_k[threadIdx.x >> 6] = key;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 0; w < 4; ++w) key = sh_k[w] > key ? sh_k[w] : key;
+    p.draw_parts[(size_t)b * kRowParts + blockIdx.x] = key;
+  }
+}
+
+__global__ __launch_bounds__(kPartThreads) void verify_commit_kernel(Params p, SampleArgs a, int R, int parts, int filtered) {
+  __shared__ float zp[kMaxK + 1];
+  __shared__ int argmax[kMaxK + 1];
+  __shared__ uint64_t sh_k[4];
+  const int b = blockIdx.x, slot = p.step_slots[b], base = slot * (kMaxK + 1);
+  int acc, y;
+  if (a.temperature == 0.f) {
+    const AcceptOperands ops = accept_operands(p, slot, filtered, true);
+    merge_rows(p, b, R, parts, zp, argmax);
+    if (threadIdx.x >= 64) return;
+    acc = count_accepted(p, a, slot, ops, zp, argmax);
+    y = argmax[acc];
+    if ((int)threadIdx.x < R) { p.logz_p[base + threadIdx.x] = zp[threadIdx.x]; p.argmax_p[base + threadIdx.x] = argmax[threadIdx.x]; }
+  } else {
+    const uint64_t part = p.draw_parts[(size_t)b * kRowParts + min((int)(threadIdx.x & 63), parts - 1)];
+    acc = p.n_acc[slot];
+    y = key_index(wave_key_dpp(part));  // (the last part repeated changes nothing); the same in every wavefront
+    if (y < 0 && acc < p.k_act) {
+      // residual empty through rounding: draw from p_t with the same counters
+      const RowFilter f = read_filter(p.flt_key_p, p.flt_tie_p, base + acc, filtered, p.V);
+      const float *row = p.verify_logits + ((size_t)slot * (1 + p.k) + acc) * p.V;
+      uint64_t key = 0;
+      for (int q = threadIdx.x; q * 4 < p.V; q += kPartThreads) {
+        uint32_t rnd[4];
+        philox4x32_10((uint32_t)q, p.iter[slot], (uint32_t)(acc + 1) | (PURPOSE_RESIDUAL << 8), p.seq_id[slot], a.seed_lo, a.seed_hi, rnd);
+        for (int e = 0; e < 4; ++e) {
+          const float x = row[q * 4 + e];
+          if (!kept(f, x, q * 4 + e)) continue;
+          const uint64_t c = best_key(x * (1.f / a.temperature) + gumbel(u01(rnd[e])), q * 4 + e);
+          key = c > key ? c : key;
+        }
+      }
+      key = wave_key_dpp(key);
+      if ((threadIdx.x & 63) == 0) sh_k[threadIdx.x >> 6] = key;
+      __syncthreads();
+      for (int w = 0; w < 4; ++w) key = sh_k[w] > key ? sh_k[w] : key;
+      y = key_index(key);
+      if (threadIdx.x == 0) atomicAdd(p.fallbacks, 1);
+    }
+  }
+  if (threadIdx.x == 0) commit_verified(p, a, slot, acc, y);
+}
+
+// Rows of a multiple of four entries, more than 4096 of them, are spread over workgroups; shorter ones stay with one (512
+// entries: 5 to 6 us, what the first of two kernels would take).  Returns the parts, 0 for one workgroup per row.
+static int row_parts_of(const Params &p, int &u) {
+  const int V4 = p.V / 4;
+  u = (V4 + kPartThreads - 1) / kPartThreads <= kRowParts ? 1 : 4;
+  const int parts = (V4 + u * kPartThreads - 1) / (u * kPartThreads);
+  return p.V % 4 == 0 && p.V > 4096 && parts <= kRowParts ? parts : 0;
+}
+
 void launch_draft_epilogue(const Params &p, const SampleArgs &a, int B, int R, hipStream_t s) {
-  draft_epilogue_kernel<<<B * R, kEpiThreads, 0, s>>>(p, a, R);
+  int u;
+  const int parts = row_parts_of(p, u);
+  if (!parts) {
+    draft_epilogue_kernel<<<B * R, kEpiThreads, 0, s>>>(p, a, R);
+    return;
+  }
+  const int filtered = a.temperature != 0.f && a.top_k > 0 && a.top_k < p.V;
+  if (filtered) row_filter_kernel<<<B * R, kEpiThreads, 0, s>>>(p, a, R, 0);
+  if (u == 1) row_part_kernel<1><<<dim3(parts, B * R), kPartThreads, 0, s>>>(p, a, R, 0, filtered);
+  else row_part_kernel<4><<<dim3(parts, B * R), kPartThreads, 0, s>>>(p, a, R, 0, filtered);
+  draft_commit_kernel<<<B, R * 64, 0, s>>>(p, a, R, parts, filtered);
 }
 
 void launch_verify_epilogue(const Params &p, const SampleArgs &a, int B, int R, hipStream_t s) {
-  verify_stats_kernel<<<B * R, kEpiThreads, 0, s>>>(p, a, R);
-  verify_decide_kernel<<<B, kEpiThreads, 0, s>>>(p, a);
+  int u;
+  const int parts = row_parts_of(p, u);
+  if (!parts) {
+    verify_stats_kernel<<<B * R, kEpiThreads, 0, s>>>(p, a, R);
+    verify_decide_kernel<<<B, kEpiThreads, 0, s>>>(p, a);
+    return;
+  }
+  const int filtered = a.temperature != 0.f && a.top_k > 0 && a.top_k < p.V;
+  if (filtered) row_filter_kernel<<<B * R, kEpiThreads, 0, s>>>(p, a, R, 1);
+  if (u == 1) row_part_kernel<1><<<dim3(parts, B * R), kPartThreads, 0, s>>>(p, a, R, 1, filtered);
+  else row_part_kernel<4><<<dim3(parts, B * R), kPartThreads, 0, s>>>(p, a, R, 1, filtered);
+  if (a.temperature != 0.f) {
+    if (u == 1) verify_draw_kernel<1><<<dim3(parts, B), kPartThreads, 0, s>>>(p, a, R, parts, filtered);
+    else verify_draw_kernel<4><<<dim3(parts, B), kPartThreads, 0, s>>>(p, a, R, parts, filtered);
+  }
+  verify_commit_kernel<<<B, kPartThreads, 0, s>>>(p, a, R, parts, filtered);
 }
 
 // The uniforms the epilogues attach to indices j0 .. j0 + n of one (sequence, iteration, row,

@@ -195,6 +195,7 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   P.argmax_p = A.take<int32_t>(S * (kMaxK + 1));
   P.flt_key_d = A.take<uint32_t>(S * (kMaxK + 1)); P.flt_key_p = A.take<uint32_t>(S * (kMaxK + 1));
   P.flt_tie_d = A.take<int32_t>(S * (kMaxK + 1)); P.flt_tie_p = A.take<int32_t>(S * (kMaxK + 1));
+  P.row_parts = A.take<float4>(M * kRowParts); P.draw_parts = A.take<uint64_t>(M * kRowParts);
   P.fallbacks = A.take<int32_t>(1);
   P.block_table = A.take<int32_t>(S * pps);
   P.draft_logits = A.take<float>(S * (1 + c.k) * V);

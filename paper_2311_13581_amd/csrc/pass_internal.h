@@ -14,6 +14,7 @@ constexpr int kMaxK = PASS_MAX_K;
 constexpr int kMaxRows = PASS_MAX_ROWS;
 constexpr int kAttnRowsPerGroup = 8;  // queries one attention workgroup carries in registers
 constexpr int kMaxSplits = 32;
+constexpr int kRowParts = 64;  // most parts a logits row is cut into by the sampling epilogues
 constexpr int kPrefillRows = 2048;  // most prompt rows the tiled prompt pass takes through the weights at once
 constexpr int kAttnResident = 768;  // matrix-core attention workgroups resident on the chip (256 CUs x 3)
 
@@ -87,6 +88,8 @@ struct Params {
   int32_t *argmax_p;       // [slot][kMaxK+1]
   uint32_t *flt_key_d, *flt_key_p;  // [slot][kMaxK+1]: top-k filter of each draft / verify row (threshold key,
   int32_t *flt_tie_d, *flt_tie_p;   //   highest index kept among the logits equal to the threshold)
+  float4 *row_parts;       // [kMaxRows][kRowParts]: (max, sum of exp, best candidate in 64 bits) of a part of a logits row
+  uint64_t *draw_parts;    // [kMaxRows][kRowParts]: best candidate of a part of a slot's residual or bonus draw
   int32_t *fallbacks;      // [1]: residual numerically empty after a reject
   int32_t *block_table;    // [slot][pages_per_seq]
   float *draft_logits, *verify_logits;  // [slot][1+k][V]

@@ -432,6 +432,47 @@ def test_attention_with_one_split(path, plen):
     g.close()
 
 
+@pytest.mark.parametrize("vocab,temp,top_k,k,slots", [
+    (v,) + c for v in (4096, 4097, 4100, 8192, 12300)
+    for c in ((0.0, 0, 4, 2), (0.9, 0, 0, 1), (0.9, 0, 15, 2), (0.9, 7, 3, 3), (1.0, 5000, 2, 2))] + [(65540, 0.9, 0, 1, 1)])
+def test_sampling_epilogue_over_parts(vocab, temp, top_k, k, slots):
+    """Rows of more than 4096 logits are sampled in parts by several workgroups: vocabularies at the line, one entry
+    above it (not a multiple of four: one workgroup per row), a last part of one quad, whole parts, a ragged one, and
+    one quad more than parts of 1024 entries can cover (parts of 4096 then);
+    greedy, plain and top-k sampling (K below, and above a part), every number of rows up to sixteen.  Against the
+    oracle through four iterations."""
+    shape = synth.ModelShape(1, 128, 2, 64, 96, vocab, dtype=synth.F32)
+    W = synth.make_weights(shape, 12, k, 10.0)
+    m = O.Model(shape, W, k)
+    rng = np.random.default_rng(vocab + k)
+    prompts = [rng.integers(0, vocab, int(n)).astype(np.int32) for n in rng.integers(1, 20, slots)]
+    g = _gpu(shape, W, k, max_slots=slots, max_seq_len=128, page_size=16)
+    ids = list(range(slots))
+    stats = parity.batch_parity(g, m, ids, [3 + i for i in ids], prompts, ids, 4, temp, 777, parity.LOGIT_TOL[synth.F32], max_len=128,
+                                top_k=top_k)
+    for sl in ids:
+        # K = 5000 cuts a dense distribution in the middle: neighbouring logits there lie closer than the logits' own
+        # error, so the oracle calls those decisions undecided whoever is right; they still may not part ways (no resync)
+        parity.check_stats(stats[sl], 4, parity.ERR_F32, max_unstable=4 * (2 * k + 2) if top_k == 5000 else 2)
+    g.close()
+
+
+def test_sampling_epilogue_ties_across_parts():
+    """Equal logits in different parts of a row: the lowest index wins, greedy (every LM-head row repeats every 4096)."""
+    shape = synth.ModelShape(1, 128, 2, 64, 96, 12288, dtype=synth.F32)
+    W = synth.make_weights(shape, 13, 3, 10.0)
+    W["lm_head"] = np.ascontiguousarray(np.concatenate([W["lm_head"][:4096]] * 3))
+    g = _gpu(shape, W, 3, max_seq_len=128, page_size=16)
+    g.prefill(0, np.arange(1, 9, dtype=np.int32))
+    for _ in range(4):
+        first, drafts = g.draft([0], 0.0, 5)
+        a, toks = g.verify([0], 0.0, 5)
+        assert first[0] < 4096 and drafts.max() < 4096 and toks.max() < 4096
+        lg = g.get_logits(0, 0)
+        assert first[0] == lg[0].argmax() and np.array_equal(drafts[0], lg[1:].argmax(1))
+    g.close()
+
+
 @pytest.mark.parametrize("lens", [(48,), (49,), (50,), (65,), (20, 29), (20, 30), (1, 49, 2)])
 def test_prompt_pass_by_length(lens):
     """Default options on both sides of the row count at which a prompt, or a batch of prompts, changes from the decode
