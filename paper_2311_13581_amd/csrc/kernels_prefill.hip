@@ -633,32 +633,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // Long prompts: the same attention with the K/V tiles shared by the workgroup.  In the kernel above
 // every block of 32 rows pulls all earlier keys through its compute unit's L1 on its own, and at
 // thousands of rows that traffic out of L2 bounds it.  Here a workgroup owns 128 rows, 32 per
-// wavefront; all four wavefronts walk the same 32-key steps, the step's K and V tiles (16 KB) are
-// fetched once, by all wavefronts together (each fetches 2 of the 8 K fragments and 2 of the 8 V
-// fragments, exactly as it would load them for itself), and laid down in LDS in fragment order, so
-// that every wavefront reads a fragment as 1 KB of consecutive 16-byte words.  Requests run two
-// steps ahead of their use (register ring, LDS double buffer, one barrier per step, as in
-// gemm_tile_kernel).  A wavefront skips the steps past its own last row but keeps fetching and
-// meeting the barriers.  No merge at the end: every wavefront owns its rows.
+// wavefront; all four wavefronts walk the same 32-key steps, whose K and V tiles (16 KB) the four copy
+// straight into LDS in fragment order, one step ahead, so that every wavefront reads a fragment as 1 KB
+// of consecutive 16-byte words.  A wavefront skips the steps past its own last row but keeps copying
+// and meeting the barriers.  No merge at the end: every wavefront owns its rows.
+//
+// The softmax's vector arithmetic costs as much as the MFMAs, so it is kept short: scores come out in
+// base-2 logarithms (log2 e is folded into the queries), only steps that reach past the wavefront's
+// first row are masked, and the reference the exponentials are taken against is not the running
+// maximum: it is moved (an exchange between lanes, a rescaling of the accumulators) only when a score
+// exceeds it by more than 8, which for most rows is the first step only.  Probabilities up to 2^8
+// keep the relative precision of their (hi, lo) halves, and the quotient at the end does not care.
+//
+// Blocks differ in their number of keys: the first half of the grid takes the longer ones, longest first,
+// the second half the shorter ones, shortest first, so that where all workgroups are resident at once
+// (two per compute unit) the shortest shares a unit with the longest (97 us; longest first throughout 108,
+// other interleavings 105 to 112).
+// Measured per 7B layer (2047 rows): 155 -> 95 us against running maxima, masks everywhere and tiles
+// through registers; 13B, rows 2048 .. 4095: 465 -> 305.  Also tried: 64-key steps (the same), 16 rows per
+// wavefront with three or four wavefronts per SIMD (5 % slower at 2047 rows, 20 % at 4096).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_shared_kernel(Params p, PrefillWs w, int layer, int slot,
-                                                                                                            int pos0, int R) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_shared_kernel(Params p, PrefillWs w, int layer,
+                                                                                                                int slot, int pos0, int R) {
   constexpr int HD = 128, RG = 2, RW = 16 * RG, RQ = 4 * RW;  // 32 rows per wavefront, 128 per workgroup
-  __shared__ u32x4 sK[2][8][64], sV[2][8][64];
+  constexpr int STEP = 32;                                    // keys per step
+  __shared__ u32x4 sK0[8][64], sK1[8][64], sV0[8][64], sV1[8][64];
 
-  const int blk = gridDim.x - 1 - blockIdx.x;  // blocks with the most keys first
-  const int head = blockIdx.y;
+  const int head = blockIdx.x, n_blk = gridDim.y, half = (n_blk + 1) / 2;
+  const int blk = (int)blockIdx.y < half ? n_blk - 1 - blockIdx.y : (int)blockIdx.y - half;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ml = lane & 15, g = lane >> 4;
   const int r0w = blk * RQ + wave * RW;        // first row of this wavefront
   const int nr = max(0, min(RW, R - r0w));     // its rows (0: the prompt ends before them)
   const int k_all = pos0 + min(R, blk * RQ + RQ);  // keys visible to the workgroup's last row
-  const int k_own = pos0 + r0w + nr;               // keys visible to this wavefront's last row
+  const int k_own = nr ? pos0 + r0w + nr : 0;      // keys visible to this wavefront's last row
   const uint16_t *kpool = (const uint16_t *)p.k_pool, *vpool = (const uint16_t *)p.v_pool;
+
+  // this wavefront's share of a step: K fragments 2 * wave, 2 * wave + 1 (fragment t * 4 + j: 16 key slots of half t, dims
+  // j * 32 ..) and the V fragments of dim blocks 2 * wave, 2 * wave + 1
+  auto issue = [&](u32x4 (*dK)[64], u32x4 (*dV)[64], int base) __attribute__((always_inline)) {
+    const int page = p.block_table[(size_t)slot * p.pages_per_seq + (base >> p.page_shift)];
+    const int poff = base & (p.page_size - 1);
+    const size_t hbase = ((size_t)layer * p.n_pages + page) * p.H + head;
+    const uint16_t *kp = kpool + (hbase * p.page_size + poff) * HD;   // K[key][dim]
+    const uint16_t *vp = vpool + hbase * HD * p.page_size + poff;     // Vt[dim][key]
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int f = wave * 2 + i, key = (ml >> 2) * 8 + (f >> 2) * 4 + (ml & 3);  // key slot ml of half f >> 2
+      copy_to_lds((const u32x4 *)(kp + (size_t)key * HD + (f & 3) * 32 + g * 8), &dK[f][0]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      copy_to_lds((const u32x4 *)(vp + (size_t)((wave * 2 + i) * 16 + ml) * p.page_size + g * 8), &dV[wave * 2 + i][0]);
+  };
+  issue(sK0, sV0, 0);
 
   u32x4 qh[RG][4], ql[RG][4];
   {
-    const float scale = rsqrtf((float)HD);
+    const float scale = rsqrtf((float)HD) * 1.4426950408889634f;
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
       const int rr = rg * 16 + ml;
@@ -684,44 +716,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 
   floatx4 o[RG][8];
-  float m_run[RG], l_run[RG];
+  float m_ref[RG], l_run[RG];  // reference of the exponentials (the same in a row's four lanes), this lane's sum
 #pragma unroll
   for (int rg = 0; rg < RG; ++rg) {
-    m_run[rg] = -INFINITY;
-    l_run[rg] = 0.f;
+    m_ref[rg] = -1e30f;  // below any score: the first step moves it.  Not -inf: a row past the last one has all its keys
+    l_run[rg] = 0.f;     //   masked in some steps, and -inf - -inf would not be a number
 #pragma unroll
     for (int db = 0; db < 8; ++db) o[rg][db] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
 
-  const int n_steps = (k_all + 31) >> 5;
-  // this wavefront's share of a step's tiles: K fragments 2 * wave, 2 * wave + 1 (fragment t * 4 + j:
-  // 16 keys of tile t x dims j * 32 ..), V fragments of dim blocks 2 * wave, 2 * wave + 1
-  u32x4 rK[3][2], rV[3][2];
-  auto fetch = [&](u32x4 (&dk)[2], u32x4 (&dv)[2], int step) __attribute__((always_inline)) {
-    const int base = step << 5;
-    const int page = p.block_table[(size_t)slot * p.pages_per_seq + (base >> p.page_shift)];
-    const int poff = base & (p.page_size - 1);
-    const size_t hbase = ((size_t)layer * p.n_pages + page) * p.H + head;
-    const uint16_t *kp = kpool + (hbase * p.page_size + poff) * HD;   // K[key][dim]
-    const uint16_t *vp = vpool + hbase * HD * p.page_size + poff;     // Vt[dim][key]
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int f = wave * 2 + i, t = f >> 2, j = f & 3;
-      const int key = (ml >> 2) * 8 + t * 4 + (ml & 3);  // key slot ml of tile t
-      dk[i] = *(const u32x4 *)(kp + (size_t)key * HD + j * 32 + g * 8);
-      dv[i] = *(const u32x4 *)(vp + (size_t)(f * 16 + ml) * p.page_size + g * 8);
-    }
-  };
-  auto put = [&](int buf, const u32x4 (&dk)[2], const u32x4 (&dv)[2]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      sK[buf][wave * 2 + i][lane] = dk[i];
-      sV[buf][wave * 2 + i][lane] = dv[i];
-    }
-  };
-  auto compute = [&](int buf, int base) __attribute__((always_inline)) {
-    if (base >= k_own) return;  // past this wavefront's last row
-    floatx4 sc[RG][2];
+  auto scores = [&](floatx4 (&sc)[RG][2], const u32x4 (*dK)[64]) __attribute__((always_inline)) {
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
@@ -730,93 +734,84 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const u32x4 kf = sK[buf][t * 4 + j][lane];
+        const bf16x8 kf = __builtin_bit_cast(bf16x8, dK[t * 4 + j][lane]);
 #pragma unroll
-        for (int rg = 0; rg < RG; ++rg) {
-          sc[rg][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf),
-                                                              __builtin_bit_cast(bf16x8, qh[rg][j]), sc[rg][t], 0, 0, 0);
-          sc[rg][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf),
-                                                              __builtin_bit_cast(bf16x8, ql[rg][j]), sc[rg][t], 0, 0, 0);
-        }
+        for (int rg = 0; rg < RG; ++rg) sc[rg][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, __builtin_bit_cast(bf16x8, qh[rg][j]), sc[rg][t], 0, 0, 0);
+#pragma unroll
+        for (int rg = 0; rg < RG; ++rg) sc[rg][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, __builtin_bit_cast(bf16x8, ql[rg][j]), sc[rg][t], 0, 0, 0);
       }
-    u32x4 ph[RG], pl[RG];
-    float alpha[RG];
+  };
+  // lane (ml, g) holds the scores of row rg * 16 + ml for keys base + 8g + 4t + r; turns them into (hi, lo) probabilities
+  auto softmax = [&](floatx4 (&sc)[RG][2], u32x4 (&ph)[RG], u32x4 (&pl)[RG], int base, bool masked) __attribute__((always_inline)) {
+    float top[RG];
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
-      const int rr = rg * 16 + ml;
-      float sv[8];
-      float m_blk = -INFINITY;
+      if (masked) {
+        const int last = pos0 + r0w + rg * 16 + ml - base - 8 * g;  // the row's last key, counted from this lane's first
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int key = base + 8 * g + 4 * t + r;
-          const bool ok = (rr < nr) && (key <= pos0 + r0w + rr);
-          const float v = ok ? sc[rg][t][r] : -INFINITY;
-          sv[4 * t + r] = v;
-          m_blk = fmaxf(m_blk, v);
-        }
-      m_blk = fmaxf(m_blk, __shfl_xor(m_blk, 16));
-      m_blk = fmaxf(m_blk, __shfl_xor(m_blk, 32));
-      const float m_new = fmaxf(m_run[rg], m_blk);
-      alpha[rg] = (m_run[rg] == -INFINITY) ? 0.f : __expf(m_run[rg] - m_new);
-      float pv[8], psum = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        pv[i] = (sv[i] == -INFINITY) ? 0.f : __expf(sv[i] - m_new);
-        psum += pv[i];
+          for (int r = 0; r < 4; ++r) sc[rg][t][r] = 4 * t + r <= last ? sc[rg][t][r] : -INFINITY;
       }
-      l_run[rg] = l_run[rg] * alpha[rg] + psum;
-      m_run[rg] = m_new;
+      top[rg] = fmaxf(fmaxf(fmaxf(sc[rg][0][0], sc[rg][0][1]), fmaxf(sc[rg][0][2], sc[rg][0][3])),
+                      fmaxf(fmaxf(sc[rg][1][0], sc[rg][1][1]), fmaxf(sc[rg][1][2], sc[rg][1][3])));
+    }
+    bool above = false;
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg) above |= top[rg] > m_ref[rg] + 8.f;
+    if (__builtin_amdgcn_ballot_w64(above) != 0) {
+#pragma unroll
+      for (int rg = 0; rg < RG; ++rg) {
+        float m = fmaxf(top[rg], m_ref[rg]);
+        m = fmaxf(m, __shfl_xor(m, 16));
+        m = fmaxf(m, __shfl_xor(m, 32));
+        const float alpha = __builtin_amdgcn_exp2f(m_ref[rg] - m);
+        m_ref[rg] = m;
+        l_run[rg] *= alpha;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) o[rg][db] *= alpha;
+      }
+    }
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg) {
+      float pv[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pv[i] = __builtin_amdgcn_exp2f(sc[rg][i >> 2][i & 3] - m_ref[rg]);
+      l_run[rg] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         ph[rg][i] = pack2_bf16(pv[2 * i], pv[2 * i + 1]);
-        pl[rg][i] = pack2_bf16(pv[2 * i] - __uint_as_float(ph[rg][i] << 16),
-                               pv[2 * i + 1] - __uint_as_float(ph[rg][i] & 0xffff0000u));
-      }
-      // once the running maxima have settled alpha is 1 in every lane: skip the rescaling then
-      if (__builtin_amdgcn_ballot_w64(alpha[rg] != 1.0f) != 0) {
-#pragma unroll
-        for (int db = 0; db < 8; ++db) o[rg][db] *= alpha[rg];
+        pl[rg][i] = pack2_bf16(pv[2 * i] - __uint_as_float(ph[rg][i] << 16), pv[2 * i + 1] - __uint_as_float(ph[rg][i] & 0xffff0000u));
       }
     }
+  };
+  auto output = [&](const u32x4 (&ph)[RG], const u32x4 (&pl)[RG], const u32x4 (*dV)[64]) __attribute__((always_inline)) {
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
-      const u32x4 vf = sV[buf][db][lane];
+      const bf16x8 vf = __builtin_bit_cast(bf16x8, dV[db][lane]);
 #pragma unroll
-      for (int rg = 0; rg < RG; ++rg) {
-        o[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf),
-                                                            __builtin_bit_cast(bf16x8, ph[rg]), o[rg][db], 0, 0, 0);
-        o[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf),
-                                                            __builtin_bit_cast(bf16x8, pl[rg]), o[rg][db], 0, 0, 0);
-      }
+      for (int rg = 0; rg < RG; ++rg) o[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, ph[rg]), o[rg][db], 0, 0, 0);
+#pragma unroll
+      for (int rg = 0; rg < RG; ++rg) o[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pl[rg]), o[rg][db], 0, 0, 0);
     }
   };
-  // step s: request the tiles of step s+2 (past the end: the last step again, in bounds, unused),
-  // lay the tiles of step s+1 (requested a step ago) down in LDS buffer (s+1) & 1, compute from
-  // buffer s & 1.  A buffer is rewritten only after the barrier that follows its last reader.
-  auto step = [&](auto I, int st) __attribute__((always_inline)) {
-    constexpr int i = decltype(I)::value;
-    fetch(rK[(i + 2) % 3], rV[(i + 2) % 3], min(st + 2, n_steps - 1));
-    __builtin_amdgcn_sched_barrier(0);
-    put((st + 1) & 1, rK[(i + 1) % 3], rV[(i + 1) % 3]);
-    compute(st & 1, st << 5);
-    __syncthreads();
-    __builtin_amdgcn_sched_barrier(0);
+  // The step's tiles have landed (every wavefront waits for its own copies, then they meet); the other stage, which
+  // everybody has finished reading, is filled with the next step's.
+  auto step = [&](const u32x4 (*dK)[64], const u32x4 (*dV)[64], u32x4 (*nK)[64], u32x4 (*nV)[64], int base) __attribute__((always_inline)) {
+    wait_copies<0>();
+    meet();
+    if (base + STEP < k_all) issue(nK, nV, base + STEP);
+    if (base >= k_own) return;  // past this wavefront's last row
+    const bool masked = base + STEP > pos0 + r0w + 1;  // some row of this wavefront does not see all of the step
+    floatx4 sc[RG][2];
+    u32x4 ph[RG], pl[RG];
+    scores(sc, dK);
+    softmax(sc, ph, pl, base, masked);
+    output(ph, pl, dV);
   };
-  fetch(rK[0], rV[0], 0);
-  fetch(rK[1], rV[1], min(1, n_steps - 1));
-  put(0, rK[0], rV[0]);
-  __syncthreads();
-  int st = 0;
-  for (; st + 2 < n_steps; st += 3) {
-    step(ic<0>{}, st);
-    step(ic<1>{}, st + 1);
-    step(ic<2>{}, st + 2);
-  }
-  if (st < n_steps) {
-    step(ic<0>{}, st);
-    if (st + 1 < n_steps) step(ic<1>{}, st + 1);
+  for (int base = 0; base < k_all; base += 2 * STEP) {
+    step(sK0, sV0, sK1, sV1, base);
+    if (base + STEP < k_all) step(sK1, sV1, sK0, sV0, base + STEP);
   }
 
   // lane (ml, g) holds dims db * 16 + 4g + r of row rg * 16 + ml; a row's sum of probabilities is
@@ -858,8 +853,7 @@ void launch_prefill_attention(const Params &p, const PrefillWs &w, int layer, in
   // 128 rows per workgroup with shared K/V tiles once a pass is long enough for the traffic out of
   // L2 to matter (measured: equal at 512 rows, -4 % of the pass at 2048, -7 % at 4096)
   if (w.attn_rows == 128 || (w.attn_rows == 0 && R > 512)) {
-    dim3 grid((R + 127) / 128, p.H);
-    attn_prefill_shared_kernel<<<grid, 256, 0, s>>>(p, w, layer, slot, pos0, R);
+    attn_prefill_shared_kernel<<<dim3(p.H, (R + 127) / 128), 256, 0, s>>>(p, w, layer, slot, pos0, R);
   } else if (w.attn_rows == 16) {
     dim3 grid((R + 15) / 16, p.H);
     attn_prefill_kernel<1><<<grid, 256, 0, s>>>(p, w, layer, slot, pos0, R);

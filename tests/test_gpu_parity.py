@@ -491,6 +491,27 @@ def test_prompt_pass_by_length(lens):
     g.close()
 
 
+@pytest.mark.parametrize("gain", [1.0, 4.0])
+@pytest.mark.parametrize("attn_rows", [32, 128])
+def test_prompt_attention_with_growing_scores(gain, attn_rows):
+    """Prompt attention where the largest score of a row keeps moving: with query and key projections four times larger the
+    scores reach 12 (17 in base-2 logarithms), so the exponentials' reference is moved in several steps and most
+    probabilities are small; 300 rows (ragged blocks, wavefronts without rows) in two passes.  Against the oracle.  Bound at
+    gain 4: a cached key entry (about 1.8) that rounds the other way moves a score by 1.8 * 1.8 * 2^-8 / sqrt(128) = 1.1e-3, a
+    probability by as much, and three layers with a few such entries per row add up to 4e-3 at most."""
+    w = MFMA_HD128
+    W = synth.make_weights(w.shape, w.seed, w.k, w.lm_head_scale)
+    for name in ("wq", "wk"):
+        W[name] = [synth.f32_to_bf16_bits(synth.bf16_bits_to_f32(x) * np.float32(gain)) for x in W[name]]
+    m = O.Model(w.shape, W, w.k)
+    prompt = np.random.default_rng(9).integers(0, w.shape.vocab, 301).astype(np.int32)
+    g = _gpu(w.shape, W, w.k, max_seq_len=384, page_size=64, options={"prefill_tiled": 1, "tune.prefill_tile": attn_rows, "tune.prefill_rows": 256})
+    st = parity.stepwise_parity(g, m, 0, 2, prompt, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=384)
+    print(st)
+    parity.check_stats(st, 2, parity.ERR_BF16_SMALL if gain == 1.0 else 4e-3, max_unstable=4)
+    g.close()
+
+
 @pytest.mark.parametrize("rows,lens", [(384, (37, 300, 129, 2, 1, 260)), (128, (200, 5, 131)), (256, (129, 128, 127, 1, 64, 65))])
 def test_prompt_pass_over_several_slots(rows, lens):
     """pass_prefill_batch: ragged prompts of several sequences share tiled passes over the weights (every
