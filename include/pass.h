@@ -116,7 +116,7 @@ int pass_load_weights(pass_ctx *ctx, const pass_weights *w, int on_device);
 /* Start a sequence in `slot` (frees what the slot held).  prompt: host, n >= 1 token ids.
  * Computes K/V of prompt[0..n-2]; prompt[n-1] becomes the pending token, so the first
  * drafting call is already a parallel one (Algorithm 1 starts from the prompt x_0..x_t).
- * seq_id selects the sequence's random streams.  Prompts of more than 48 rows on
+ * seq_id selects the sequence's random streams.  Prompts of more than PASS_MAX_ROWS rows on
  * the matrix-core path go through tiled, compute-bound kernels, up to 2048 rows per pass over the
  * weights; shorter ones (and every prompt on the generic path) through the decode kernels,
  * PASS_MAX_ROWS rows per pass ("prefill_*" options).  Returns when the cache is filled.
@@ -127,7 +127,7 @@ int pass_prefill(pass_ctx *ctx, int slot, uint32_t seq_id, const int32_t *prompt
 /* pass_prefill for several sequences at once (Algorithm 1's "initial prompt sequence" of a batch; the prefixes
  * of a training batch): slots[n_slots] distinct, seq_ids[n_slots], lens[n_slots] >= 1, prompts: the prompts one
  * after the other (host, sum of lens tokens).  The state afterwards is what n_slots calls of pass_prefill
- * leave.  Where the tiled kernels apply (matrix-core path, more than 48 rows in all), rows of
+ * leave.  Where the tiled kernels apply (matrix-core path, more than PASS_MAX_ROWS rows in all), rows of
  * several sequences share a pass over the weights: every sequence starts on a block of 128 rows of the pass, a
  * prompt that does not fit goes on in the next pass, attention runs per sequence.  A row's arithmetic is that of
  * pass_prefill up to the grouping of the RMSNorm's partial sums, which follows the pass's row count (logits
@@ -314,7 +314,7 @@ int pass_seq_len(pass_ctx *ctx, int slot, int32_t *kv_len, int32_t *n_generated)
  *                      resets the counters pass_kernel_time reports
  *   "prefill_chunk"    1 .. PASS_MAX_ROWS: prompt rows per pass over the weights when the prompt goes through
  *                      the decode kernels
- *   "prefill_tiled"    -1 = prompts of more than 48 rows take the tiled, compute-bound prompt pass
+ *   "prefill_tiled"    -1 = prompts of more than PASS_MAX_ROWS rows take the tiled, compute-bound prompt pass
  *                      when the model runs on the matrix-core path with the matrix-core attention kernel,
  *                      0 = never, 1 = every prompt does
  * Names that start with "tune." are sweep knobs of the kernels' launch shapes for development; they are not part

@@ -4,7 +4,7 @@
 // of tokens pushed through them re-reads the model dozens of times and leaves the matrix cores
 // idle.  Here up to 2048 prompt rows go through each layer in one pass:
 //
-//   gemm_tile_kernel   a workgroup of eight wavefronts computes 256 x 128 (or 256 x 256, 384 x 128) output features x
+//   gemm_tile_kernel   a workgroup of eight wavefronts computes 256 x 128 (or 256 x 256, 384 x 128, 192 x 128) output features x
 //                      rows; both operands stream from memory straight into a ring of LDS stages.  Accumulators
 //                      stay in the register file for the whole K loop, one fixed summation order.  Same operand
 //                      formats and the same fused epilogues as the decode GEMM (RMSNorm scale, rotary embedding and
@@ -154,12 +154,12 @@ __device__ __forceinline__ void finish_gateup(const Params &p, int m, int f, flo
 template <int EPI, int WF, int WR, int SW, int RG>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tile_kernel(Params p, PrefillWs w, TileArgs a) {
   constexpr int TS = WF * SW, TG = WR * RG;         // strips and 16-row groups of the tile
-  constexpr int NA = TS / 8, NB = TG * 2 / 8;       // 1 KB copies of a wavefront per step
+  constexpr int NC = (TS + 2 * TG + 7) / 8;         // 1 KB copies of a wavefront per step
   constexpr int ROWS = TG * 16;
   constexpr bool NORM = (EPI == TILE_QKV || EPI == TILE_GATEUP);
-  static_assert(WF * WR == 8 && TS % 8 == 0 && TG % 4 == 0, "eight wavefronts share the copies evenly");
+  static_assert(WF * WR == 8, "eight wavefronts");
   static_assert(EPI != TILE_GATEUP || SW % 2 == 0, "a wavefront needs a gate strip and its up strip");
-  __shared__ u32x4 sA0[TS][64], sA1[TS][64], sA2[TS][64], sB0[TG * 2][64], sB1[TG * 2][64], sB2[TG * 2][64];
+  __shared__ u32x4 s0[TS + 2 * TG][64], s1[TS + 2 * TG][64], s2[TS + 2 * TG][64];  // weight tiles, then activation fragments
   __shared__ float s_inv[ROWS], s_part[512];
 
   // tile of this workgroup: consecutive workgroup ids go to different dies (XCDs), each with its own L2; every die
@@ -181,27 +181,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int kt0 = slice * a.kt_slice, kt1 = min(KT, kt0 + a.kt_slice);
   const int m0 = tm * ROWS;
 
-  // sources of this wavefront's copies.  Strips past the end repeat the last one, row groups past the end the last
-  // one (in bounds; their results are dropped).  Fragment (16-row group, half): lane (c, kq) takes the slot of row
-  // c & 7 of 8-row group c >> 3.
-  const u32x4 *ap[NA], *bp[NB];
+  // sources of this wavefront's copies: tiles wave * NC .. of the stage (past its end: the last one again).  Strips past
+  // the end repeat the last one, row groups past the end the last one (in bounds; their results are dropped).  Fragment
+  // (16-row group, half): lane (c, kq) takes the slot of row c & 7 of 8-row group c >> 3.
+  const u32x4 *src[NC];
+  int dst[NC];
 #pragma unroll
-  for (int i = 0; i < NA; ++i) ap[i] = a.W + ((size_t)min(tn * TS + wave * NA + i, a.n_strips - 1) * KT) * 64 + lane;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int f = wave * NB + i, rg = f >> 1, half = f & 1;
-    const int g8 = min(tm * TG * 2 + 2 * rg + (c >> 3), n_groups - 1);
-    bp[i] = a.X + (size_t)g8 * KT * 64 + kq * 16 + half * 8 + (c & 7);
+  for (int i = 0; i < NC; ++i) {
+    dst[i] = min(wave * NC + i, TS + 2 * TG - 1);
+    if (dst[i] < TS) {
+      src[i] = a.W + ((size_t)min(tn * TS + dst[i], a.n_strips - 1) * KT) * 64 + lane;
+    } else {
+      const int f = dst[i] - TS, rg = f >> 1, half = f & 1;
+      const int g8 = min(tm * TG * 2 + 2 * rg + (c >> 3), n_groups - 1);
+      src[i] = a.X + (size_t)g8 * KT * 64 + kq * 16 + half * 8 + (c & 7);
+    }
   }
-  auto issue = [&](u32x4 (*dA)[64], u32x4 (*dB)[64], int kt) __attribute__((always_inline)) {
+  auto issue = [&](u32x4 (*st)[64], int kt) __attribute__((always_inline)) {
     const size_t off = (size_t)min(kt, kt1 - 1) * 64;  // steps past the end repeat the last one (never read)
 #pragma unroll
-    for (int i = 0; i < NA; ++i) copy_to_lds(ap[i] + off, &dA[wave * NA + i][0]);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) copy_to_lds(bp[i] + off, &dB[wave * NB + i][0]);
+    for (int i = 0; i < NC; ++i) copy_to_lds(src[i] + off, &st[dst[i]][0]);
   };
-  issue(sA0, sB0, kt0);
-  issue(sA1, sB1, kt0 + 1);
+  issue(s0, kt0);
+  issue(s1, kt0 + 1);
 
   // 1 / rms of the tile's rows from the producer's partial sums of h^2
   if constexpr (NORM) {
@@ -235,18 +237,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int g = 0; g < RG; ++g) acc[s][g] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  auto step = [&](const u32x4 (*dA)[64], const u32x4 (*dB)[64], u32x4 (*nA)[64], u32x4 (*nB)[64], int kt) __attribute__((always_inline)) {
+  auto step = [&](const u32x4 (*st)[64], u32x4 (*nxt)[64], int kt) __attribute__((always_inline)) {
     bf16x8 av[SW], bv[RG][2];
 #pragma unroll
-    for (int s = 0; s < SW; ++s) av[s] = __builtin_bit_cast(bf16x8, dA[wf * SW + s][lane]);
+    for (int s = 0; s < SW; ++s) av[s] = __builtin_bit_cast(bf16x8, st[wf * SW + s][lane]);
 #pragma unroll
     for (int g = 0; g < RG; ++g)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) bv[g][h] = __builtin_bit_cast(bf16x8, dB[(wr * RG + g) * 2 + h][lane]);
-    issue(nA, nB, kt + 2);
+      for (int h = 0; h < 2; ++h) bv[g][h] = __builtin_bit_cast(bf16x8, st[TS + (wr * RG + g) * 2 + h][lane]);
+    issue(nxt, kt + 2);
     __builtin_amdgcn_sched_barrier(0);
     wait_lds_reads();
-    if (grp) wait_copies<NA + NB>();
+    if (grp) wait_copies<NC>();
     meet();
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -257,21 +259,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int s = 0; s < SW; ++s) acc[s][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[s], bv[g][h], acc[s][g], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
-    if (!grp) wait_copies<NA + NB>();
+    if (!grp) wait_copies<NC>();
     meet();
   };
-  wait_copies<NA + NB>();
+  wait_copies<NC>();
   wait_lds_reads();
   meet();
   if (grp) meet();
   int kt = kt0;
   for (; kt + 2 < kt1; kt += 3) {
-    step(sA0, sB0, sA2, sB2, kt);
-    step(sA1, sB1, sA0, sB0, kt + 1);
-    step(sA2, sB2, sA1, sB1, kt + 2);
+    step(s0, s2, kt);
+    step(s1, s0, kt + 1);
+    step(s2, s1, kt + 2);
   }
-  if (kt < kt1) step(sA0, sB0, sA2, sB2, kt);
-  if (kt + 1 < kt1) step(sA1, sB1, sA0, sB0, kt + 1);
+  if (kt < kt1) step(s0, s2, kt);
+  if (kt + 1 < kt1) step(s1, s0, kt + 1);
   if (!grp) meet();
   wait_copies<0>();  // no copy may land in LDS that the next workgroup already owns
 
@@ -367,7 +369,7 @@ __global__ __launch_bounds__(256) void tile_reduce_kernel(Params p, PrefillWs w,
 
 // Shapes of the tiled GEMM: features x rows of a tile, and what a k-step of it takes when every compute unit has one.
 struct TileShape { int ts, rows, strips_per_wave; float step_us; };
-constexpr TileShape kTileShapes[3] = {{16, 128, 4, 0.74f}, {16, 256, 8, 1.40f}, {24, 128, 12, 1.10f}};
+constexpr TileShape kTileShapes[4] = {{16, 128, 4, 0.74f}, {16, 256, 8, 1.40f}, {24, 128, 12, 1.10f}, {12, 128, 6, 0.57f}};
 struct TilePlan { int shape, slices; };
 
 // Which tile and how many slices of K.  The tiles run in rounds of one per compute unit (256), a round takes the
@@ -378,11 +380,10 @@ TilePlan plan_tiles(int n_strips, int K, int M, size_t part_floats, int want) {
   const int KT = K / 32;
   TilePlan best{0, 1};
   float best_us = 1e30f;
-  for (int s = 0; s < 3; ++s) {
+  constexpr int kAsked[6] = {-1, 0, 0, 2, 1, 3};  // shape of each tune.prefill_strips value
+  for (int s = 0; s < 4; ++s) {
     const TileShape &t = kTileShapes[s];
-    if (want == 2 && s != 0) continue;
-    if (want == 4 && s != 1) continue;
-    if (want == 3 && s != 2) continue;
+    if (want > 1 && s != kAsked[want]) continue;
     const int tiles = ((n_strips + t.ts - 1) / t.ts) * ((M + t.rows - 1) / t.rows);
     for (int ks = 1; ks <= 8; ++ks) {
       const int kts = (KT + ks - 1) / ks;
@@ -418,6 +419,7 @@ int launch_tile(const Params &p, const PrefillWs &w, TileArgs a, hipStream_t s) 
     constexpr int e = decltype(E)::value;
     if (pl.shape == 1) gemm_tile_kernel<e, 2, 4, 8, 4><<<grid, 512, 0, s>>>(p, w, a);
     else if (pl.shape == 2) gemm_tile_kernel<e, 2, 4, 12, 2><<<grid, 512, 0, s>>>(p, w, a);
+    else if (pl.shape == 3) gemm_tile_kernel<e, 2, 4, 6, 2><<<grid, 512, 0, s>>>(p, w, a);
     else gemm_tile_kernel<e, 4, 2, 4, 4><<<grid, 512, 0, s>>>(p, w, a);
   };
   if (a.slices == 1) {

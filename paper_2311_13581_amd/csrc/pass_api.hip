@@ -118,7 +118,7 @@ struct pass_ctx {
   TrainWs train;
   float *train_loss_host = nullptr;  // pinned [kMaxRows]  // launch shapes of the decode GEMMs (captured graphs carry them: cleared when it changes)
   int opt_prefill_chunk = 64;
-  int opt_prefill_tiled = -1;  // -1: prompts of more than 2 * kMaxRows rows take the tiled pass; 0 never; 1 always
+  int opt_prefill_tiled = -1;  // -1: prompts of more than kTiledMinRows rows take the tiled pass; 0 never; 1 always
   Params PP;                   // P with the row buffers of the tiled prompt pass
   PrefillWs pws;
   std::vector<hipEvent_t> kev;
@@ -427,10 +427,10 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
 struct PassSeg { int slot, pos0, rows, row_base; };
 
 // Rows above which a prompt (or a batch of prompts, whose every prompt starts on a block of 128 rows) takes the tiled
-// pass.  Measured per 7B layer: 32 rows 123 us through the decode kernels, 151 tiled; 48 rows 160 and 159; 64 rows
-// 194 and 165; 100 rows (two chunks) 318 and 184; 384 rows 1140 and 340.  A further prompt of a batch adds about 70 us
-// to a tiled pass and at least 100 us as a call of its own.
-constexpr int kTiledMinRows = 48;
+// pass: what one pass of the decode kernels holds.  Measured per 7B layer: 48 rows 133 us through the decode kernels, 156
+// tiled; 64 rows 152 and 166; 100 rows (two passes) 268 and 183; 384 rows 893 and 333.  A further prompt of a batch adds
+// about 64 us to a tiled pass and at least 92 us as a call of its own.
+constexpr int kTiledMinRows = kMaxRows;
 
 // How pass_prefill_batch packs prompts into tiled passes of at most `cap` rows (a multiple of 128): prompt b has
 // lens[b] - 1 rows to cache; its rows start on a block of 128 rows of a pass; what does not fit goes on in the next
@@ -1399,7 +1399,7 @@ int pass_train_step(pass_ctx *c, const int32_t *slots, int n_slots, const int32_
     // ---- backward: every dx = W^T dy is a matrix-core product with the packed transpose; its input travels as
     // (hi, lo) tiles (T.x), its output as slices over the contraction (T.part) that the consumer adds up ----
     const size_t rows = kMaxRows;
-    launch_ce_grad(T.logits, T.targets, loss_scale, T.row_loss, M, P.V, T.x, s);
+    launch_ce_grad(T.logits, T.targets, loss_scale, T.row_loss, M, P.V, (float2 *)P.row_parts, T.x, s);
     int KS = launch_gemm_plain(P, T.lm_head_t, T.x, M, (int)d, (int)V, T.part, s);
     launch_rmsnorm_bwd(P, dt, T.save_hl, c->final_norm, T.part, KS, rows * d, T.dh, M, 0, T.x, s);
     for (int l = P.L - 1; l >= 0; --l) {
@@ -1441,7 +1441,7 @@ int pass_train_step(pass_ctx *c, const int32_t *slots, int n_slots, const int32_
     launch_rmsnorm(P, dt, P.h, c->final_norm, P.xn, M, s);
     launch_gemm_generic(dt, P.xn, c->lm_head, T.logits, M, P.V, P.d, P.V, nullptr, 0, s);
     // ---- loss on the look-ahead rows and its gradient, back through the frozen model ----
-    launch_ce_grad(T.logits, T.targets, loss_scale, T.row_loss, M, P.V, nullptr, s);
+    launch_ce_grad(T.logits, T.targets, loss_scale, T.row_loss, M, P.V, (float2 *)P.row_parts, nullptr, s);
     launch_gemm_t(dt, T.logits, (int)V, c->lm_head, T.part, T.dxn, (int)d, M, (int)V, (int)d, s);
     launch_rmsnorm_bwd(P, dt, T.save_hl, c->final_norm, T.dxn, 1, 0, T.dh, M, 0, nullptr, s);
     for (int l = P.L - 1; l >= 0; --l) {
@@ -1549,7 +1549,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   //   tune.prefill_tile   query rows per attention workgroup of the tiled prompt pass (0, 16, 32, 128)
   //   tune.prefill_block  (1 .. 64) * 100 + row tiles of a panel of the tiled GEMMs' tile order (0 = 1024 rows)
   //   tune.prefill_strips tile of the tiled GEMMs: 0 = by shape, 1 = 256 x 128 features x rows with K in slices,
-  //                       2 = 256 x 128, 3 = 384 x 128, 4 = 256 x 256
+  //                       2 = 256 x 128, 3 = 384 x 128, 4 = 256 x 256, 5 = 192 x 128
   if (!strcmp(name, "tune.gemm_cfg")) {
     if (value >= 2000000) {
       if (c->tuning.set_split(value - 2000000)) return fail(c, PASS_EINVAL, "tune.gemm_cfg (split residual GEMM): 0 .. 8 slices of K");
@@ -1598,7 +1598,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
     return PASS_OK;
   }
   if (!strcmp(name, "tune.prefill_strips")) {
-    if (value < 0 || value > 4) return fail(c, PASS_EINVAL, "tune.prefill_strips: 0 (by shape) .. 4");
+    if (value < 0 || value > 5) return fail(c, PASS_EINVAL, "tune.prefill_strips: 0 (by shape) .. 5");
     c->pws.strips_opt = value;
     return PASS_OK;
   }

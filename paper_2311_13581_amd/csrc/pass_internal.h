@@ -220,7 +220,8 @@ __device__ __forceinline__ void store_split4(uint16_t *xs, int m, int K, int k, 
 struct PrefillWs {
   int rows;       // capacity in rows (multiple of 128); also the row stride of the partial sums of h^2
   int np;         // partial sums of h^2 per row that the last producer of rows has left
-  int strips_opt; // GEMM tiles: 0 = by shape; 1 = split along K, 2 = 256 x 128, 4 = 256 x 256, 3 = 384 x 128 features x rows
+  int strips_opt; // GEMM tiles: 0 = by shape; 1 = split along K, 2 = 256 x 128, 4 = 256 x 256, 3 = 384 x 128,
+                  //   5 = 192 x 128 features x rows
   int panel;      // row tiles of a panel of the GEMMs' tile order; 0 = 1024 rows
   float *part;    // sums over slices of K: part_floats floats
   size_t part_floats;
@@ -263,7 +264,7 @@ void launch_assemble_train(const Params &p, int dtype, const void *tok_emb, cons
 void launch_assemble_train_mfma(const Params &p, const void *tok_emb, const float *master, const void *gain0, int B, int R,
                                 hipStream_t s);
 // x_out not null: the gradient leaves as (hi, lo) tiles of V features instead of in place
-void launch_ce_grad(float *logits, const int32_t *targets, float scale, float *row_loss, int M, int V, uint16_t *x_out,
+void launch_ce_grad(float *logits, const int32_t *targets, float scale, float *row_loss, int M, int V, float2 *parts, uint16_t *x_out,
                     hipStream_t s);
 void launch_gemm_t(int dtype, const float *dY, int ldy, const void *W, float *part, float *out, int ldo, int M, int N, int K,
                    hipStream_t s);

@@ -355,12 +355,12 @@ def test_tiled_prompt_pass(plen, attn_rows, rows, strips, block):
     g.close()
 
 
-@pytest.mark.parametrize("strips", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("strips", [0, 1, 2, 3, 4, 5])
 @pytest.mark.parametrize("d,ffn,plen", [(32, 32, 18), (64, 96, 130), (96, 160, 258), (544, 1184, 140)])
 def test_tiled_gemm_shapes(d, ffn, plen, strips):
     """Every tile of the prompt pass's GEMM where its ring of stages, its remainders and its slices can go wrong: one,
     two, three, five, 17 and 37 k-steps (fewer than the ring's three stages, and every remainder of them), row tiles with
-    one row left (129, 257) or a fraction of a 16-row group, strips that end inside a tile (2 .. 74 against 16 or 24), and
+    one row left (129, 257) or a fraction of a 16-row group, strips that end inside a tile (2 .. 74 against 12, 16 or 24), and
     K in as many slices as have steps (strips = 1: up to eight, the last one shorter).  The calls on top of the prompt are
     compared with the oracle, which prefills row by row."""
     shape = synth.ModelShape(2, d, 1, 128, ffn, 1008, dtype=synth.BF16)
@@ -473,18 +473,18 @@ def test_sampling_epilogue_ties_across_parts():
     g.close()
 
 
-@pytest.mark.parametrize("lens", [(48,), (49,), (50,), (65,), (20, 29), (20, 30), (1, 49, 2)])
+@pytest.mark.parametrize("lens", [(64,), (65,), (66,), (129,), (30, 36), (31, 36), (1, 65, 2)])
 def test_prompt_pass_by_length(lens):
     """Default options on both sides of the row count at which a prompt, or a batch of prompts, changes from the decode
-    kernels to the tiled pass (47, 48, 49, 64 rows; 47 and 48 rows in two prompts, 49 in three), against the oracle."""
+    kernels to the tiled pass (63, 64, 65, 128 rows; 64 and 65 rows in two prompts, 65 in three), against the oracle."""
     w = MFMA_HD128
     W = synth.make_weights(w.shape, w.seed, w.k, w.lm_head_scale)
     m = O.Model(w.shape, W, w.k)
     rng = np.random.default_rng(sum(lens))
     prompts = [rng.integers(0, w.shape.vocab, n).astype(np.int32) for n in lens]
     slots = list(range(len(lens)))
-    g = _gpu(w.shape, W, w.k, max_slots=len(lens), max_seq_len=128, page_size=64)
-    stats = parity.batch_parity(g, m, slots, [7 + i for i in slots], prompts, slots, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=128,
+    g = _gpu(w.shape, W, w.k, max_slots=len(lens), max_seq_len=192, page_size=64)
+    stats = parity.batch_parity(g, m, slots, [7 + i for i in slots], prompts, slots, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=192,
                                 one_call=True)
     for sl in slots:
         parity.check_stats(stats[sl], 2, parity.ERR_BF16_SMALL)
