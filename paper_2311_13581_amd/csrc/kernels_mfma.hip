@@ -275,9 +275,9 @@ __device__ __forceinline__ void gemm_finish(const Params &p, const GemmArgs &a, 
       int n = strip * 16 + 4 * g;
       float ss = 0.f;
       if (live) {
-        float *hp = p.h + (size_t)m * p.d + n;
-        floatx4 hv = *(floatx4 *)hp + y[0];
-        *(floatx4 *)hp = hv;
+        const size_t at = (size_t)m * p.d + n;
+        floatx4 hv = *(const floatx4 *)(p.h + at) + y[0];
+        *(floatx4 *)(p.h_out + at) = hv;
         float t[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -670,8 +670,8 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(Params p, const float
   const int strip = blockIdx.x, m = threadIdx.x >> 2, n = strip * 16 + (threadIdx.x & 3) * 4;
   float ss = 0.f;
   if (m < M) {
-    float *hp = p.h + (size_t)m * p.d + n;
-    floatx4 hv = *(floatx4 *)hp;
+    const size_t at = (size_t)m * p.d + n;
+    floatx4 hv = *(const floatx4 *)(p.h + at);
     floatx4 part[8];
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks)  // all slices requested at once (index clamped, surplus dropped)
@@ -681,7 +681,7 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(Params p, const float
     for (int ks = 1; ks < 8; ++ks)
       if (ks < KS) y += part[ks];
     hv += y;
-    *(floatx4 *)hp = hv;
+    *(floatx4 *)(p.h_out + at) = hv;
     float t[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {

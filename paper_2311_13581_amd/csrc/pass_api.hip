@@ -204,7 +204,7 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   P.row_pos = A.take<int32_t>(M); P.row_slot = A.take<int32_t>(M); P.row_out = A.take<int32_t>(M);
   P.rope_cos = A.take<float>(M * c.head_dim / 2); P.rope_sin = A.take<float>(M * c.head_dim / 2);
   P.rope_theta = A.take<double>(c.head_dim / 2);
-  P.h = A.take<float>(M * d); P.xn = A.take<float>(M * d); P.qkv = A.take<float>(M * 3 * D);
+  P.h = P.h_out = A.take<float>(M * d); P.xn = A.take<float>(M * d); P.qkv = A.take<float>(M * 3 * D);
   P.attn = A.take<float>(M * D); P.gu = A.take<float>(M * 2 * F); P.act = A.take<float>(M * F);
   P.attn_x = A.take<uint16_t>(2 * M * D); P.act_x = A.take<uint16_t>(2 * M * F); P.xg = A.take<uint16_t>(2 * M * d);
   P.ssq = A.take<float>((d / 16 + 1) * M);
@@ -1379,22 +1379,25 @@ int pass_train_step(pass_ctx *c, const int32_t *slots, int n_slots, const int32_
   const float loss_scale = 1.0f / (float)(n_slots * k);
   if (T.mfma) {
     // ---- forward: the drafting call's own kernels (the gate/up product also keeps its pre-activations); each
-    // layer's q, attention output and ln-sum-exp land in that layer's area ----
+    // layer's q, attention output and ln-sum-exp land in that layer's area, and the residual projections leave the
+    // residual stream in the area the backward pass wants it in (it was copied there, twice per layer, 5 us each) ----
+    P.h = T.save_h0;
     launch_assemble_train_mfma(P, c->tok_emb, T.master, c->layers[0].attn_norm, n_slots, R, s);
     for (int l = 0; l < P.L; ++l) {
       const LayerW &w = c->layers[l];
       P.qkv = T.save_qkv + (size_t)l * kMaxRows * 3 * D;
       P.attn_x = (uint16_t *)(T.save_attn + (size_t)l * kMaxRows * D);
       P.lse = T.save_lse + (size_t)l * kMaxRows * H;
-      HIP_TRY(c, hipMemcpyAsync(T.save_h0 + (size_t)l * kMaxRows * d, P.h, sizeof(float) * M * d, hipMemcpyDeviceToDevice, s));
       launch_gemm_qkv(P, c->tuning, w.wqkv, l, M, s);
       launch_attention(P, dt, l, n_slots, R, S, 1, s);
+      P.h_out = T.save_h1 + (size_t)l * kMaxRows * d;
       launch_gemm_resid(P, c->tuning, w.wo, P.attn_x, P.D, w.ffn_norm, M, s);
-      HIP_TRY(c, hipMemcpyAsync(T.save_h1 + (size_t)l * kMaxRows * d, P.h, sizeof(float) * M * d, hipMemcpyDeviceToDevice, s));
+      P.h = P.h_out;
       launch_gemm_gateup_save(P, w.wgu, T.save_gu + (size_t)l * kMaxRows * 2 * F, M, s);
+      P.h_out = l + 1 < P.L ? T.save_h0 + (size_t)(l + 1) * kMaxRows * d : T.save_hl;
       launch_gemm_resid(P, c->tuning, w.wdown, P.act_x, P.F, l + 1 < P.L ? c->layers[l + 1].attn_norm : c->final_norm, M, s);
+      P.h = P.h_out;
     }
-    HIP_TRY(c, hipMemcpyAsync(T.save_hl, P.h, sizeof(float) * M * d, hipMemcpyDeviceToDevice, s));
     launch_gemm_logits(P, c->tuning, c->lm_head, T.logits, M, s);
     // ---- backward: every dx = W^T dy is a matrix-core product with the packed transpose; its input travels as
     // (hi, lo) tiles (T.x), its output as slices over the contraction (T.part) that the consumer adds up ----

@@ -101,6 +101,7 @@ struct Params {
   double *rope_theta;                     // [hd/2] base^(-2i/hd), filled at create
   // workspaces
   float *h;        // [M][d]   residual stream
+  float *h_out;    // matrix-core decode GEMMs: where the residual projections leave it (h itself, except in training)
   float *xn;       // [M][d]
   float *qkv;      // [M][3D]  q | k | v
   float *attn;     // [M][D]
