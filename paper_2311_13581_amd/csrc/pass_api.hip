@@ -236,7 +236,8 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   const size_t R = W.rows;
   // sums over slices of K of the GEMMs that are split: at most one tile of 384 x 128 per compute unit, and never more
   // than eight slices of the widest product
-  W.part_floats = std::min<size_t>((size_t)256 * 384 * 128, 8 * R * std::max(3 * D, std::max(2 * F, d)));
+  // (fp32 models have no tiled pass)
+  W.part_floats = c.dtype == PASS_BF16 ? std::min<size_t>((size_t)256 * 384 * 128, 8 * R * std::max(3 * D, std::max(2 * F, d))) : 0;
   const size_t ws_bytes = R * 4 * (d + d + D + D + F + W.np + c.head_dim) + W.part_floats * 4 + 9 * 256;
   if (ws_bytes > stage_bytes) stage_bytes = ws_bytes;
   void *staging = A.take<char>(stage_bytes);
