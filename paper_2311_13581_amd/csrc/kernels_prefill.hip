@@ -4,7 +4,7 @@
 // of tokens pushed through them re-reads the model dozens of times and leaves the matrix cores
 // idle.  Here up to 2048 prompt rows go through each layer in one pass:
 //
-//   gemm_tile_kernel   a workgroup of eight wavefronts computes 256 x 128 (or 256 x 256, 384 x 128, 192 x 128) output features x
+//   gemm_tile_kernel   a workgroup of eight wavefronts computes 256 x 128 (or 192 x 128) output features x
 //                      rows; both operands stream from memory straight into a ring of LDS stages.  Accumulators
 //                      stay in the register file for the whole K loop, one fixed summation order.  Same operand
 //                      formats and the same fused epilogues as the decode GEMM (RMSNorm scale, rotary embedding and
@@ -139,18 +139,19 @@ __device__ __forceinline__ void finish_gateup(const Params &p, int m, int f, flo
 // The tiled GEMM.  Y[rows][features] += W . X over k-steps of 32; a workgroup of eight wavefronts owns 16 * WF * SW
 // features x 16 * WR * RG rows, a wavefront SW strips of 16 features x RG groups of 16 rows.
 // Both operands of a k-step go straight from memory to LDS, into a ring of three stages, two steps ahead of their
-// use.  The (hi, lo) halves of an activation row are two B operands of one accumulator (a weight fragment is read
-// once for both), so a k-step is 2 * SW * RG MFMAs per wavefront.
+// use.  The (hi, lo) halves of an activation row are two B operands (a weight fragment is read once for both), so a
+// k-step is 2 * SW * RG MFMAs per wavefront.  The two halves' sums have accumulators of their own: in a common one the
+// sum is rounded twice as often (2047 rows, error of the sums alone relative to the result: K = 4096 5.7e-7 against 4.0e-7,
+// K = 11008 9.5e-7 against 6.7e-7, the whole product 2.63e-6 against 2.54e-6).  That holds the tile to 128 rows: the larger
+// ones (256 x 256, 384 x 128) took 2 to 6 % less time of a prompt pass, with one accumulator.
 // The wavefronts form two groups, one wavefront of each group per SIMD, that alternate: while one group reads the
 // fragments of its next k-step out of LDS and requests a later stage, the other keeps the matrix cores busy; the
 // workgroup meets after every half step.  Timeline of half steps: group 0 reads step t in 2t and multiplies in
 // 2t + 1, group 1 reads it in 2t + 1 and multiplies in 2t + 2.  A stage is overwritten by requests issued two half
 // steps after group 0's reads (one after group 1's) have returned; its copies have landed, in every wavefront, at
 // the meeting before group 0 reads it (each group waits for its own at the end of half step 2t - 1).
-// Bound by power: at 2047 x 12288 x 4096 the matrix cores are busy 76 % of the cycles at the 1.8 GHz the chip then
-// holds.  Against a form that kept weight fragments in registers, staged the activations through registers and gave
-// hi and lo columns accumulators of their own (4 wavefronts, 256 x 64 tiles): QKV 363 -> 283 us, Wo 124 -> 97,
-// gate/up 633 -> 590, down 326 -> 247 (7B shapes, 2047 rows).
+// Bound by power.  Against a form that kept weight fragments in registers and staged the activations through registers
+// (4 wavefronts, 256 x 64 tiles): QKV 363 -> 291 us, Wo 124 -> 113, gate/up 633 -> 552, down 326 -> 263 (7B shapes, 2047 rows).
 template <int EPI, int WF, int WR, int SW, int RG>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tile_kernel(Params p, PrefillWs w, TileArgs a) {
   constexpr int TS = WF * SW, TG = WR * RG;         // strips and 16-row groups of the tile
@@ -231,11 +232,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // published by the meetings of the main loop
   }
 
-  floatx4 acc[SW][RG];
+  floatx4 acc[2][SW][RG];
 #pragma unroll
-  for (int s = 0; s < SW; ++s)
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int g = 0; g < RG; ++g) acc[s][g] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < SW; ++s)
+#pragma unroll
+      for (int g = 0; g < RG; ++g) acc[h][s][g] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   auto step = [&](const u32x4 (*st)[64], u32x4 (*nxt)[64], int kt) __attribute__((always_inline)) {
     bf16x8 av[SW], bv[RG][2];
@@ -256,7 +259,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int s = 0; s < SW; ++s) acc[s][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[s], bv[g][h], acc[s][g], 0, 0, 0);
+        for (int s = 0; s < SW; ++s) acc[h][s][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[s], bv[g][h], acc[h][s][g], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
     if (!grp) wait_copies<NC>();
@@ -277,6 +280,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (!grp) meet();
   wait_copies<0>();  // no copy may land in LDS that the next workgroup already owns
 
+  auto total = [&](int s, int g) __attribute__((always_inline)) { return acc[0][s][g] + acc[1][s][g]; };
   // lane (c, kq) holds Y[row 16 g + c][features 16 strip + 4 kq .. + 3]
   const int strip0 = tn * TS + wf * SW;
 #pragma unroll
@@ -290,18 +294,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int s = 0; s < SW; s += 2)
         if (row_live && strip0 + s + 1 < a.n_strips)
-          finish_gateup(p, m, ((strip0 + s) >> 1) * 16 + 4 * kq, acc[s][g], acc[s + 1][g], inv);
+          finish_gateup(p, m, ((strip0 + s) >> 1) * 16 + 4 * kq, total(s, g), total(s + 1, g), inv);
     } else {
 #pragma unroll
       for (int s = 0; s < SW; ++s) {
         const int n = (strip0 + s) * 16 + 4 * kq;
         if (row_live && strip0 + s < a.n_strips) {
           if constexpr (EPI == TILE_RESID)
-            ss += finish_resid(p, a.gain_next, m, n, acc[s][g]);
+            ss += finish_resid(p, a.gain_next, m, n, total(s, g));
           else if constexpr (EPI == TILE_QKV)
-            finish_qkv(p, w, a, m, n, acc[s][g] * inv);
+            finish_qkv(p, w, a, m, n, total(s, g) * inv);
           else
-            *(floatx4 *)(a.part + ((size_t)slice * a.M + m) * (a.n_strips * 16) + n) = acc[s][g];
+            *(floatx4 *)(a.part + ((size_t)slice * a.M + m) * (a.n_strips * 16) + n) = total(s, g);
         }
       }
     }
@@ -367,38 +371,40 @@ __global__ __launch_bounds__(256) void tile_reduce_kernel(Params p, PrefillWs w,
   }
 }
 
-// Shapes of the tiled GEMM: features x rows of a tile, and what a k-step of it takes when every compute unit has one.
-struct TileShape { int ts, rows, strips_per_wave; float step_us; };
-constexpr TileShape kTileShapes[4] = {{16, 128, 4, 0.74f}, {16, 256, 8, 1.40f}, {24, 128, 12, 1.10f}, {12, 128, 6, 0.57f}};
+// Shapes of the tiled GEMM: 256 x 128 and 192 x 128 features x rows, and what a k-step takes when every compute unit has one.
+struct TileShape { int ts, strips_per_wave; float step_us; };
+constexpr int kTileRows = 128;
+constexpr TileShape kTileShapes[2] = {{16, 4, 0.74f}, {12, 6, 0.57f}};
 struct TilePlan { int shape, slices; };
 
 // Which tile and how many slices of K.  The tiles run in rounds of one per compute unit (256), a round takes the
 // steps of a tile; what a shape leaves idle in its last round decides, as long as the weights do not have to be
 // waited for.  Slices fill the chip when there are fewer tiles than units; their sums cost a write, a read and a
-// launch.
+// launch.  `want` > 0 asks for a tile, whole or in slices, whatever it costs (the workspace still has to hold the sums).
 TilePlan plan_tiles(int n_strips, int K, int M, size_t part_floats, int want) {
   const int KT = K / 32;
-  TilePlan best{0, 1};
+  const int most = want == 2 || want == 5 ? 1 : want == 4 ? 2 : 8;
+  TilePlan best{want == 3 || want == 5, 1};
   float best_us = 1e30f;
-  constexpr int kAsked[6] = {-1, 0, 0, 2, 1, 3};  // shape of each tune.prefill_strips value
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < 2; ++s) {
     const TileShape &t = kTileShapes[s];
-    if (want > 1 && s != kAsked[want]) continue;
-    const int tiles = ((n_strips + t.ts - 1) / t.ts) * ((M + t.rows - 1) / t.rows);
-    for (int ks = 1; ks <= 8; ++ks) {
+    if (want && s != (want == 3 || want == 5)) continue;
+    const int tiles = ((n_strips + t.ts - 1) / t.ts) * ((M + kTileRows - 1) / kTileRows);
+    for (int ks = 1; ks <= most; ++ks) {
       const int kts = (KT + ks - 1) / ks;
-      if ((kts < 8 && want != 1 && ks > 1) || (KT + kts - 1) / kts != ks) continue;  // every slice has steps
-      if (ks > 1 && (want > 1 || (size_t)ks * M * n_strips * 16 > part_floats)) continue;
-      if (want == 1 && ks == 1 && KT > 1) continue;
+      if ((KT + kts - 1) / kts != ks) continue;  // every slice has steps
+      if (ks > 1 && (size_t)ks * M * n_strips * 16 > part_floats) continue;
+      if (want) { best.slices = ks; continue; }  // as many as asked for, or as there are
+      if (kts < 8 && ks > 1) continue;
       const float rounds = (float)((tiles * ks + 255) / 256);
       float us = rounds * (kts * t.step_us + 4.f);
       const float stream = (float)n_strips * K * 32 / 5.0e6f;  // the weights at 5 TB/s
       if (us < stream) us = stream;
       if (ks > 1) us += 4.f + (float)ks * M * n_strips * 16 * 8 / 4.0e6f;
-      // the estimate is good to a few percent: the smallest tile, which pulls the most bytes per multiply-add, has to win
+      // the estimate is good to a few percent: the smaller tile, which pulls more bytes per multiply-add, has to win
       // clearly (QKV and gate/up up to 511 rows: 10 to 20 %; taking it for Wo as well, where it is 3 % ahead in the
       // estimate: prompt of 100 tokens 1186 us against 1196, two runs of one side differ by 7)
-      if (us < best_us * (s == 3 ? 0.95f : 1.f)) { best_us = us; best = TilePlan{s, ks}; }
+      if (us < best_us * (s == 1 ? 0.95f : 1.f)) { best_us = us; best = TilePlan{s, ks}; }
     }
   }
   return best;
@@ -410,9 +416,9 @@ int launch_tile(const Params &p, const PrefillWs &w, TileArgs a, hipStream_t s) 
   const TilePlan pl = plan_tiles(a.n_strips, a.K, a.M, w.part_floats, w.strips_opt);
   const TileShape &t = kTileShapes[pl.shape];
   a.tiles_n = (a.n_strips + t.ts - 1) / t.ts;
-  a.tiles_m = (a.M + t.rows - 1) / t.rows;
+  a.tiles_m = (a.M + kTileRows - 1) / kTileRows;
   // a die works on 32 tiles at a time: about 1024 rows x 1024 features re-read the least per multiply-add
-  a.panel = w.panel ? w.panel : 1024 / t.rows;
+  a.panel = w.panel ? w.panel : 1024 / kTileRows;
   const int KT = a.K / 32;
   a.kt_slice = (KT + pl.slices - 1) / pl.slices;
   a.slices = (KT + a.kt_slice - 1) / a.kt_slice;
@@ -420,9 +426,7 @@ int launch_tile(const Params &p, const PrefillWs &w, TileArgs a, hipStream_t s) 
   const int grid = a.tiles_n * a.tiles_m * a.slices;
   auto go = [&](auto E) {
     constexpr int e = decltype(E)::value;
-    if (pl.shape == 1) gemm_tile_kernel<e, 2, 4, 8, 4><<<grid, 512, 0, s>>>(p, w, a);
-    else if (pl.shape == 2) gemm_tile_kernel<e, 2, 4, 12, 2><<<grid, 512, 0, s>>>(p, w, a);
-    else if (pl.shape == 3) gemm_tile_kernel<e, 2, 4, 6, 2><<<grid, 512, 0, s>>>(p, w, a);
+    if (pl.shape == 1) gemm_tile_kernel<e, 2, 4, 6, 2><<<grid, 512, 0, s>>>(p, w, a);
     else gemm_tile_kernel<e, 4, 2, 4, 4><<<grid, 512, 0, s>>>(p, w, a);
   };
   if (a.slices == 1) {

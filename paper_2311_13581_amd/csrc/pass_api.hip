@@ -1552,8 +1552,9 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   //   tune.prefill_rows   prompt rows per pass of the tiled prompt pass (a multiple of 128)
   //   tune.prefill_tile   query rows per attention workgroup of the tiled prompt pass (0, 16, 32, 128)
   //   tune.prefill_block  (1 .. 64) * 100 + row tiles of a panel of the tiled GEMMs' tile order (0 = 1024 rows)
-  //   tune.prefill_strips tile of the tiled GEMMs: 0 = by shape, 1 = 256 x 128 features x rows with K in slices,
-  //                       2 = 256 x 128, 3 = 384 x 128, 4 = 256 x 256, 5 = 192 x 128
+  //   tune.prefill_strips tile of the tiled GEMMs, features x rows, and slices of K: 0 = by cost, 1 = 256 x 128 and as many
+  //                       slices as there are steps for (up to eight, as far as the workspace holds them), 2 = 256 x 128,
+  //                       3 = 192 x 128 and as many slices, 4 = 256 x 128 in two slices, 5 = 192 x 128
   if (!strcmp(name, "tune.gemm_cfg")) {
     if (value >= 2000000) {
       if (c->tuning.set_split(value - 2000000)) return fail(c, PASS_EINVAL, "tune.gemm_cfg (split residual GEMM): 0 .. 8 slices of K");
@@ -1602,7 +1603,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
     return PASS_OK;
   }
   if (!strcmp(name, "tune.prefill_strips")) {
-    if (value < 0 || value > 5) return fail(c, PASS_EINVAL, "tune.prefill_strips: 0 (by shape) .. 5");
+    if (value < 0 || value > 5) return fail(c, PASS_EINVAL, "tune.prefill_strips: 0 (by cost) .. 5");
     c->pws.strips_opt = value;
     return PASS_OK;
   }

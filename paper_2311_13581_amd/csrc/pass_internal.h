@@ -221,8 +221,7 @@ __device__ __forceinline__ void store_split4(uint16_t *xs, int m, int K, int k, 
 struct PrefillWs {
   int rows;       // capacity in rows (multiple of 128); also the row stride of the partial sums of h^2
   int np;         // partial sums of h^2 per row that the last producer of rows has left
-  int strips_opt; // GEMM tiles: 0 = by shape; 1 = split along K, 2 = 256 x 128, 4 = 256 x 256, 3 = 384 x 128,
-                  //   5 = 192 x 128 features x rows
+  int strips_opt; // GEMM tile and slices of K: 0 = by cost, else as "tune.prefill_strips" names them (pass_api.hip)
   int panel;      // row tiles of a panel of the GEMMs' tile order; 0 = 1024 rows
   float *part;    // sums over slices of K: part_floats floats
   size_t part_floats;

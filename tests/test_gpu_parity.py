@@ -360,8 +360,9 @@ def test_tiled_prompt_pass(plen, attn_rows, rows, strips, block):
 def test_tiled_gemm_shapes(d, ffn, plen, strips):
     """Every tile of the prompt pass's GEMM where its ring of stages, its remainders and its slices can go wrong: one,
     two, three, five, 17 and 37 k-steps (fewer than the ring's three stages, and every remainder of them), row tiles with
-    one row left (129, 257) or a fraction of a 16-row group, strips that end inside a tile (2 .. 74 against 12, 16 or 24), and
-    K in as many slices as have steps (strips = 1: up to eight, the last one shorter).  The calls on top of the prompt are
+    one row left (129, 257) or a fraction of a 16-row group, strips that end inside a tile (2 .. 74 against 12 or 16), and
+    K in slices: for both tiles as many as there are steps for (strips = 1, 3: one to eight, six and eight with a shorter last
+    one) and two (strips = 4).  The calls on top of the prompt are
     compared with the oracle, which prefills row by row."""
     shape = synth.ModelShape(2, d, 1, 128, ffn, 1008, dtype=synth.BF16)
     W = synth.make_weights(shape, 5, 2, 6.0)

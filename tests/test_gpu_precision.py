@@ -1,0 +1,70 @@
+"""How much the matrix-core GEMMs lose in their sums, which is far less than the parity tests can see (there the (hi, lo)
+split of the activations and the cache's bf16 rows decide).  The weights repeat the first half of K negated in the second
+half, the activations repeat it as it is: the exact result is zero, and what comes out is the rounding of the sums alone.
+
+Bound: a matrix instruction adds its 32 products in four groups of eight and rounds the accumulator after each.  An entry's
+running sum is a random walk that grows over the first half of K and shrinks over the second; with T groups of eight, C
+accumulators that share them and one rounding of half a unit in the last place each, the error relative to the sum at the
+middle is sqrt(T / (2 C) * 0.541 * 2^-46 / 12) (0.541: mean of the squared unit over a value's octave); 1.1 times that is allowed."""
+import numpy as np
+import pytest
+
+from paper_2311_13581_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+D = 4096
+bits = synth.f32_to_bf16_bits
+
+
+def rounded(x):
+    return synth.bf16_bits_to_f32(bits(x)).reshape(np.shape(x))
+
+
+def bound(groups, chains):
+    return 1.1 * np.sqrt(groups / (2 * chains) * 0.541 * 2.0 ** -46 / 12)
+
+
+def weights(shape, k, **given):
+    """All zeros (norm gains one) but what is given, as bf16 bits."""
+    d, F, V, H = shape.d_model, shape.d_ffn, shape.vocab, shape.n_heads * shape.head_dim
+    z = {"tok_emb": (V, d), "lm_head": (V, d), "lookahead": (k, d)}
+    W = {n: bits(given.get(n, np.zeros(s, np.float32))).reshape(s) for n, s in z.items()}
+    W["final_norm"] = bits(given.get("final_norm", np.ones(d, np.float32)))
+    for n, s in (("wq", (H, d)), ("wk", (H, d)), ("wv", (H, d)), ("wo", (d, H)), ("w_gate", (F, d)), ("w_up", (F, d)), ("w_down", (d, F))):
+        W[n] = [bits(given.get(n, np.zeros(s, np.float32))).reshape(s)]
+    for n in ("attn_norm", "ffn_norm"):
+        W[n] = [bits(given.get(n, np.ones(d, np.float32)))]
+    return W
+
+
+@pytest.mark.parametrize("strips", range(6))
+def test_sums_of_the_prompt_pass(strips):
+    """Values of one layer's V projection over a prompt of 200 equal tokens (every tile of the tiled GEMM, whole and in slices):
+    queries are zero, so the next call's attention output is their mean, and the LM head reads it off feature by feature."""
+    from paper_2311_13581_amd import binding
+    rng = np.random.default_rng(0)
+    n, lead = 200, 128  # features 0 .. 127 belong to the pending token alone, the rest to the prompt's token
+    half = (D - lead) // 2
+    shape = synth.ModelShape(1, D, 8, 128, 32, 1040, dtype=synth.BF16)
+    H = shape.n_heads * shape.head_dim
+    twice = lambda x, sign=1: np.concatenate([np.zeros(x.shape[:-1] + (lead,), np.float32), x, sign * x], -1)
+    emb, gain = rng.standard_normal(half), 1 + 0.25 * rng.random(half)
+    w = rounded(rng.standard_normal((H, half)).astype(np.float32))
+    tok = np.zeros((shape.vocab, D), np.float32)
+    tok[0], tok[1, :lead] = twice(emb.astype(np.float32)), 1
+    head, wo = np.zeros((shape.vocab, D), np.float32), np.zeros((D, H), np.float32)
+    wo[lead + np.arange(H), np.arange(H)] = 1
+    head[np.arange(H), lead + np.arange(H)] = 1
+    g = binding.Pass(binding.make_config(shape, 0, 1, 256, 64), {"prefill_tiled": 1, "tune.prefill_strips": strips})
+    g.load_weights(weights(shape, 0, tok_emb=tok, lm_head=head, wv=twice(w, -1), wo=wo, attn_norm=twice(gain.astype(np.float32))))
+    g.prefill(0, np.array([0] * n + [1], np.int32))
+    g.draft([0], 0.0, 1)
+    logits = g.get_logits(0, 0)[0, :H].astype(np.float64)
+    g.close()
+    err = logits * np.sqrt(lead / D + shape.rms_eps) * (n + 1) / n
+    x = rounded(emb.astype(np.float32)).astype(np.float64)
+    mid = (w * (x * rounded(gain.astype(np.float32)))).sum(1) / np.sqrt(2 * (x ** 2).sum() / D + shape.rms_eps)
+    rel = np.sqrt((err ** 2).mean() / (mid ** 2).mean())
+    print("tile", strips, "error of the sums", rel, "bound", bound(2 * half / 8, 1))
+    assert 0 < rel < bound(2 * half / 8, 1)
