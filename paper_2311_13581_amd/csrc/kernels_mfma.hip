@@ -169,7 +169,7 @@ struct GemmArgs {
   float *logits;              // LOGITS: base of the [slot][1+k][V] logits
   int kt_split;               // PARTIAL: k-tiles per workgroup row (blockIdx.y picks the slice of K); else 0
   float *partial;             // PARTIAL: [gridDim.y][kMaxRows][N] sums over the slice of K
-  int n_strips;               // strips of the matrix (NB = 3: the last workgroup may own fewer blocks)
+  int n_strips;               // strips of the matrix (the last workgroup may own fewer blocks)
   int ldy;                    // PARTIAL: features per row of `partial`
   float *gu_save;             // GATEUP_SAVE: [M][2F] gate | up before the activation (what its derivative needs)
 };
@@ -443,12 +443,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
 // Every wavefront owns a ring of D stages of one k-tile (its NS weight tiles and MT activation groups, 1 KB each), fills
 // it by itself and reads it by itself: no barrier before the final reduction, and the wavefronts' rings together keep
 // up to 150 KB of requests in flight per compute unit with no registers spent on them, so that more strips fit a
-// workgroup.  The areas of the reduction are the rings themselves, the accumulators live in the accumulation registers.
-// Measured on 7B shapes (operands through registers -> rings), 40 rows: QKV 31.1 -> 28.5 us, gate/up 39.3 -> 36.9, Wo and
-// down slices 17.7 -> 16.2 on average, LM head 63 -> 49; 64 rows: QKV 40.4 -> 37.4, gate/up 78.9 -> 46.1.  Bound by the unit's
-// vector memory path all the same: every further 8 rows (128 KB per unit at K = 4096) cost 3.3 us, 40 GB/s per unit, a
-// third of what the path delivers when nothing comes from HBM (its returns are in order, so a row out of L2 waits for
-// the weights requested before it).
+// workgroup.  The areas of the reduction are the rings themselves.
+// Measured on 7B shapes (operands through registers -> rings), 40 rows: QKV 30.1 -> 29.2 us, gate/up 39.0 -> 38.0, Wo and
+// down slices 17.3 -> 16.6 on average, LM head 60.7 -> 51.6; 64 rows: QKV 40.3 -> 37.5, gate/up 78.6 -> 53.9, LM head
+// 108.7 -> 78.2.  Bound by the unit's vector memory path all the same: its returns are in order, so a row out of L2 waits
+// for the weights requested before it.
 template <bool NT>
 __device__ __forceinline__ void copy_to_lds(const void *src, u32x4 *dst) {
   // in assembly: the compiler, which cannot tell the stages apart, would wait for every copy in flight before each LDS
@@ -491,11 +490,23 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
   for (int mt = 0; mt < MT; ++mt) xp[mt] = (const u32x4 *)a.X + ((size_t)mt * KT + kbase + wave) * 64 + lane;
   u32x4 *mine = ring + wave * (D * T * 64);
 
-  floatx4 acc[NS][MT];
+  // The sums lose as little as with eight wavefronts or more sharing K: either two accumulators per tile, one of the
+  // wavefront's even and one of its odd k-tiles, or, where the registers do not hold those, a product of one k-tile at a
+  // time that is added to the sum as a whole (a matrix instruction rounds its accumulator four times, an addition once).
+  // K = 4096, error of the sums relative to the result: 1.3e-7 and 1.2e-7; with one accumulator 1.9e-7, in 1 % less time at 40
+  // rows (gate/up 37.5 us against 38.0) and 14 % less at 64 (46.2 against 53.9).
+  constexpr bool PAIRS = NS * MT <= 30;
+  floatx4 acc[NS][MT], odd[PAIRS ? NS : 1][PAIRS ? MT : 1];
+  float sum[PAIRS ? 1 : NS][PAIRS ? 1 : MT][4];
 #pragma unroll
   for (int s = 0; s < NS; ++s)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[s][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MT; ++mt) {
+      if constexpr (PAIRS) acc[s][mt] = odd[s][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+      else
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[s][mt][r] = 0.f;
+    }
 
   // this wavefront's k-tiles: wave, wave + WAVES, ...  (the workgroup walks its strips front to back)
   const int n = (KTl - wave + WAVES - 1) / WAVES;
@@ -510,7 +521,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
   for (int d = 0; d < D; ++d)
     if (d < n) issue(d, mine + d * T * 64);
   int at = 0;
-  for (int i = 0; i < n; ++i) {
+  auto tile = [&](int i, auto &into) __attribute__((always_inline)) {
     u32x4 *st = mine + at * T * 64;
     const int left = n - 1 - i;  // stages requested after this one: min(left, D - 1)
     if (left >= D - 1) wait_copies<(D - 1) * T>();
@@ -528,13 +539,47 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
       issue(i + D, st);
     }
     __builtin_amdgcn_sched_barrier(0);
+    auto product = [&](int s, int mt, floatx4 c) __attribute__((always_inline)) {
+      return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[s]), __builtin_bit_cast(bf16x8, bv[mt]), c, 0, 0, 0);
+    };
+    if constexpr (PAIRS) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) into[s][mt] = product(s, mt, into[s][mt]);
+    } else {
+      floatx4 y[2][MT];
+#pragma unroll
+      for (int s = 0; s <= NS; ++s) {  // a strip's products, beside the additions of the strip before
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          if (s < NS) y[s & 1][mt] = product(s < NS ? s : 0, mt, floatx4{0.f, 0.f, 0.f, 0.f});
+          if (s > 0)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) into[s - 1][mt][r] += y[(s - 1) & 1][mt][r];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    at = at + 1 == D ? 0 : at + 1;
+  };
+  if constexpr (PAIRS) {
+    int i = 0;
+    for (; i + 1 < n; i += 2) {
+      tile(i, acc);
+      tile(i + 1, odd);
+    }
+    if (i < n) tile(i, acc);
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[s]),
-                                                             __builtin_bit_cast(bf16x8, bv[mt]), acc[s][mt], 0, 0, 0);
-    at = at + 1 == D ? 0 : at + 1;
+      for (int mt = 0; mt < MT; ++mt) acc[s][mt] += odd[s][mt];
+  } else {
+    for (int i = 0; i < n; ++i) tile(i, sum);
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[s][mt] = floatx4{sum[s][mt][0], sum[s][mt][1], sum[s][mt][2], sum[s][mt][3]};
   }
   constexpr int MB = D * T / NS < MT ? D * T / NS : MT;  // row groups whose partial tiles fit a wavefront's ring
   gemm_finish<MT, EPI, WAVES, NB, NS, MB>(p, a, acc, (floatx4 *)ring, D * T * 64, red_ss, strip0);
@@ -576,8 +621,8 @@ static void launch_one(const Params &p, const GemmArgs &a, int grid, hipStream_t
   gemm_mfma_kernel<EPI, W, U><<<grid, W * 64, 0, s>>>(p, a);
 }
 
-// Blocks a workgroup of the ring form may own: its accumulators (in the accumulation registers; one wavefront per SIMD)
-// and two stages of its ring must fit.
+// Blocks a workgroup of the ring form may own: its sums (of the 512 registers that one wavefront per SIMD has) and two
+// stages of its ring must fit.
 constexpr bool ring_fits(int strips, int mt) { return strips * mt <= 64 && kRingWaves * 2 * (strips + mt) <= 156; }
 
 template <int MT, int EPI>

@@ -392,8 +392,7 @@ def test_row_gemm_shapes(d, ffn, slots, k, blocks):
         g.set_option("tune.gemm_cfg", 1000000 + kind * 10000 + 400 + blocks)
     ids = list(range(slots))
     stats = parity.batch_parity(g, m, ids, [3 + i for i in ids], prompts, ids, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=64)
-    for sl in ids:
-        parity.check_stats(stats[sl], 2, parity.ERR_BF16_SMALL)
+    parity.check_batch(stats, 2, parity.ERR_BF16_SMALL)
     g.close()
 
 

@@ -68,3 +68,31 @@ def test_sums_of_the_prompt_pass(strips):
     rel = np.sqrt((err ** 2).mean() / (mid ** 2).mean())
     print("tile", strips, "error of the sums", rel, "bound", bound(2 * half / 8, 1))
     assert 0 < rel < bound(2 * half / 8, 1)
+
+
+@pytest.mark.parametrize("slots,k,blocks", [(1, 4, 0), (1, 8, 0), (2, 7, 0), (8, 4, 0), (8, 4, 6), (8, 4, 8), (8, 7, 0), (8, 7, 3), (8, 7, 8)])
+def test_sums_of_the_decode_gemm(slots, k, blocks):
+    """Logits of a drafting call on a model without layers' contributions: 5, 9, 16, 40 and 64 rows, with the launch shapes'
+    own and more blocks per workgroup (pairs of accumulators and products added one by one).  Eight accumulators share K."""
+    from paper_2311_13581_amd import binding
+    rng = np.random.default_rng(1)
+    shape = synth.ModelShape(1, D, 1, 128, 32, 1024, dtype=synth.BF16)
+    twice = lambda x, sign=1: np.concatenate([x, sign * x], -1).astype(np.float32)
+    w = rounded(rng.standard_normal((shape.vocab, D // 2)).astype(np.float32))
+    emb, gain = rng.standard_normal((shape.vocab, D // 2)), 1 + 0.25 * rng.random(D // 2)
+    la = rng.standard_normal((k, D // 2))
+    g = binding.Pass(binding.make_config(shape, k, slots, 64, 64))
+    g.load_weights(weights(shape, k, tok_emb=twice(emb), lm_head=twice(w, -1), lookahead=twice(la), final_norm=twice(gain)))
+    if blocks:
+        g.set_option("tune.gemm_cfg", 1000000 + 3 * 10000 + 400 + blocks)
+    for s in range(slots):
+        g.prefill(s, np.array([s], np.int32))
+    g.draft(list(range(slots)), 0.0, 1)
+    err = np.concatenate([g.get_logits(s, 0) for s in range(slots)]).astype(np.float64)
+    g.close()
+    x = rounded(np.concatenate([np.concatenate([emb[s:s + 1], la]) for s in range(slots)]).astype(np.float32)).astype(np.float64)
+    inv = 1 / np.sqrt(2 * (x ** 2).sum(1) / D + shape.rms_eps)
+    mid = (x * rounded(gain.astype(np.float32))) @ w.T.astype(np.float64) * inv[:, None]
+    rel = np.sqrt((err ** 2).mean() / (mid ** 2).mean())
+    print("rows", slots * (k + 1), "blocks", blocks, "error of the sums", rel, "bound", bound(D / 8, 8))
+    assert 0 < rel < bound(D / 8, 8)
