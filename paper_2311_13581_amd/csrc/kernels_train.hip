@@ -137,7 +137,8 @@ __global__ __launch_bounds__(256) void ce_part_kernel(const float *logits, const
   float mx = -INFINITY, se = 0.f;
   for (int j = lo + threadIdx.x; j < hi; j += 256) mx = fmaxf(mx, lg[j]);
   mx = block_max_256(mx, red);
-  for (int j = lo + threadIdx.x; j < hi; j += 256) se += expf(lg[j] - mx);
+  // (a logit of -inf adds nothing: where all of a part's are, the difference to their maximum would not be a number)
+  for (int j = lo + threadIdx.x; j < hi; j += 256) se += lg[j] == -INFINITY ? 0.f : expf(lg[j] - mx);
   se = block_sum_256(se, red);
   if (threadIdx.x == 0) parts[(size_t)m * kRowParts + blockIdx.x] = make_float2(mx, se);
 }

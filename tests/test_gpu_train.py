@@ -111,6 +111,41 @@ def test_one_training_step_for_every_row_bound(shape, page, path, k):
     g.close()
 
 
+@pytest.mark.parametrize("dtype,path", [(synth.F32, 1), (synth.BF16, 1), (synth.BF16, 0)], ids=["fp32", "bf16-generic", "bf16"])
+def test_training_step_with_a_part_of_the_logits_at_minus_infinity(dtype, path):
+    """The LM-head rows of the second of three parts of 1024 entries (the cross-entropy's unit) overflow to -inf for every hidden
+    row: those tokens have probability zero, and loss and gradient are those of the others."""
+    shape = synth.ModelShape(1, 64, 1, 64, 128, 3072, dtype=dtype)
+    k = 3
+    W = synth.make_weights(shape, 23, k, 4.0)
+    store = synth.f32_to_bf16_bits if dtype == synth.BF16 else (lambda x: x)
+    one = lambda x: store(np.array([x], np.float32))[0]
+    for name in ("tok_emb", "lookahead"):
+        W[name][:, 0] = one(2.0)        # feature 0: positive in every row ...
+    W["final_norm"][0] = one(8.0)
+    W["lm_head"][:, 0] = one(0.0)
+    W["lm_head"][1024:2048] = one(0.0)
+    W["lm_head"][1024:2048, 0] = one(-1e38)  # ... and beyond the range of fp32 here
+    g = _gpu(shape, W, k, 2, 64, 64, {"path": path})
+    g.train_begin(-1)
+    la = TO._t(W["lookahead"], dtype).numpy()
+    rng = np.random.default_rng(5)
+    prefixes = [rng.integers(0, shape.vocab, n).astype(np.int32) for n in (1, 20)]
+    targets = rng.integers(0, 1024, (2, k)).astype(np.int32) + 2048 * rng.integers(0, 2, (2, k)).astype(np.int32)
+    for i, p in enumerate(prefixes):
+        g.prefill(i, p, seq_id=i)
+    loss = g.train_step([0, 1], targets, 0.01)
+    g.draft([0], 0.0, 1)
+    assert np.all(np.isneginf(g.get_logits(0, 0)[:, 1024:2048]))
+    o_loss, o_grad = TO.loss_and_grad(shape, W, la, [p.tolist() for p in prefixes], targets)
+    grad = g.train_read(1)
+    e_loss, e_grad, g_max = abs(loss - o_loss) / abs(o_loss), float(np.abs(grad - o_grad).max()), float(np.abs(o_grad).max())
+    print(f"loss {loss} rel {e_loss:.1e} grad err {e_grad / g_max:.1e} of max {g_max:.3f}")
+    assert np.isfinite(loss) and np.isfinite(g.train_read(0)).all()
+    assert e_loss <= (1e-6 if dtype == synth.F32 else 6e-5) and e_grad <= (5e-6 if dtype == synth.F32 else 4e-4) * g_max
+    g.close()
+
+
 def test_training_step_at_13b_width_vs_oracle():
     """One step at the 13B model's width (one layer, full vocabulary, bf16: d_model 5120, 40 heads of
     128, d_ffn 13824 -- 320 and 864 strips, 160 and 432 k-tiles, none a power of two), k = 4, four ragged
