@@ -728,8 +728,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   float m_ref[RG], l_run[RG];  // reference of the exponentials (the same in a row's four lanes), this lane's sum
 #pragma unroll
   for (int rg = 0; rg < RG; ++rg) {
-    m_ref[rg] = -1e30f;  // below any score: the first step moves it.  Not -inf: a row past the last one has all its keys
-    l_run[rg] = 0.f;     //   masked in some steps, and -inf - -inf would not be a number
+    m_ref[rg] = -__FLT_MAX__;  // no score is lower: the first step moves it.  Not -inf: a row past the last one has all its
+    l_run[rg] = 0.f;           //   keys masked in some steps, and -inf - -inf would not be a number
 #pragma unroll
     for (int db = 0; db < 8; ++db) o[rg][db] = floatx4{0.f, 0.f, 0.f, 0.f};
   }

@@ -535,6 +535,29 @@ def test_prompt_attention_with_growing_scores(gain, attn_rows):
     g.close()
 
 
+@pytest.mark.parametrize("attn_rows", [16, 32, 128])
+def test_prompt_attention_with_scores_far_below_zero(attn_rows):
+    """Every score of the first layer is about -1e33 (queries and keys are opposite multiples of 1e17 along one slowly turning
+    dimension): the softmax is one of differences all the same.  All tokens of the prompt are equal, so the values are too
+    and the attention's output does not depend on the weights: the logits are those of the model with queries of zero."""
+    shape = synth.ModelShape(2, 256, 1, 128, 96, 1008, dtype=synth.BF16)
+    lg = []
+    for scale in (1e17, 0.0):
+        W = synth.make_weights(shape, 15, 0, 6.0)
+        one = lambda x: synth.f32_to_bf16_bits(np.array([x], np.float32))[0]
+        W["tok_emb"][:, 0] = one(0.1)
+        for name, sign in (("wq", -scale), ("wk", 1e17)):
+            W[name][0][:] = one(0.0)
+            W[name][0][126, 0] = one(sign)
+        g = _gpu(shape, W, 0, max_seq_len=384, page_size=64, options={"prefill_tiled": 1, "tune.prefill_tile": attn_rows})
+        g.prefill(0, np.full(301, 5, np.int32))
+        g.draft([0], 0.0, 1)
+        lg.append(g.get_logits(0, 0).copy())
+        g.close()
+    assert np.isfinite(lg[0]).all()
+    assert np.abs(lg[0] - lg[1]).max() <= 1e-3 * np.abs(lg[1]).max()  # bf16 rounding of the second layer's keys and values
+
+
 @pytest.mark.parametrize("rows,lens", [(384, (37, 300, 129, 2, 1, 260)), (128, (200, 5, 131)), (256, (129, 128, 127, 1, 64, 65))])
 def test_prompt_pass_over_several_slots(rows, lens):
     """pass_prefill_batch: ragged prompts of several sequences share tiled passes over the weights (every
