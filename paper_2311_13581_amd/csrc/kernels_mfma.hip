@@ -38,6 +38,7 @@
 #include <algorithm>
 #include <cstdlib>
 
+#include "lds_copy.h"
 #include "pass_internal.h"
 
 namespace pass {
@@ -448,23 +449,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
 // down slices 17.3 -> 16.6 on average, LM head 60.7 -> 51.6; 64 rows: QKV 40.3 -> 37.5, gate/up 78.6 -> 53.9, LM head
 // 108.7 -> 78.2.  Bound by the unit's vector memory path all the same: its returns are in order, so a row out of L2 waits
 // for the weights requested before it.
-template <bool NT>
-__device__ __forceinline__ void copy_to_lds(const void *src, u32x4 *dst) {
-  // in assembly: the compiler, which cannot tell the stages apart, would wait for every copy in flight before each LDS
-  // read.  No register result; the copies of a wavefront complete in order (wait_copies leaves the youngest N in flight)
-  const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
-  if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(src), "s"(off) : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_copies() {
-  static_assert(N >= 0 && N < 64, "six bits");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-  asm volatile("" ::: "memory");
-}
-
 constexpr int kRingWaves = 4;  // (eight wavefronts with two stages each: 3 to 5 % slower in every product)
 constexpr int ring_stages(int waves, int tiles) { return waves * tiles * 3 <= 156 ? 3 : (waves * tiles * 2 <= 156 ? 2 : 1); }
 
@@ -533,9 +517,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
 #pragma unroll
     for (int s = 0; s < NS; ++s) av[s] = st[s * 64 + lane];
     if (i + D < n) {
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // the stage has been read: it can be filled again
+      wait_lds_reads();  // the stage has been read: it can be filled again
       issue(i + D, st);
     }
     __builtin_amdgcn_sched_barrier(0);

@@ -16,6 +16,7 @@
 //                      tiles are used for all row groups of the block.
 //   attn_prefill_shared_kernel  the same for passes of more than 512 rows: 128 rows per workgroup,
 //                      the K and V tiles of a step fetched once into LDS for all four wavefronts.
+#include "lds_copy.h"
 #include "pass_internal.h"
 
 namespace pass {
@@ -49,29 +50,6 @@ struct TileArgs {
   int slices, kt_slice;       // PART: slices of K and k-steps of each
   float *part;                // PART: [slice][M][16 * n_strips] sums over a slice of K
 };
-
-// Copy of 64 x 16 bytes from memory (one address per lane) to 1 KB of LDS (wavefront-uniform), past the register
-// file: a compute unit draws 59 B per clock out of its die's L2 this way, through registers it draws 36 (measured
-// with all units on a 1 MB buffer).  In assembly because the compiler, which cannot tell the stages of a ring of
-// buffers apart, would wait for every copy in flight before each LDS read; it has no register result.  The copies
-// of a wavefront complete in order; wait_copies<N> leaves the youngest N in flight.
-__device__ __forceinline__ void copy_to_lds(const u32x4 *src, u32x4 *dst) {
-  const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_copies() {
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-__device__ __forceinline__ void wait_lds_reads() { __builtin_amdgcn_s_waitcnt(0xC07F); }
-// the workgroup meets; neither the compiler nor the instruction scheduler moves memory accesses across
-__device__ __forceinline__ void meet() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::: "memory");
-}
 
 // What becomes of four consecutive output features n .. n + 3 (n % 4 == 0) of row m, `inv` = 1 / rms of the row.
 __device__ __forceinline__ void finish_qkv(const Params &p, const PrefillWs &w, const TileArgs &a, int m, int n, floatx4 v) {
@@ -249,7 +227,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int h = 0; h < 2; ++h) bv[g][h] = __builtin_bit_cast(bf16x8, st[TS + (wr * RG + g) * 2 + h][lane]);
     issue(nxt, kt + 2);
-    __builtin_amdgcn_sched_barrier(0);
     wait_lds_reads();
     if (grp) wait_copies<NC>();
     meet();
@@ -689,11 +666,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int f = wave * 2 + i, key = (ml >> 2) * 8 + (f >> 2) * 4 + (ml & 3);  // key slot ml of half f >> 2
-      copy_to_lds((const u32x4 *)(kp + (size_t)key * HD + (f & 3) * 32 + g * 8), &dK[f][0]);
+      copy_to_lds(kp + (size_t)key * HD + (f & 3) * 32 + g * 8, &dK[f][0]);
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      copy_to_lds((const u32x4 *)(vp + (size_t)((wave * 2 + i) * 16 + ml) * p.page_size + g * 8), &dV[wave * 2 + i][0]);
+      copy_to_lds(vp + (size_t)((wave * 2 + i) * 16 + ml) * p.page_size + g * 8, &dV[wave * 2 + i][0]);
   };
   issue(sK0, sV0, 0);
 
@@ -804,10 +781,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int rg = 0; rg < RG; ++rg) o[rg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pl[rg]), o[rg][db], 0, 0, 0);
     }
   };
-  // The step's tiles have landed (every wavefront waits for its own copies, then they meet); the other stage, which
-  // everybody has finished reading, is filled with the next step's.
+  // The step's tiles have landed (every wavefront waits for its own copies, and for its reads of the step before, then
+  // they meet); the other stage, which everybody has finished reading, is filled with the next step's.
   auto step = [&](const u32x4 (*dK)[64], const u32x4 (*dV)[64], u32x4 (*nK)[64], u32x4 (*nV)[64], int base) __attribute__((always_inline)) {
     wait_copies<0>();
+    wait_lds_reads();
     meet();
     if (base + STEP < k_all) issue(nK, nV, base + STEP);
     if (base >= k_own) return;  // past this wavefront's last row
