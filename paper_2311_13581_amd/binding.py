@@ -7,7 +7,6 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-import weakref
 
 import numpy as np
 
@@ -124,34 +123,6 @@ def make_config(shape, k, max_slots, max_seq_len, page_size=64, n_pages=0) -> Pa
                       shape.rms_eps, shape.rope_base, shape.dtype, k, max_slots, max_seq_len, page_size, n_pages)
 
 
-class _PinnedResults:
-    """Host arrays for results of one size, in pinned memory that is used again once an array is gone.
-
-    A fresh array of a few hundred KB is fresh pages: the copy into it faults on every one of them and the runtime pins
-    and unpins them (53 to 125 us for 640 KB, depending on whether the C heap had given the pages back).  At most `limit`
-    buffers exist; beyond that, and below 128 KB (which the heap serves from pages it keeps), arrays are ordinary ones.
-    A buffer comes back when the array and every view of it are gone, on whatever thread that happens (list.append and
-    list.pop are atomic); the pool goes with the object that owns it, arrays that are still held keep their buffer."""
-
-    def __init__(self, torch, shape, limit):
-        self._torch, self._shape, self._left, self._free = torch, shape, limit, []
-        self._n = int(np.prod(shape))
-
-    def take(self) -> np.ndarray:
-        if self._n * 4 < 128 * 1024:
-            return np.empty(self._shape, dtype=np.float32)
-        try:
-            buf = self._free.pop()
-        except IndexError:
-            if self._left <= 0:
-                return np.empty(self._shape, dtype=np.float32)
-            self._left -= 1
-            buf = self._torch.empty(self._n, dtype=self._torch.float32, pin_memory=True)
-        flat = buf.numpy()  # what every view of the result holds on to
-        weakref.finalize(flat, self._free.append, buf).atexit = False
-        return flat.reshape(self._shape)
-
-
 class Pass:
     """One model instance on the current CUDA(HIP) device.  Methods mirror the C entry points."""
 
@@ -179,8 +150,6 @@ class Pass:
         if rc != 0:
             raise PassError(rc, self.lib.pass_last_error(None).decode())
         self.h = h
-        # the logits of both calls of every slot, twice: a loop still holds an iteration's results while it reads the next one's
-        self._logits_pool = _PinnedResults(torch, (cfg.k + 1, cfg.vocab), 4 * cfg.max_slots)
         for name, val in (options or {}).items():
             self.set_option(name, val)
 
@@ -313,7 +282,7 @@ class Pass:
         return out
 
     def get_logits(self, slot: int, which: int) -> np.ndarray:
-        out = self._logits_pool.take()
+        out = np.empty((self.k + 1, self.vocab), dtype=np.float32)
         self._check(self.lib.pass_get_logits(self.h, slot, which, out.ctypes.data_as(C.POINTER(C.c_float))))
         return out
 
