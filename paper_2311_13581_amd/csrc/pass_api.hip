@@ -427,10 +427,8 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
 // No LM head: the last prompt token stays pending and goes through the first draft call.
 struct PassSeg { int slot, pos0, rows, row_base; };
 
-// Rows above which a prompt (or a batch of prompts, whose every prompt starts on a block of 128 rows) takes the tiled
-// pass: what one pass of the decode kernels holds.  Measured per 7B layer: 48 rows 133 us through the decode kernels, 156
-// tiled; 64 rows 152 and 166; 100 rows (two passes) 268 and 183; 384 rows 893 and 333.  A further prompt of a batch adds
-// about 64 us to a tiled pass and at least 92 us as a call of its own.
+// Rows above which a prompt takes the tiled pass: what one pass of the decode kernels holds.  Measured per 7B layer: 48 rows
+// 133 us through the decode kernels, 156 tiled; 64 rows 152 and 166; 100 rows (two passes) 268 and 183; 384 rows 893 and 372.
 constexpr int kTiledMinRows = kMaxRows;
 
 // How pass_prefill_batch packs prompts into tiled passes of at most `cap` rows (a multiple of 128): prompt b has
@@ -452,6 +450,29 @@ std::vector<PlanSeg> plan_prefill(int cap, const int32_t *lens, int n) {
   }
   return out;
 }
+// Whether the prompts of a batch share tiled passes: from 2 * kMaxRows rows on always; below what one pass of the decode
+// kernels holds never; in between it depends on how they pack, because every prompt starts on a block of 128 rows and a pass
+// holds no more than max_seq_len allows.  Per 7B layer a call of the decode kernels takes about 92 us and 1 us a row, a
+// tiled pass about 100 us and 60 a block.  Four layers, one by one against shared passes: two prompts of 33 rows 1.09 ms against
+// 1.23 in two passes and 0.95 in one; eight of 9 rows 3.34 against 4.85 in eight passes, 3.72 in four, 2.83 in one.
+bool batch_takes_tiles(const int32_t *lens, int n, int chunk, int cap) {
+  int64_t total = 0, alone_us = 0, shared_us = 0;
+  for (int b = 0; b < n; ++b) {
+    const int rows = lens[b] - 1;
+    total += rows;
+    alone_us += rows > kTiledMinRows ? 100 + 60 * ((rows + kPrefillBlockRows - 1) / kPrefillBlockRows)
+                                     : 92 * ((rows + chunk - 1) / chunk) + rows;
+  }
+  if (total <= kTiledMinRows || total > 2 * kMaxRows) return total > kTiledMinRows;
+  int pass = -1;
+  for (const PlanSeg &g : plan_prefill(cap, lens, n)) {
+    if (g.pass != pass) shared_us += 100;
+    shared_us += 60 * ((g.rows + kPrefillBlockRows - 1) / kPrefillBlockRows);
+    pass = g.pass;
+  }
+  return shared_us < alone_us;
+}
+
 int run_prefill_pass(pass_ctx *c, const std::vector<PassSeg> &parts, int M, const int32_t *ids) {
   Params P = c->P;
   const Params &B = c->PP;
@@ -848,10 +869,11 @@ int pass_prefill_batch(pass_ctx *c, const int32_t *slots, const uint32_t *seq_id
     total += lens[b] - 1;
   }
   // the tiled kernels take rows of several sequences through one pass over the weights; where they do not
-  // apply (generic path, untransposed V pages, switched off, or too few rows: kTiledMinRows) the
+  // apply (generic path, untransposed V pages, switched off, or too few rows to pay for it) the
   // prompts go one by one
   const bool tiled = c->use_mfma && c->P.v_transposed &&
-                     (c->opt_prefill_tiled == 1 || (c->opt_prefill_tiled < 0 && total > kTiledMinRows));
+                     (c->opt_prefill_tiled == 1 ||
+                      (c->opt_prefill_tiled < 0 && batch_takes_tiles(lens, n_slots, c->opt_prefill_chunk, c->pws.rows)));
   int rc;
   if (!tiled) {
     const int32_t *pr = prompts;

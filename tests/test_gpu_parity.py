@@ -514,6 +514,33 @@ def test_prompt_pass_by_length(lens):
     g.close()
 
 
+@pytest.mark.parametrize("lens,max_len,shared", [
+    ((34, 34), 128, False), ((34, 34), 256, True), ((18,) * 4, 128, False), ((18,) * 4, 256, False), ((18,) * 4, 512, True),
+    ((10,) * 8, 256, False), ((10,) * 8, 1024, True), ((30, 30), 256, False), ((70, 3), 128, False), ((70, 3), 256, True)])
+def test_short_prompts_share_passes_where_it_pays(lens, max_len, shared):
+    """Batches of 65 to 128 rows in all: a pass holds max_seq_len rows, rounded up to blocks of 128, and every prompt takes a block
+    of its own; where that makes too many passes the prompts go one by one.  Which way a batch went shows in the last bits."""
+    w = MFMA_HD128
+    W = synth.make_weights(w.shape, w.seed, w.k, w.lm_head_scale)
+    rng = np.random.default_rng(sum(lens))
+    prompts = [rng.integers(0, w.shape.vocab, n).astype(np.int32) for n in lens]
+    slots = list(range(len(lens)))
+    g = _gpu(w.shape, W, w.k, max_slots=len(lens), max_seq_len=max_len, page_size=64)
+    got = []
+    for way in ("batch", "shared", "alone"):
+        g.set_option("prefill_tiled", 1 if way == "shared" else -1)
+        if way == "alone":
+            for s in slots:
+                g.prefill(s, prompts[s], seq_id=s)
+        else:
+            g.prefill_batch(slots, prompts, slots)
+        g.draft(slots, 0.0, 1)
+        got.append(np.stack([g.get_logits(s, 0) for s in slots]))
+    g.close()
+    assert not np.array_equal(got[1], got[2])
+    assert np.array_equal(got[0], got[1 if shared else 2])
+
+
 @pytest.mark.parametrize("gain", [1.0, 4.0])
 @pytest.mark.parametrize("attn_rows", [32, 128])
 def test_prompt_attention_with_growing_scores(gain, attn_rows):
