@@ -355,20 +355,34 @@ __global__ __launch_bounds__(256) void row_gemm_kernel(Params p, RowGemm a) {
   }
 }
 
+template <int V> struct vec_c { static constexpr int value = V; };
+
 template <typename T, int EPI>
 static void launch_row_gemm(const Params &p, const RowGemm &a, hipStream_t s) {
   const int grid = ((a.N + 1) / 2 + 3) / 4;
-  // chunks of 4 below K = 512: with 8 half of the lanes would have nothing to do at K = 256.  (The chunk decides the
-  // order of a row's sums: it follows K alone.)
-  if (a.K < 512) {
-    if (a.M <= 2) row_gemm_kernel<T, EPI, 4, 2><<<grid, 256, 0, s>>>(p, a);
-    else if (a.M <= 4) row_gemm_kernel<T, EPI, 4, 4><<<grid, 256, 0, s>>>(p, a);
-    else row_gemm_kernel<T, EPI, 4, 8><<<grid, 256, 0, s>>>(p, a);
-  } else {
-    if (a.M <= 2) row_gemm_kernel<T, EPI, 8, 2><<<grid, 256, 0, s>>>(p, a);
-    else if (a.M <= 4) row_gemm_kernel<T, EPI, 8, 4><<<grid, 256, 0, s>>>(p, a);
-    else row_gemm_kernel<T, EPI, 8, 8><<<grid, 256, 0, s>>>(p, a);
-  }
+  // Chunks: 16 bytes of a weight row per lane, so that a wavefront's loads are whole lines (fp32 in chunks of 8: d 4096, 8 rows
+  // 1.70 ms a call pair against 1.20); bf16 of a row of fewer than 512 in chunks of 4, or half of the lanes would have nothing
+  // to do.  (The chunk decides the order of a row's sums: it follows type and K alone.)
+  // Rows: as few blocks of up to eight as hold them, all of one size, because a row past the last one costs as much as any.
+  // fp32, d 4096, two layers, a call pair: 5 rows in a block of eight 1.53 ms, now 0.98; 9 rows in two blocks of eight 2.53,
+  // now 1.53.  With a wavefront per column and the norm, the rotary embedding and the activation in kernels of their own: 1.43
+  // and 2.20.
+  const int blocks = (a.M + 7) / 8, rows = (a.M + blocks - 1) / blocks;
+  auto go = [&](auto V) {
+    constexpr int VEC = decltype(V)::value;
+    switch (rows) {
+      case 1: row_gemm_kernel<T, EPI, VEC, 1><<<grid, 256, 0, s>>>(p, a); break;
+      case 2: row_gemm_kernel<T, EPI, VEC, 2><<<grid, 256, 0, s>>>(p, a); break;
+      case 3: row_gemm_kernel<T, EPI, VEC, 3><<<grid, 256, 0, s>>>(p, a); break;
+      case 4: row_gemm_kernel<T, EPI, VEC, 4><<<grid, 256, 0, s>>>(p, a); break;
+      case 5: row_gemm_kernel<T, EPI, VEC, 5><<<grid, 256, 0, s>>>(p, a); break;
+      case 6: row_gemm_kernel<T, EPI, VEC, 6><<<grid, 256, 0, s>>>(p, a); break;
+      case 7: row_gemm_kernel<T, EPI, VEC, 7><<<grid, 256, 0, s>>>(p, a); break;
+      default: row_gemm_kernel<T, EPI, VEC, 8><<<grid, 256, 0, s>>>(p, a); break;
+    }
+  };
+  if (sizeof(T) == 4 || a.K < 512) go(vec_c<4>{});
+  else if constexpr (sizeof(T) == 2) go(vec_c<8>{});
 }
 template <int EPI>
 static void launch_row_gemm_dt(int dtype, const Params &p, const RowGemm &a, hipStream_t s) {

@@ -399,10 +399,11 @@ def test_row_gemm_shapes(d, ffn, slots, k, blocks):
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("d,heads,hd,ffn,vocab,slots,k", [
     (8, 1, 64, 8, 3, 1, 0), (72, 3, 64, 40, 257, 1, 1), (256, 4, 64, 504, 130, 1, 3), (504, 2, 128, 520, 77, 2, 3),
-    (512, 8, 64, 1000, 201, 3, 4), (520, 1, 128, 264, 64, 5, 11)])
+    (512, 8, 64, 1000, 201, 3, 4), (520, 1, 128, 264, 64, 5, 11), (264, 2, 64, 520, 90, 1, 2), (520, 2, 64, 248, 91, 1, 4),
+    (256, 1, 128, 512, 92, 2, 2), (512, 2, 64, 776, 93, 1, 6), (264, 2, 64, 1032, 94, 3, 2), (520, 1, 64, 512, 95, 4, 4)])
 def test_generic_row_gemm_shapes(d, heads, hd, ffn, vocab, slots, k, dtype):
-    """The generic path's fused GEMMs: K below, at and above one chunk per lane (8 .. 1000, both chunk sizes, remainders),
-    an odd number of output columns, one to sixty rows (2, 4 or 8 at a time, full and not), both head sizes and both
+    """The generic path's fused GEMMs: K below, at and above one chunk per lane (8 .. 1032, both chunk sizes, remainders),
+    an odd number of output columns, one to sixty rows (one to eight at a time, in blocks that are full and not), both head sizes and both
     storage types; every slot follows the oracle through two iterations."""
     shape = synth.ModelShape(2, d, heads, hd, ffn, vocab, dtype=dtype)
     W = synth.make_weights(shape, 8, k, 4.0)
