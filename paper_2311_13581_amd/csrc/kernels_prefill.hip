@@ -378,10 +378,7 @@ TilePlan plan_tiles(int n_strips, int K, int M, size_t part_floats, int want) {
       const float stream = (float)n_strips * K * 32 / 5.0e6f;  // the weights at 5 TB/s
       if (us < stream) us = stream;
       if (ks > 1) us += 4.f + (float)ks * M * n_strips * 16 * 8 / 4.0e6f;
-      // the estimate is good to a few percent: the smaller tile, which pulls more bytes per multiply-add, has to win
-      // clearly (QKV and gate/up up to 511 rows: 10 to 20 %; taking it for Wo as well, where it is 3 % ahead in the
-      // estimate: prompt of 100 tokens 1186 us against 1196, two runs of one side differ by 7)
-      if (us < best_us * (s == 1 ? 0.95f : 1.f)) { best_us = us; best = TilePlan{s, ks}; }
+      if (us < best_us) { best_us = us; best = TilePlan{s, ks}; }
     }
   }
   return best;

@@ -107,12 +107,48 @@ def test_config3_lookahead_sweep_is_deterministic_and_flat():
     assert lat[4] < 1.15 * lat[0]  # Section 2.2: a (1+k)-row call costs about what a one-row call costs (measured: 1.00 - 1.02)
 
 
+def _decisions(g, prompts, slots, slot, n_iters, temp, seed, logits_at=-1):
+    """What `slot` decides in each iteration of `slots` stepping together (first token, drafts, accepted, tokens), and its
+    logits of both calls of iteration `logits_at`."""
+    for i in slots:
+        g.prefill(i, prompts[i], seq_id=i)
+    at, seen, lg = slots.index(slot), [], None
+    for it in range(n_iters):
+        first, drafts = g.draft(slots, temp, seed)
+        ld = g.get_logits(slot, 0) if it == logits_at else None
+        acc, out = g.verify(slots, temp, seed)
+        if it == logits_at:
+            lg = (ld, g.get_logits(slot, 1))
+        seen.append((int(first[at]), drafts[at].tolist(), int(acc[at]), out[at].tolist()))
+    return seen, lg
+
+
+def _undecided(k, temp, seed, seq_id, it, mine, theirs, decided):
+    """Names of the decisions of one iteration that logits as far apart as `mine` and `theirs` leave open."""
+    (ld, lv), (_, drafts, acc, _) = mine, decided
+    err_d, err_v = (float(np.abs(a - b).max()) for a, b in zip(mine, theirs))
+    tau = err_d / temp * 1.01 + parity.F32_ARITH
+    open_ = ["draft %d" % t for t in range(k + 1) if not O.sample_softmax(ld[t], temp, seed, seq_id, it, t, O.DRAFT, tau)[1]]
+    if open_:
+        return open_  # the validation call saw other rows
+    tau = max(err_d, err_v) / temp * 1.01 + parity.F32_ARITH
+    open_ = ["accept %d" % t for t in range(1, min(acc + 1, k) + 1)
+             if not O.accept(lv[t - 1], ld[t], drafts[t - 1], temp, seed, seq_id, it, t, tau)[1]]
+    if acc < k:
+        stable = O.sample_residual(lv[acc], ld[acc + 1], temp, seed, seq_id, it, acc + 1, tau)[1]
+    else:
+        stable = O.sample_softmax(lv[k], temp, seed, seq_id, it, k + 1, O.BONUS, tau)[1]
+    return open_ + ([] if stable else ["last token"])
+
+
 def test_config4_ragged_batch_matches_single_slot_runs():
     """Configuration 4 (7B, 8 ragged prompts 128..2048, k = 4, temperature 1.0, 128 tokens each):
     the sampled slots produce the same tokens as their single-slot runs (M = 40 rows vs 5).  Random
     streams and the attention split plan never depend on the batch; the GEMMs' reduction order does
-    (different launch shapes), which moves logits by rounding only: far below every decision margin
-    of this seeded run, and the runs are deterministic."""
+    (different launch shapes), which moves logits by rounding only, and the runs are deterministic.
+    Where the two part ways all the same, the first decision that differs has to be one that the distance
+    of their logits at that point leaves open.  That distance grows with the tokens (cached values round to bf16 either way, and
+    what comes of it travels): 1e-3 to 1.5e-2 as measured over the 128 tokens, 2e-2 is allowed."""
     w = synth.WORKLOADS["7b_b8_ragged_t1"]
     prompts = synth.make_prompts(w)
     assert len(prompts) == 8 and min(map(len, prompts)) >= 128 and max(map(len, prompts)) <= 2048
@@ -124,8 +160,19 @@ def test_config4_ragged_batch_matches_single_slot_runs():
     print(st, flush=True)
     for i in (0, 3, 7):
         g.prefill(i, prompts[i], seq_id=i)
-        single, _ = g.generate([i], w.max_new, 1.0, seed)
-        assert np.array_equal(single[0], toks[i]), f"slot {i} depends on its batch"
+        single, st = g.generate([i], w.max_new, 1.0, seed)
+        if np.array_equal(single[0], toks[i]):
+            continue
+        n = st["iterations"]
+        alone, _ = _decisions(g, prompts, [i], i, n, 1.0, seed)
+        shared, _ = _decisions(g, prompts, list(range(8)), i, n, 1.0, seed)
+        it = next(t for t in range(n) if alone[t] != shared[t])
+        _, mine = _decisions(g, prompts, [i], i, it + 1, 1.0, seed, it)
+        _, theirs = _decisions(g, prompts, list(range(8)), i, it + 1, 1.0, seed, it)
+        far = float(np.abs(mine[0] - theirs[0]).max())
+        open_ = _undecided(w.k, 1.0, seed, i, it, mine, theirs, alone[it])
+        print("slot %d: iteration %d, logits %.1e apart, open: %s" % (i, it, far, open_), flush=True)
+        assert far <= 2e-2 and open_, f"slot {i} depends on its batch"
     g.close()
 
 
