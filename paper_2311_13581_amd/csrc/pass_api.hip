@@ -234,10 +234,11 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   W.rows = std::min(kPrefillRows, (c.max_seq_len + 127) / 128 * 128);
   W.np = (int)(d / 16);  // most partial sums of h^2 a row can have (one per strip)
   const size_t R = W.rows;
-  // sums over slices of K of the GEMMs that are split: at most one tile of 384 x 128 per compute unit, and never more
-  // than eight slices of the widest product
-  // (fp32 models have no tiled pass)
-  W.part_floats = c.dtype == PASS_BF16 ? std::min<size_t>((size_t)256 * 384 * 128, 8 * R * std::max(3 * D, std::max(2 * F, d))) : 0;
+  // sums over slices of K of the tiled pass's GEMMs (models that can take it only: matrix-core path with transposed V pages):
+  // eight slices of the widest product, but no more than 50 MB, which is what three slices of the widest product of a 7B model
+  // take at 190 rows, six of Wo at 511
+  const bool tiled = c.dtype == PASS_BF16 && c.head_dim == 128 && c.page_size % 32 == 0 && d % 32 == 0 && F % 32 == 0 && V % 16 == 0;
+  W.part_floats = tiled ? std::min<size_t>((size_t)256 * 384 * 128, 8 * R * std::max(3 * D, std::max(2 * F, d))) : 0;
   const size_t ws_bytes = R * 4 * (d + d + D + D + F + W.np + c.head_dim) + W.part_floats * 4 + 9 * 256;
   if (ws_bytes > stage_bytes) stage_bytes = ws_bytes;
   void *staging = A.take<char>(stage_bytes);

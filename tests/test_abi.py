@@ -37,6 +37,19 @@ def test_arena_size_and_config_validation():
         assert lib.pass_arena_bytes(C.byref(c2)) == 0, field
 
 
+def test_arena_holds_slice_sums_only_where_prompts_can_be_tiled():
+    """The tiled prompt pass keeps up to 50 MB of partial sums; contexts that can never take it (fp32, a head size of 64, pages that
+    the matrix-core attention does not read, dimensions off its tiles) have no room set aside for them."""
+    lib = binding.load_library()
+
+    def arena(dtype=synth.BF16, heads=4, hd=128, ffn=1184, vocab=1008, page=64, d=512):
+        return lib.pass_arena_bytes(C.byref(binding.make_config(synth.ModelShape(1, d, heads, hd, ffn, vocab, dtype=dtype), 2, 1, 2048, page)))
+
+    with_sums = arena()
+    for other in (dict(heads=8, hd=64), dict(page=16), dict(ffn=1192), dict(vocab=1012), dict(d=520)):
+        assert arena(**other) < with_sums - 40 * 2 ** 20, other
+
+
 def test_struct_layouts_match_header_sizes():
     assert C.sizeof(binding.PassConfig) == 14 * 4
     assert C.sizeof(binding.PassSampling) == 16
