@@ -453,25 +453,28 @@ std::vector<PlanSeg> plan_prefill(int cap, const int32_t *lens, int n) {
 }
 // Whether the prompts of a batch share tiled passes: from 2 * kMaxRows rows on always; below what one pass of the decode
 // kernels holds never; in between it depends on how they pack, because every prompt starts on a block of 128 rows and a pass
-// holds no more than max_seq_len allows.  Per 7B layer a call of the decode kernels takes about 92 us and 1 us a row, a
-// tiled pass about 100 us and 60 a block.  Four layers, one by one against shared passes: two prompts of 33 rows 1.09 ms against
-// 1.23 in two passes and 0.95 in one; eight of 9 rows 3.34 against 4.85 in eight passes, 3.72 in four, 2.83 in one.
-bool batch_takes_tiles(const int32_t *lens, int n, int chunk, int cap) {
-  int64_t total = 0, alone_us = 0, shared_us = 0;
+// holds no more than max_seq_len allows.  Priced per layer in us, between a layer of 26 MB (d 1024) and a 7B one of 405 MB:
+// a call of the decode kernels 42 .. 97 and up to 1.5 a row beyond 16, a tiled pass 64 .. 90 and 10 .. 90 a block.  Measured, four layers,
+// one by one against shared: 7B, two prompts of 33 rows 1.01 ms against 1.23 in two passes, 1.04 in one; eight of 9 rows 3.15
+// against 4.85 in eight passes, 3.32 in one; four of 29 rows 1.91 against 1.70 in one; d 1024, eight of 9 rows 1.47 against 0.78.
+bool batch_takes_tiles(const Params &p, const int32_t *lens, int n, int chunk, int cap) {
+  const double w = (4.0 * p.d * p.D + 3.0 * p.d * p.F) / 202.4e6;  // a layer's weights, in those of a 7B model
+  auto tiled_us = [&](int rows) { return (10 + 80 * w) * ((rows + kPrefillBlockRows - 1) / kPrefillBlockRows); };
+  const double pass_us = 64 + 26 * w;
+  int64_t total = 0;
+  double alone = 0, shared = 0;
   for (int b = 0; b < n; ++b) {
     const int rows = lens[b] - 1;
     total += rows;
-    alone_us += rows > kTiledMinRows ? 100 + 60 * ((rows + kPrefillBlockRows - 1) / kPrefillBlockRows)
-                                     : 92 * ((rows + chunk - 1) / chunk) + rows;
+    alone += rows > kTiledMinRows ? pass_us + tiled_us(rows) : (42 + 55 * w) * ((rows + chunk - 1) / chunk) + 1.5 * w * std::max(0, rows - 16);
   }
   if (total <= kTiledMinRows || total > 2 * kMaxRows) return total > kTiledMinRows;
   int pass = -1;
   for (const PlanSeg &g : plan_prefill(cap, lens, n)) {
-    if (g.pass != pass) shared_us += 100;
-    shared_us += 60 * ((g.rows + kPrefillBlockRows - 1) / kPrefillBlockRows);
+    shared += tiled_us(g.rows) + (g.pass != pass ? pass_us : 0);
     pass = g.pass;
   }
-  return shared_us < alone_us;
+  return shared < alone;
 }
 
 int run_prefill_pass(pass_ctx *c, const std::vector<PassSeg> &parts, int M, const int32_t *ids) {
@@ -485,6 +488,9 @@ int run_prefill_pass(pass_ctx *c, const std::vector<PassSeg> &parts, int M, cons
   PrefillSegs segs;
   memset(&segs, 0, sizeof segs);
   segs.n_blocks = (M + kPrefillBlockRows - 1) / kPrefillBlockRows;
+  int rows = 0;
+  for (const PassSeg &g : parts) rows += g.rows;
+  W.few = rows <= 2 * kMaxRows;
   for (const PassSeg &g : parts)
     for (int done = 0; done < g.rows; done += kPrefillBlockRows) {
       const int b = (g.row_base + done) / kPrefillBlockRows;
@@ -874,7 +880,7 @@ int pass_prefill_batch(pass_ctx *c, const int32_t *slots, const uint32_t *seq_id
   // prompts go one by one
   const bool tiled = c->use_mfma && c->P.v_transposed &&
                      (c->opt_prefill_tiled == 1 ||
-                      (c->opt_prefill_tiled < 0 && batch_takes_tiles(lens, n_slots, c->opt_prefill_chunk, c->pws.rows)));
+                      (c->opt_prefill_tiled < 0 && batch_takes_tiles(c->P, lens, n_slots, c->opt_prefill_chunk, c->pws.rows)));
   int rc;
   if (!tiled) {
     const int32_t *pr = prompts;

@@ -222,6 +222,7 @@ struct PrefillWs {
   int rows;       // capacity in rows (multiple of 128); also the row stride of the partial sums of h^2
   int np;         // partial sums of h^2 per row that the last producer of rows has left
   int strips_opt; // GEMM tile and slices of K: 0 = by cost, else as "tune.prefill_strips" names them (pass_api.hip)
+  int few;        // the rows of this pass would make no more than two calls of the decode kernels: sums as exact as theirs
   int panel;      // row tiles of a panel of the GEMMs' tile order; 0 = 1024 rows
   float *part;    // sums over slices of K: part_floats floats
   size_t part_floats;

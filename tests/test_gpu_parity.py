@@ -555,7 +555,7 @@ def test_prompt_pass_by_length(lens):
 
 
 @pytest.mark.parametrize("lens,max_len,shared", [
-    ((34, 34), 128, False), ((34, 34), 256, True), ((18,) * 4, 128, False), ((18,) * 4, 256, False), ((18,) * 4, 512, True),
+    ((34, 34), 128, False), ((40, 41, 42), 512, True), ((18,) * 4, 128, False), ((18,) * 4, 256, False), ((18,) * 4, 512, True),
     ((10,) * 8, 256, False), ((10,) * 8, 1024, True), ((30, 30), 256, False), ((70, 3), 128, False), ((70, 3), 256, True)])
 def test_short_prompts_share_passes_where_it_pays(lens, max_len, shared):
     """Batches of 65 to 128 rows in all: a pass holds max_seq_len rows, rounded up to blocks of 128, and every prompt takes a block

@@ -38,13 +38,14 @@ def weights(shape, k, **given):
     return W
 
 
+@pytest.mark.parametrize("n,chains", [(200, 1), (100, 4)])
 @pytest.mark.parametrize("strips", range(6))
-def test_sums_of_the_prompt_pass(strips):
-    """Values of one layer's V projection over a prompt of 200 equal tokens (every tile of the tiled GEMM, whole and in slices):
-    queries are zero, so the next call's attention output is their mean, and the LM head reads it off feature by feature."""
+def test_sums_of_the_prompt_pass(strips, n, chains):
+    """Values of one layer's V projection over a prompt of equal tokens (every tile of the tiled GEMM, whole and in slices; 100
+    rows, which add their products step by step, may lose no more than if four accumulators shared K): queries are zero, so the next call's attention output is their mean, and the LM head reads it off feature by feature."""
     from paper_2311_13581_amd import binding
     rng = np.random.default_rng(0)
-    n, lead = 200, 128  # features 0 .. 127 belong to the pending token alone, the rest to the prompt's token
+    lead = 128  # features 0 .. 127 belong to the pending token alone, the rest to the prompt's token
     half = (D - lead) // 2
     shape = synth.ModelShape(1, D, 8, 128, 32, 1040, dtype=synth.BF16)
     H = shape.n_heads * shape.head_dim
@@ -66,8 +67,8 @@ def test_sums_of_the_prompt_pass(strips):
     x = rounded(emb.astype(np.float32)).astype(np.float64)
     mid = (w * (x * rounded(gain.astype(np.float32)))).sum(1) / np.sqrt(2 * (x ** 2).sum() / D + shape.rms_eps)
     rel = np.sqrt((err ** 2).mean() / (mid ** 2).mean())
-    print("tile", strips, "error of the sums", rel, "bound", bound(2 * half / 8, 1))
-    assert 0 < rel < bound(2 * half / 8, 1)
+    print("rows", n, "tile", strips, "error of the sums", rel, "bound", bound(2 * half / 8, chains))
+    assert 0 < rel < bound(2 * half / 8, chains)
 
 
 @pytest.mark.parametrize("slots,k,blocks", [(1, 4, 0), (1, 8, 0), (2, 7, 0), (8, 4, 0), (8, 4, 6), (8, 4, 8), (8, 7, 0), (8, 7, 3), (8, 7, 8)])
