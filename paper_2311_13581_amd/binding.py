@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import weakref
 
 import numpy as np
 
@@ -123,6 +124,39 @@ def make_config(shape, k, max_slots, max_seq_len, page_size=64, n_pages=0) -> Pa
                       shape.rms_eps, shape.rope_base, shape.dtype, k, max_slots, max_seq_len, page_size, n_pages)
 
 
+class _Results:
+    """Arrays for results of one size, in ordinary memory that is used again once an array is gone.
+
+    A fresh array of a few hundred KB is fresh pages each time the C heap maps it anew (which it may do or not for the whole of
+    a process): 125 us for 640 KB instead of 40.  A buffer comes back when the array and every view of it are gone, on whatever
+    thread that happens; `limit` of them are kept.  Ordinary and not pinned memory: a copy to the GPU that does not block takes
+    what it needs of it before it returns, so an array may be dropped at once.  Below 128 KB (which the heap serves from pages
+    it keeps) arrays are the heap's own."""
+
+    def __init__(self, shape, limit):
+        self._shape, self._limit, self._free = shape, limit, []
+        self._bytes = 4 * int(np.prod(shape))
+
+    def take(self) -> np.ndarray:
+        if self._bytes < 128 * 1024:
+            return np.empty(self._shape, dtype=np.float32)
+        try:
+            buf = self._free.pop()
+        except IndexError:
+            buf = bytearray(self._bytes)
+        flat = np.frombuffer(buf, dtype=np.float32)  # what every view of the result holds on to (its base is no array)
+        weakref.finalize(flat, self._back, buf).atexit = False
+        return flat.reshape(self._shape)
+
+    def _back(self, buf):
+        if len(self._free) < self._limit:
+            self._free.append(buf)
+
+    def drop(self):
+        self._limit = 0
+        self._free.clear()
+
+
 class Pass:
     """One model instance on the current CUDA(HIP) device.  Methods mirror the C entry points."""
 
@@ -150,6 +184,8 @@ class Pass:
         if rc != 0:
             raise PassError(rc, self.lib.pass_last_error(None).decode())
         self.h = h
+        # the logits of both calls of every slot, twice: a loop still holds an iteration's results while it reads the next one's
+        self._logits = _Results((cfg.k + 1, cfg.vocab), 4 * cfg.max_slots)
         for name, val in (options or {}).items():
             self.set_option(name, val)
 
@@ -162,6 +198,7 @@ class Pass:
             self.lib.pass_destroy(self.h)
             self.h = None
             self.arena = None
+            self._logits.drop()
 
     def __del__(self):
         try:
@@ -282,7 +319,7 @@ class Pass:
         return out
 
     def get_logits(self, slot: int, which: int) -> np.ndarray:
-        out = np.empty((self.k + 1, self.vocab), dtype=np.float32)
+        out = self._logits.take()
         self._check(self.lib.pass_get_logits(self.h, slot, which, out.ctypes.data_as(C.POINTER(C.c_float))))
         return out
 

@@ -514,9 +514,9 @@ def test_sampling_epilogue_ties_across_parts():
 
 
 def test_logits_results_are_the_callers():
-    """get_logits hands out arrays that are the caller's alone: they own ordinary memory (a copy to the GPU that does not block
-    takes what it needs before it returns, so an array may be dropped at once), and results that are held, or of which only
-    a view is left, keep their values through later calls."""
+    """get_logits hands out arrays that stay the caller's, in ordinary memory (a copy to the GPU that does not block takes what it
+    needs before it returns, so an array may be dropped at once): results that are held, views of results that are gone, and more
+    results than buffers are kept keep their values through later calls; buffers are used again, and dropped by close()."""
     import torch
     shape = synth.ModelShape(1, 128, 2, 64, 96, 36000, dtype=synth.F32)
     W = synth.make_weights(shape, 14, 1, 10.0)
@@ -526,14 +526,25 @@ def test_logits_results_are_the_callers():
         g.prefill(0, np.arange(1 + i, 9 + i, dtype=np.int32))
         g.draft([0], 0.0, 5)
         a = g.get_logits(0, 0)
-        assert a.flags.owndata and not torch.from_numpy(a).is_pinned()
+        assert not torch.from_numpy(a).is_pinned() and a.flags.writeable and a.flags.c_contiguous
         want.append(a.copy())
         held.append(a[1:, 5:] if i % 2 else a)  # every other result only survives as a view
         del a
     for i, (h, x) in enumerate(zip(held, want)):
         assert np.array_equal(h, x[1:, 5:] if i % 2 else x), i
     assert len({x.tobytes() for x in want}) == 6
+    where = {x.ctypes.data for x in held[::2]}
+    on_gpu = [torch.from_numpy(x).to("cuda", non_blocking=True) for x in held[::2]]
+    del held, h
+    later = [g.get_logits(0, 1) for _ in range(6)]
+    assert where & {x.ctypes.data for x in later}  # some of that memory holds other values now, the copies their own
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(on_gpu, want[::2]))
+    del later
+    last = g.get_logits(0, 0)
     g.close()
+    assert np.array_equal(last, want[5])
+    del last
+    assert not g._logits._free
 
 
 @pytest.mark.parametrize("lens", [(64,), (65,), (66,), (129,), (30, 36), (31, 36), (1, 65, 2)])
