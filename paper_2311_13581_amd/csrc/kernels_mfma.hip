@@ -461,8 +461,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KT = a.K >> 5;                                        // k-tiles of the whole K (strip stride)
-  const int KTl = (EPI == EPI_PARTIAL) ? a.kt_split : KT;         // k-tiles this workgroup walks
-  const int kbase = (EPI == EPI_PARTIAL) ? blockIdx.y * KTl : 0;  // first of them
+  const int kbase = (EPI == EPI_PARTIAL) ? blockIdx.y * a.kt_split : 0;     // first k-tile this workgroup walks
+  const int KTl = (EPI == EPI_PARTIAL) ? min(a.kt_split, KT - kbase) : KT;  // how many (the last slice may hold fewer)
   const int strip0 = blockIdx.x * NS;
 
   // strips past the end repeat the last one (in bounds; their results are dropped).  Rows >= M of the last group hold
@@ -722,12 +722,15 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(Params p, const float
   if ((threadIdx.x & 3) == 0) p.ssq[(size_t)strip * kMaxRows + m] = ss;  // rows >= M get 0
 }
 
-static bool launch_resid_split(const Params &p, const GemmTuning &tn, const GemmArgs &a0, int mt, int kind, hipStream_t s) {
-  const int n_strips = p.d / 16, KT = a0.K >> 5, KS = tn.split_ks;
-  if (KS < 2 || KT % KS != 0) return false;
-  if ((size_t)KS * p.d > (size_t)2 * p.F) return false;  // the slices' sums borrow the generic path's gate/up workspace
+static bool launch_resid_split(const Params &p, const GemmTuning &tn, const GemmArgs &a0, int kind, hipStream_t s) {
+  const int n_strips = p.d / 16, KT = a0.K >> 5;
+  if (tn.split_ks < 2) return false;
   GemmArgs a = a0;
-  a.kt_split = KT / KS;
+  // K need not divide evenly, the last slice holds what is left (40 rows, down of d 4096, K 9408, 294 k-tiles: 22.5 us in
+  // slices of 74, 74, 74 and 72, 31.7 whole; d 5120, K 13760: 32.9 and 56.1)
+  a.kt_split = (KT + tn.split_ks - 1) / tn.split_ks;
+  const int KS = (KT + a.kt_split - 1) / a.kt_split;
+  if (KS < 2 || (size_t)KS * p.d > (size_t)2 * p.F) return false;  // the slices' sums borrow the generic path's gate/up workspace
   a.partial = p.gu;
   a.ldy = p.d;
   launch_rows<EPI_PARTIAL>(p, a, n_strips, tn.big_blocks[kind], KS, s);
@@ -742,7 +745,7 @@ void launch_gemm_qkv(const Params &p, const GemmTuning &tn, const void *W, int l
 void launch_gemm_resid(const Params &p, const GemmTuning &tn, const void *W, const uint16_t *X, int K,
                        const void *gain_next, int M, hipStream_t s) {
   GemmArgs a{(const u32x4 *)W, X, M, K, 0, (const uint16_t *)gain_next, nullptr, 0, nullptr, p.d / 16};
-  if (M > 8 && launch_resid_split(p, tn, a, (M + 7) / 8, K == p.F ? 4 : 1, s)) return;
+  if (M > 8 && launch_resid_split(p, tn, a, K == p.F ? 4 : 1, s)) return;
   launch_gemm_epi<EPI_RESID>(p, tn, a, p.d / 16, s, K == p.F ? 4 : 1);  // the down projection has its own shape
 }
 void launch_gemm_gateup(const Params &p, const GemmTuning &tn, const void *W, int M, hipStream_t s) {
@@ -769,22 +772,23 @@ void launch_gemm_gateup_save(const Params &p, const void *W, float *gu_save, int
 }
 
 // Plain product Y = X W^T on packed tiles: X as (hi, lo) tiles of K features, W packed [N][K], Y fp32.
-// K is cut into KS slices across workgroups; slice ks leaves its
-// sums in part[ks][kMaxRows][N] and the consumer adds the slices in order.  Needs N % 64 == 0 and
-// (K / 32) % KS == 0; returns the KS it used (plain_gemm_slices: what the consumer must add up).
+// K is cut into KS slices across workgroups (the last one may be shorter); slice ks leaves its
+// sums in part[ks][kMaxRows][N] and the consumer adds the slices in order.  Needs N % 64 == 0; returns the KS it
+// used (plain_gemm_slices: what the consumer must add up).
 int plain_gemm_slices(int N, int K) {
   const int KT = K / 32, wgs = N / 64;
   int best = 1;
   for (int ks = 1; ks <= 8; ks *= 2) {
-    if (KT % ks != 0 || KT / ks < 8) break;
+    if (KT / ks < 8) break;
     best = ks;
     if (wgs * ks >= 256) break;  // one workgroup per compute unit: each pulls its slice of the rows once
   }
-  return best;
+  const int kts = (KT + best - 1) / best;
+  return (KT + kts - 1) / kts;  // every slice holds something
 }
 int launch_gemm_plain(const Params &p, const void *W, const uint16_t *X, int M, int N, int K, float *part, hipStream_t s) {
-  const int KS = plain_gemm_slices(N, K);
-  GemmArgs a{(const u32x4 *)W, X, M, K, 0, nullptr, nullptr, (K / 32) / KS, part, N / 16, N, nullptr};
+  const int KT = K / 32, KS = plain_gemm_slices(N, K);
+  GemmArgs a{(const u32x4 *)W, X, M, K, 0, nullptr, nullptr, (KT + KS - 1) / KS, part, N / 16, N, nullptr};
   launch_rows<EPI_PARTIAL>(p, a, N / 16, 0, KS, s);
   return KS;
 }

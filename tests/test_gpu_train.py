@@ -111,6 +111,29 @@ def test_one_training_step_for_every_row_bound(shape, page, path, k):
     g.close()
 
 
+@pytest.mark.parametrize("d,ffn,vocab", [(256, 320, 544), (320, 1088, 1056), (576, 576, 4064)])
+def test_training_step_with_uneven_slices(d, ffn, vocab):
+    """Backward products whose K does not divide into its slices (17, 33 and 127 k-tiles of the vocabulary in two, four and
+    eight, 34 of 2 d_ffn and 18 of d in four and two): the last slice holds what is left."""
+    shape = synth.ModelShape(1, d, 2, 128, ffn, vocab, dtype=synth.BF16)
+    k = 4
+    W = synth.make_weights(shape, 29, k, 6.0)
+    g = _gpu(shape, W, k, 2, 64, 64, {"path": 0})
+    g.train_begin(-1)
+    la = TO._t(W["lookahead"], shape.dtype).numpy()
+    rng = np.random.default_rng(vocab)
+    prefixes = [rng.integers(0, vocab, n).astype(np.int32) for n in (1, 30)]
+    targets = rng.integers(0, vocab, (2, k)).astype(np.int32)
+    for i, p in enumerate(prefixes):
+        g.prefill(i, p, seq_id=i)
+    loss = g.train_step([0, 1], targets, 0.01)
+    o_loss, o_grad = TO.loss_and_grad(shape, W, la, [p.tolist() for p in prefixes], targets)
+    e_loss, e_grad = abs(loss - o_loss) / abs(o_loss), float(np.abs(g.train_read(1) - o_grad).max() / np.abs(o_grad).max())
+    print(f"vocab={vocab}: loss rel {e_loss:.1e} grad err {e_grad:.1e}")
+    assert e_loss <= 6e-5 and e_grad <= 4e-4
+    g.close()
+
+
 @pytest.mark.parametrize("dtype,path", [(synth.F32, 1), (synth.BF16, 1), (synth.BF16, 0)], ids=["fp32", "bf16-generic", "bf16"])
 def test_training_step_with_a_part_of_the_logits_at_minus_infinity(dtype, path):
     """The LM-head rows of the second of three parts of 1024 entries (the cross-entropy's unit) overflow to -inf for every hidden
