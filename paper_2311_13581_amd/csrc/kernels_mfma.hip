@@ -6,8 +6,8 @@
 // order of v_mfma_f32_16x16x32_bf16's A operand, so that one wavefront fetches a tile as 64
 // adjacent 16-byte loads (1 KB, fully coalesced) and a strip of 16 output features is one
 // contiguous run of K/32 KB.  The M <= 64 activation rows are the B operand (rows padded to 16
-// per MFMA).  A workgroup of 4 to 16 wavefronts owns one strip (a gate and an up strip for
-// gate/up; up to eight strips for calls with more than 8 rows) and splits K among its wavefronts;
+// per MFMA).  A workgroup of 4 to 16 wavefronts owns one to four strips (or pairs of a gate and an up
+// strip; up to eight strips for calls with more than 8 rows) and splits K among its wavefronts;
 // the next trip's weight tiles are requested before the current trip computes (calls with more than
 // 8 rows: through rings of LDS stages); partial tiles are reduced through LDS in a fixed order (deterministic).  No workgroup shares weights with another,
 // and the activation rows (tens of KB) sit in every XCD's L2, so the block-to-XCD mapping needs
@@ -334,108 +334,103 @@ __device__ __forceinline__ void gemm_finish(const Params &p, const GemmArgs &a, 
   }
 }
 
-// Calls of up to 8 rows: one MFMA column block, one output block per workgroup (a block is one strip of 16 features, or
-// the gate strip and the up strip of 16 FFN features), operands through registers.
-template <int EPI, int WAVES, int U>
+// Calls of up to 8 rows: one MFMA column block, operands through registers.  A workgroup owns NB output blocks (a block is
+// one strip of 16 features, or the gate strip and the up strip of 16 FFN features) and its wavefronts share K: wavefront w
+// takes k-tiles w, w + WAVES, ..., U of them a trip, and requests a trip while it computes the one before.  The last trip may
+// hold k-tiles past the end: those are requested too (clamped), so that nothing is waited for one by one, and not computed.
+// Bound by how evenly the weights are spread over the compute units: a unit takes in about 30 GB/s of weights and the
+// activation tile that goes with NB strips costs a third of a weight tile whatever rows it holds (1 or 8 rows: the same
+// time), the chip 6.9 TB/s.  Which NB, WAVES and U that asks for: few_rows_shape.
+// The sums of a strip have WAVES x NA accumulators, at least 4 for QKV and gate/up and 16 for the other products (fewer
+// would round more often).
+template <int EPI, int WAVES>
+constexpr int few_rows_chains() {
+  constexpr int need = (EPI == EPI_QKV || EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 4 : 16;
+  return need > WAVES ? need / WAVES : 1;
+}
+template <int EPI, int WAVES, int U, int NB>
 __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArgs a) {
-  constexpr int MT = 1, NB = 1, kGemmWaves = WAVES;
-  constexpr int NS = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;  // strips
-  static_assert(WAVES * NS <= 32, "reduction buffer must fit the static LDS limit");
-  __shared__ floatx4 red[kGemmWaves * NS * 64];
-  __shared__ float red_ss[kGemmWaves][MT][8];
+  constexpr int NS = NB * ((EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1);  // strips
+  constexpr int NA = few_rows_chains<EPI, WAVES>();
+  constexpr int G = NA > U ? NA / U : 1;  // trips until an accumulator's turn comes again
+  __shared__ floatx4 red[WAVES * NS * 64];
+  __shared__ float red_ss[WAVES][1][8];
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ml = lane & 15;  // MFMA column = pseudo-row
-  const int KT = a.K >> 5;  // k-tiles of K (strip stride)
+  const int KT = a.K >> 5;   // k-tiles of K (strip stride)
   const int strip0 = blockIdx.x * NS;
 
-  floatx4 acc[NS][MT];
+  floatx4 acc[NA][NS];
 #pragma unroll
-  for (int s = 0; s < NS; ++s)
+  for (int c = 0; c < NA; ++c)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[s][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < NS; ++s) acc[c][s] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // Activation loads go through a buffer descriptor: a lane whose pseudo-row belongs to a row
-  // >= M gets an out-of-range offset and the hardware returns zeros without touching memory.
-  // All loads are unconditional instructions, so outstanding requests are counted exactly and a
-  // trip can wait for its activations while the next trip's weight tiles stay in flight.
-  const int n_groups = (a.M + 7) >> 3;
-  const __amdgpu_buffer_rsrc_t xr =
-      __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, n_groups * 16 * a.K * 2, 0x00020000);
-  int xoff[MT];  // byte offset of this lane's 16 bytes in k-tile 0
+  // Activation loads go through a buffer descriptor: a lane whose pseudo-row belongs to a row >= M gets an out-of-range
+  // offset and the hardware returns zeros without touching memory.  All loads are unconditional instructions, so
+  // outstanding requests are counted exactly and a trip can wait for its operands while the next trip's stay in flight.
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, 16 * a.K * 2, 0x00020000);
+  const int xoff = (ml & 7) < a.M ? lane * 16 : 0x40000000;  // byte offset of this lane's 16 bytes in k-tile 0
+  const u32x4 *wp[NS];  // strips past the end repeat the last one (in bounds; their results are dropped)
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    int m = mt * 8 + (ml & 7);
-    xoff[mt] = (m < a.M) ? (mt * KT * 64 + lane) * 16 : 0x40000000;
-  }
-  const u32x4 *wp = a.W + (size_t)strip0 * KT * 64 + lane;
+  for (int s = 0; s < NS; ++s) wp[s] = a.W + (size_t)(NB > 1 ? min(strip0 + s, a.n_strips - 1) : strip0 + s) * KT * 64;
 
-  auto load_a = [&](u32x4 (&dst)[U][NS], int kt0) {
+  u32x4 av[2][U][NS], bv[2][U];
+  auto load = [&](int buf, int trip) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      const int kt = min(wave + (trip * U + u) * WAVES, KT - 1);
+      bv[buf][u] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff, kt * 1024, 0);
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        dst[u][s] = __builtin_nontemporal_load(wp + ((size_t)s * KT + kt0 + u * kGemmWaves) * 64);
-  };
-  auto load_b = [&](u32x4 (&dst)[U][MT], int kt0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        dst[u][mt] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff[mt] + (kt0 + u * kGemmWaves) * 1024, 0, 0);
-  };
-  auto mma = [&](const u32x4 (&av)[U][NS], const u32x4 (&bv)[U][MT]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[u][s]),
-                                                               __builtin_bit_cast(bf16x8, bv[u][mt]), acc[s][mt], 0, 0, 0);
-  };
-
-  // full trips: k-tiles kt0 + u * WAVES, u < U, with kt0 = wave + trip * WAVES * U (interleaved
-  // over the wavefronts, so the workgroup walks its strip front to back)
-  const int trip_tiles = kGemmWaves * U;
-  const int n_trips = KT / trip_tiles;
-  if (n_trips > 0) {
-    // Both operands of trip t+1 are requested during trip t, activations first, so a trip only
-    // ever waits for requests that have had a whole trip to complete.
-    u32x4 a_cur[U][NS], a_nxt[U][NS], b_cur[U][MT], b_nxt[U][MT];
-    load_b(b_cur, wave);
-    load_a(a_cur, wave);
-    for (int t = 0; t < n_trips - 1; ++t) {
-      const int kt1 = wave + (t + 1) * trip_tiles;
-      load_b(b_nxt, kt1);
-      load_a(a_nxt, kt1);
-      mma(a_cur, b_cur);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) a_cur[u][s] = a_nxt[u][s];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) b_cur[u][mt] = b_nxt[u][mt];
-      }
+      for (int s = 0; s < NS; ++s) av[buf][u][s] = __builtin_nontemporal_load(wp[s] + (size_t)kt * 64 + lane);
     }
-    mma(a_cur, b_cur);
-  }
-  // tail: the k-tiles that do not fill a trip, one per wavefront and step (wavefront-uniform bound)
-  for (int kt = n_trips * trip_tiles + wave; kt < KT; kt += kGemmWaves) {
-    u32x4 bv[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) bv[mt] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff[mt] + kt * 1024, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);  // requested here: left alone, the scheduler moves the requests behind the products
+  };
+  auto mma = [&](int buf, int g, int u) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      u32x4 av = __builtin_nontemporal_load(wp + ((size_t)s * KT + kt) * 64);
+      floatx4 &c = acc[(g * U + u) % NA][s];
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[buf][u][s]), __builtin_bit_cast(bf16x8, bv[buf][u]), c, 0, 0, 0);
+    }
+  };
+  const int trips = (KT + WAVES * U - 1) / (WAVES * U);
+  constexpr int STEP = G > 2 ? G : 2;  // trips per turn of the loop: whole turns of the accumulators and of the two buffers
+  int t = 0;
+  load(0, 0);
+  for (; t + STEP < trips; t += STEP) {  // (all of these are full)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        acc[s][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
-                                                             __builtin_bit_cast(bf16x8, bv[mt]), acc[s][mt], 0, 0, 0);
+    for (int g = 0; g < STEP; ++g) {
+      load((g + 1) & 1, t + g + 1);
+#pragma unroll
+      for (int u = 0; u < U; ++u) mma(g & 1, g, u);
     }
   }
-
-  gemm_finish<MT, EPI, WAVES, NB, NS, 1>(p, a, acc, red, NS * 64, red_ss, strip0);
+  // the last one to STEP trips, each number of them in a line of its own (a request under a condition would be waited for)
+  auto rest = [&](auto self, auto gc) __attribute__((always_inline)) -> void {
+    constexpr int g = decltype(gc)::value;
+    if constexpr (g + 1 < STEP) {
+      if (t + g + 1 < trips) {
+        load((g + 1) & 1, t + g + 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u) mma(g & 1, g, u);
+        self(self, nb_c<g + 1>{});
+        return;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (wave + ((t + g) * U + u) * WAVES < KT) mma(g & 1, g, u);
+  };
+  rest(rest, nb_c<0>{});
+  floatx4 sum[NS][1];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    sum[s][0] = acc[0][s];
+#pragma unroll
+    for (int c = 1; c < NA; ++c) sum[s][0] += acc[c][s];
+  }
+  gemm_finish<1, EPI, WAVES, NB, NS, 1>(p, a, sum, red, NS * 64, red_ss, strip0);
 }
 
 // Calls with more than 8 rows: the same product with both operands in LDS rings.  Such a call pulls two to three times
@@ -570,8 +565,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
 // Launch shape of the decode-sized GEMMs: GemmTuning (a member of the context, so two contexts
 // never share a setting).  Defaults chosen by sweeping the benchmark on MI355X.
 GemmTuning::GemmTuning()
-    : waves{0, 0, 4, 16, 0},       // QKV, Wo, gate/up, LM head, down; 0 = by strip count (launch_gemm_epi)
-      unroll{1, 1, 1, 2, 1},
+    : waves{0, 0, 0, 0, 0},        // QKV, Wo, gate/up, LM head, down; 0 = by the count of blocks (few_rows_shape)
+      unroll{1, 1, 1, 1, 1},
       big_blocks{0, 0, 0, 0, 0},   // 0 = by the count of blocks (ring_blocks)
       split_ks(4) {}
 
@@ -598,9 +593,89 @@ int GemmTuning::set_split(int ks) {
   return 0;
 }
 
-template <int EPI, int W, int U>
-static void launch_one(const Params &p, const GemmArgs &a, int grid, hipStream_t s) {
-  gemm_mfma_kernel<EPI, W, U><<<grid, W * 64, 0, s>>>(p, a);
+// Launch shape of a call of up to 8 rows: output blocks per workgroup, wavefronts, k-tiles per trip.  A compute unit should
+// own as many blocks as any other and share the activation tile between them, with some 24 weight tiles or more requested
+// at a time; where the blocks do not divide evenly among the 256 units, smaller workgroups even it out.
+struct FewShape { int w, u, nb; };
+static FewShape few_rows_shape(int epi, int n) {
+  switch (epi) {
+    case EPI_QKV:  // one workgroup a unit, or two (d 5120: 960 strips, four a workgroup 26.0 us, one in workgroups of 4
+                   // wavefronts 28.5; 4096: 17.8 and, of 8, 18.6; 2048: 7.2 and 11.0; 1024: 4.5 and 6.6)
+      if (n <= 256) return {8, 2, 1};
+      if (n <= 512) return {4, 2, 2};
+      if (n <= 768) return {8, 2, 3};
+      if (n <= 1024) return {8, 1, 4};
+      return {n % 256 ? 4 : 8, 1, 1};
+    case EPI_GATEUP:
+    case EPI_GATEUP_SAVE:  // (against one pair and one tile a trip in workgroups of 4: d 5120, 864 pairs 43.6 us and 47.0; 4096, 588
+                           // pairs 25.6 and 26.6; 2048, 344 pairs 9.9 and 11.6; 1024, 172 pairs 4.7 and 6.7)
+      if (n <= 256) return {4, 2, 1};
+      if (n <= 384) return {4, 1, 2};
+      if (n <= 512) return {4, 1, 1};
+      if (n <= 768) return {8, 1, 3};
+      if (n <= 1024) return {8, 1, 4};
+      return {8, 2, 1};
+    case EPI_LOGITS:  // many rounds: two strips share the activation tile (V 32000: 41.4 us, one strip 47.8; d 5120 51.5 and 59.0)
+      return n <= 256 ? FewShape{8, 2, 1} : FewShape{4, 2, 2};
+    default:  // Wo and down: 16 features a workgroup while there are units for them (d 4096: Wo 8.1 us, 16 wavefronts 8.6; 2048:
+              // 5.0 and, of 8 with one tile a trip, 6.5), two strips beyond (d 5120, 320 strips: Wo 12.7 us, one strip 14.2)
+      return n <= 256 ? FewShape{8, 4, 1} : FewShape{16, 1, 2};
+  }
+}
+// Slices of K of Wo and down in calls of up to 8 rows, and strips per workgroup; 1 = whole K.  Fewer strips than units leave
+// units idle, 257 to 511 strips give some of them two: then the product is bound by those, and slices over all of them pay for
+// the kernel that adds their sums.  In us, fitted to 81 shapes (d 1024 .. 6144, K 1024 .. 21504; worst choice 8 % off): a unit
+// takes 0.033 us per KB of weights and 0.010 per KB of activation tile, the chip 6.9 TB/s, both kernels together 5.2.
+// d 5120, K 13824: 33.5 us whole in one strip a workgroup, 28.8 in two, 25.3 in four slices of five; d 2048, K 5632: 9.7 and 8.2.
+static int few_rows_slices(int n, int K, int d, int F, int &nb_best) {
+  const int KT = K / 32;
+  const float whole = n <= 256 ? 2.8f + K * (1.1e-3f + 0.7e-6f * n) : 3.0f + ((n + 1) / 2 + 255) / 256 * K * 1.97e-3f;
+  float best = 0.95f * whole;
+  int ks_best = 1;
+  for (int ks = 2; ks <= 8; ++ks) {
+    const int kts = (KT + ks - 1) / ks;
+    if ((KT + kts - 1) / kts != ks || kts < 8) continue;
+    if ((size_t)ks * d > (size_t)2 * F) continue;  // the slices' sums borrow the generic path's gate/up workspace
+    for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
+      const float unit = ((n + nb - 1) / nb * ks + 255) / 256 * (nb * 0.033f + 0.010f) * kts;
+      const float us = 5.2f + std::max(unit, (float)n * K * 32 / 6.9e6f);
+      if (us < best) { best = us; ks_best = ks; nb_best = nb; }
+    }
+  }
+  return ks_best;
+}
+template <int EPI>
+static void launch_few(const Params &p, const GemmArgs &a, int n_blocks, FewShape sh, hipStream_t s) {
+  auto go = [&](auto W, auto U, auto B) {
+    constexpr int w = decltype(W)::value, u = decltype(U)::value, nb = decltype(B)::value;
+    gemm_mfma_kernel<EPI, w, u, nb><<<(n_blocks + nb - 1) / nb, w * 64, 0, s>>>(p, a);
+  };
+  constexpr bool GU = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE);
+  const int key = sh.w * 100 + sh.u * 10 + sh.nb;
+  if constexpr (EPI == EPI_QKV) {
+    if (key == 422) return go(nb_c<4>{}, nb_c<2>{}, nb_c<2>{});
+    if (key == 823) return go(nb_c<8>{}, nb_c<2>{}, nb_c<3>{});
+    if (key == 814) return go(nb_c<8>{}, nb_c<1>{}, nb_c<4>{});
+  } else if constexpr (GU) {
+    if (key == 412) return go(nb_c<4>{}, nb_c<1>{}, nb_c<2>{});
+    if (key == 813) return go(nb_c<8>{}, nb_c<1>{}, nb_c<3>{});
+    if (key == 814) return go(nb_c<8>{}, nb_c<1>{}, nb_c<4>{});
+  } else if constexpr (EPI == EPI_LOGITS) {
+    if (key == 422) return go(nb_c<4>{}, nb_c<2>{}, nb_c<2>{});
+  } else {
+    if (key == 1612) return go(nb_c<16>{}, nb_c<1>{}, nb_c<2>{});
+  }
+  switch (sh.w * 10 + sh.u) {
+    case 161: return go(nb_c<16>{}, nb_c<1>{}, nb_c<1>{});
+    case 162: return go(nb_c<16>{}, nb_c<2>{}, nb_c<1>{});
+    case 164: return go(nb_c<16>{}, nb_c<4>{}, nb_c<1>{});
+    case 81: return go(nb_c<8>{}, nb_c<1>{}, nb_c<1>{});
+    case 82: return go(nb_c<8>{}, nb_c<2>{}, nb_c<1>{});
+    case 84: return go(nb_c<8>{}, nb_c<4>{}, nb_c<1>{});
+    case 41: return go(nb_c<4>{}, nb_c<1>{}, nb_c<1>{});
+    case 42: return go(nb_c<4>{}, nb_c<2>{}, nb_c<1>{});
+    default: return go(nb_c<4>{}, nb_c<4>{}, nb_c<1>{});
+  }
 }
 
 // Blocks a workgroup of the ring form may own: its sums (of the 512 registers that one wavefront per SIMD has) and two
@@ -657,26 +732,8 @@ static void launch_gemm_epi(const Params &p, const GemmTuning &tn, const GemmArg
                             int kind = EPI) {
   constexpr int PER = (EPI == EPI_GATEUP) ? 2 : 1;
   const int n_blocks = n_strips / PER;
-  int mt = (a.M + 7) / 8;
-  if (mt == 1) {
-    const int grid = n_blocks;
-    // QKV and the residual projections: when the strips fill the 256 compute units evenly
-    // (d = 4096: 768 and 256 strips) coarse workgroups are best (8 and 16 wavefronts); otherwise
-    // (d = 5120: 960 and 320 strips) finer ones, of which a unit holds several, balance better.
-    const bool even = n_blocks % 256 == 0;
-    const int w = tn.waves[kind] ? tn.waves[kind] : (kind == 0 ? (even ? 8 : 4) : (even ? 16 : 8));
-    const int u = tn.unroll[kind];
-    switch (w * 10 + u) {
-      case 161: launch_one<EPI, 16, 1>(p, a, grid, s); break;
-      case 162: launch_one<EPI, 16, 2>(p, a, grid, s); break;
-      case 164: launch_one<EPI, 16, 4>(p, a, grid, s); break;
-      case 81: launch_one<EPI, 8, 1>(p, a, grid, s); break;
-      case 82: launch_one<EPI, 8, 2>(p, a, grid, s); break;
-      case 84: launch_one<EPI, 8, 4>(p, a, grid, s); break;
-      case 41: launch_one<EPI, 4, 1>(p, a, grid, s); break;
-      case 42: launch_one<EPI, 4, 2>(p, a, grid, s); break;
-      default: launch_one<EPI, 4, 4>(p, a, grid, s); break;
-    }
+  if (a.M <= 8) {
+    launch_few<EPI>(p, a, n_blocks, tn.waves[kind] ? FewShape{tn.waves[kind], tn.unroll[kind], 1} : few_rows_shape(EPI, n_blocks), s);
     return;
   }
   launch_rows<EPI>(p, a, n_blocks, tn.big_blocks[kind], 1, s);
@@ -724,16 +781,18 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(Params p, const float
 
 static bool launch_resid_split(const Params &p, const GemmTuning &tn, const GemmArgs &a0, int kind, hipStream_t s) {
   const int n_strips = p.d / 16, KT = a0.K >> 5;
-  if (tn.split_ks < 2) return false;
+  int KS = tn.split_ks, nb = tn.big_blocks[kind];
+  if (a0.M <= 8 && KS) KS = tn.waves[kind] ? 1 : few_rows_slices(n_strips, a0.K, p.d, p.F, nb);
+  if (KS < 2) return false;
   GemmArgs a = a0;
   // K need not divide evenly, the last slice holds what is left (40 rows, down of d 4096, K 9408, 294 k-tiles: 22.5 us in
   // slices of 74, 74, 74 and 72, 31.7 whole; d 5120, K 13760: 32.9 and 56.1)
-  a.kt_split = (KT + tn.split_ks - 1) / tn.split_ks;
-  const int KS = (KT + a.kt_split - 1) / a.kt_split;
+  a.kt_split = (KT + KS - 1) / KS;
+  KS = (KT + a.kt_split - 1) / a.kt_split;
   if (KS < 2 || (size_t)KS * p.d > (size_t)2 * p.F) return false;  // the slices' sums borrow the generic path's gate/up workspace
   a.partial = p.gu;
   a.ldy = p.d;
-  launch_rows<EPI_PARTIAL>(p, a, n_strips, tn.big_blocks[kind], KS, s);
+  launch_rows<EPI_PARTIAL>(p, a, n_strips, nb, KS, s);
   resid_reduce_kernel<<<n_strips, 256, 0, s>>>(p, a.partial, KS, a.M, a.gain_next);
   return true;
 }
@@ -745,7 +804,7 @@ void launch_gemm_qkv(const Params &p, const GemmTuning &tn, const void *W, int l
 void launch_gemm_resid(const Params &p, const GemmTuning &tn, const void *W, const uint16_t *X, int K,
                        const void *gain_next, int M, hipStream_t s) {
   GemmArgs a{(const u32x4 *)W, X, M, K, 0, (const uint16_t *)gain_next, nullptr, 0, nullptr, p.d / 16};
-  if (M > 8 && launch_resid_split(p, tn, a, K == p.F ? 4 : 1, s)) return;
+  if (launch_resid_split(p, tn, a, K == p.F ? 4 : 1, s)) return;
   launch_gemm_epi<EPI_RESID>(p, tn, a, p.d / 16, s, K == p.F ? 4 : 1);  // the down projection has its own shape
 }
 void launch_gemm_gateup(const Params &p, const GemmTuning &tn, const void *W, int M, hipStream_t s) {
@@ -764,11 +823,9 @@ void launch_gemm_logits(const Params &p, const GemmTuning &tn, const void *W, fl
 // The gate/up GEMM that also keeps gate | up before the activation, in the decode call's launch shapes.
 void launch_gemm_gateup_save(const Params &p, const void *W, float *gu_save, int M, hipStream_t s) {
   GemmArgs a{(const u32x4 *)W, p.xg, M, p.d, 0, nullptr, nullptr, 0, nullptr, 2 * p.F / 16, 0, gu_save};
-  const int n_blocks = p.F / 16, mt = (M + 7) / 8;
-  if (mt == 1)
-    launch_one<EPI_GATEUP_SAVE, 4, 1>(p, a, n_blocks, s);
-  else
-    launch_rows<EPI_GATEUP_SAVE>(p, a, n_blocks, 0, 1, s);
+  const int n_blocks = p.F / 16;
+  if (M <= 8) launch_few<EPI_GATEUP_SAVE>(p, a, n_blocks, few_rows_shape(EPI_GATEUP_SAVE, n_blocks), s);
+  else launch_rows<EPI_GATEUP_SAVE>(p, a, n_blocks, 0, 1, s);
 }
 
 // Plain product Y = X W^T on packed tiles: X as (hi, lo) tiles of K features, W packed [N][K], Y fp32.

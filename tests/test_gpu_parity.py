@@ -396,6 +396,26 @@ def test_row_gemm_shapes(d, ffn, slots, k, blocks):
     g.close()
 
 
+@pytest.mark.parametrize("k", [0, 4, 7])
+@pytest.mark.parametrize("d,heads,ffn,vocab", [
+    (64, 11, 4128, 4144), (96, 22, 8224, 1008), (160, 33, 12320, 4112), (544, 43, 16416, 4112), (4128, 1, 4096, 1008),
+    (512, 2, 7200, 528)])
+def test_few_row_gemm_shapes(d, heads, ffn, vocab, k):
+    """The decode GEMM of calls of up to 8 rows (one, five and eight): every launch shape its rule names, at the smallest count
+    of output blocks it is for (QKV strips 264, 528, 792, 1032; gate/up pairs 256 to 258, 450, 514, 770, 1026; LM head 33, 63,
+    257, 259; residual 4 to 34, and 258), last workgroups with one block or more too few, two to 513 k-tiles (fewer than the wavefronts,
+    trips that end anywhere), and residual products in slices of K, the last one shorter.  Against the oracle."""
+    shape = synth.ModelShape(1, d, heads, 128, ffn, vocab, dtype=synth.BF16)
+    W = synth.make_weights(shape, 9, k, 6.0)
+    m = O.Model(shape, W, k)
+    prompt = np.random.default_rng(d).integers(0, vocab, 5).astype(np.int32)
+    g = _gpu(shape, W, k, max_seq_len=64, page_size=32)
+    st = parity.stepwise_parity(g, m, 0, 2, prompt, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=64)
+    print(st)
+    parity.check_stats(st, 2, parity.ERR_BF16_SMALL)
+    g.close()
+
+
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("d,heads,hd,ffn,vocab,slots,k", [
     (8, 1, 64, 8, 3, 1, 0), (72, 3, 64, 40, 257, 1, 1), (256, 4, 64, 504, 130, 1, 3), (504, 2, 128, 520, 77, 2, 3),
