@@ -303,7 +303,7 @@ int pass_seq_len(pass_ctx *ctx, int slot, int32_t *kv_len, int32_t *n_generated)
  *   "graph"            1 = replay each model call and its epilogue as a captured HIP graph; ignored when the
  *                      context runs on the null stream, which cannot be captured
  *   "path"             0 = auto, 1 = force the generic kernels; before pass_load_weights
- *   "attention"        0 = auto, 1 = never use the matrix-core attention kernel and its transposed V pages;
+ *   "attention"        0 = auto, 1 = never use the matrix-core attention kernel and its tiled K/V pages;
  *                      before pass_load_weights
  *   "lookahead_rows"   look-ahead rows per call from now on, 0 .. k: the drafting call uses the first that many
  *                      look-ahead embeddings; outputs and logits keep their k-sized layout with unused entries

@@ -5,8 +5,8 @@
 // K/V byte is read once for all rows of a group: that is the premise of the method (Section 2.2:
 // a few extra tokens cost about as much as one because decoding is bound by memory traffic).
 //
-// Two split kernels, one merge kernel.  The matrix-core kernel (bf16 cache, head_dim 128, V pages
-// transposed; described at its definition) carries the benchmarked configurations; the
+// Two split kernels, one merge kernel.  The matrix-core kernel (bf16 cache, head_dim 128, tiled
+// pages; described at its definition) carries the benchmarked configurations; the
 // lane-per-key kernel below carries fp32 caches, head_dim 64 and odd page sizes.
 //
 // Grid: (split, head, group).  A group is up to 8 consecutive rows of one slot.  Within the
@@ -205,8 +205,11 @@ __global__ __launch_bounds__(256) void attn_split_kernel(Params p, int layer, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// Matrix-core variant for bf16 caches with head_dim 128 and V stored transposed
-// ([page][head][dim][page_size], page_size a multiple of 32).
+// Matrix-core variant for bf16 caches with head_dim 128 and tiled pages (K [page][head][dim / 8][page_size][8], V
+// [page][head][page_size / 8][dim][8], page_size a multiple of 32): the 16 bytes that a lane takes of a K or V tile lie beside
+// those of its neighbours.  With K as [key][dim] and V as [dim][key] every lane's 16 bytes were in a line of their own, and
+// the address unit, which takes a load four neighbouring lanes at a time, took four times as long (11.6 million cache
+// accesses a launch instead of 5.3 on a batch of eight, 7600 keys).
 //
 // A wavefront owns 32 consecutive keys per step.  Scores: S^T[key][col] = K[key][:] . Q[col][:]
 // with the K rows as the MFMA A operand (two 16-key tiles x four 32-dim blocks) and the queries as
@@ -215,12 +218,18 @@ __global__ __launch_bounds__(256) void attn_split_kernel(Params p, int layer, in
 // The key order inside the two tiles is chosen so that a lane ends up with the scores of 8
 // consecutive keys -- exactly the 8 key slots it feeds, as probabilities (again hi / lo halves by
 // column), into the second MFMA O^T[dim][col] += V^T[dim][key] P[key][col], whose A operand is
-// eight consecutive keys of one dimension: one 16-byte load from the transposed V page.
+// eight consecutive keys of one dimension: one 16-byte load from the V page.
 // Online softmax keeps one running maximum per query row, shared by the lanes of a wavefront.
+// Bound by the chain of a workgroup (three rounds of requests, scores, softmax, products, merge: 6 us alone) at three workgroups a unit.
+// Measured (pages not tiled and the merge one element per thread and turn -> now): 640 keys 7.2 -> 5.9 us, 2100 keys 12.6 ->
+// 10.3, batch of eight 32.4 -> 28.0, 13B at 4300 keys 20.5 -> 18.8.  Several splits per workgroup one after the other
+// take longer (2.4 us each, 31 .. 39 us on the batch).
 // ---------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+template <int I> struct yes_c { static constexpr int value = I; };
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void attn_split_mfma_kernel(Params p, int layer, int R, int direct) {
   constexpr int HD = 128, RQ = kAttnRowsPerGroup;
@@ -257,22 +266,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const uint16_t *kpool = (const uint16_t *)p.k_pool, *vpool = (const uint16_t *)p.v_pool;
 
   u32x4_t kt[2][4], vt[8];
-  // requests the K tiles and V rows of the 32 keys from `at` on (one page holds them: page_size is a
-  // multiple of 32; the lookup is wavefront-uniform)
-  auto request = [&](int at) __attribute__((always_inline)) {
-    const int page = p.block_table[(size_t)slot * p.pages_per_seq + (at >> p.page_shift)];
-    const int poff = at & (p.page_size - 1);
+  const int koff = (g * p.page_size + (ml >> 2) * 8 + (ml & 3)) * 8, voff = (g * HD + ml) * 8;  // this lane's element of a step's first K, V
+  // where the 32 keys from `at` on lie (one page holds them: page_size is a multiple of 32; the lookup is wavefront-uniform)
+  auto page_of = [&](int at) __attribute__((always_inline)) { return p.block_table[(size_t)slot * p.pages_per_seq + (at >> p.page_shift)]; };
+  auto request_k = [&](int at, int page) __attribute__((always_inline)) {
     const size_t hbase = ((size_t)layer * p.n_pages + page) * p.H + head;
-    const uint16_t *kp = kpool + (hbase * p.page_size + poff) * HD;   // K[key][dim]
-    const uint16_t *vp = vpool + hbase * HD * p.page_size + poff;     // Vt[dim][key]
+    const uint16_t *kp = kpool + (hbase * HD * p.page_size + (at & (p.page_size - 1)) * 8);  // K[dim / 8][key][8]
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int key = (ml >> 2) * 8 + t * 4 + (ml & 3);  // key slot ml of tile t
+    for (int t = 0; t < 2; ++t)  // key slot ml of tile t: key (ml / 4) * 8 + t * 4 + ml % 4
 #pragma unroll
-      for (int j = 0; j < 4; ++j) kt[t][j] = *(const u32x4_t *)(kp + (size_t)key * HD + j * 32 + g * 8);
-    }
+      for (int j = 0; j < 4; ++j) kt[t][j] = *(const u32x4_t *)(kp + (j * 4 * p.page_size + t * 4) * 8 + koff);
+  };
+  auto request_v = [&](int at, int page) __attribute__((always_inline)) {
+    const size_t hbase = ((size_t)layer * p.n_pages + page) * p.H + head;
+    const uint16_t *vp = vpool + (hbase * p.page_size + (at & (p.page_size - 1))) * HD;  // V[key / 8][dim][8]
 #pragma unroll
-    for (int db = 0; db < 8; ++db) vt[db] = *(const u32x4_t *)(vp + (size_t)(db * 16 + ml) * p.page_size + g * 8);
+    for (int db = 0; db < 8; ++db) vt[db] = *(const u32x4_t *)(vp + db * 128 + voff);
   };
 
   // query fragment: column ml = hi (ml < 8) or lo (ml >= 8) half of row (ml & 7), scaled by 1/sqrt(hd)
@@ -292,8 +301,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     }
     // the first step's K and V leave before the query rows are waited for (a wavefront without keys
     // in this split asks for the split's first keys, which exist, and skips the loop)
-    request(base < k_hi ? base : k_lo);
-    __builtin_amdgcn_sched_barrier(0);
+    const int at = base < k_hi ? base : k_lo, page = page_of(at);
+    request_k(at, page);
+    request_v(at, page);
+    __builtin_amdgcn_sched_barrier(0);  // all sixteen leave before anything is computed
     const float sc_q = live ? scale : 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -305,13 +316,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   }
 
   f32x4_t o[8];
-#pragma unroll
-  for (int db = 0; db < 8; ++db) o[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
 
-  for (; base < k_hi; base += 128) {
-    // (the step's sixteen requests are in flight: those of the first step since before the loop,
-    // those of a later step since the end of the step before it)
+  // One step of 32 keys, whose sixteen requests are in flight.  Where another step follows, its K leave as soon as the scores
+  // have used this one's, its V after the last product.  The first step starts the accumulators.
+  auto step = [&](auto first, auto more) __attribute__((always_inline)) {
+    constexpr bool kFirst = decltype(first)::value != 0, kMore = decltype(more)::value != 0;
     f32x4_t sc[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -320,6 +330,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       for (int j = 0; j < 4; ++j)
         sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kt[t][j]),
                                                         __builtin_bit_cast(bf16x8_t, qf[j]), sc[t], 0, 0, 0);
+    }
+    int page = 0;
+    if constexpr (kMore) {
+      page = page_of(base + 128);
+      __builtin_amdgcn_sched_barrier(0);
+      request_k(base + 128, page);
+      __builtin_amdgcn_sched_barrier(0);
     }
     // lane (column ml, g) now holds the scores of keys base + 8g + 4t + r; add the lo-half column
     float s[8];
@@ -338,31 +355,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       }
     m_blk = fmaxf(m_blk, __shfl_xor(m_blk, 16));
     m_blk = fmaxf(m_blk, __shfl_xor(m_blk, 32));
-    const float m_new = fmaxf(m_run, m_blk);
-    const float alpha = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
+    const float m_new = kFirst ? m_blk : fmaxf(m_run, m_blk);
+    const float alpha = kFirst || m_run == -INFINITY ? 0.f : __expf(m_run - m_new);
     float pv[8], psum = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       pv[i] = (s[i] == -INFINITY) ? 0.f : __expf(s[i] - m_new);
       psum += pv[i];
     }
-    l_run = l_run * alpha + psum;
+    l_run = kFirst ? psum : l_run * alpha + psum;
     m_run = m_new;
     const u32x4_t pf = {split2_bf16(pv[0], pv[1], ml < 8), split2_bf16(pv[2], pv[3], ml < 8),
                         split2_bf16(pv[4], pv[5], ml < 8), split2_bf16(pv[6], pv[7], ml < 8)};
 #pragma unroll
-    for (int db = 0; db < 8; ++db) {
-      o[db] *= alpha;
-      o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vt[db]),
-                                                      __builtin_bit_cast(bf16x8_t, pf), o[db], 0, 0, 0);
-    }
-    if (base + 128 < k_hi) {
-      request(base + 128);
-      // all sixteen requests leave before anything is computed: left alone, the instruction
-      // scheduler moves the V requests behind the score MFMAs to save registers, and the step
-      // pays two trips to memory in a row
+    for (int db = 0; db < 8; ++db)
+      o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vt[db]), __builtin_bit_cast(bf16x8_t, pf),
+                                                      kFirst ? f32x4_t{0.f, 0.f, 0.f, 0.f} : o[db] * alpha, 0, 0, 0);
+    if constexpr (kMore) {
       __builtin_amdgcn_sched_barrier(0);
+      request_v(base + 128, page);
+      __builtin_amdgcn_sched_barrier(0);
+      base += 128;
     }
+  };
+  if (base + 128 < k_hi) {
+    step(yes_c<1>{}, yes_c<1>{});
+    while (base + 128 < k_hi) step(yes_c<0>{}, yes_c<1>{});
+    step(yes_c<0>{}, yes_c<0>{});
+  } else if (base < k_hi) {
+    step(yes_c<1>{}, yes_c<0>{});
+  } else {  // no keys of this split for this wavefront
+#pragma unroll
+    for (int db = 0; db < 8; ++db) o[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 
   // a row's sum of probabilities is spread over the four g groups
@@ -381,38 +405,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       for (int r = 0; r < 4; ++r) s_acc[wave][ml][db * 16 + 4 * g + r] = o[db][r];
   }
   __syncthreads();
-  const size_t pbase = ((size_t)m0 * p.H + head) * kMaxSplits;
-  for (int e = threadIdx.x; e < nr * HD; e += 256) {
-    int r = e / HD, dim = e % HD;
-    float m_n = fmaxf(fmaxf(s_m[0][r], s_m[1][r]), fmaxf(s_m[2][r], s_m[3][r]));
-    float l_n = 0.f, v = 0.f;
+  // the four wavefronts' triples: four dimensions of a row per thread, everything read at once
+  static_assert(RQ * HD == 256 * 4, "one turn");
+  const int r = threadIdx.x >> 5, dim = (threadIdx.x & 31) * 4;
+  float mw[4], lw[4];
+  f32x4_t aw[4];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      float f = (s_m[w][r] == -INFINITY) ? 0.f : __expf(s_m[w][r] - m_n);
-      l_n += s_l[w][r] * f;
-      v += s_acc[w][r][dim] * f;
-    }
-    if (direct) {
-      store_attn_split(p, m0 + r, head * HD + dim, v / l_n);
-      continue;
-    }
-    size_t pi = pbase + (size_t)r * p.H * kMaxSplits + split;
-    p.part_acc[pi * HD + dim] = v;
-    if (dim == 0) { p.part_m[pi] = m_n; p.part_l[pi] = l_n; }
+  for (int w = 0; w < 4; ++w) {
+    mw[w] = s_m[w][r];
+    lw[w] = s_l[w][r];
+    aw[w] = *(const f32x4_t *)&s_acc[w][r][dim];
   }
+  if (r >= nr) return;
+  const float m_n = fmaxf(fmaxf(mw[0], mw[1]), fmaxf(mw[2], mw[3]));
+  float l_n = 0.f;
+  f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float f = (mw[w] == -INFINITY) ? 0.f : __expf(mw[w] - m_n);
+    l_n += lw[w] * f;
+    v += aw[w] * f;
+  }
+  if (direct) {
+    const float t[4] = {v[0] / l_n, v[1] / l_n, v[2] / l_n, v[3] / l_n};
+    store_split4(p.attn_x, m0 + r, p.D, head * HD + dim, t);
+    return;
+  }
+  const size_t pi = (((size_t)(m0 + r) * p.H + head) * kMaxSplits + split);
+  *(f32x4_t *)(p.part_acc + pi * HD + dim) = v;
+  if (dim == 0) { p.part_m[pi] = m_n; p.part_l[pi] = l_n; }
 }
 
 // Merge the split partials of one (row, head): out = sum_s acc_s e^{m_s - m} / sum_s l_s e^{m_s - m}.
 // A kernel of its own: handing partials between workgroups inside one kernel needs device-scope
 // fences, which on this multi-die part write back and invalidate the per-die L2s and cost far more
 // than a launch.
-// Q = 1: HD threads, one per dimension, walk all splits.  Q = 4 (more than 8 splits): 4 * HD
-// threads, quarter q takes splits 8q .. 8q+7 (one batch of requests each), the quarters' triples
-// are merged through LDS in quarter order.  Both give the same bits for up to 8 splits.
+// Four dimensions per thread, HD / 4 threads per (row, head) and quarter.  Q = 1: they walk all splits; eight (row, head)
+// pairs of 64 dimensions share a workgroup, or four of 128.  Q = 4 (more than 8 splits): quarter q takes splits 8q .. 8q+7 (one
+// batch of requests each), the quarters' triples are merged through LDS in quarter order.  Both give the same bits for up to 8
+// splits.
 template <int HD, int OUT, int Q>
-__global__ __launch_bounds__(HD * Q) void attn_combine_kernel(Params p, int R, int mfma_plan) {
-  __shared__ float sm[Q], sl[Q], sv[Q][HD];
-  const int m = blockIdx.x, head = blockIdx.y, dim = threadIdx.x % HD, q = threadIdx.x / HD;
+__global__ __launch_bounds__(128) void attn_combine_kernel(Params p, int R, int n_pairs, int mfma_plan) {
+  constexpr int T = HD / 4, PAIRS = 128 / (T * Q);  // threads of a quarter; (row, head) pairs of a workgroup
+  __shared__ float sm[PAIRS][Q], sl[PAIRS][Q];
+  __shared__ f32x4_t sv[PAIRS][Q][T];
+  const int pair = threadIdx.x / (T * Q), q = threadIdx.x / T % Q, dim = threadIdx.x % T * 4;
+  const int at = min((int)blockIdx.x * PAIRS + pair, n_pairs - 1), m = at / p.H, head = at - m * p.H;
   // One batch of eight splits per thread, requested before the plan is known so that the lookup of the
   // row's position and the partials share one round trip to memory: slots 0 .. kMaxSplits - 1 of a
   // (row, head) always exist, those beyond the plan hold stale values that are never used.
@@ -423,12 +461,13 @@ __global__ __launch_bounds__(HD * Q) void attn_combine_kernel(Params p, int R, i
   const bool dead = p.row_slot[m] < 0;     // no split kernel ran for this row: its output is zero
   const size_t pi = ((size_t)m * p.H + head) * kMaxSplits;
   const int s_begin = (Q == 1) ? 0 : q * 8;
-  float pm[8], pl[8], pa[8];
+  float pm[8], pl[8];
+  f32x4_t pa[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
     pm[u] = p.part_m[pi + s_begin + u];
     pl[u] = p.part_l[pi + s_begin + u];
-    pa[u] = p.part_acc[(pi + s_begin + u) * HD + dim];
+    pa[u] = *(const f32x4_t *)(p.part_acc + (pi + s_begin + u) * HD + dim);
   }
   // the split plan of the row's group, recomputed exactly as the split kernel did
   const int n_keys = pos0 + min(RQ, R - r0);
@@ -439,7 +478,8 @@ __global__ __launch_bounds__(HD * Q) void attn_combine_kernel(Params p, int R, i
     split_plan(n_keys, n_splits, chunk);
   const int s_end = min(n_splits, s_begin + 8);
   // merged in split order
-  float m_n = -INFINITY, l_n = 0.f, v = 0.f;
+  float m_n = -INFINITY, l_n = 0.f;
+  f32x4_t v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int u = 0; u < 8; ++u)
     if (s_begin + u < s_end) m_n = fmaxf(m_n, pm[u]);
@@ -451,64 +491,64 @@ __global__ __launch_bounds__(HD * Q) void attn_combine_kernel(Params p, int R, i
       v += pa[u] * f;
     }
   if constexpr (Q > 1) {
-    if (dim == 0) { sm[q] = m_n; sl[q] = l_n; }
-    sv[q][dim] = v;
+    if (dim == 0) { sm[pair][q] = m_n; sl[pair][q] = l_n; }
+    sv[pair][q][dim / 4] = v;
     __syncthreads();
     if (q != 0) return;
-    float m_all = sm[0];
+    float m_all = sm[pair][0];
 #pragma unroll
-    for (int i = 1; i < Q; ++i) m_all = fmaxf(m_all, sm[i]);
+    for (int i = 1; i < Q; ++i) m_all = fmaxf(m_all, sm[pair][i]);
     l_n = 0.f;
-    v = 0.f;
+    v = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const float f = (sm[i] == -INFINITY) ? 0.f : __expf(sm[i] - m_all);
-      l_n += sl[i] * f;
-      v += sv[i][dim] * f;
+      const float f = (sm[pair][i] == -INFINITY) ? 0.f : __expf(sm[pair][i] - m_all);
+      l_n += sl[pair][i] * f;
+      v += sv[pair][i][dim / 4] * f;
     }
     m_n = m_all;
   }
+  if ((int)blockIdx.x * PAIRS + pair >= n_pairs) return;
   if (p.lse != nullptr && dim == 0) p.lse[(size_t)m * p.H + head] = dead ? 0.f : m_n + logf(l_n);
-  float o = dead ? 0.f : v / l_n;
-  if (OUT == 1) {
-    // (hi, lo) pair in the tiled activation layout of the matrix-core GEMMs
-    uint16_t hi = f32_to_bf16(o);
-    size_t xi = xs_index(m, p.D, head * HD + dim);
-    p.attn_x[xi] = hi;
-    p.attn_x[xi + kXsLoOffset] = f32_to_bf16(o - bf16_to_f32(hi));
-  } else {
-    p.attn[(size_t)m * p.D + head * HD + dim] = o;
-  }
+  float o[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = dead ? 0.f : v[e] / l_n;
+  if (OUT == 1)  // (hi, lo) pairs in the tiled activation layout of the matrix-core GEMMs
+    store_split4(p.attn_x, m, p.D, head * HD + dim, o);
+  else
+    *(f32x4_t *)(p.attn + (size_t)m * p.D + head * HD + dim) = f32x4_t{o[0], o[1], o[2], o[3]};
 }
 
 template <int I> struct hd_c { static constexpr int value = I; };
 
 template <int HD>
-static void launch_combine(const Params &p, dim3 cgrid, int R, int n_splits, int out_split, int mfma_plan,
+static void launch_combine(const Params &p, int n_pairs, int R, int n_splits, int out_split, int mfma_plan,
                            hipStream_t s) {
   if (n_splits > 8) {
+    const int grid = (n_pairs * HD + 127) / 128;
     if (out_split)
-      attn_combine_kernel<HD, 1, 4><<<cgrid, HD * 4, 0, s>>>(p, R, mfma_plan);
+      attn_combine_kernel<HD, 1, 4><<<grid, 128, 0, s>>>(p, R, n_pairs, mfma_plan);
     else
-      attn_combine_kernel<HD, 0, 4><<<cgrid, HD * 4, 0, s>>>(p, R, mfma_plan);
+      attn_combine_kernel<HD, 0, 4><<<grid, 128, 0, s>>>(p, R, n_pairs, mfma_plan);
   } else {
+    const int grid = (n_pairs * HD / 4 + 127) / 128;
     if (out_split)
-      attn_combine_kernel<HD, 1, 1><<<cgrid, HD, 0, s>>>(p, R, mfma_plan);
+      attn_combine_kernel<HD, 1, 1><<<grid, 128, 0, s>>>(p, R, n_pairs, mfma_plan);
     else
-      attn_combine_kernel<HD, 0, 1><<<cgrid, HD, 0, s>>>(p, R, mfma_plan);
+      attn_combine_kernel<HD, 0, 1><<<grid, 128, 0, s>>>(p, R, n_pairs, mfma_plan);
   }
 }
 
 void launch_attention(const Params &p, int dtype, int layer, int B, int R, int n_splits, int out_split,
                       hipStream_t s) {
   int groups = B * ((R + kAttnRowsPerGroup - 1) / kAttnRowsPerGroup);
-  dim3 grid(n_splits, p.H, groups), cgrid(B * R, p.H);
+  dim3 grid(n_splits, p.H, groups);
   // one split whatever the group: the split kernel finishes the rows (training also wants their ln-sum-exp: the merge kernel)
   const int direct = n_splits == 1 && p.lse == nullptr ? 1 + out_split : 0;
   auto merge = [&](auto HD, int mfma_plan) {
-    if (!direct) launch_combine<decltype(HD)::value>(p, cgrid, R, n_splits, out_split, mfma_plan, s);
+    if (!direct) launch_combine<decltype(HD)::value>(p, B * R * p.H, R, n_splits, out_split, mfma_plan, s);
   };
-  if (p.v_transposed) {  // bf16, head_dim 128, page_size % 32 == 0: matrix-core kernel (its rows leave as (hi, lo) tiles)
+  if (p.kv_tiled) {  // bf16, head_dim 128, page_size % 32 == 0: matrix-core kernel (its rows leave as (hi, lo) tiles)
     attn_split_mfma_kernel<<<grid, 256, 0, s>>>(p, layer, R, direct);
     merge(hd_c<128>{}, 1);
     return;

@@ -312,14 +312,19 @@ __device__ __forceinline__ void gemm_finish(const Params &p, const GemmArgs &a, 
         } else if (p.row_slot[m] >= 0) {  // a dead row (see row_is_dead) has no place in the cache
           // the cache is bf16 storage: the one place besides the weights where values are rounded
           uint16_t *pool = (uint16_t *)(which == 1 ? p.k_pool : p.v_pool);
-          if (which == 2 && p.v_transposed) {
-            // V page for the matrix-core attention: [head][dim][page_size]
-            int pos = p.row_pos[m];
-            int page = p.block_table[(size_t)p.row_slot[m] * p.pages_per_seq + (pos >> p.page_shift)];
-            size_t base = ((((size_t)a.layer * p.n_pages + page) * p.H + head) * p.hd + dim) * p.page_size +
-                          (pos & (p.page_size - 1));
+          if (p.kv_tiled) {
+            const int pos = p.row_pos[m], off = pos & (p.page_size - 1);
+            const int page = p.block_table[(size_t)p.row_slot[m] * p.pages_per_seq + (pos >> p.page_shift)];
+            pool += (((size_t)a.layer * p.n_pages + page) * p.H + head) * p.page_size * p.hd;
+            if (which == 1) {
+              uint2 pk;
+              pk.x = pack2_bf16(v[0], v[1]);
+              pk.y = pack2_bf16(v[2], v[3]);
+              *(uint2 *)(pool + k_tile(p, off, dim)) = pk;
+            } else {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) pool[base + (size_t)r * p.page_size] = f32_to_bf16(v[r]);
+              for (int r = 0; r < 4; ++r) pool[v_tile(p, off, dim + r)] = f32_to_bf16(v[r]);
+            }
           } else {
             size_t off = kv_offset(p, a.layer, p.row_slot[m], p.row_pos[m], head) + dim;
             uint2 pk;

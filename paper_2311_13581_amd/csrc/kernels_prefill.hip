@@ -70,7 +70,7 @@ __device__ __forceinline__ void finish_qkv(const Params &p, const PrefillWs &w, 
     *(floatx4 *)(w.q + (size_t)m * p.D + c) = v;
     return;
   }
-  // K rows [page][head][pos][dim], V pages transposed [page][head][dim][pos]; bf16 storage
+  // pages tiled (k_tile, v_tile); bf16 storage
   // (the rows of a 16-row group share a block: the index is uniform over the wavefront)
   const int sb = __builtin_amdgcn_readfirstlane(m / kPrefillBlockRows), sr = m % kPrefillBlockRows;
   if (sr >= a.segs.rows[sb]) return;  // a padding row: nothing to cache
@@ -82,11 +82,11 @@ __device__ __forceinline__ void finish_qkv(const Params &p, const PrefillWs &w, 
     uint2 pk;
     pk.x = pack2_bf16(v[0], v[1]);
     pk.y = pack2_bf16(v[2], v[3]);
-    *(uint2 *)((uint16_t *)p.k_pool + (hbase * p.page_size + off) * p.hd + dim) = pk;
+    *(uint2 *)((uint16_t *)p.k_pool + hbase * p.page_size * p.hd + k_tile(p, off, dim)) = pk;
   } else {
-    uint16_t *vp = (uint16_t *)p.v_pool + (hbase * p.hd + dim) * p.page_size + off;
+    uint16_t *vp = (uint16_t *)p.v_pool + hbase * p.page_size * p.hd + v_tile(p, off, dim);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) vp[(size_t)r * p.page_size] = f32_to_bf16(v[r]);
+    for (int r = 0; r < 4; ++r) vp[8 * r] = f32_to_bf16(v[r]);
   }
 }
 // residual add, (hi, lo) of h * gain of the next norm; returns the four features' share of sum h^2
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // Adds the slices of a product that was split along K (in slice order) and finishes it as the fused epilogues do.
 // One workgroup: 16 rows x 64 features (a gate strip, its up strip, twice); thread = (row, four features), so that
-// the (hi, lo) tiles and the transposed V pages are written as whole runs of rows.
+// the (hi, lo) tiles and the cache's pages are written as whole runs of rows.
 template <int EPI>
 __global__ __launch_bounds__(256) void tile_reduce_kernel(Params p, PrefillWs w, TileArgs a) {
   __shared__ float s_part[16][17];
@@ -465,11 +465,11 @@ int launch_tile(const Params &p, const PrefillWs &w, TileArgs a, hipStream_t s) 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Causal attention of RG * 16 consecutive prompt rows of one head (bf16 cache, head_dim 128, V pages
-// transposed).  Scores S^T[key][row] = K[key][:] . Q[row][:] with K rows as the MFMA A operand (key
+// Causal attention of RG * 16 consecutive prompt rows of one head (bf16 cache, head_dim 128, pages
+// tiled).  Scores S^T[key][row] = K[key][:] . Q[row][:] with K rows as the MFMA A operand (key
 // order inside the two 16-key tiles chosen so that a lane ends up with 8 consecutive keys) and 16
 // query rows as the columns of the B operand; the probabilities of 8 consecutive keys feed
-// O^T[dim][row] += V^T[dim][key] P[key][row] with one 16-byte load of the transposed V page as A
+// O^T[dim][row] += V^T[dim][key] P[key][row] with one 16-byte load of the tiled V page as A
 // operand.  Queries and probabilities keep fp32-like precision as (hi, lo) bf16 pairs; unlike the
 // decode kernel, which puts the two halves of 8 rows side by side in the 16 columns, the halves go
 // into separate MFMAs here: S = K q_hi + K q_lo accumulate into one score tile, the softmax runs
@@ -539,17 +539,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int page = p.block_table[(size_t)slot * p.pages_per_seq + (base >> p.page_shift)];
     const int poff = base & (p.page_size - 1);
     const size_t hbase = ((size_t)layer * p.n_pages + page) * p.H + head;
-    const uint16_t *kp = kpool + (hbase * p.page_size + poff) * HD;   // K[key][dim]
-    const uint16_t *vp = vpool + hbase * HD * p.page_size + poff;     // Vt[dim][key]
+    const uint16_t *kp = kpool + (hbase * HD * p.page_size + poff * 8);    // K[dim / 8][key][8]
+    const uint16_t *vp = vpool + (hbase * p.page_size + poff) * HD;        // V[key / 8][dim][8]
     u32x4 kt[2][4], vt[8];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int key = (ml >> 2) * 8 + t * 4 + (ml & 3);  // key slot ml of tile t
 #pragma unroll
-      for (int j = 0; j < 4; ++j) kt[t][j] = *(const u32x4 *)(kp + (size_t)key * HD + j * 32 + g * 8);
+      for (int j = 0; j < 4; ++j) kt[t][j] = *(const u32x4 *)(kp + ((j * 4 + g) * p.page_size + key) * 8);
     }
 #pragma unroll
-    for (int db = 0; db < 8; ++db) vt[db] = *(const u32x4 *)(vp + (size_t)(db * 16 + ml) * p.page_size + g * 8);
+    for (int db = 0; db < 8; ++db) vt[db] = *(const u32x4 *)(vp + (g * HD + db * 16 + ml) * 8);
     __builtin_amdgcn_sched_barrier(0);  // all sixteen requests leave before anything is computed
 
 #pragma unroll
@@ -710,16 +710,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int page = p.block_table[(size_t)slot * p.pages_per_seq + (base >> p.page_shift)];
     const int poff = base & (p.page_size - 1);
     const size_t hbase = ((size_t)layer * p.n_pages + page) * p.H + head;
-    const uint16_t *kp = kpool + (hbase * p.page_size + poff) * HD;   // K[key][dim]
-    const uint16_t *vp = vpool + hbase * HD * p.page_size + poff;     // Vt[dim][key]
+    const uint16_t *kp = kpool + (hbase * HD * p.page_size + poff * 8);    // K[dim / 8][key][8]
+    const uint16_t *vp = vpool + (hbase * p.page_size + poff) * HD;        // V[key / 8][dim][8]
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int f = wave * 2 + i, key = (ml >> 2) * 8 + (f >> 2) * 4 + (ml & 3);  // key slot ml of half f >> 2
-      copy_to_lds(kp + (size_t)key * HD + (f & 3) * 32 + g * 8, &dK[f][0]);
+      copy_to_lds(kp + (((f & 3) * 4 + g) * p.page_size + key) * 8, &dK[f][0]);
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      copy_to_lds(vp + (size_t)((wave * 2 + i) * 16 + ml) * p.page_size + g * 8, &dV[wave * 2 + i][0]);
+      copy_to_lds(vp + (g * HD + (wave * 2 + i) * 16 + ml) * 8, &dV[wave * 2 + i][0]);
   };
   issue(sK0, sV0, 0);
 

@@ -504,29 +504,29 @@ __global__ __launch_bounds__(256) void attn_bwd_split_kernel(Params p, int layer
   for (int r = 0; r < RMAX; ++r) dq[r] = 0.f;
 
   // The next tile's K and V travel from memory into registers while the tile in hand is worked on; a thread
-  // carries NCH chunks of eight values of each.  K: chunk = (key, eight dimensions).  V: the same when its pages
-  // hold [position][dim]; when they hold [dim][position] (matrix-core attention), chunk = (dimension, eight
-  // consecutive keys: a tile starts at a multiple of 32 keys and a page holds a multiple of 32, so they share a page).
+  // carries NCH chunks of eight values of each: (key, eight dimensions), of V, where the cache is tiled (matrix-core
+  // attention), (dimension, eight consecutive keys: a tile starts at a multiple of 32 keys and a page holds a multiple
+  // of 32, so they share a page).  Neighbouring threads take neighbouring chunks of a page.
   constexpr int NCH = TK * HD / 8 / 256;
   Raw8<T> kraw[NCH], vraw[NCH];
   auto fetch = [&](int t0) {
 #pragma unroll
     for (int u = 0; u < NCH; ++u) {
       const int c = u * 256 + tid;
-      {
+      if (!p.kv_tiled) {
         const int key = c / (HD / 8), d0 = (c % (HD / 8)) * 8, j = t0 + key;
         const bool in = j < k_hi;
         const size_t off =
             in ? ((((size_t)layer * p.n_pages + pages_s[(j >> p.page_shift) - page_lo]) * p.H + head) * p.page_size + (j & (p.page_size - 1))) * HD + d0 : 0;
         kraw[u].load(kpool, off, in);
-        if (!p.v_transposed) vraw[u].load(vpool, off, in);
-      }
-      if (p.v_transposed) {
-        const int dv = c / (TK / 8), j0 = t0 + (c % (TK / 8)) * 8;
-        const bool in = j0 < k_hi;
-        const size_t off =
-            in ? ((((size_t)layer * p.n_pages + pages_s[(j0 >> p.page_shift) - page_lo]) * p.H + head) * HD + dv) * p.page_size + (j0 & (p.page_size - 1)) : 0;
         vraw[u].load(vpool, off, in);
+      } else {
+        const int j = t0 + c % TK, d0 = c / TK * 8, j0 = t0 + c / HD * 8, dv = c % HD;
+        auto at = [&](int pos) __attribute__((always_inline)) {
+          return (((size_t)layer * p.n_pages + pages_s[(pos >> p.page_shift) - page_lo]) * p.H + head) * p.page_size * HD;
+        };
+        kraw[u].load(kpool, j < k_hi ? at(j) + k_tile(p, j & (p.page_size - 1), d0) : 0, j < k_hi);
+        vraw[u].load(vpool, j0 < k_hi ? at(j0) + v_tile(p, j0 & (p.page_size - 1), dv) : 0, j0 < k_hi);
       }
     }
   };
@@ -537,14 +537,14 @@ __global__ __launch_bounds__(256) void attn_bwd_split_kernel(Params p, int layer
       float kv[8], vv[8];
       kraw[u].get(kv);
       vraw[u].get(vv);
-      const int key = c / (HD / 8), d0 = (c % (HD / 8)) * 8;
+      const int key = p.kv_tiled ? c % TK : c / (HD / 8), d0 = (p.kv_tiled ? c / TK : c % (HD / 8)) * 8;
       *(float4 *)&tiles[0][key][d0] = make_float4(kv[0], kv[1], kv[2], kv[3]);
       *(float4 *)&tiles[0][key][d0 + 4] = make_float4(kv[4], kv[5], kv[6], kv[7]);
-      if (!p.v_transposed) {
+      if (!p.kv_tiled) {
         *(float4 *)&tiles[1][key][d0] = make_float4(vv[0], vv[1], vv[2], vv[3]);
         *(float4 *)&tiles[1][key][d0 + 4] = make_float4(vv[4], vv[5], vv[6], vv[7]);
       } else {
-        const int dv = c / (TK / 8), key0 = (c % (TK / 8)) * 8;
+        const int dv = c % HD, key0 = c / HD * 8;
 #pragma unroll
         for (int e = 0; e < 8; ++e) tiles[1][key0 + e][dv] = (t0 + key0 + e < k_hi) ? vv[e] : 0.f;  // unwritten positions hold anything
       }
@@ -731,20 +731,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
     for (int u = 0; u < NCH; ++u) {
       const int ch = u * 256 + tid;
-      {
+      if (!p.kv_tiled) {
         const int key = ch / (HD / 8), d0 = (ch % (HD / 8)) * 8, j = t0 + key;
         const bool in = j < k_hi;
         const size_t off =
             in ? ((((size_t)layer * p.n_pages + pages_s[(j >> p.page_shift) - page_lo]) * p.H + head) * p.page_size + (j & (p.page_size - 1))) * HD + d0 : 0;
         kraw[u].load(kpool, off, in);
-        if (!p.v_transposed) vraw[u].load(vpool, off, in);
-      }
-      if (p.v_transposed) {
-        const int dv = ch / (TK / 8), j0 = t0 + (ch % (TK / 8)) * 8;
-        const bool in = j0 < k_hi;
-        const size_t off =
-            in ? ((((size_t)layer * p.n_pages + pages_s[(j0 >> p.page_shift) - page_lo]) * p.H + head) * HD + dv) * p.page_size + (j0 & (p.page_size - 1)) : 0;
         vraw[u].load(vpool, off, in);
+      } else {
+        const int j = t0 + ch % TK, d0 = ch / TK * 8, j0 = t0 + ch / HD * 8, dv = ch % HD;
+        auto at = [&](int pos) __attribute__((always_inline)) {
+          return (((size_t)layer * p.n_pages + pages_s[(pos >> p.page_shift) - page_lo]) * p.H + head) * p.page_size * HD;
+        };
+        kraw[u].load(kpool, j < k_hi ? at(j) + k_tile(p, j & (p.page_size - 1), d0) : 0, j < k_hi);
+        vraw[u].load(vpool, j0 < k_hi ? at(j0) + v_tile(p, j0 & (p.page_size - 1), dv) : 0, j0 < k_hi);
       }
     }
   };
@@ -752,12 +752,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
     for (int u = 0; u < NCH; ++u) {
       const int ch = u * 256 + tid;
-      const int key = ch / (HD / 8), d0 = (ch % (HD / 8)) * 8;
+      const int key = p.kv_tiled ? ch % TK : ch / (HD / 8), d0 = (p.kv_tiled ? ch / TK : ch % (HD / 8)) * 8;
       *(uint4 *)&kv_s[0][key][d0] = kraw[u].a;
-      if (!p.v_transposed) {
+      if (!p.kv_tiled) {
         *(uint4 *)&kv_s[1][key][d0] = vraw[u].a;
       } else {
-        const int dv = ch / (TK / 8), key0 = (ch % (TK / 8)) * 8;
+        const int dv = ch % HD, key0 = ch / HD * 8;
         const uint32_t w[4] = {vraw[u].a.x, vraw[u].a.y, vraw[u].a.z, vraw[u].a.w};
 #pragma unroll
         for (int e = 0; e < 8; ++e)  // unwritten positions hold anything

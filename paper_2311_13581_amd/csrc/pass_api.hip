@@ -234,7 +234,7 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   W.rows = std::min(kPrefillRows, (c.max_seq_len + 127) / 128 * 128);
   W.np = (int)(d / 16);  // most partial sums of h^2 a row can have (one per strip)
   const size_t R = W.rows;
-  // sums over slices of K of the tiled pass's GEMMs (models that can take it only: matrix-core path with transposed V pages):
+  // sums over slices of K of the tiled pass's GEMMs (models that can take it only: matrix-core path with a tiled cache):
   // eight slices of the widest product, but no more than 50 MB, which is what three slices of the widest product of a 7B model
   // take at 190 rows, six of Wo at 511
   const bool tiled = c.dtype == PASS_BF16 && c.head_dim == 128 && c.page_size % 32 == 0 && d % 32 == 0 && F % 32 == 0 && V % 16 == 0;
@@ -351,7 +351,7 @@ int choose_splits(const pass_ctx *c, int B, int R, int max_keys) {
   // grid width only: each row group cuts its own keys by a rule of its own length (split_plan in
   // the attention kernel); workgroups beyond a group's split count exit at once
   (void)B; (void)R;
-  if (c->P.v_transposed)  // the most splits any group of at most max_keys keys can have (the plan is not monotone)
+  if (c->P.kv_tiled)  // the most splits any group of at most max_keys keys can have (the plan is not monotone)
     return max_splits_mfma(std::max(1, max_keys), c->P.H);
   return std::max(1, std::min(kMaxSplits, (max_keys + 63) / 64));
 }
@@ -736,8 +736,8 @@ int pass_load_weights(pass_ctx *c, const pass_weights *w, int on_device) {
   int rc = PASS_OK;
   c->use_mfma = c->opt_path != 1 && c->cfg.dtype == PASS_BF16 && d % 32 == 0 && D % 32 == 0 && F % 32 == 0 &&
                 V % 16 == 0;
-  // matrix-core attention: transposed V pages (nothing is cached yet, so the layout can still be chosen)
-  c->P.v_transposed = c->use_mfma && c->opt_attn != 1 && c->cfg.head_dim == 128 && c->cfg.page_size % 32 == 0;
+  // matrix-core attention: tiled pages (nothing is cached yet, so the layout can still be chosen)
+  c->P.kv_tiled = c->use_mfma && c->opt_attn != 1 && c->cfg.head_dim == 128 && c->cfg.page_size % 32 == 0;
   if (c->use_mfma) {
     // matrices go through the tile packer; on_device = 0 stages each tensor in the arena first
     auto pack = [&](void *dst, const void *src, size_t N, size_t K, int strip_off, int strip_stride) -> int {
@@ -841,7 +841,7 @@ int pass_prefill(pass_ctx *c, int slot, uint32_t seq_id, const int32_t *prompt, 
     HIP_TRY(c, hipMemcpyAsync(c->prompt_buf, prompt, sizeof(int32_t) * (n - 1), hipMemcpyHostToDevice, c->stream));
     // longer prompts on the matrix-core path: tiled kernels, up to pws.rows rows per pass over the
     // weights; otherwise the decode kernels, prefill_chunk rows per pass
-    const bool tiled = c->use_mfma && c->P.v_transposed &&
+    const bool tiled = c->use_mfma && c->P.kv_tiled &&
                        (c->opt_prefill_tiled == 1 || (c->opt_prefill_tiled < 0 && n - 1 > kTiledMinRows));
     const int chunk = tiled ? c->pws.rows : c->opt_prefill_chunk;
     for (int done = 0; done < n - 1; done += chunk) {
@@ -876,9 +876,9 @@ int pass_prefill_batch(pass_ctx *c, const int32_t *slots, const uint32_t *seq_id
     total += lens[b] - 1;
   }
   // the tiled kernels take rows of several sequences through one pass over the weights; where they do not
-  // apply (generic path, untransposed V pages, switched off, or too few rows to pay for it) the
+  // apply (generic path, no tiled cache, switched off, or too few rows to pay for it) the
   // prompts go one by one
-  const bool tiled = c->use_mfma && c->P.v_transposed &&
+  const bool tiled = c->use_mfma && c->P.kv_tiled &&
                      (c->opt_prefill_tiled == 1 ||
                       (c->opt_prefill_tiled < 0 && batch_takes_tiles(c->P, lens, n_slots, c->opt_prefill_chunk, c->pws.rows)));
   int rc;

@@ -77,7 +77,8 @@ struct Params {
   int la_token;  // < 0: drafting rows are the look-ahead embeddings; >= 0: this token's embedding, k_act times
   int max_slots, max_seq_len, page_size, page_shift, n_pages, pages_per_seq;
   int gen_cap;
-  int v_transposed;  // V pages hold [head][dim][page_size] (matrix-core attention) instead of [head][page_size][dim]
+  int kv_tiled;  // pages hold K as [head][hd / 8][page_size][8] and V as [head][page_size / 8][hd][8] (matrix-core attention: sixteen
+                 //   lanes that read neighbouring keys, or dimensions, read whole lines) instead of [head][page_size][hd]
   float eps, rope_base;
   // per-slot state (device), indexed by slot
   int32_t *kv_len, *pending, *first, *drafts /*[slot][kMaxK]*/, *n_gen, *n_acc, *frozen, *gen_limit;
@@ -124,6 +125,10 @@ __device__ __forceinline__ size_t kv_offset(const Params &p, int layer, int slot
   int off = pos & (p.page_size - 1);
   return ((((size_t)layer * p.n_pages + page) * p.H + head) * p.page_size + off) * (size_t)p.hd;
 }
+
+// Element of a (page, head)'s K or V where the cache is tiled: position `off` of the page, dimension `dim`
+__device__ __forceinline__ size_t k_tile(const Params &p, int off, int dim) { return ((size_t)(dim >> 3) * p.page_size + off) * 8 + (dim & 7); }
+__device__ __forceinline__ size_t v_tile(const Params &p, int off, int dim) { return ((size_t)(off >> 3) * p.hd + dim) * 8 + (off & 7); }
 
 // A slot whose rows would lie beyond max_seq_len is dead for this call: pass_generate keeps a slot
 // that has reached its token target stepping with the batch (its state is frozen, its outputs are
@@ -215,7 +220,7 @@ __device__ __forceinline__ void store_split4(uint16_t *xs, int m, int K, int k, 
   *(uint2 *)(hp + kXsLoOffset) = pl;
 }
 
-// Tiled prompt pass (bf16 models on the matrix-core path with transposed V pages): up to `rows`
+// Tiled prompt pass (bf16 models on the matrix-core path with a tiled cache): up to `rows`
 // prompt rows per pass over the weights.  The kernels take a Params copy whose h, xg, ssq,
 // rope_cos, rope_sin, attn_x and act_x point at buffers of that many rows; the rest is here.
 struct PrefillWs {

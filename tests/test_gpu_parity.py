@@ -438,6 +438,24 @@ def test_generic_row_gemm_shapes(d, heads, hd, ffn, vocab, slots, k, dtype):
     g.close()
 
 
+@pytest.mark.parametrize("attn_rows", [16, 32, 128])
+@pytest.mark.parametrize("page", [32, 128, 256])
+def test_pages_of_the_tiled_cache(page, attn_rows):
+    """K and V pages as the matrix-core attention stores them, for page sizes other than the 64 of most tests: filled by the
+    tiled prompt pass and read by each of its attention kernels, then filled and read by calls of 1 + 9 rows (two row groups),
+    across page ends.  Against the oracle."""
+    shape = synth.ModelShape(1, 256, 2, 128, 352, 512, dtype=synth.BF16)
+    k = 9
+    W = synth.make_weights(shape, 14, k, 6.0)
+    m = O.Model(shape, W, k)
+    prompt = np.random.default_rng(page).integers(0, shape.vocab, 253).astype(np.int32)
+    g = _gpu(shape, W, k, max_seq_len=512, page_size=page, options={"prefill_tiled": 1, "tune.prefill_tile": attn_rows})
+    st = parity.stepwise_parity(g, m, 0, 2, prompt, 4, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=512)
+    print(st)
+    parity.check_stats(st, 4, parity.ERR_BF16_SMALL)
+    g.close()
+
+
 @pytest.mark.parametrize("path,plen", [(0, 118), (0, 123), (0, 130), (1, 52), (1, 57), (1, 66)])
 def test_attention_with_one_split(path, plen):
     """Around the key count at which a group's keys no longer fit one split (128 on the matrix-core path, 64 on the generic
