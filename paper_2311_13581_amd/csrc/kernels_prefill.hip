@@ -34,6 +34,14 @@ __device__ __forceinline__ float dpp_mov(float v) {
 // value of the lane 8 columns further in the same row of 16 (row_ror 8): lo half <-> hi half
 __device__ __forceinline__ float other_half(float v) { return dpp_mov<0x128>(v); }
 
+// sum over the sixteen lanes of a row, in each of them
+__device__ __forceinline__ float row_total(float v) {
+  v += dpp_mov<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_mov<0x141>(v);  // row_half_mirror
+  return v + dpp_mov<0x140>(v);  // row_mirror
+}
+
 template <int I> struct ic { static constexpr int value = I; };
 
 enum { TILE_QKV = 0, TILE_RESID = 1, TILE_GATEUP = 2, TILE_PART = 3 };
@@ -345,55 +353,52 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-// Adds the slices of a product that was split along K (in slice order) and finishes it as the fused epilogues do.
-// One workgroup: 16 rows x 64 features (a gate strip, its up strip, twice); thread = (row, four features), so that
-// the (hi, lo) tiles and the cache's pages are written as whole runs of rows.
-template <int EPI>
+// Adds the SL slices of a product that was split along K (in slice order) and finishes it as the fused epilogues do.
+// One workgroup: 16 rows x 64 features (a gate strip, its up strip, twice); thread = (row, four features), sixteen
+// neighbouring threads of a row, so that a slice is read in runs of 256 bytes (sixteen rows side by side, 16 bytes of
+// each, kept the address unit busy four times as long).  What belongs to a row is summed across its sixteen lanes.
+// Bound by the slices' bytes and, for the small ones, by the launch and two trips to memory.  Measured (7B, before ->
+// now): 100 rows gate/up, two slices, 12.5 -> 7.4 us, QKV, four, 9.2 -> 7.4; 511 rows Wo and down, four, 14.0 -> 11.0; 836 rows, two, 20.6 -> 13.8.
+template <int EPI, int SL>
 __global__ __launch_bounds__(256) void tile_reduce_kernel(Params p, PrefillWs w, TileArgs a) {
-  __shared__ float s_part[16][17];
-  const int r = threadIdx.x & 15, qd = threadIdx.x >> 4;
-  const int m = blockIdx.y * 16 + r, n = blockIdx.x * 64 + qd * 4, N = a.n_strips * 16;
+  const int qd = threadIdx.x & 15, m = blockIdx.y * 16 + (threadIdx.x >> 4), n = blockIdx.x * 64 + qd * 4, N = a.n_strips * 16;
   const bool live = m < a.M && n < N;
-  const size_t stride = (size_t)a.M * N, at = (size_t)min(m, a.M - 1) * N + min(n, N - 4);
-  constexpr int MAXS = 8;
-  floatx4 v[MAXS];
+  const int mc = min(m, a.M - 1);
+  const size_t stride = (size_t)a.M * N, at = (size_t)mc * N + min(n, N - 4);
+  floatx4 v[SL];
 #pragma unroll
-  for (int i = 0; i < MAXS; ++i)  // all slices requested at once (index clamped, surplus dropped)
-    v[i] = *(const floatx4 *)(a.part + min(i, a.slices - 1) * stride + at);
+  for (int i = 0; i < SL; ++i) v[i] = *(const floatx4 *)(a.part + i * stride + at);
   float inv = 1.f;
   if constexpr (EPI != TILE_RESID) {
+    // the partial sums lie row beside row: thread (group, row) here
+    __shared__ float s_part[16][17];
+    const int r = min((int)blockIdx.y * 16 + qd, a.M - 1);
     float ss = 0.f;
-    if (m < a.M)
-      for (int i = qd; i < w.np; i += 16) ss += p.ssq[(size_t)i * w.rows + m];
-    s_part[qd][r] = ss;
-    __syncthreads();
-    float tot = 0.f;
+    for (int i0 = threadIdx.x >> 4; i0 < w.np; i0 += 64) {  // four requests at a time (indices past the end repeat the last partial, dropped)
+      float t[4];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) tot += s_part[j][r];
-    inv = 1.0f / sqrtf(tot / (float)p.d + p.eps);
+      for (int u = 0; u < 4; ++u) t[u] = p.ssq[(size_t)min(i0 + 16 * u, w.np - 1) * w.rows + r];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) ss += i0 + 16 * u < w.np ? t[u] : 0.f;
+    }
+    s_part[threadIdx.x >> 4][qd] = ss;
+    __syncthreads();
+    inv = 1.0f / sqrtf(row_total(s_part[qd][threadIdx.x >> 4]) / (float)p.d + p.eps);
   }
   floatx4 y = v[0];
 #pragma unroll
-  for (int i = 1; i < MAXS; ++i)
-    if (i < a.slices) y += v[i];
+  for (int i = 1; i < SL; ++i) y += v[i];
   if constexpr (EPI == TILE_QKV) {
     if (live) finish_qkv(p, w, a, m, n, y * inv);
   } else if constexpr (EPI == TILE_GATEUP) {
-    // quads 0..3 gate, 4..7 up of one strip pair, 8..11 gate, 12..15 up of the next: the up quad is four quads on
-    __shared__ floatx4 s_up[8][16];
-    if (qd & 4) s_up[(qd >> 3) * 4 + (qd & 3)][r] = y;
-    __syncthreads();
-    if (!(qd & 4) && live) finish_gateup(p, m, (n >> 5) * 16 + (n & 15), y, s_up[(qd >> 3) * 4 + (qd & 3)][r], inv);
-  } else {
-    float ss = live ? finish_resid(p, a.gain_next, m, n, y) : 0.f;
-    s_part[qd][r] = ss;
-    __syncthreads();
-    if (threadIdx.x < 16 && m < a.M) {
-      float tot = 0.f;
+    // quads 0..3 gate, 4..7 up of one strip pair, 8..11 gate, 12..15 up of the next: the up quad is four lanes on
+    floatx4 up;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) tot += s_part[j][threadIdx.x];
-      p.ssq[(size_t)blockIdx.x * w.rows + m] = tot;
-    }
+    for (int r = 0; r < 4; ++r) up[r] = dpp_mov<0x104>(y[r]);  // row_shl 4
+    if (!(qd & 4) && live) finish_gateup(p, m, (n >> 5) * 16 + (n & 15), y, up, inv);
+  } else {
+    const float ss = row_total(live ? finish_resid(p, a.gain_next, m, n, y) : 0.f);
+    if (qd == 0 && m < a.M) p.ssq[(size_t)blockIdx.x * w.rows + m] = ss;
   }
 }
 
@@ -460,7 +465,16 @@ int launch_tile(const Params &p, const PrefillWs &w, TileArgs a, hipStream_t s) 
     return (a.n_strips + t.strips_per_wave - 1) / t.strips_per_wave;
   }
   go(ic<TILE_PART>{});
-  tile_reduce_kernel<EPI><<<dim3((a.n_strips + 3) / 4, (a.M + 15) / 16), 256, 0, s>>>(p, w, a);
+  auto add = [&](auto SL) { tile_reduce_kernel<EPI, decltype(SL)::value><<<dim3((a.n_strips + 3) / 4, (a.M + 15) / 16), 256, 0, s>>>(p, w, a); };
+  switch (a.slices) {
+    case 2: add(ic<2>{}); break;
+    case 3: add(ic<3>{}); break;
+    case 4: add(ic<4>{}); break;
+    case 5: add(ic<5>{}); break;
+    case 6: add(ic<6>{}); break;
+    case 7: add(ic<7>{}); break;
+    default: add(ic<8>{}); break;
+  }
   return (a.n_strips + 3) / 4;
 }
 
