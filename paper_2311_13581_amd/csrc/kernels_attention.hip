@@ -23,7 +23,7 @@ namespace pass {
 // How a row group's keys are cut into splits.  A function of the group's own key count only, so
 // that a sequence's arithmetic (and therefore its tokens) cannot depend on what else is batched.
 __device__ __forceinline__ void split_plan(int n_keys, int &n_splits, int &chunk) {
-  n_splits = min(kMaxSplits, (n_keys + 63) / 64);
+  n_splits = plain_splits(n_keys);
   chunk = ((n_keys + n_splits - 1) / n_splits + 15) & ~15;
 }
 

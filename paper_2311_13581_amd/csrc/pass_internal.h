@@ -44,6 +44,14 @@ inline int max_splits_mfma(int max_keys, int n_heads) {
   return best;
 }
 
+// Splits of the lane-per-key kernel: 64 keys (one iteration of a workgroup) each, but one up to 192 keys, where the rows leave
+// the split kernel finished: a further iteration costs less than the merge kernel.
+__host__ __device__ inline int plain_splits(int n_keys) {
+  if (n_keys <= 192) return 1;
+  const int n = (n_keys + 63) / 64;
+  return n < kMaxSplits ? n : kMaxSplits;
+}
+
 // bfloat16 storage type: raw bits, converted with shifts (round-to-nearest-even on store)
 struct bf16_t {
   uint16_t bits;

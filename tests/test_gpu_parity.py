@@ -471,6 +471,38 @@ def test_attention_with_one_split(path, plen):
     g.close()
 
 
+@pytest.mark.parametrize("w", [TINY, TINY_BF16, MFMA_HD128], ids=["fp32", "bf16", "hd128"])
+@pytest.mark.parametrize("plen", [125, 180, 186, 193])
+def test_generic_attention_with_one_split_of_several_iterations(w, plen):
+    """The generic path keeps up to 192 keys in one split of three iterations: inside it, across the line while the sequence
+    grows, and above it."""
+    W = synth.make_weights(w.shape, w.seed, w.k, w.lm_head_scale)
+    m = O.Model(w.shape, W, w.k)
+    prompt = np.random.default_rng(plen).integers(0, w.shape.vocab, plen).astype(np.int32)
+    g = _gpu(w.shape, W, w.k, max_seq_len=256, page_size=64, options={"path": 1})
+    st = parity.stepwise_parity(g, m, 0, 2, prompt, 4, 0.9, 777, parity.LOGIT_TOL[w.shape.dtype], max_len=256)
+    parity.check_stats(st, 4, parity.ERR_F32 if w.shape.dtype == synth.F32 else parity.ERR_BF16_SMALL)
+    g.close()
+
+
+@pytest.mark.parametrize("temp,k,slots", [(0.0, 4, 2), (0.0, 15, 1), (0.9, 0, 3), (0.9, 6, 2), (1.0, 15, 2)])
+@pytest.mark.parametrize("vocab", [8, 252, 256, 260, 512, 516, 1020, 1022, 1024, 1028])
+def test_sampling_epilogue_of_small_vocabularies(vocab, temp, k, slots):
+    """Rows of up to 1024 logits are taken by a wavefront each: vocabularies around one, two and four quads per lane, at the
+    line, above it and no multiple of four (a workgroup per row then), one row and sixteen."""
+    shape = synth.ModelShape(1, 128, 2, 64, 96, vocab, dtype=synth.F32)
+    W = synth.make_weights(shape, 14, k, 10.0)
+    m = O.Model(shape, W, k)
+    rng = np.random.default_rng(vocab + k)
+    prompts = [rng.integers(0, vocab, int(n)).astype(np.int32) for n in rng.integers(1, 20, slots)]
+    g = _gpu(shape, W, k, max_slots=slots, max_seq_len=128, page_size=16)
+    ids = list(range(slots))
+    stats = parity.batch_parity(g, m, ids, [3 + i for i in ids], prompts, ids, 4, temp, 777, parity.LOGIT_TOL[synth.F32], max_len=128)
+    for sl in ids:
+        parity.check_stats(stats[sl], 4, parity.ERR_F32)
+    g.close()
+
+
 @pytest.mark.parametrize("vocab,temp,top_k,k,slots", [
     (v,) + c for v in (4096, 4097, 4100, 8192, 12300)
     for c in ((0.0, 0, 4, 2), (0.9, 0, 0, 1), (0.9, 0, 15, 2), (0.9, 7, 3, 3), (1.0, 5000, 2, 2))] + [(65540, 0.9, 0, 1, 1)])
