@@ -134,6 +134,28 @@ def test_training_step_with_uneven_slices(d, ffn, vocab):
     g.close()
 
 
+@pytest.mark.parametrize("k,heads,hd,page", [(2, 10, 128, 64), (3, 2, 64, 16), (4, 10, 128, 64)])
+def test_attention_backward_over_many_chunks(k, heads, hd, page):
+    """Chunks of 256 keys, added up eight at a time (2300 keys: nine) by a workgroup per 1024 features (1280: one and a quarter),
+    with three to five rows; the other slot ends inside its first tile."""
+    shape = synth.ModelShape(1, 128, heads, hd, 192, 544, dtype=synth.BF16)
+    W = synth.make_weights(shape, 31, k, 6.0)
+    g = _gpu(shape, W, k, 2, 2400, page, {"path": 0})
+    g.train_begin(-1)
+    la = TO._t(W["lookahead"], shape.dtype).numpy()
+    rng = np.random.default_rng(k)
+    prefixes = [rng.integers(0, 544, n).astype(np.int32) for n in (2300, 3)]
+    targets = rng.integers(0, 544, (2, k)).astype(np.int32)
+    for i, p in enumerate(prefixes):
+        g.prefill(i, p, seq_id=i)
+    loss = g.train_step([0, 1], targets, 0.01)
+    o_loss, o_grad = TO.loss_and_grad(shape, W, la, [p.tolist() for p in prefixes], targets)
+    e_loss, e_grad = abs(loss - o_loss) / abs(o_loss), float(np.abs(g.train_read(1) - o_grad).max() / np.abs(o_grad).max())
+    print(f"k={k} heads={heads}: loss rel {e_loss:.1e} grad err {e_grad:.1e}")
+    assert e_loss <= 6e-5 and e_grad <= 4e-4
+    g.close()
+
+
 @pytest.mark.parametrize("dtype,path", [(synth.F32, 1), (synth.BF16, 1), (synth.BF16, 0)], ids=["fp32", "bf16-generic", "bf16"])
 def test_training_step_with_a_part_of_the_logits_at_minus_infinity(dtype, path):
     """The LM-head rows of the second of three parts of 1024 entries (the cross-entropy's unit) overflow to -inf for every hidden
