@@ -300,8 +300,9 @@ int pass_prefill_plan(int rows_per_pass, const int32_t *lens, int n, int max_seg
 int pass_seq_len(pass_ctx *ctx, int slot, int32_t *kv_len, int32_t *n_generated);
 
 /* Options:
- *   "graph"            1 = replay each model call and its epilogue as a captured HIP graph; ignored when the
- *                      context runs on the null stream, which cannot be captured
+ *   "graph"            1 = replay each model call and its epilogue as a captured HIP graph, in pass_generate and
+ *                      pass_run_iterations both calls of an iteration in one; ignored when the context runs
+ *                      on the null stream, which cannot be captured
  *   "path"             0 = auto, 1 = force the generic kernels; before pass_load_weights
  *   "attention"        0 = auto, 1 = never use the matrix-core attention kernel and its tiled K/V pages;
  *                      before pass_load_weights

@@ -88,6 +88,7 @@ __global__ __launch_bounds__(256) void assemble_mfma_kernel(Params p, const uint
   int m = blockIdx.x, b = m / R, r = m % R;
   int slot = p.step_slots[b];
   int pos = p.kv_len[slot] + r;
+  if (m == 0 && threadIdx.x == 0 && mode != MODE_PREFILL) p.clock[mode == MODE_DRAFT ? 0 : 1] = wall_clock64();
   const bool dead = row_is_dead(p, mode, slot, R);
   const uint16_t *src;
   if (mode == MODE_PREFILL) {

@@ -67,6 +67,7 @@ struct TrainWs {
 };
 
 constexpr int kReportStride = 4 + kMaxK + kMaxK + 1 + 1;  // ... and the slot's iteration counter
+constexpr int kReportClocks = 3;  // beside the slots' lines: when the drafting call, the validation call and the report began
 
 // Scratch of pass_draft_static: the attention partials (running maximum, sum and accumulator of
 // every (row, head, split)) of one call, for callers that may not allocate.  One copy per GPU,
@@ -103,12 +104,13 @@ struct pass_ctx {
   int32_t *report_host = nullptr;       // pinned, written by the report kernel; two reports (one may be in flight)
   int32_t *block_table_host = nullptr;  // pinned mirror of P.block_table
   hipEvent_t ev[3];
-  hipEvent_t ev2[2][4];  // run_iterations: per in-flight iteration, start / middle / end of the calls and report landed
+  hipEvent_t reported[2];  // run_iterations: the report of each iteration in flight has landed
+  int wall_khz = 100000;   // rate of the GPU's wall clock
   int kv_slack = 0;      // positions an unreported iteration may have added to every running slot
   int device = 0;        // the GPU the context lives on (current when pass_create ran)
   bool static_scratch = false;  // this call keeps its attention partials in the library's static array (pass_draft_static)
   // optional timing of the dominant kernel (the gate/up GEMM): one event pair per layer
-  // captured (model call + epilogue) graphs, keyed by everything that is baked into the launches:
+  // captured graphs (a model call and its epilogue, or a whole iteration), keyed by everything that is baked into the launches:
   // mode, batch, attention grid width, sampling arguments
   typedef std::tuple<int, int, int, uint32_t, uint32_t, uint32_t, int, int, int, int, int> GraphKey;
   int row_base = 0;  // SampleArgs::row_base of the calls issued now (pass_sps_iteration's drafting steps)
@@ -197,6 +199,7 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   P.flt_tie_d = A.take<int32_t>(S * (kMaxK + 1)); P.flt_tie_p = A.take<int32_t>(S * (kMaxK + 1));
   P.row_parts = A.take<float4>(M * kRowParts); P.draw_parts = A.take<uint64_t>(M * kRowParts);
   P.fallbacks = A.take<int32_t>(1);
+  P.clock = A.take<uint64_t>(2); P.round = A.take<int32_t>(1);
   P.block_table = A.take<int32_t>(S * pps);
   P.draft_logits = A.take<float>(S * (1 + c.k) * V);
   P.verify_logits = A.take<float>(S * (1 + c.k) * V);
@@ -290,16 +293,34 @@ size_t carve_train(const pass_config &c, bool mfma, char *base, TrainWs *out) {
   return (A.off + 255) & ~(size_t)255;
 }
 
-// Slot blockIdx.x's line of the report, a value per lane: one store of the wavefront to the host's memory (a thread per slot
-// made as many as there are values: 5.5 us, now 2.9)
-__global__ __launch_bounds__(64) void gather_report_kernel(Params p, int32_t *out) {
+// The slots' lines of the report, a value per lane: one store of a wavefront to the host's memory each (a thread per slot made as
+// many as there are values: 5.5 us, now 2.9).  `pipelined`: two reports take turns, and the clocks go with them.
+size_t report_ints(int slots) { return (size_t)slots * kReportStride + 2 * kReportClocks; }
+__global__ __launch_bounds__(1024) void gather_report_kernel(Params p, int B, int pipelined, int32_t *out) {
   static_assert(kReportStride == 4 + kMaxK + kMaxK + 1 + 1 && kReportStride <= 64, "a lane per value");
-  const int b = blockIdx.x, i = threadIdx.x, slot = p.step_slots[b];
+  static_assert(kReportStride % 2 == 0, "the clocks are 64 bits wide");
+  const int i = threadIdx.x & 63;
+  if (pipelined) {
+    const int round = p.round[0];
+    out += (round & 1) * ((size_t)p.max_slots * kReportStride + 2 * kReportClocks);
+    __syncthreads();  // everyone has read it
+    if (threadIdx.x == 0) {
+      p.round[0] = round + 1;
+      uint64_t *clocks = (uint64_t *)(out + (size_t)p.max_slots * kReportStride);
+      clocks[0] = p.clock[0]; clocks[1] = p.clock[1]; clocks[2] = wall_clock64();
+    }
+  }
   if (i >= kReportStride) return;
-  const int32_t *v = i == 0 ? p.kv_len + slot : i == 1 ? p.n_gen + slot : i == 2 ? p.n_acc + slot : i == 3 ? p.first + slot
-                     : i < 4 + kMaxK ? p.drafts + slot * kMaxK + (i - 4)
-                     : i < kReportStride - 1 ? p.last_out + slot * (kMaxK + 1) + (i - 4 - kMaxK) : (const int32_t *)p.iter + slot;
-  out[b * kReportStride + i] = *v;
+  for (int b = threadIdx.x >> 6; b < B; b += blockDim.x >> 6) {
+    const int slot = p.step_slots[b];
+    const int32_t *v = i == 0 ? p.kv_len + slot : i == 1 ? p.n_gen + slot : i == 2 ? p.n_acc + slot : i == 3 ? p.first + slot
+                       : i < 4 + kMaxK ? p.drafts + slot * kMaxK + (i - 4)
+                       : i < kReportStride - 1 ? p.last_out + slot * (kMaxK + 1) + (i - 4 - kMaxK) : (const int32_t *)p.iter + slot;
+    out[b * kReportStride + i] = *v;
+  }
+}
+void launch_report(const pass_ctx *c, int B, int pipelined) {
+  gather_report_kernel<<<1, 64 * std::min(B, 16), 0, c->stream>>>(c->P, B, pipelined, c->report_host);
 }
 
 int poke(pass_ctx *c, std::vector<int32_t *> &ptrs, std::vector<int32_t> &vals) {
@@ -342,8 +363,8 @@ int ensure_pages(pass_ctx *c, int slot, int n_pos) {
 }
 
 int set_step_slots(pass_ctx *c, const int32_t *slots, int B) {
-  std::vector<int32_t *> ptrs;
-  std::vector<int32_t> vals;
+  std::vector<int32_t *> ptrs{c->P.round};  // a pipelined run's first report is of parity 0
+  std::vector<int32_t> vals{0};
   for (int b = 0; b < B; ++b) { ptrs.push_back(c->P.step_slots + b); vals.push_back(slots[b]); }
   return poke(c, ptrs, vals);
 }
@@ -558,7 +579,7 @@ SampleArgs sample_args(const pass_sampling *sp, int commit) {
 
 int fetch_report(pass_ctx *c, int B) {
   // the kernel stores straight into the pinned (device-visible, coherent) host buffer: no copy
-  gather_report_kernel<<<B, 64, 0, c->stream>>>(c->P, c->report_host);
+  launch_report(c, B, 0);
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return PASS_OK;
@@ -570,12 +591,25 @@ int max_keys_of(pass_ctx *c, const int32_t *slots, int B, int extra) {
   return mk;
 }
 
-// the two halves of an iteration, without host synchronisation
-int issue_call_eager(pass_ctx *c, int mode, const int32_t *slots, int B, const pass_sampling *sp, int commit) {
+// What issue_call is to launch: a drafting call, a validation call, or an iteration of run_pipeline (both and their report)
+constexpr int kWholeIteration = -1;
+// the longest any sequence can be in the call(s): an iteration commits one token before its validation call
+int issue_max_keys(pass_ctx *c, int mode, const int32_t *slots, int B) {
+  return max_keys_of(c, slots, B, 1 + c->P.k_act + (mode == MODE_DRAFT ? 0 : 1));
+}
+// Without host synchronisation
+int issue_call_eager(pass_ctx *c, int mode, const int32_t *slots, int B, const pass_sampling *sp, int commit, int max_keys) {
+  if (mode == kWholeIteration) {
+    int rc = issue_call_eager(c, MODE_DRAFT, slots, B, sp, commit, max_keys);
+    if (!rc) rc = issue_call_eager(c, MODE_VERIFY, slots, B, sp, commit, max_keys);
+    if (rc) return rc;
+    launch_report(c, B, 1);
+    HIP_TRY(c, hipGetLastError());
+    return PASS_OK;
+  }
   const int R = 1 + c->P.k_act;
   const bool draft = mode == MODE_DRAFT;
-  int rc = run_step(c, mode, B, R, draft ? c->P.draft_logits : c->P.verify_logits,
-                    max_keys_of(c, slots, B, draft ? R : R + 1), nullptr);
+  int rc = run_step(c, mode, B, R, draft ? c->P.draft_logits : c->P.verify_logits, max_keys, nullptr);
   if (rc) return rc;
   if (draft) {
     SampleArgs a = sample_args(sp, commit);
@@ -587,15 +621,16 @@ int issue_call_eager(pass_ctx *c, int mode, const int32_t *slots, int B, const p
   return PASS_OK;
 }
 
-// One model call plus its sampling epilogue.  With the "graph" option the launches are captured
-// once per (mode, batch, attention grid width, sampling arguments) and replayed: every kernel
+// One model call plus its sampling epilogue, or both of an iteration and its report in one go: between two graphs, or
+// one and a kernel or an event, the GPU waits 8 us and more (tiny fp32 model, 123 us an iteration in two graphs, four events and
+// the report's own launch: 103).  With the "graph" option the launches are captured once per (mode, batch, attention grid width, sampling arguments) and replayed: every kernel
 // reads positions, slots and tokens from device memory, so a replay needs no new arguments.
 int issue_call(pass_ctx *c, int mode, const int32_t *slots, int B, const pass_sampling *sp, int commit) {
+  const int max_keys = issue_max_keys(c, mode, slots, B);
   // the null stream cannot be captured: graphs need a stream of their own
   if (!c->opt_graph || c->opt_kernel_timing || c->stream == nullptr || c->static_scratch)
-    return issue_call_eager(c, mode, slots, B, sp, commit);
-  const int R = 1 + c->P.k_act;
-  const int S = choose_splits(c, B, R, max_keys_of(c, slots, B, mode == MODE_DRAFT ? R : R + 1));
+    return issue_call_eager(c, mode, slots, B, sp, commit, max_keys);
+  const int S = choose_splits(c, B, 1 + c->P.k_act, max_keys);
   uint32_t tbits;
   memcpy(&tbits, &sp->temperature, 4);
   pass_ctx::GraphKey key(mode, B, S, tbits, (uint32_t)sp->seed, (uint32_t)(sp->seed >> 32), commit, sp->top_k, c->P.k_act, c->P.la_token, c->row_base);
@@ -607,7 +642,7 @@ int issue_call(pass_ctx *c, int mode, const int32_t *slots, int B, const pass_sa
     }
     hipGraph_t graph = nullptr;
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    int rc = issue_call_eager(c, mode, slots, B, sp, commit);
+    int rc = issue_call_eager(c, mode, slots, B, sp, commit, max_keys);
     hipError_t e = hipStreamEndCapture(c->stream, &graph);
     if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
     if (e != hipSuccess) return fail(c, PASS_EDEVICE, "hipStreamEndCapture: %s", hipGetErrorString(e));
@@ -676,7 +711,7 @@ int pass_create(const pass_config *cfg, void *hip_stream, void *device_arena, si
     delete c;
     return PASS_EDEVICE;
   };
-  hipError_t e = hipHostMalloc((void **)&c->report_host, sizeof(int32_t) * 2 * S * kReportStride, hipHostMallocDefault);
+  hipError_t e = hipHostMalloc((void **)&c->report_host, sizeof(int32_t) * 2 * report_ints((int)S), hipHostMallocDefault);
   if (e != hipSuccess) return die(e);
   e = hipHostMalloc((void **)&c->block_table_host, sizeof(int32_t) * S * c->P.pages_per_seq, hipHostMallocDefault);
   if (e != hipSuccess) return die(e);
@@ -685,11 +720,12 @@ int pass_create(const pass_config *cfg, void *hip_stream, void *device_arena, si
     e = hipEventCreate(&ev);
     if (e != hipSuccess) return die(e);
   }
-  for (auto &set : c->ev2)
-    for (auto &ev : set) {
-      e = hipEventCreate(&ev);
-      if (e != hipSuccess) return die(e);
-    }
+  for (auto &ev : c->reported) {
+    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e != hipSuccess) return die(e);
+  }
+  e = hipDeviceGetAttribute(&c->wall_khz, hipDeviceAttributeWallClockRate, c->device);
+  if (e != hipSuccess) return die(e);
   // per-slot state starts at zero; block table at page 0 (valid memory, never read before set)
   size_t state_ints = (size_t)((char *)c->P.gen - (char *)c->P.kv_len) / 4;
   launch_fill_i32(c->P.kv_len, 0, state_ints, c->stream);
@@ -1122,15 +1158,14 @@ int pass_sps_iteration(pass_ctx *t, pass_ctx *d, const int32_t *t_slots, const i
 static int run_pipeline(pass_ctx *c, const int32_t *slots, int n_slots, int n_iters, int target, const int *start,
                         const pass_sampling *sp, pass_stats &st) {
   const int k = c->cfg.k;
-  const size_t rep_ints = (size_t)c->cfg.max_slots * kReportStride;
+  const size_t rep_ints = report_ints(c->cfg.max_slots);
   const int grow = c->P.k_act + 2;
   auto retire = [&](int par) -> int {
-    HIP_TRY(c, hipEventSynchronize(c->ev2[par][3]));
-    float ms_d = 0, ms_v = 0;
-    HIP_TRY(c, hipEventElapsedTime(&ms_d, c->ev2[par][0], c->ev2[par][1]));
-    HIP_TRY(c, hipEventElapsedTime(&ms_v, c->ev2[par][1], c->ev2[par][2]));
-    st.draft_ms += ms_d;
-    st.verify_ms += ms_v;
+    HIP_TRY(c, hipEventSynchronize(c->reported[par]));
+    uint64_t clocks[kReportClocks];
+    memcpy(clocks, c->report_host + par * rep_ints + (size_t)c->cfg.max_slots * kReportStride, sizeof clocks);
+    st.draft_ms += (double)(clocks[1] - clocks[0]) / c->wall_khz;
+    st.verify_ms += (double)(clocks[2] - clocks[1]) / c->wall_khz;
     for (int b = 0; b < n_slots; ++b) {
       const int32_t *r = c->report_host + par * rep_ints + b * kReportStride;
       Slot &s = c->slots[slots[b]];
@@ -1185,14 +1220,8 @@ static int run_pipeline(pass_ctx *c, const int32_t *slots, int n_slots, int n_it
       }
       if (again) { --it; continue; }
       c->kv_slack = pending >= 0 ? grow : 0;
-      HIP_TRY(c, hipEventRecord(c->ev2[par][0], c->stream));
-      if ((rc2 = issue_draft(c, slots, n_slots, sp, 1))) return rc2;
-      HIP_TRY(c, hipEventRecord(c->ev2[par][1], c->stream));
-      if ((rc2 = issue_verify(c, slots, n_slots, sp, 1))) return rc2;
-      HIP_TRY(c, hipEventRecord(c->ev2[par][2], c->stream));
-      gather_report_kernel<<<n_slots, 64, 0, c->stream>>>(c->P, c->report_host + par * rep_ints);
-      HIP_TRY(c, hipGetLastError());
-      HIP_TRY(c, hipEventRecord(c->ev2[par][3], c->stream));
+      if ((rc2 = issue_call(c, kWholeIteration, slots, n_slots, sp, 1))) return rc2;
+      HIP_TRY(c, hipEventRecord(c->reported[par], c->stream));
       const int was = pending;
       pending = par;
       if (was >= 0 && (rc2 = retire(was))) return rc2;
@@ -1692,8 +1721,7 @@ void pass_destroy(pass_ctx *c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
   for (auto &ev : c->ev) (void)hipEventDestroy(ev);
-  for (auto &set : c->ev2)
-    for (auto &ev : set) (void)hipEventDestroy(ev);
+  for (auto &ev : c->reported) (void)hipEventDestroy(ev);
   for (auto &ev : c->kev) (void)hipEventDestroy(ev);
   for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.second);
   if (c->report_host) (void)hipHostFree(c->report_host);

@@ -91,6 +91,8 @@ struct Params {
   // per-slot state (device), indexed by slot
   int32_t *kv_len, *pending, *first, *drafts /*[slot][kMaxK]*/, *n_gen, *n_acc, *frozen, *gen_limit;
   uint32_t *iter, *seq_id;
+  uint64_t *clock;     // [2] when the last drafting and the last validation call began (wall_clock64)
+  int32_t *round;      // iterations a pipelined run has finished: its parity picks the report that the next one fills
   int32_t *last_out;  // [slot][kMaxK+1]: accepted drafts then the final token of the last verify
   int32_t *gen;       // [slot][gen_cap]: every generated token since the prefill
   float *logz_d, *logz_p;  // [slot][kMaxK+1]: ln sum exp(logit/T) of each draft / verify row

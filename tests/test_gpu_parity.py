@@ -1,4 +1,6 @@
 """GPU parity: the HIP path (through the C ABI) against the CPU oracle, element by element."""
+import time
+
 import numpy as np
 import pytest
 
@@ -1108,6 +1110,40 @@ def test_run_iterations_equals_stepwise_calls(w):
     assert res[0][0] == res[1][0] and res[0][1] == res[1][1]
     assert np.array_equal(res[0][2], res[1][2]) and np.array_equal(res[0][3], res[1][3])
     assert res[0][4] == res[1][4] and res[0][4] > 0
+
+
+@pytest.mark.parametrize("graph", [0, 1], ids=["eager", "graph"])
+@pytest.mark.parametrize("w,len0", [(TINY, 187), (MFMA_HD128, 123)], ids=["fp32", "mfma"])
+def test_iterations_and_single_calls_take_turns(w, len0, graph):
+    """An iteration of the pipelined loop is one launch (both calls and the report), whose reports take turns; single calls report
+    by themselves.  Runs of odd and even length with single calls and a batch of another size between them, across the
+    length at which a second attention split begins: the sequences end where single calls alone leave them."""
+    w = synth.scaled(w, k=3)
+    W = synth.make_weights(w.shape, 6, 3, 1.0)
+    prompts = [np.random.default_rng(i).integers(0, w.shape.vocab, n).astype(np.int32) for i, n in enumerate((len0, 40))]
+    res = []
+    for mode in ("mixed", "single"):
+        g = _gpu(w.shape, W, 3, max_slots=2, max_seq_len=384, page_size=64, options={"graph": graph})
+        for i, p in enumerate(prompts):
+            g.prefill(i, p, seq_id=60 + i)
+        for slots, n in (([0, 1], 3), ([1], 2), ([1, 0], 1), ([0], 5), ([0, 1], 4)):
+            if mode == "mixed":
+                t0 = time.perf_counter()
+                st = g.run_iterations(slots, n, 2.0, 99)
+                wall_ms = (time.perf_counter() - t0) * 1e3
+                assert st["iterations"] == n * len(slots)
+                assert 0 < st["draft_ms"] < wall_ms and 0 < st["verify_ms"] and st["draft_ms"] + st["verify_ms"] < wall_ms
+            else:
+                for _ in range(n):
+                    g.draft(slots, 2.0, 99)
+                    g.verify(slots, 2.0, 99)
+            g.draft(slots, 2.0, 99)
+            g.verify(slots, 2.0, 99)
+        res.append([g.seq_len(0), g.seq_len(1)] + [g.get_logits(sl, which) for sl in (0, 1) for which in (0, 1)])
+        g.close()
+    assert res[0][:2] == res[1][:2]
+    for a, b in zip(res[0][2:], res[1][2:]):
+        assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("w", [TINY, MFMA_HD128], ids=["fp32", "mfma"])
