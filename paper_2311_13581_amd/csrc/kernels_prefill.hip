@@ -494,17 +494,19 @@ int launch_tile(const Params &p, const PrefillWs &w, TileArgs a, hipStream_t s) 
 // the four in wavefront order, normalises and stores the rows as (hi, lo) pairs for the Wo GEMM.
 // ---------------------------------------------------------------------------------------------
 template <int RG>  // groups of 16 rows per workgroup
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_kernel(Params p, PrefillWs w, int layer, int slot, int pos0,
-                                                                                                       int R) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_kernel(Params p, PrefillWs w, int layer, PrefillAttn a) {
   constexpr int HD = 128, RQ = 16 * RG;
   __shared__ float s_m[3][RQ], s_l[3][RQ];
   __shared__ float s_acc[3][RQ][HD];
 
-  const int blk = gridDim.x - 1 - blockIdx.x;  // blocks with the most keys first
+  constexpr int SUB = kPrefillBlockRows / RQ;
+  const int blk = blockIdx.x / SUB, first = (SUB - 1 - blockIdx.x % SUB) * RQ;  // rows with the most keys first
   const int head = blockIdx.y;
-  const int r0 = blk * RQ;
-  const int nr = min(RQ, R - r0);
-  const int k_hi = pos0 + r0 + nr;  // keys 0 .. k_hi - 1 are visible to the block's last row
+  const int nr = min(RQ, a.rows[blk] - first);
+  if (nr <= 0) return;  // uniform over the workgroup
+  const int slot = a.slot[blk], r0 = a.row[blk] + first;  // r0: row of the pass, at position `at` of the sequence
+  const int at = a.pos[blk] + first;
+  const int k_hi = at + nr;  // keys 0 .. k_hi - 1 are visible to the block's last row
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ml = lane & 15, g = lane >> 4;
@@ -569,7 +571,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
       // a row group whose last row comes before this step's first key sees none of the step
-      if (base > pos0 + r0 + rg * 16 + 15) continue;
+      if (base > at + rg * 16 + 15) continue;
       floatx4 sc[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -591,7 +593,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int key = base + 8 * g + 4 * t + r;
-          const bool ok = (rr < nr) && (key <= pos0 + r0 + rr);
+          const bool ok = (rr < nr) && (key <= at + rr);
           const float v = ok ? sc[t][r] : -INFINITY;
           sv[4 * t + r] = v;
           m_blk = fmaxf(m_blk, v);
@@ -702,20 +704,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // through registers; 13B, rows 2048 .. 4095: 465 -> 305.  Also tried: 64-key steps (the same), 16 rows per
 // wavefront with three or four wavefronts per SIMD (5 % slower at 2047 rows, 20 % at 4096).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_shared_kernel(Params p, PrefillWs w, int layer,
-                                                                                                                int slot, int pos0, int R) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_shared_kernel(Params p, PrefillWs w, int layer, PrefillAttn a) {
   constexpr int HD = 128, RG = 2, RW = 16 * RG, RQ = 4 * RW;  // 32 rows per wavefront, 128 per workgroup
   constexpr int STEP = 32;                                    // keys per step
   __shared__ u32x4 sK0[8][64], sK1[8][64], sV0[8][64], sV1[8][64];
 
   const int head = blockIdx.x, n_blk = gridDim.y, half = (n_blk + 1) / 2;
-  const int blk = (int)blockIdx.y < half ? n_blk - 1 - blockIdx.y : (int)blockIdx.y - half;
+  const int blk = (int)blockIdx.y < half ? (int)blockIdx.y : n_blk - 1 - ((int)blockIdx.y - half);
+  const int slot = a.slot[blk], rows = a.rows[blk];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ml = lane & 15, g = lane >> 4;
-  const int r0w = blk * RQ + wave * RW;        // first row of this wavefront
-  const int nr = max(0, min(RW, R - r0w));     // its rows (0: the prompt ends before them)
-  const int k_all = pos0 + min(R, blk * RQ + RQ);  // keys visible to the workgroup's last row
-  const int k_own = nr ? pos0 + r0w + nr : 0;      // keys visible to this wavefront's last row
+  const int r0w = a.row[blk] + wave * RW;        // first row of this wavefront (of the pass), at position `at` of the sequence
+  const int at = a.pos[blk] + wave * RW;
+  const int nr = max(0, min(RW, rows - wave * RW));  // its rows (0: the prompt ends before them)
+  const int k_all = a.pos[blk] + rows;               // keys visible to the workgroup's last row
+  const int k_own = nr ? at + nr : 0;                // keys visible to this wavefront's last row
   const uint16_t *kpool = (const uint16_t *)p.k_pool, *vpool = (const uint16_t *)p.v_pool;
 
   // this wavefront's share of a step: K fragments 2 * wave, 2 * wave + 1 (fragment t * 4 + j: 16 key slots of half t, dims
@@ -744,7 +747,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int rg = 0; rg < RG; ++rg) {
       const int rr = rg * 16 + ml;
       const bool live = rr < nr;
-      const float *qp = w.q + (size_t)(live ? r0w + rr : 0) * p.D + head * HD + g * 8;
+      const float *qp = w.q + (size_t)(live ? r0w + rr : a.row[blk]) * p.D + head * HD + g * 8;
       floatx4 raw[4][2];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -796,7 +799,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
       if (masked) {
-        const int last = pos0 + r0w + rg * 16 + ml - base - 8 * g;  // the row's last key, counted from this lane's first
+        const int last = at + rg * 16 + ml - base - 8 * g;  // the row's last key, counted from this lane's first
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -852,7 +855,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     meet();
     if (base + STEP < k_all) issue(nK, nV, base + STEP);
     if (base >= k_own) return;  // past this wavefront's last row
-    const bool masked = base + STEP > pos0 + r0w + 1;  // some row of this wavefront does not see all of the step
+    const bool masked = base + STEP > at + 1;  // some row of this wavefront does not see all of the step
     floatx4 sc[RG][2];
     u32x4 ph[RG], pl[RG];
     scores(sc, dK);
@@ -898,19 +901,14 @@ void launch_prefill_gateup(const Params &p, const PrefillWs &w, const void *W, i
   TileArgs a{(const u32x4 *)W, (const u32x4 *)p.xg, M, p.d, 2 * p.F / 16, 0, nullptr, PrefillSegs{}, 0, 0, 0, 1, 0, nullptr};
   launch_tile<TILE_GATEUP>(p, w, a, s);
 }
-void launch_prefill_attention(const Params &p, const PrefillWs &w, int layer, int slot, int pos0, int R,
-                              hipStream_t s) {
-  // 128 rows per workgroup with shared K/V tiles once a pass is long enough for the traffic out of
-  // L2 to matter (measured: equal at 512 rows, -4 % of the pass at 2048, -7 % at 4096)
-  if (w.attn_rows == 128 || (w.attn_rows == 0 && R > 512)) {
-    attn_prefill_shared_kernel<<<dim3(p.H, (R + 127) / 128), 256, 0, s>>>(p, w, layer, slot, pos0, R);
-  } else if (w.attn_rows == 16) {
-    dim3 grid((R + 15) / 16, p.H);
-    attn_prefill_kernel<1><<<grid, 256, 0, s>>>(p, w, layer, slot, pos0, R);
-  } else {
-    dim3 grid((R + 31) / 32, p.H);
-    attn_prefill_kernel<2><<<grid, 256, 0, s>>>(p, w, layer, slot, pos0, R);
-  }
+void launch_prefill_attention(const Params &p, const PrefillWs &w, int layer, const PrefillAttn &a, bool shared, hipStream_t s) {
+  if (a.n == 0) return;
+  if (shared)
+    attn_prefill_shared_kernel<<<dim3(p.H, a.n), 256, 0, s>>>(p, w, layer, a);
+  else if (w.attn_rows == 16)
+    attn_prefill_kernel<1><<<dim3(a.n * (kPrefillBlockRows / 16), p.H), 256, 0, s>>>(p, w, layer, a);
+  else
+    attn_prefill_kernel<2><<<dim3(a.n * (kPrefillBlockRows / 32), p.H), 256, 0, s>>>(p, w, layer, a);
 }
 
 // Row assembly of a tiled pass that carries rows of several sequences (see PrefillSegs): h (fp32), (hi, lo) of

@@ -445,8 +445,8 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
 }
 
 // One tiled pass over the weights: the rows `segs` describes (M rows including padding, M <= pws.rows), token
-// ids of all M rows at `ids` (device).  Attention runs per sequence on its own rows of the pass (row_base:
-// multiples of 128, so a sequence's rows are whole 8-row groups of the (hi, lo) tiles).
+// ids of all M rows at `ids` (device).  Attention runs on blocks of 128 rows of one sequence each (row_base:
+// multiples of 128).
 // No LM head: the last prompt token stays pending and goes through the first draft call.
 struct PassSeg { int slot, pos0, rows, row_base; };
 
@@ -520,18 +520,27 @@ int run_prefill_pass(pass_ctx *c, const std::vector<PassSeg> &parts, int M, cons
       segs.pos[b] = g.pos0 + done;
       segs.rows[b] = std::min(kPrefillBlockRows, g.rows - done);
     }
+  // the blocks of the attention kernel of 32 rows a workgroup, of that of 128: one launch each, whatever the number of sequences
+  // (eight prompts of 25 .. 600 tokens, d 1024, two layers, first drafting call included: 1323 us with a launch per sequence, now 1234)
+  PrefillAttn attn[2];
+  memset(attn, 0, sizeof attn);
+  for (const PassSeg &g : parts) {
+    PrefillAttn &a = attn[prefill_attn_shared(W, g.rows)];
+    for (int done = 0; done < g.rows; done += kPrefillBlockRows) {
+      const int rows = std::min(kPrefillBlockRows, g.rows - done), keys = g.pos0 + done + rows;
+      int i = a.n++;  // insertion in descending order of keys
+      for (; i > 0 && a.pos[i - 1] + a.rows[i - 1] < keys; --i) {
+        a.row[i] = a.row[i - 1]; a.slot[i] = a.slot[i - 1]; a.pos[i] = a.pos[i - 1]; a.rows[i] = a.rows[i - 1];
+      }
+      a.row[i] = g.row_base + done; a.slot[i] = g.slot; a.pos[i] = g.pos0 + done; a.rows[i] = rows;
+    }
+  }
   hipStream_t s = c->stream;
   launch_assemble_prefill_segs(P, c->tok_emb, c->layers[0].attn_norm, segs, M, W.np, W.rows, s);
   for (int l = 0; l < P.L; ++l) {
     const LayerW &w = c->layers[l];
     launch_prefill_qkv(P, W, w.wqkv, l, segs, M, s);
-    for (const PassSeg &g : parts) {
-      Params Pg = P;
-      PrefillWs Wg = W;
-      Pg.attn_x = P.attn_x + (size_t)g.row_base * 2 * P.D;  // 8-row groups of 16 * D elements
-      Wg.q = W.q + (size_t)g.row_base * P.D;
-      launch_prefill_attention(Pg, Wg, l, g.slot, g.pos0, g.rows, s);
-    }
+    for (int i = 0; i < 2; ++i) launch_prefill_attention(P, W, l, attn[i], i == 1, s);
     W.np = launch_prefill_resid(P, W, w.wo, P.attn_x, P.D, w.ffn_norm, M, s);
     launch_prefill_gateup(P, W, w.wgu, M, s);
     W.np = launch_prefill_resid(P, W, w.wdown, P.act_x, P.F, l + 1 < P.L ? c->layers[l + 1].attn_norm : c->final_norm, M, s);
@@ -621,10 +630,11 @@ int issue_call_eager(pass_ctx *c, int mode, const int32_t *slots, int B, const p
   return PASS_OK;
 }
 
-// One model call plus its sampling epilogue, or both of an iteration and its report in one go: between two graphs, or
-// one and a kernel or an event, the GPU waits 8 us and more (tiny fp32 model, 123 us an iteration in two graphs, four events and
-// the report's own launch: 103).  With the "graph" option the launches are captured once per (mode, batch, attention grid width, sampling arguments) and replayed: every kernel
-// reads positions, slots and tokens from device memory, so a replay needs no new arguments.
+// One model call plus its sampling epilogue, or both of an iteration and its report in one go: between two graphs, or one and a
+// kernel or an event, the GPU waits 8 us and more (tiny fp32 model: 123 us an iteration in two graphs, four events and the report's
+// own launch, 103 in one graph).  With the "graph" option the launches are captured once per (mode, batch, attention grid width,
+// sampling arguments) and replayed: every kernel reads positions, slots and tokens from device memory, so a replay needs no
+// new arguments.
 int issue_call(pass_ctx *c, int mode, const int32_t *slots, int B, const pass_sampling *sp, int commit) {
   const int max_keys = issue_max_keys(c, mode, slots, B);
   // the null stream cannot be captured: graphs need a stream of their own

@@ -257,8 +257,18 @@ void launch_assemble_prefill_segs(const Params &p, const void *tok_emb, const vo
                                   int ssq_parts, int ssq_stride, hipStream_t s);
 void launch_prefill_qkv(const Params &p, const PrefillWs &w, const void *W, int layer, const PrefillSegs &segs, int M,
                         hipStream_t s);
-void launch_prefill_attention(const Params &p, const PrefillWs &w, int layer, int slot, int pos0, int R,
-                              hipStream_t s);
+// Blocks of up to 128 query rows of a pass, whichever sequences they belong to, those with the most keys first: block i is rows
+// row[i] .. row[i] + rows[i] of the pass, at positions pos[i] .. of the sequence in slot[i].
+struct PrefillAttn {
+  int n;
+  int row[kPrefillRows / kPrefillBlockRows], slot[kPrefillRows / kPrefillBlockRows], pos[kPrefillRows / kPrefillBlockRows],
+      rows[kPrefillRows / kPrefillBlockRows];
+};
+// 128 rows per workgroup with shared K/V tiles once a sequence's rows in a pass are enough for the traffic out of L2 to matter
+// (measured: equal at 512 rows, -4 % of the pass at 2048, -7 % at 4096); by the sequence's own rows, so that its arithmetic cannot
+// depend on what shares the pass
+inline bool prefill_attn_shared(const PrefillWs &w, int rows) { return w.attn_rows == 128 || (w.attn_rows == 0 && rows > 512); }
+void launch_prefill_attention(const Params &p, const PrefillWs &w, int layer, const PrefillAttn &a, bool shared, hipStream_t s);
 // returns the number of partial sums of h^2 per row it leaves (PrefillWs::np of the next launches)
 int launch_prefill_resid(const Params &p, const PrefillWs &w, const void *W, const uint16_t *X, int K,
                          const void *gain_next, int M, hipStream_t s);

@@ -708,6 +708,30 @@ def test_prompt_attention_with_scores_far_below_zero(attn_rows):
     assert np.abs(lg[0] - lg[1]).max() <= 1e-3 * np.abs(lg[1]).max()  # bf16 rounding of the second layer's keys and values
 
 
+@pytest.mark.parametrize("attn_rows,lens", [(0, (601, 70, 514, 5, 300, 131)), (0, (700, 690, 3)), (16, (33, 200, 17, 260)), (128, (129, 40, 385))])
+def test_prompt_attention_of_several_slots_in_one_launch(attn_rows, lens):
+    """The blocks of all sequences of a pass go through one launch of their attention kernel, most keys first: sequences of more
+    and of fewer than 512 rows together (one kernel each), one that goes on in the next pass, blocks that end after one row.
+    The logits of the next call against those of one pass_prefill per slot, which the tests above hold against the oracle."""
+    w = MFMA_HD128
+    W = synth.make_weights(w.shape, w.seed, w.k, w.lm_head_scale)
+    rng = np.random.default_rng(attn_rows + len(lens))
+    prompts = [rng.integers(0, w.shape.vocab, n).astype(np.int32) for n in lens]
+    slots = list(range(len(lens)))[::-1]
+    g = _gpu(w.shape, W, w.k, max_slots=len(lens), max_seq_len=1024, page_size=64,
+             options={"prefill_tiled": 1, "tune.prefill_rows": 1024, "tune.prefill_tile": attn_rows})
+    g.prefill_batch(slots, prompts, slots)
+    g.draft(slots, 0.0, 1)
+    a = [g.get_logits(sl, 0).copy() for sl in slots]
+    for sl, p in zip(slots, prompts):
+        g.prefill(sl, p, seq_id=sl)
+    g.draft(slots, 0.0, 1)
+    for i, sl in enumerate(slots):
+        b = g.get_logits(sl, 0)
+        assert np.abs(a[i] - b).max() <= 1e-3 * np.abs(b).max(), (sl, np.abs(a[i] - b).max() / np.abs(b).max())
+    g.close()
+
+
 @pytest.mark.parametrize("rows,lens", [(384, (37, 300, 129, 2, 1, 260)), (128, (200, 5, 131)), (256, (129, 128, 127, 1, 64, 65))])
 def test_prompt_pass_over_several_slots(rows, lens):
     """pass_prefill_batch: ragged prompts of several sequences share tiled passes over the weights (every
