@@ -114,7 +114,7 @@ struct pass_ctx {
   // mode, batch, attention grid width, sampling arguments
   typedef std::tuple<int, int, int, uint32_t, uint32_t, uint32_t, int, int, int, int, int> GraphKey;
   int row_base = 0;  // SampleArgs::row_base of the calls issued now (pass_sps_iteration's drafting steps)
-  std::map<GraphKey, hipGraphExec_t> graphs;
+  std::map<GraphKey, hipGraphExec_t> graphs;  // null: launched once, not captured yet
   int opt_kernel_timing = 0;
   GemmTuning tuning;
   TrainWs train;
@@ -600,6 +600,12 @@ int max_keys_of(pass_ctx *c, const int32_t *slots, int B, int extra) {
   return mk;
 }
 
+void drop_graphs(pass_ctx *c) {
+  for (auto &g : c->graphs)
+    if (g.second) (void)hipGraphExecDestroy(g.second);
+  c->graphs.clear();
+}
+
 // What issue_call is to launch: a drafting call, a validation call, or an iteration of run_pipeline (both and their report)
 constexpr int kWholeIteration = -1;
 // the longest any sequence can be in the call(s): an iteration commits one token before its validation call
@@ -632,7 +638,7 @@ int issue_call_eager(pass_ctx *c, int mode, const int32_t *slots, int B, const p
 
 // One model call plus its sampling epilogue, or both of an iteration and its report in one go: between two graphs, or one and a
 // kernel or an event, the GPU waits 8 us and more (tiny fp32 model: 123 us an iteration in two graphs, four events and the report's
-// own launch, 103 in one graph).  With the "graph" option the launches are captured once per (mode, batch, attention grid width,
+// own launch, 103 in one graph).  With the "graph" option the launches are captured, when they come a second time, once per (mode, batch, attention grid width,
 // sampling arguments) and replayed: every kernel reads positions, slots and tokens from device memory, so a replay needs no
 // new arguments.
 int issue_call(pass_ctx *c, int mode, const int32_t *slots, int B, const pass_sampling *sp, int commit) {
@@ -646,10 +652,13 @@ int issue_call(pass_ctx *c, int mode, const int32_t *slots, int B, const pass_sa
   pass_ctx::GraphKey key(mode, B, S, tbits, (uint32_t)sp->seed, (uint32_t)(sp->seed >> 32), commit, sp->top_k, c->P.k_act, c->P.la_token, c->row_base);
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
-    if (c->graphs.size() >= 64) {  // bound the cache: drop everything, recapture on demand
-      for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.second);
-      c->graphs.clear();
-    }
+    // The first time the kernels are launched one by one: the GPU starts at once, where it would wait for the capture of all of
+    // them (a batch of eight, eight layers: 1 ms).  The capture, the second time, is hidden behind the iteration in flight.
+    if (c->graphs.size() >= 64) drop_graphs(c);  // bound the cache: recapture on demand
+    c->graphs.emplace(key, nullptr);
+    return issue_call_eager(c, mode, slots, B, sp, commit, max_keys);
+  }
+  if (it->second == nullptr) {
     hipGraph_t graph = nullptr;
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     int rc = issue_call_eager(c, mode, slots, B, sp, commit, max_keys);
@@ -660,7 +669,7 @@ int issue_call(pass_ctx *c, int mode, const int32_t *slots, int B, const pass_sa
     e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
     if (e != hipSuccess) return fail(c, PASS_EDEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
-    it = c->graphs.emplace(key, exec).first;
+    it->second = exec;
   }
   HIP_TRY(c, hipGraphLaunch(it->second, c->stream));
   return PASS_OK;
@@ -1633,8 +1642,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
         return fail(c, PASS_EINVAL, "tune.gemm_cfg (more than 8 rows): kind 0..4, wavefronts 4/8/16, blocks 0..8");
     } else if (c->tuning.set(value / 10000, (value / 100) % 100, value % 100))
       return fail(c, PASS_EINVAL, "tune.gemm_cfg: kind 0..4, wavefronts 4/8/16, unroll 1/2/4");
-    for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.second);  // captured launches carry the old shape
-    c->graphs.clear();
+    drop_graphs(c);  // captured launches carry the old shape
     return PASS_OK;
   }
   if (!strcmp(name, "lookahead_rows") || !strcmp(name, "lookahead_token")) {
@@ -1733,7 +1741,7 @@ void pass_destroy(pass_ctx *c) {
   for (auto &ev : c->ev) (void)hipEventDestroy(ev);
   for (auto &ev : c->reported) (void)hipEventDestroy(ev);
   for (auto &ev : c->kev) (void)hipEventDestroy(ev);
-  for (auto &g : c->graphs) (void)hipGraphExecDestroy(g.second);
+  drop_graphs(c);
   if (c->report_host) (void)hipHostFree(c->report_host);
   if (c->block_table_host) (void)hipHostFree(c->block_table_host);
   if (c->train_loss_host) (void)hipHostFree(c->train_loss_host);

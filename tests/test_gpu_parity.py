@@ -1170,6 +1170,27 @@ def test_iterations_and_single_calls_take_turns(w, len0, graph):
         assert np.array_equal(a, b)
 
 
+def test_more_shapes_than_graphs_are_kept():
+    """A shape's launches go out one by one the first time, are captured the second and replayed from then on; past 64 shapes all are
+    dropped.  Forty seeds, every other one three times and every other one once, twice over, equal the eager launches."""
+    w = synth.scaled(TINY, k=2)
+    W = synth.make_weights(w.shape, 8, 2, 1.0)
+    res = []
+    for graph in (0, 1):
+        g = _gpu(w.shape, W, 2, max_seq_len=768, options={"graph": graph})
+        g.prefill(0, np.arange(1, 6, dtype=np.int32))
+        out = []
+        for _ in range(2):
+            for seed in range(40):
+                if seed % 2:
+                    g.run_iterations([0], 3, 1.0, seed)
+                else:
+                    out += [int(g.draft([0], 1.0, seed)[0][0])] + g.verify([0], 1.0, seed)[1].ravel().tolist()
+        res.append((out, g.seq_len(0), g.get_logits(0, 1)))
+        g.close()
+    assert res[0][0] == res[1][0] and res[0][1] == res[1][1] and np.array_equal(res[0][2], res[1][2])
+
+
 @pytest.mark.parametrize("w", [TINY, MFMA_HD128], ids=["fp32", "mfma"])
 def test_generate_equals_stepwise_calls(w):
     """pass_generate runs Algorithm 1's loop with the report of an iteration read one iteration late
