@@ -10,7 +10,7 @@
 // Every "draw" is a Gumbel-max: argmax_j (score_j - ln(-ln u_j)), u_j from Philox4x32-10 with
 // key = seed and counter = (j/4, iteration, row | purpose << 8, sequence id); an argmax is
 // independent of reduction order, so wavefront reductions give the same winner as a serial loop.
-// Ties go to the lowest index.  temperature == 0 is greedy (argmax of the logits).
+// Ties go to the lowest index, a NaN loses against every number.  temperature == 0 is greedy (argmax of the logits).
 //
 // Top-k sampling (the paper's sampler, Experimental setup: k = 10, and 25 for pass@10): the draft
 // and the target distribution are each the softmax over the row's own K largest logits, zero
@@ -51,10 +51,11 @@ struct Best {
   int idx;
 };
 __device__ __forceinline__ Best better(Best a, Best b) {
-  // larger score wins; equal scores: lower index; idx < 0 means "no candidate"
+  // larger score wins, any number wins against a NaN; equal scores: lower index; idx < 0 means "no candidate"
   if (b.idx < 0) return a;
   if (a.idx < 0) return b;
-  if (b.s > a.s || (b.s == a.s && b.idx < a.idx)) return b;
+  const bool nan_a = a.s != a.s, nan_b = b.s != b.s;
+  if (b.s > a.s || (nan_a && !nan_b) || ((b.s == a.s || (nan_a && nan_b)) && b.idx < a.idx)) return b;
   return a;
 }
 __device__ __forceinline__ Best wave_best(Best v) {
@@ -553,8 +554,8 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   });
   return lane63(v);
 }
-// A candidate as an integer that orders like better(): larger score first, then the lower index; 0 = no candidate
-__device__ __forceinline__ uint64_t best_key(float s, int idx) { return (uint64_t)order_key(s) << 32 | (uint32_t)~idx; }
+// A candidate as an integer that orders like better(): larger score first, a NaN last, then the lower index; 0 = no candidate
+__device__ __forceinline__ uint64_t best_key(float s, int idx) { return (uint64_t)(s == s ? order_key(s) : 0u) << 32 | (uint32_t)~idx; }
 __device__ __forceinline__ int key_index(uint64_t key) { return key ? (int)~(uint32_t)key : -1; }
 __device__ __forceinline__ uint64_t wave_key_dpp(uint64_t k) {
   dpp_steps([&](auto C, auto R) {

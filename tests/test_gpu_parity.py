@@ -505,6 +505,33 @@ def test_sampling_epilogue_of_small_vocabularies(vocab, temp, k, slots):
     g.close()
 
 
+@pytest.mark.parametrize("temp", [0.0, 0.9])
+@pytest.mark.parametrize("vocab", [8, 252, 1024, 1026, 1028, 4096, 8192])
+def test_logits_that_are_not_numbers_are_never_chosen(vocab, temp):
+    """A NaN loses against every number, whichever kernel takes the row and wherever it stands in it (first of a quad, between
+    others, at both ends): drafts and final tokens are numbers' indices, greedy ones the argmax of the numbers.  A row of nothing
+    but NaN still gives a token of the vocabulary."""
+    shape = synth.ModelShape(1, 128, 2, 64, 96, vocab, dtype=synth.F32)
+    k, bad = 3, np.unique([0, 1, 4, 5, 6, vocab - 4, vocab - 1])[:vocab - 3]
+    W = synth.make_weights(shape, 14, k, 10.0)
+    W["lm_head"] = np.array(W["lm_head"], np.float32).reshape(vocab, shape.d_model)
+    for rows in (bad, slice(None)):
+        W["lm_head"][rows] = np.nan
+        g = _gpu(shape, W, k, max_seq_len=64)
+        g.prefill(0, np.array([2, 3, 2], np.int32))
+        for _ in range(3):
+            first, drafts = g.draft([0], temp, 777)
+            n_acc, tokens = g.verify([0], temp, 777)
+            d, v, made = g.get_logits(0, 0), g.get_logits(0, 1), np.concatenate([first, drafts[0], tokens[0, :n_acc[0] + 1]])
+            assert np.isnan(d[:, rows]).all() and np.isnan(v[:, rows]).all() and ((made >= 0) & (made < vocab)).all()
+            if rows is not bad:
+                continue
+            assert np.isfinite(np.delete(d, bad, 1)).all() and not np.isin(made, bad).any()
+            if temp == 0:
+                assert np.array_equal(np.append(first, drafts[0]), np.nanargmax(d, 1)) and made[-1] == np.nanargmax(v, 1)[n_acc[0]]
+        g.close()
+
+
 @pytest.mark.parametrize("vocab,temp,top_k,k,slots", [
     (v,) + c for v in (4096, 4097, 4100, 8192, 12300)
     for c in ((0.0, 0, 4, 2), (0.9, 0, 0, 1), (0.9, 0, 15, 2), (0.9, 7, 3, 3), (1.0, 5000, 2, 2))] + [(65540, 0.9, 0, 1, 1)])
