@@ -574,7 +574,7 @@ GemmTuning::GemmTuning()
     : waves{0, 0, 0, 0, 0},        // QKV, Wo, gate/up, LM head, down; 0 = by the count of blocks (few_rows_shape)
       unroll{1, 1, 1, 1, 1},
       big_blocks{0, 0, 0, 0, 0},   // 0 = by the count of blocks (ring_blocks)
-      split_ks(4) {}
+      split_ks(-1) {}              // -1 = by the rows (launch_resid_split)
 
 int GemmTuning::set(int kind, int w, int u) {
   if (kind < 0 || kind > 4) return -1;
@@ -746,11 +746,11 @@ static void launch_gemm_epi(const Params &p, const GemmTuning &tn, const GemmArg
 }
 
 // ---------------------------------------------------------------------------------------------
-// Residual projections (Wo, down) of calls with more than 8 rows.  N = d gives only d/16 strips,
+// Residual projections (Wo, down) in slices of K.  Calls with more than 8 rows: N = d gives only d/16 strips,
 // one per compute unit at best, and every workgroup would have to pull all M activation rows
 // through its L1: that traffic, not HBM, bounds the kernel.  So K is cut into KS slices across
 // workgroups that own that many times the strips (7B: 4 slices, 4 strips; 8 and 8 took 23.2 us for down where
-// these take 22.0, 2 and 2 took 27.7); the slices'
+// these take 22.0, 2 and 2 took 27.7).  Calls of up to 8 rows: where the strips alone leave units idle (few_rows_slices).  The slices'
 // sums go to a workspace and this kernel adds them in slice order (deterministic), then does what
 // the fused epilogue does: residual add into h, (hi, lo) of h * gain of the next norm, per-strip
 // partial sums of h^2.  One workgroup per strip of 16 features: thread = (row, 4 features).
@@ -788,7 +788,13 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(Params p, const float
 static bool launch_resid_split(const Params &p, const GemmTuning &tn, const GemmArgs &a0, int kind, hipStream_t s) {
   const int n_strips = p.d / 16, KT = a0.K >> 5;
   int KS = tn.split_ks, nb = tn.big_blocks[kind];
-  if (a0.M <= 8 && KS) KS = tn.waves[kind] ? 1 : few_rows_slices(n_strips, a0.K, p.d, p.F, nb);
+  if (KS < 0 && a0.M > 8) KS = 4;
+  if (KS < 0 && tn.waves[kind]) KS = 1;  // a launch shape of the whole product was asked for
+  if (KS < 0) {
+    int best = 0;
+    KS = few_rows_slices(n_strips, a0.K, p.d, p.F, best);
+    if (!nb) nb = best;
+  }
   if (KS < 2) return false;
   GemmArgs a = a0;
   // K need not divide evenly, the last slice holds what is left (40 rows, down of d 4096, K 9408, 294 k-tiles: 22.5 us in

@@ -1624,9 +1624,12 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   // "tune.*": sweep knobs for development, not part of the stable interface (listed here only)
   //   tune.gemm_cfg       launch shape of the decode-sized matrix-core GEMMs of this context:
   //                       kind * 10000 + wavefronts * 100 + unroll (kind 0 QKV, 1 Wo, 2 gate/up, 3 LM head, 4 down;
-  //                       wavefronts 4/8/16; unroll 1/2/4); calls with more than 8 rows: 1000000 + kind * 10000 +
-  //                       400 + blocks (strips of 16 output features, or gate / up pairs, per workgroup, 0..8);
-  //                       2000000 + K slices of the split residual GEMM (0 = never split)
+  //                       wavefronts 4/8/16; unroll 1/2/4): calls of up to 8 rows, one block per workgroup, K whole unless
+  //                       slices are set as well; calls with more than 8 rows and, of any number, the residual GEMMs
+  //                       where they run in slices of K: 1000000 + kind * 10000 +
+  //                       400 + blocks (strips of 16 output features, or gate / up pairs, per workgroup, 0..8, 0 = by cost);
+  //                       2000000 + K slices of the residual GEMMs, 0..8 (0 and 1 = whole K; until it is set, 4, and by
+  //                       cost for calls of up to 8 rows)
   //   tune.prefill_rows   prompt rows per pass of the tiled prompt pass (a multiple of 128)
   //   tune.prefill_tile   query rows per attention workgroup of the tiled prompt pass (0, 16, 32, 128)
   //   tune.prefill_block  (1 .. 64) * 100 + row tiles of a panel of the tiled GEMMs' tile order (0 = 1024 rows)
@@ -1635,7 +1638,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   //                       3 = 192 x 128 and as many slices, 4 = 256 x 128 in two slices, 5 = 192 x 128
   if (!strcmp(name, "tune.gemm_cfg")) {
     if (value >= 2000000) {
-      if (c->tuning.set_split(value - 2000000)) return fail(c, PASS_EINVAL, "tune.gemm_cfg (split residual GEMM): 0 .. 8 slices of K");
+      if (c->tuning.set_split(value - 2000000)) return fail(c, PASS_EINVAL, "tune.gemm_cfg (residual GEMMs): 0 .. 8 slices of K");
     } else if (value >= 1000000) {
       int v = value - 1000000;
       if (c->tuning.set_big(v / 10000, (v / 100) % 100, v % 100))

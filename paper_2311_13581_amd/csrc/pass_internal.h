@@ -200,8 +200,8 @@ void launch_assemble_mfma(const Params &p, const void *tok_emb, const void *look
 // 3 LM head, 4 down.  The "tune.gemm_cfg" option writes it (see pass_set_option in pass_api.hip).
 struct GemmTuning {
   int waves[5], unroll[5];          // calls of up to 8 rows: wavefronts per workgroup (0 = by strip count), k-tiles per trip
-  int big_blocks[5];                // calls with more than 8 rows: output blocks per workgroup (0 = by their count)
-  int split_ks;                     // K slices of the split residual GEMMs (0 = never split)
+  int big_blocks[5];                // calls with more than 8 rows, and residual GEMMs in slices of K: output blocks per workgroup (0 = by cost)
+  int split_ks;                     // K slices of the residual GEMMs, as far as the workspace holds their sums (0, 1 = whole K, -1 = by cost)
   GemmTuning();
   int set(int kind, int w, int u);            // wavefronts 4/8/16, k-tiles per trip 1/2/4; -1 = rejected
   int set_big(int kind, int w, int blocks);   // blocks 0..8 (wavefronts: 4/8/16 accepted, no effect)

@@ -418,6 +418,34 @@ def test_few_row_gemm_shapes(d, heads, ffn, vocab, k):
     g.close()
 
 
+def test_slices_of_the_residual_products_as_asked_for():
+    """One, five and eight rows: the residual products take the number of K slices and of strips per workgroup that was set (three
+    to eight slices of 257 and 20 k-tiles, the last one shorter; more strips than a matrix has; 0 and 1 slices are the whole K, the same bits),
+    beside an asked-for launch shape of the whole product too.  Against the oracle."""
+    for k in (0, 4, 7):
+        shape = synth.ModelShape(1, 544, 5, 128, 8224, 528, dtype=synth.BF16)
+        W = synth.make_weights(shape, 9, k, 6.0)
+        m = O.Model(shape, W, k)
+        prompt = np.random.default_rng(k).integers(0, shape.vocab, 5).astype(np.int32)
+        logits = {}
+        for slices, blocks, shaped in ((0, 0, 0), (1, 0, 0), (1, 3, 0), (2, 1, 0), (3, 0, 0), (3, 8, 0), (5, 3, 0), (8, 6, 0), (8, 2, 1)):
+            g = _gpu(shape, W, k, max_seq_len=64, page_size=32)
+            g.set_option("tune.gemm_cfg", 2000000 + slices)
+            for kind in (1, 4):
+                g.set_option("tune.gemm_cfg", 1000000 + kind * 10000 + 400 + blocks)
+                if shaped:
+                    g.set_option("tune.gemm_cfg", kind * 10000 + 401)
+            st = parity.stepwise_parity(g, m, 0, 2, prompt, 2, 0.9, 777, parity.LOGIT_TOL[synth.BF16], max_len=64)
+            parity.check_stats(st, 2, parity.ERR_BF16_SMALL)
+            g.prefill(0, prompt)
+            g.draft([0], 0.0, 1)
+            logits[slices, blocks] = g.get_logits(0, 0).copy()
+            g.close()
+        same = lambda a, b: np.array_equal(logits[a], logits[b])
+        assert same((0, 0), (1, 0)) and same((0, 0), (1, 3)) and same((3, 0), (3, 8))
+        assert not any(same((0, 0), x) for x in ((2, 1), (3, 0), (5, 3), (8, 6), (8, 2))) and not same((3, 0), (5, 3))
+
+
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("d,heads,hd,ffn,vocab,slots,k", [
     (8, 1, 64, 8, 3, 1, 0), (72, 3, 64, 40, 257, 1, 1), (256, 4, 64, 504, 130, 1, 3), (504, 2, 128, 520, 77, 2, 3),
