@@ -328,7 +328,7 @@ int pass_set_option(pass_ctx *ctx, const char *name, int value);
 
 /* Timed replay of one drafting-shaped step on the given slots without changing any sequence
  * state (no sampling state is committed): returns the mean device milliseconds of `iters`
- * steps after `warmup`.  Used by the benchmark to time the dominant kernels in isolation. */
+ * steps after `warmup` (with the "graph" option at least two, so that only replays are timed).  Used by the benchmark to time the dominant kernels in isolation. */
 int pass_time_step(pass_ctx *ctx, const int32_t *slots, int n_slots, int warmup, int iters,
                    double *out_ms);
 

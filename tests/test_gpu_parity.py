@@ -312,6 +312,22 @@ def test_graph_replay_equals_eager_launches():
         assert np.array_equal(a, b)
 
 
+def test_timed_steps_are_replays():
+    """What pass_time_step times with graphs on is replays, whatever warm-up is asked for: a shape's first launch and its capture
+    come before the clock starts (here they would add between a third and twice the time of a replay)."""
+    W = synth.make_weights(TINY.shape, TINY.seed, 2, TINY.lm_head_scale)
+    for warmup in (0, 1):
+        ratio = []
+        for _ in range(5):
+            g = _gpu(TINY.shape, W, 2, max_seq_len=64, options={"graph": 1})
+            g.prefill(0, np.arange(20, dtype=np.int32))
+            fresh = g.time_step([0], warmup, 1)
+            ratio.append(fresh / min(g.time_step([0], 4, 1) for _ in range(4)))
+            g.close()
+        print("warm-up", warmup, "first call over replays", ratio)
+        assert np.median(ratio) < 1.2
+
+
 @pytest.mark.parametrize("temp", [0.0, 0.9])
 @pytest.mark.parametrize("plen", [5, 70, 200])
 def test_matrix_core_attention(temp, plen):
