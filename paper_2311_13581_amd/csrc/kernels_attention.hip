@@ -241,7 +241,7 @@ template <int I> struct yes_c { static constexpr int value = I; };
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void attn_split_mfma_kernel(Params p, int layer, int R, int direct) {
   constexpr int HD = 128, RQ = kAttnRowsPerGroup;
   __shared__ float s_m[4][RQ], s_l[4][RQ];
-  __shared__ float s_acc[4][RQ][HD];
+  __shared__ __align__(16) float s_acc[4][RQ][HD];
 
   const int split = blockIdx.x, head = blockIdx.y, grp_id = blockIdx.z;
   const int groups_per_slot = (R + RQ - 1) / RQ;

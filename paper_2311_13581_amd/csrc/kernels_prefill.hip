@@ -497,7 +497,7 @@ template <int RG>  // groups of 16 rows per workgroup
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_kernel(Params p, PrefillWs w, int layer, PrefillAttn a) {
   constexpr int HD = 128, RQ = 16 * RG;
   __shared__ float s_m[3][RQ], s_l[3][RQ];
-  __shared__ float s_acc[3][RQ][HD];
+  __shared__ __align__(16) float s_acc[3][RQ][HD];
 
   constexpr int SUB = kPrefillBlockRows / RQ;
   const int blk = blockIdx.x / SUB, first = (SUB - 1 - blockIdx.x % SUB) * RQ;  // rows with the most keys first
