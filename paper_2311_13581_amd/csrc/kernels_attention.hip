@@ -185,8 +185,8 @@ __global__ __launch_bounds__(256) void attn_split_kernel(Params p, int layer, in
     float m_n = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NG; ++w) m_n = fmaxf(m_n, s_m[w][r]);
-    // Pair by pair: sixteen additions one after the other round a sum over 192 keys more often than three splits and their merge
-    // did (outputs' distance from 64 bits at 184 keys of about the same probability: three splits 1.49e-7, one 1.60e-7, now 1.46e-7; the time is the same).
+    // Pair by pair, which rounds less than sixteen additions one after the other (outputs' distance from 64 bits where keys are about
+    // equally probable, fp32: 44 keys 1.58e-7 and 1.41e-7, 604 keys 1.44e-7 and 1.39e-7) in the same time.
     float lw[NG], vw[NG];
 #pragma unroll
     for (int w = 0; w < NG; ++w) {

@@ -44,10 +44,11 @@ inline int max_splits_mfma(int max_keys, int n_heads) {
   return best;
 }
 
-// Splits of the lane-per-key kernel: 64 keys (one iteration of a workgroup) each, but one up to 192 keys, where the rows leave
-// the split kernel finished: a further iteration costs less than the merge kernel.
+// Splits of the lane-per-key kernel: 64 keys (one iteration of a workgroup) each.  Keeping more keys in one split, whose rows leave
+// the split kernel finished, does not pay: an iteration costs what the merge kernel does, and beside longer sequences that
+// kernel runs all the same (a drafting step of five rows, two fp32 layers of d 256, in splits of 64 keys and with up to 192 in one:
+// 96 keys 60.4 us and 60.8, 188 keys 60.9 and 66.7; sequences of 150, 60, 300 and 100 keys together 100.4 and 109.5).
 __host__ __device__ inline int plain_splits(int n_keys) {
-  if (n_keys <= 192) return 1;
   const int n = (n_keys + 63) / 64;
   return n < kMaxSplits ? n : kMaxSplits;
 }

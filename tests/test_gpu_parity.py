@@ -331,7 +331,7 @@ def test_timed_steps_are_replays():
 @pytest.mark.parametrize("temp", [0.0, 0.9])
 @pytest.mark.parametrize("plen", [5, 70, 200])
 def test_matrix_core_attention(temp, plen):
-    """bf16, head_dim 128, 64-position pages: the MFMA attention kernel over transposed V pages
+    """bf16, head_dim 128, 64-position pages: the MFMA attention kernel over tiled K/V pages
     (prompt lengths below one 32-key block, inside one step, and over several splits), against the
     oracle, and against the lane-per-key kernel on the same model ("attention" option)."""
     w = MFMA_HD128
@@ -519,9 +519,9 @@ def test_attention_with_one_split(path, plen):
 
 @pytest.mark.parametrize("w", [TINY, TINY_BF16, MFMA_HD128], ids=["fp32", "bf16", "hd128"])
 @pytest.mark.parametrize("plen", [125, 180, 186, 193])
-def test_generic_attention_with_one_split_of_several_iterations(w, plen):
-    """The generic path keeps up to 192 keys in one split of three iterations: inside it, across the line while the sequence
-    grows, and above it."""
+def test_generic_attention_with_two_to_four_splits(w, plen):
+    """The generic path's splits of 64 keys: two, three and four of them, and across the line between three and four while the
+    sequence grows."""
     W = synth.make_weights(w.shape, w.seed, w.k, w.lm_head_scale)
     m = O.Model(w.shape, W, w.k)
     prompt = np.random.default_rng(plen).integers(0, w.shape.vocab, plen).astype(np.int32)
@@ -529,6 +529,20 @@ def test_generic_attention_with_one_split_of_several_iterations(w, plen):
     st = parity.stepwise_parity(g, m, 0, 2, prompt, 4, 0.9, 777, parity.LOGIT_TOL[w.shape.dtype], max_len=256)
     parity.check_stats(st, 4, parity.ERR_F32 if w.shape.dtype == synth.F32 else parity.ERR_BF16_SMALL)
     g.close()
+
+
+@pytest.mark.parametrize("heads,hd", [(4, 64), (2, 128)])
+def test_generic_attention_takes_no_longer_for_fewer_keys(heads, hd):
+    """A drafting step on 154 keys takes no longer than one on 224 (three splits and four, each of one iteration)."""
+    shape = synth.ModelShape(2, 256, heads, hd, 688, 512, dtype=synth.F32)
+    g = _gpu(shape, synth.make_weights(shape, 3, 4, 8.0), 4, max_seq_len=256, options={"graph": 1})
+    ms = []
+    for n in (150, 220):
+        g.prefill(0, np.arange(n, dtype=np.int32))
+        ms.append(min(g.time_step([0], 5, 100) for _ in range(5)))
+    g.close()
+    print("ms a step on 154 and 224 keys", ms)
+    assert ms[0] < 1.04 * ms[1]
 
 
 @pytest.mark.parametrize("temp,k,slots", [(0.0, 4, 2), (0.0, 15, 1), (0.9, 0, 3), (0.9, 6, 2), (1.0, 15, 2)])

@@ -111,8 +111,8 @@ def as_splits(v):
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("n", [100, 150, 184])
 def test_sums_of_the_generic_attention(n, hd):
-    """65 to 192 keys share one split of the generic attention: its sums over the keys lose no more than splits of 64 keys
-    would.  Queries are zero, so a drafting call's attention output is the mean of the prompt's values (positive ones, each a feature of the token's
+    """The generic attention's sums over 65 to 192 keys lose no more than a running sum for every sixteenth key of a split of 64, these
+    added one by one, and the splits' after them would.  Queries are zero, so a drafting call's attention output is the mean of the prompt's values (positive ones, each a feature of the token's
     embedding) and the pending token's zeros, and the LM head reads it off; a factor common to all features (the final norm's) is taken
     out.  Bound: the same sums in 32 bits as splits, followed by the three roundings on the way out (division, norm, their product)."""
     from paper_2311_13581_amd import binding
