@@ -605,34 +605,37 @@ int GemmTuning::set_split(int ks) {
 struct FewShape { int w, u, nb; };
 static FewShape few_rows_shape(int epi, int n) {
   switch (epi) {
-    case EPI_QKV:  // one workgroup a unit, or two (d 5120: 960 strips, four a workgroup 26.0 us, one in workgroups of 4
-                   // wavefronts 28.5; 4096: 17.8 and, of 8, 18.6; 2048: 7.2 and 11.0; 1024: 4.5 and 6.6)
+    case EPI_QKV:  // one workgroup a unit, or two (d 5120: 960 strips, four a workgroup 25.8 us, one in workgroups of 4
+                   // wavefronts 31.3; 4096: 17.7 and, of 8, 20.4; 2048: 7.2 and 7.9; 1024: 4.5 and 5.2)
       if (n <= 256) return {8, 2, 1};
       if (n <= 512) return {4, 2, 2};
       if (n <= 768) return {8, 2, 3};
       if (n <= 1024) return {8, 1, 4};
-      return {n % 256 ? 4 : 8, 1, 1};
+      return {n % 256 ? 4 : 8, 1, 1};  // two rounds and more: one strip as ever (d 6144, 1152 strips, 46.6 us; three a workgroup 40.3)
     case EPI_GATEUP:
-    case EPI_GATEUP_SAVE:  // (against one pair and one tile a trip in workgroups of 4: d 5120, 864 pairs 43.6 us and 47.0; 4096, 588
-                           // pairs 25.6 and 26.6; 2048, 344 pairs 9.9 and 11.6; 1024, 172 pairs 4.7 and 6.7)
+    case EPI_GATEUP_SAVE:  // (against one pair and one tile a trip in workgroups of 4, us: d 1024, 172 pairs 4.7 and 5.1; 2048, 344 9.8
+                           // and 10.3, 448 11.4 both; 3072, 440 15.8 both; 4096, 588 25.5 and 30.8; 5120, 860 43.7 and 49.4, 1120 59.6 and
+                           // 61.2; 8192, 1792 137 and 142)
       if (n <= 256) return {4, 2, 1};
       if (n <= 384) return {4, 1, 2};
       if (n <= 512) return {4, 1, 1};
       if (n <= 768) return {8, 1, 3};
       if (n <= 1024) return {8, 1, 4};
       return {8, 2, 1};
-    case EPI_LOGITS:  // many rounds: two strips share the activation tile (V 32000: 41.4 us, one strip 47.8; d 5120 51.5 and 59.0)
+    case EPI_LOGITS:  // many rounds: two strips share the activation tile (V 32000: 41.3 us, one strip of 16 wavefronts 47.0; d 5120 51.4
+                      // and 58.2; d 1024, V 2000, 125 strips, one a workgroup of 8: 3.7 and 3.8)
       return n <= 256 ? FewShape{8, 2, 1} : FewShape{4, 2, 2};
-    default:  // Wo and down: 16 features a workgroup while there are units for them (d 4096: Wo 8.1 us, 16 wavefronts 8.6; 2048:
-              // 5.0 and, of 8 with one tile a trip, 6.5), two strips beyond (d 5120, 320 strips: Wo 12.7 us, one strip 14.2)
+    default:  // Wo and down: 16 features a workgroup while there are units for them (d 4096: Wo 8.2 us, 16 wavefronts 8.7; 2048:
+              // 5.0 and, of 8 with one tile a trip, 5.1), two strips beyond (d 5120, 320 strips: Wo 12.6 us, one strip 15.8; d 8192, 512: 25.6 and 25.1)
       return n <= 256 ? FewShape{8, 4, 1} : FewShape{16, 1, 2};
   }
 }
 // Slices of K of Wo and down in calls of up to 8 rows, and strips per workgroup; 1 = whole K.  Fewer strips than units leave
 // units idle, 257 to 511 strips give some of them two: then the product is bound by those, and slices over all of them pay for
-// the kernel that adds their sums.  In us, fitted to 81 shapes (d 1024 .. 6144, K 1024 .. 21504; worst choice 8 % off): a unit
-// takes 0.033 us per KB of weights and 0.010 per KB of activation tile, the chip 6.9 TB/s, both kernels together 5.2.
-// d 5120, K 13824: 33.5 us whole in one strip a workgroup, 28.8 in two, 25.3 in four slices of five; d 2048, K 5632: 9.7 and 8.2.
+// the kernel that adds their sums.  In us, fitted to d 1024 .. 5120 (K up to 3.5 d): a unit takes 0.033 us per KB of weights and 0.010
+// per KB of activation tile, the chip 6.9 TB/s, both kernels together 5.2.  The choice is within 9 % of the fastest there, within 6 % at
+// d 6656 and 8192; d 6144 (384 strips) stays whole where two slices of three strips would take 10 % less (one K in six 21 %).
+// d 5120, K 13760: 38.0 us whole in one strip a workgroup, 28 in two, 25.6 in slices; d 2048, K 5504: 9.4 and 8.1.
 static int few_rows_slices(int n, int K, int d, int F, int &nb_best) {
   const int KT = K / 32;
   const float whole = n <= 256 ? 2.8f + K * (1.1e-3f + 0.7e-6f * n) : 3.0f + ((n + 1) / 2 + 255) / 256 * K * 1.97e-3f;

@@ -116,9 +116,9 @@ struct pass_ctx {
   int row_base = 0;  // SampleArgs::row_base of the calls issued now (pass_sps_iteration's drafting steps)
   std::map<GraphKey, hipGraphExec_t> graphs;  // null: launched once, not captured yet
   int opt_kernel_timing = 0;
-  GemmTuning tuning;
+  GemmTuning tuning;  // launch shapes of the decode GEMMs (captured graphs carry them: cleared when it changes)
   TrainWs train;
-  float *train_loss_host = nullptr;  // pinned [kMaxRows]  // launch shapes of the decode GEMMs (captured graphs carry them: cleared when it changes)
+  float *train_loss_host = nullptr;  // pinned [kMaxRows]
   int opt_prefill_chunk = 64;
   int opt_prefill_tiled = -1;  // -1: prompts of more than kTiledMinRows rows take the tiled pass; 0 never; 1 always
   Params PP;                   // P with the row buffers of the tiled prompt pass
@@ -477,8 +477,9 @@ std::vector<PlanSeg> plan_prefill(int cap, const int32_t *lens, int n) {
 // kernels holds never; in between it depends on how they pack, because every prompt starts on a block of 128 rows and a pass
 // holds no more than max_seq_len allows.  Priced per layer in us, between a layer of 26 MB (d 1024) and a 7B one of 405 MB:
 // a call of the decode kernels 42 .. 97 and up to 1.5 a row beyond 16, a tiled pass 64 .. 90 and 10 .. 90 a block.  Measured, four layers,
-// one by one against shared: 7B, two prompts of 33 rows 1.01 ms against 1.23 in two passes, 1.04 in one; eight of 9 rows 3.15
-// against 4.85 in eight passes, 3.32 in one; four of 29 rows 1.91 against 1.70 in one; d 1024, eight of 9 rows 1.47 against 0.78.
+// one by one against shared: 7B, two prompts of 33 rows 0.98 ms against 1.20 in two passes; eight of 9 rows 3.08 against 4.84 in eight
+// passes, 3.17 in one; four of 29 rows 1.79 against 1.74 in one, 1.96 in two; d 1024, eight of 9 rows 1.26 against 0.58.  (Two of 33 rows in
+// one pass would take 0.94 ms, d 2048 0.50 instead of 0.57: the prices, older than the attention's one launch per pass, say the opposite.)
 bool batch_takes_tiles(const Params &p, const int32_t *lens, int n, int chunk, int cap) {
   const double w = (4.0 * p.d * p.D + 3.0 * p.d * p.F) / 202.4e6;  // a layer's weights, in those of a 7B model
   auto tiled_us = [&](int rows) { return (10 + 80 * w) * ((rows + kPrefillBlockRows - 1) / kPrefillBlockRows); };

@@ -45,9 +45,10 @@ inline int max_splits_mfma(int max_keys, int n_heads) {
 }
 
 // Splits of the lane-per-key kernel: 64 keys (one iteration of a workgroup) each.  Keeping more keys in one split, whose rows leave
-// the split kernel finished, does not pay: an iteration costs what the merge kernel does, and beside longer sequences that
-// kernel runs all the same (a drafting step of five rows, two fp32 layers of d 256, in splits of 64 keys and with up to 192 in one:
-// 96 keys 60.4 us and 60.8, 188 keys 60.9 and 66.7; sequences of 150, 60, 300 and 100 keys together 100.4 and 109.5).
+// the split kernel finished, does not pay: an iteration of five rows costs what the merge kernel does, and beside longer sequences
+// that kernel runs all the same (a drafting step of five rows, two fp32 layers of d 256, in splits of 64 keys and with up to 192 in
+// one: 96 keys 60.4 us and 60.6, 188 keys 60.9 and 66.3; sequences of 150, 60, 300 and 100 keys together 100.0 and 108.9.  Three rows:
+// 96 keys alone 51.9 and 50.4, beside 300 keys 58.6 and 61.1).
 __host__ __device__ inline int plain_splits(int n_keys) {
   const int n = (n_keys + 63) / 64;
   return n < kMaxSplits ? n : kMaxSplits;
@@ -242,7 +243,7 @@ struct PrefillWs {
   int panel;      // row tiles of a panel of the GEMMs' tile order; 0 = 1024 rows
   float *part;    // sums over slices of K: part_floats floats
   size_t part_floats;
-  int attn_rows;  // query rows of an attention workgroup: 16, 32 or 128 (0 = 128 for passes of more than 512 rows, else 32)
+  int attn_rows;  // query rows of an attention workgroup: 16, 32 or 128 (0 = by a sequence's rows in the pass, prefill_attn_shared)
   float *q;       // [rows][D] rotated queries
 };
 // Whose rows a tiled pass carries: the pass is cut into blocks of 128 rows, block i holds `rows[i]` prompt rows
@@ -266,8 +267,8 @@ struct PrefillAttn {
       rows[kPrefillRows / kPrefillBlockRows];
 };
 // 128 rows per workgroup with shared K/V tiles once a sequence's rows in a pass are enough for the traffic out of L2 to matter
-// (measured: equal at 512 rows, -4 % of the pass at 2048, -7 % at 4096); by the sequence's own rows, so that its arithmetic cannot
-// depend on what shares the pass
+// (measured: equal at 512 rows, -4 % of the pass at 2048, -7 % at 4096).  By the sequence's rows in this pass, not by all rows of the pass;
+// how a long prompt is cut where others share its passes decides those, and with them the order of its sums
 inline bool prefill_attn_shared(const PrefillWs &w, int rows) { return w.attn_rows == 128 || (w.attn_rows == 0 && rows > 512); }
 void launch_prefill_attention(const Params &p, const PrefillWs &w, int layer, const PrefillAttn &a, bool shared, hipStream_t s);
 // returns the number of partial sums of h^2 per row it leaves (PrefillWs::np of the next launches)
