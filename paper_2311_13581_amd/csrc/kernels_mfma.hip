@@ -439,7 +439,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
   gemm_finish<1, EPI, WAVES, NB, NS, 1>(p, a, sum, red, NS * 64, red_ss, strip0);
 }
 
-// Calls with more than 8 rows: the same product with both operands in LDS rings.  Such a call pulls two to three times
+// Calls with more than 8 rows (and slices of K of any call): the same product with both operands in LDS rings.  Such a call pulls two to three times
 // the weights' bytes out of L2 as activation rows, every workgroup all of its rows once, and through registers a compute
 // unit draws no more than 36 B per clock whatever is in flight (measured); copies from memory to LDS run at 59.
 // Every wavefront owns a ring of D stages of one k-tile (its NS weight tiles and MT activation groups, 1 KB each), fills
