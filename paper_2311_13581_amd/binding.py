@@ -17,7 +17,7 @@ LIB_PATH = os.path.join(_HERE, "libpass_hip.so")
 PASS_F32, PASS_BF16 = 0, 1
 MAX_K, MAX_ROWS = 15, 64
 
-SYMBOLS = ["pass_arena_bytes", "pass_create", "pass_load_weights", "pass_prefill", "pass_prefill_batch", "pass_release",
+SYMBOLS = ["pass_arena_bytes", "pass_create", "pass_load_weights", "pass_coded_bytes", "pass_coded_begin", "pass_prefill", "pass_prefill_batch", "pass_release",
            "pass_draft", "pass_draft_static", "pass_verify", "pass_generate", "pass_sps_iteration", "pass_run_iterations", "pass_kernel_time", "pass_plain_read", "pass_rng_uniforms", "pass_get_logits", "pass_seq_len",
            "pass_train_bytes", "pass_train_begin", "pass_train_step", "pass_train_read", "pass_train_resume", "pass_set_option", "pass_attention_plan", "pass_prefill_plan", "pass_get_tokens", "pass_time_step", "pass_last_error", "pass_destroy"]
 
@@ -82,6 +82,9 @@ def load_library():
     L.pass_arena_bytes.argtypes = [C.POINTER(PassConfig)]
     L.pass_create.argtypes = [C.POINTER(PassConfig), C.c_void_p, C.c_void_p, C.c_size_t, C.POINTER(C.c_void_p)]
     L.pass_load_weights.argtypes = [C.c_void_p, C.POINTER(PassWeights), C.c_int]
+    L.pass_coded_bytes.restype = C.c_size_t
+    L.pass_coded_bytes.argtypes = [C.c_void_p]
+    L.pass_coded_begin.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t]
     L.pass_prefill.argtypes = [C.c_void_p, C.c_int, C.c_uint32, ip, C.c_int]
     L.pass_prefill_batch.argtypes = [C.c_void_p, ip, C.POINTER(C.c_uint32), ip, ip, C.c_int]
     L.pass_release.argtypes = [C.c_void_p, C.c_int]
@@ -184,6 +187,7 @@ class Pass:
         if rc != 0:
             raise PassError(rc, self.lib.pass_last_error(None).decode())
         self.h = h
+        self.coded = None
         # the logits of both calls of every slot, twice: a loop still holds an iteration's results while it reads the next one's
         self._logits = _Results((cfg.k + 1, cfg.vocab), 4 * cfg.max_slots)
         for name, val in (options or {}).items():
@@ -197,7 +201,7 @@ class Pass:
         if getattr(self, "h", None):
             self.lib.pass_destroy(self.h)
             self.h = None
-            self.arena = None
+            self.arena = self.coded = None
             self._logits.drop()
 
     def __del__(self):
@@ -239,6 +243,25 @@ class Pass:
             keep.append(arr)
             setattr(w, name, C.cast(arr, _PP))
         self._check(self.lib.pass_load_weights(self.h, C.byref(w), int(on_device)))
+        self._code_weights()
+
+    def _code_weights(self):
+        """The 12-bit copies for the small calls, where that leaves an eighth of the card's memory free (without them those calls
+        read the plain matrices)."""
+        torch = self._torch
+        self.coded = None
+        nbytes = self.lib.pass_coded_bytes(self.h)
+        free, total = torch.cuda.mem_get_info()
+        free += torch.cuda.memory_reserved() - torch.cuda.memory_allocated()
+        if nbytes == 0 or nbytes + total // 8 > free:
+            return
+        try:
+            ws = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+        except torch.OutOfMemoryError:  # free, but not in one piece
+            return
+        torch.cuda.synchronize()
+        self._check(self.lib.pass_coded_begin(self.h, C.c_void_p((ws.data_ptr() + 255) & ~255), nbytes))
+        self.coded = ws
 
     def prefill(self, slot: int, prompt, seq_id: int = 0):
         p = np.ascontiguousarray(prompt, dtype=np.int32)

@@ -93,6 +93,9 @@ struct pass_ctx {
   void *tok_emb, *lm_head, *final_norm, *lookahead, *staging;
   size_t staging_bytes;
   std::vector<LayerW> layers;
+  // matrix-core path, after pass_coded_begin: the LM head's coded copy, then wqkv, wo, wgu and wdown of every layer; else empty
+  std::vector<Coded> coded;
+  bool opt_coded = true;
   bool weights_loaded = false;
   bool use_mfma = false;  // matrix-core path active (set by pass_load_weights)
   int opt_graph = 0, opt_path = 0, opt_attn = 0;
@@ -261,6 +264,33 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   return (A.off + 255) & ~(size_t)255;
 }
 
+// The coded copies in the caller's workspace.  counts: what the coding counts, [matrices][128] exponents, then [matrices][2] of the
+// overflow lists.
+size_t carve_coded(const pass_config &c, char *base, std::vector<Coded> *out, uint32_t **counts) {
+  Arena A{base, 0};
+  const size_t d = c.d_model, D = (size_t)c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
+  std::vector<Coded> coded;
+  bool any = false;
+  auto add = [&](size_t N, size_t K) {
+    Coded z{};
+    // small products are bound by their start (d 1024: QKV 4.4 us on plain tiles and 4.6 on coded ones, gate/up of 448 strips 5.0
+    // and 5.2; but LM heads of 500 and 1000 strips 5.1 and 4.9, 7.6 and 6.8; d 2048, 63 strips 4.7 and 4.6)
+    if (K >= 2048 || N * K >= (size_t)8000 * 1024) {
+      any = z.wanted = true;
+      z.tiles = A.take<char>(coded_tile_bytes(N, K));
+      z.fix = A.take<uint2>(coded_fix_words(N, K));
+      z.more_room = (uint32_t)coded_more_words(N, K);
+      z.more = A.take<uint32_t>(z.more_room);
+    }
+    coded.push_back(z);
+  };
+  add(V, d);
+  for (int l = 0; l < c.n_layers; ++l) { add(3 * D, d); add(d, D); add(2 * F, d); add(d, F); }
+  uint32_t *n = A.take<uint32_t>(coded.size() * 130);
+  if (out) { *out = coded; *counts = n; }
+  return any ? (A.off + 255) & ~(size_t)255 : 0;
+}
+
 size_t carve_train(const pass_config &c, bool mfma, char *base, TrainWs *out) {
   Arena A{base, 0};
   const size_t d = c.d_model, D = (size_t)c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab, L = c.n_layers, M = kMaxRows;
@@ -378,6 +408,41 @@ int choose_splits(const pass_ctx *c, int B, int R, int max_keys) {
   return plain_splits(std::max(1, max_keys));
 }
 
+// A matrix as the decode-sized products take it.  which: 0 the LM head, 1 + 4 * layer + 0 .. 3 wqkv, wo, wgu, wdown
+Matrix matrix(const pass_ctx *c, const void *tiles, int which) {
+  return Matrix{tiles, c->opt_coded && !c->coded.empty() && c->coded[which].on ? c->coded[which] : Coded{}};
+}
+
+// The coded copies of all matrices: a table each, then the tiles.  A matrix that its table suits badly (the overflow list does not
+// take what lies outside: every tile of it would wait for its fixes) is left without.
+int code_weights(pass_ctx *c, std::vector<Coded> &coded, uint32_t *counts) {
+  const size_t n = coded.size(), d = c->P.d, D = c->P.D, F = c->P.F, V = c->P.V;
+  struct Src { const void *p; size_t N, K; };
+  std::vector<Src> src{{c->lm_head, V, d}};
+  for (const LayerW &l : c->layers) {
+    src.push_back({l.wqkv, 3 * D, d}); src.push_back({l.wo, d, D});
+    src.push_back({l.wgu, 2 * F, d}); src.push_back({l.wdown, d, F});
+  }
+  uint32_t *used = counts + n * 128;
+  launch_fill_i32((int32_t *)counts, 0, n * 130, c->stream);
+  for (size_t i = 0; i < n; ++i)
+    if (coded[i].wanted) launch_exponents(src[i].p, src[i].N * src[i].K, counts + i * 128, c->stream);
+  HIP_TRY(c, hipGetLastError());
+  std::vector<uint32_t> host(n * 128);
+  HIP_TRY(c, hipMemcpyAsync(host.data(), counts, host.size() * 4, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  for (size_t i = 0; i < n; ++i) {
+    if (!coded[i].wanted) continue;
+    coded_table(host.data() + i * 128, &coded[i].lut0, &coded[i].lut1);
+    launch_code_tiles(src[i].p, coded[i], (int)src[i].N, (int)src[i].K, used + 2 * i, c->stream);
+  }
+  HIP_TRY(c, hipGetLastError());
+  HIP_TRY(c, hipMemcpyAsync(host.data(), used, n * 8, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  for (size_t i = 0; i < n; ++i) coded[i].on = coded[i].wanted && !host[2 * i + 1];
+  return PASS_OK;
+}
+
 // One model call on B*R rows.  logits_base == nullptr: no LM head (prefill).
 int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_keys, const int32_t *prefill_ids) {
   Params P = c->P;
@@ -401,14 +466,14 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
     launch_assemble_mfma(P, c->tok_emb, c->lookahead, c->layers[0].attn_norm, mode, B, R, s);
     for (int l = 0; l < P.L; ++l) {
       const LayerW &w = c->layers[l];
-      launch_gemm_qkv(P, c->tuning, w.wqkv, l, M, s);
+      launch_gemm_qkv(P, c->tuning, matrix(c, w.wqkv, 1 + 4 * l), l, M, s);
       launch_attention(P, dt, l, B, R, S, 1, s);
-      launch_gemm_resid(P, c->tuning, w.wo, P.attn_x, P.D, w.ffn_norm, M, s);
-      launch_gemm_gateup(P, c->tuning, w.wgu, M, s);
-      launch_gemm_resid(P, c->tuning, w.wdown, P.act_x, P.F,
+      launch_gemm_resid(P, c->tuning, matrix(c, w.wo, 2 + 4 * l), P.attn_x, P.D, w.ffn_norm, M, s);
+      launch_gemm_gateup(P, c->tuning, matrix(c, w.wgu, 3 + 4 * l), M, s);
+      launch_gemm_resid(P, c->tuning, matrix(c, w.wdown, 4 + 4 * l), P.act_x, P.F,
                         l + 1 < P.L ? c->layers[l + 1].attn_norm : c->final_norm, M, s);
     }
-    if (logits_base) launch_gemm_logits(P, c->tuning, c->lm_head, logits_base, M, s);
+    if (logits_base) launch_gemm_logits(P, c->tuning, matrix(c, c->lm_head, 0), logits_base, M, s);
   } else {
     launch_assemble(P, dt, c->tok_emb, c->lookahead, mode, B, R, s);
     for (int l = 0; l < P.L; ++l) {
@@ -429,7 +494,7 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
     HIP_TRY(c, hipEventRecord(c->kev[0], s));
     for (int l = 0; l < P.L; ++l) {
       if (c->use_mfma)
-        launch_gemm_gateup(P, c->tuning, c->layers[l].wgu, M, s);
+        launch_gemm_gateup(P, c->tuning, matrix(c, c->layers[l].wgu, 3 + 4 * l), M, s);
       else
         launch_row_gateup(P, dt, c->layers[l].ffn_norm, c->layers[l].wgu, M, s);
     }
@@ -784,6 +849,11 @@ int pass_load_weights(pass_ctx *c, const pass_weights *w, int on_device) {
     return fail(c, PASS_EINVAL, "null weight pointer");
   const size_t e = c->esz, d = c->P.d, D = c->P.D, F = c->P.F, V = c->P.V;
   c->train.on = false;  // a training set-up belongs to the weights it was made from (their packed transposes)
+  if (!c->coded.empty()) {  // so do the coded copies, and captured launches read them
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    drop_graphs(c);
+    c->coded.clear();
+  }
   const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
   auto cp = [&](void *dst, const void *src, size_t elems) -> int {
     if (!src) return fail(c, PASS_EINVAL, "null weight pointer");
@@ -848,6 +918,28 @@ int pass_load_weights(pass_ctx *c, const pass_weights *w, int on_device) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->weights_loaded = true;
   return PASS_OK;
+}
+
+size_t pass_coded_bytes(pass_ctx *c) {
+  return c && c->weights_loaded && c->use_mfma ? carve_coded(c->cfg, nullptr, nullptr, nullptr) : 0;
+}
+
+int pass_coded_begin(pass_ctx *c, void *device_workspace, size_t bytes) {
+  if (!c) return PASS_EINVAL;
+  if (!c->weights_loaded) return fail(c, PASS_ESTATE, "weights not loaded");
+  const size_t need = pass_coded_bytes(c);
+  if (!need) return fail(c, PASS_ESTATE, "this model has no matrices worth coding");
+  if (!device_workspace || ((uintptr_t)device_workspace & 255) || bytes < need)
+    return fail(c, PASS_EINVAL, "workspace null, misaligned or smaller than pass_coded_bytes");
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  drop_graphs(c);  // captured launches read the plain matrices, or copies in an earlier workspace
+  c->coded.clear();
+  std::vector<Coded> coded;
+  uint32_t *counts;
+  carve_coded(c->cfg, (char *)device_workspace, &coded, &counts);
+  const int rc = code_weights(c, coded, counts);
+  if (rc == PASS_OK) c->coded = coded;
+  return rc;
 }
 
 int pass_release(pass_ctx *c, int slot) {
@@ -1468,34 +1560,34 @@ int pass_train_step(pass_ctx *c, const int32_t *slots, int n_slots, const int32_
       P.qkv = T.save_qkv + (size_t)l * kMaxRows * 3 * D;
       P.attn_x = (uint16_t *)(T.save_attn + (size_t)l * kMaxRows * D);
       P.lse = T.save_lse + (size_t)l * kMaxRows * H;
-      launch_gemm_qkv(P, c->tuning, w.wqkv, l, M, s);
+      launch_gemm_qkv(P, c->tuning, matrix(c, w.wqkv, 1 + 4 * l), l, M, s);
       launch_attention(P, dt, l, n_slots, R, S, 1, s);
       P.h_out = T.save_h1 + (size_t)l * kMaxRows * d;
-      launch_gemm_resid(P, c->tuning, w.wo, P.attn_x, P.D, w.ffn_norm, M, s);
+      launch_gemm_resid(P, c->tuning, matrix(c, w.wo, 2 + 4 * l), P.attn_x, P.D, w.ffn_norm, M, s);
       P.h = P.h_out;
-      launch_gemm_gateup_save(P, w.wgu, T.save_gu + (size_t)l * kMaxRows * 2 * F, M, s);
+      launch_gemm_gateup_save(P, matrix(c, w.wgu, 3 + 4 * l), T.save_gu + (size_t)l * kMaxRows * 2 * F, M, s);
       P.h_out = l + 1 < P.L ? T.save_h0 + (size_t)(l + 1) * kMaxRows * d : T.save_hl;
-      launch_gemm_resid(P, c->tuning, w.wdown, P.act_x, P.F, l + 1 < P.L ? c->layers[l + 1].attn_norm : c->final_norm, M, s);
+      launch_gemm_resid(P, c->tuning, matrix(c, w.wdown, 4 + 4 * l), P.act_x, P.F, l + 1 < P.L ? c->layers[l + 1].attn_norm : c->final_norm, M, s);
       P.h = P.h_out;
     }
-    launch_gemm_logits(P, c->tuning, c->lm_head, T.logits, M, s);
+    launch_gemm_logits(P, c->tuning, matrix(c, c->lm_head, 0), T.logits, M, s);
     // ---- backward: every dx = W^T dy is a matrix-core product with the packed transpose; its input travels as
     // (hi, lo) tiles (T.x), its output as slices over the contraction (T.part) that the consumer adds up ----
     const size_t rows = kMaxRows;
     launch_ce_grad(T.logits, T.targets, loss_scale, T.row_loss, M, P.V, (float2 *)P.row_parts, T.x, s);
-    int KS = launch_gemm_plain(P, T.lm_head_t, T.x, M, (int)d, (int)V, T.part, s);
+    int KS = launch_gemm_plain(P, Matrix{T.lm_head_t, {}}, T.x, M, (int)d, (int)V, T.part, s);
     launch_rmsnorm_bwd(P, dt, T.save_hl, c->final_norm, T.part, KS, rows * d, T.dh, M, 0, T.x, s);
     for (int l = P.L - 1; l >= 0; --l) {
       const LayerW &w = c->layers[l], &t = T.layers_t[l];
-      KS = launch_gemm_plain(P, t.wdown, T.x, M, (int)F, (int)d, T.part, s);
+      KS = launch_gemm_plain(P, Matrix{t.wdown, {}}, T.x, M, (int)F, (int)d, T.part, s);
       launch_swiglu_bwd_tiles(P, T.save_gu + (size_t)l * kMaxRows * 2 * F, T.part, KS, rows * F, T.x, M, s);
-      KS = launch_gemm_plain(P, t.wgu, T.x, M, (int)d, (int)(2 * F), T.part, s);
+      KS = launch_gemm_plain(P, Matrix{t.wgu, {}}, T.x, M, (int)d, (int)(2 * F), T.part, s);
       launch_rmsnorm_bwd(P, dt, T.save_h1 + (size_t)l * kMaxRows * d, w.ffn_norm, T.part, KS, rows * d, T.dh, M, 1, T.x, s);
-      KS = launch_gemm_plain(P, t.wo, T.x, M, (int)D, (int)d, T.part, s);
+      KS = launch_gemm_plain(P, Matrix{t.wo, {}}, T.x, M, (int)D, (int)d, T.part, s);
       launch_attn_bwd(P, dt, l, n_slots, R, max_keys, T.save_qkv + (size_t)l * kMaxRows * 3 * D, (int)(3 * D), nullptr,
                       (const uint16_t *)(T.save_attn + (size_t)l * kMaxRows * D), T.save_lse + (size_t)l * kMaxRows * H, T.part, KS,
                       rows * D, T.dq_part, T.dqkv, T.x, s);
-      KS = launch_gemm_plain(P, t.wqkv, T.x, M, (int)d, (int)(3 * D), T.part, s);
+      KS = launch_gemm_plain(P, Matrix{t.wqkv, {}}, T.x, M, (int)d, (int)(3 * D), T.part, s);
       launch_rmsnorm_bwd(P, dt, T.save_h0 + (size_t)l * kMaxRows * d, w.attn_norm, T.part, KS, rows * d, T.dh, M, 1, T.x, s);
     }
   } else {
@@ -1631,6 +1723,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   //                       400 + blocks (strips of 16 output features, or gate / up pairs, per workgroup, 0..8, 0 = by cost);
   //                       2000000 + K slices of the residual GEMMs, 0..8 (0 and 1 = whole K; until it is set, 4, and by
   //                       cost for calls of up to 8 rows)
+  //   tune.coded          1 = the decode-sized products read the coded copies of the matrices that have one, 0 = the plain ones
   //   tune.prefill_rows   prompt rows per pass of the tiled prompt pass (a multiple of 128)
   //   tune.prefill_tile   query rows per attention workgroup of the tiled prompt pass (0, 16, 32, 128)
   //   tune.prefill_block  (1 .. 64) * 100 + row tiles of a panel of the tiled GEMMs' tile order (0 = 1024 rows)
@@ -1669,6 +1762,12 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   if (!strcmp(name, "prefill_tiled")) {
     if (value < -1 || value > 1) return fail(c, PASS_EINVAL, "prefill_tiled: -1 (by prompt length), 0 (never) or 1 (always)");
     c->opt_prefill_tiled = value;
+    return PASS_OK;
+  }
+  if (!strcmp(name, "tune.coded")) {
+    if (value < 0 || value > 1) return fail(c, PASS_EINVAL, "tune.coded: 0 or 1");
+    c->opt_coded = value;
+    drop_graphs(c);  // captured launches read the one or the other
     return PASS_OK;
   }
   if (!strcmp(name, "tune.prefill_rows")) {

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "pass.h"
 
 namespace pass {
@@ -194,6 +196,26 @@ void launch_rng_uniforms(float *out, uint32_t j0, int n, uint64_t seed, uint32_t
                          uint32_t row, uint32_t purpose, hipStream_t s);
 
 // matrix-core path (bf16, 16x32 weight tiles)
+// A matrix of packed tiles once more, in 12 bits a weight (kernels_mfma.hip); tiles null: there is no such copy
+struct Coded {
+  void *tiles;          // [strip][K/32][64 lanes][12 bytes]
+  uint2 *fix;           // [strip][fix_stride(K/32)]: weights of a tile that the table does not hold
+  uint32_t *more;       // [more_room]: those of tiles with more than two
+  uint32_t more_room;
+  uint32_t lut0, lut1;  // the table: eight values of the exponent's upper seven bits
+  bool wanted, on;      // the product is large enough to gain; the copy holds the matrix
+};
+// a weight matrix of the matrix-core path as the decode-sized products take it
+struct Matrix {
+  const void *tiles;
+  Coded coded;
+};
+inline size_t coded_tile_bytes(size_t N, size_t K) { return N * K / 2 * 3; }
+inline size_t coded_fix_words(size_t N, size_t K) { return N / 16 * ((K / 32 + 3) / 4 * 4); }
+void launch_exponents(const void *src, size_t weights, uint32_t *hist /*[128], added to*/, hipStream_t s);
+void coded_table(const uint32_t *hist, uint32_t *lut0, uint32_t *lut1);
+inline size_t coded_more_words(size_t N, size_t K) { return std::min<size_t>(N * K / 1024, (size_t)1 << 24); }
+void launch_code_tiles(const void *src, const Coded &z, int N, int K, uint32_t *counts /*[2], zero*/, hipStream_t s);
 void launch_pack_tiles(const uint16_t *src, uint16_t *dst, int N, int K, int strip_off, int strip_stride,
                        hipStream_t s);
 void launch_assemble_mfma(const Params &p, const void *tok_emb, const void *lookahead, const void *gain0, int mode,
@@ -209,10 +231,10 @@ struct GemmTuning {
   int set_big(int kind, int w, int blocks);   // blocks 0..8 (wavefronts: 4/8/16 accepted, no effect)
   int set_split(int ks);                      // 0..8
 };
-void launch_gemm_qkv(const Params &p, const GemmTuning &tn, const void *W, int layer, int M, hipStream_t s);
-void launch_gemm_resid(const Params &p, const GemmTuning &tn, const void *W, const uint16_t *X, int K,
+void launch_gemm_qkv(const Params &p, const GemmTuning &tn, const Matrix &W, int layer, int M, hipStream_t s);
+void launch_gemm_resid(const Params &p, const GemmTuning &tn, const Matrix &W, const uint16_t *X, int K,
                        const void *gain_next, int M, hipStream_t s);
-void launch_gemm_gateup(const Params &p, const GemmTuning &tn, const void *W, int M, hipStream_t s);
+void launch_gemm_gateup(const Params &p, const GemmTuning &tn, const Matrix &W, int M, hipStream_t s);
 // (hi, lo) activation buffers of the matrix-core path, K features per row, tiled like the MFMA B
 // operand: [m / 8][K / 32][64 lanes][8 features]; lane = (k / 8 % 4) * 16 + m % 8 for the hi half,
 // 8 lanes further for the lo half.  Element index of the hi half of feature k of row m:
@@ -276,12 +298,12 @@ int launch_prefill_resid(const Params &p, const PrefillWs &w, const void *W, con
                          const void *gain_next, int M, hipStream_t s);
 void launch_prefill_gateup(const Params &p, const PrefillWs &w, const void *W, int M, hipStream_t s);
 
-void launch_gemm_logits(const Params &p, const GemmTuning &tn, const void *W, float *logits, int M, hipStream_t s);
+void launch_gemm_logits(const Params &p, const GemmTuning &tn, const Matrix &W, float *logits, int M, hipStream_t s);
 
 // ---- look-ahead embedding training: matrix-core pieces (kernels_mfma.hip) ----
-void launch_gemm_gateup_save(const Params &p, const void *W, float *gu_save, int M, hipStream_t s);
+void launch_gemm_gateup_save(const Params &p, const Matrix &W, float *gu_save, int M, hipStream_t s);
 int plain_gemm_slices(int N, int K);
-int launch_gemm_plain(const Params &p, const void *W, const uint16_t *X, int M, int N, int K, float *part, hipStream_t s);
+int launch_gemm_plain(const Params &p, const Matrix &W, const uint16_t *X, int M, int N, int K, float *part, hipStream_t s);
 void launch_transpose_packed(const void *src, void *dst, int N, int K, hipStream_t s);
 // ---- look-ahead embedding training (kernels_train.hip) ----
 constexpr int kTrainSplits = 32;    // row slices of a transposed projection (partial sums: kTrainSplits x M x K floats)

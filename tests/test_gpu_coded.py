@@ -1,0 +1,156 @@
+"""The 12-bit copies of the weights (pass_coded_begin): what a product reads back out of them is bit for bit the plain weight, and
+the products that read them agree with the plain ones."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2311_13581_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+bits = synth.f32_to_bf16_bits
+
+
+def rounded(x):
+    return synth.bf16_bits_to_f32(bits(x)).reshape(np.shape(x))
+
+
+def random_weights(shape, k, seed, spread=0.0):
+    """Normal weights; spread > 0: with zeros, weights far below and far above the rest."""
+    rng = np.random.default_rng(seed)
+    d, F, V, H, L = shape.d_model, shape.d_ffn, shape.vocab, shape.n_heads * shape.head_dim, shape.n_layers
+
+    def m(r, c):
+        w = rng.standard_normal((r, c), dtype=np.float32) * np.float32(0.02)
+        u = rng.random((r, c), dtype=np.float32)
+        w[u < spread] = 0
+        w[u > 1 - spread / 8] *= 1e-6
+        w[(u > 0.5) & (u < 0.5 + spread / 200)] *= 300
+        return bits(w).reshape(r, c)
+
+    one = bits(np.ones(d, np.float32))
+    W = {"tok_emb": m(V, d), "lm_head": m(V, d), "final_norm": one, "lookahead": m(max(k, 1), d)[:k], "attn_norm": [one] * L, "ffn_norm": [one] * L}
+    for n, (r, c) in (("wq", (H, d)), ("wk", (H, d)), ("wv", (H, d)), ("wo", (d, H)), ("w_gate", (F, d)), ("w_up", (F, d)), ("w_down", (d, F))):
+        W[n] = [m(r, c) for _ in range(L)]
+    return W
+
+
+# strips: one, two, three and four a workgroup of the LM head, the last workgroup with fewer; the last: exponents all over, no copy
+@pytest.mark.parametrize("V,wide", [(2000, False), (6416, False), (10000, False), (15984, False), (2000, True)])
+def test_what_is_read_back(V, wide):
+    """Rows that are one-hot make a logit a weight of the LM head times the row's norm, which one weight of 1 gives."""
+    from paper_2311_13581_amd import binding
+    d, k, rng = 2048, 7, np.random.default_rng(V)
+    shape = synth.ModelShape(1, d, 1, 128, 32, V, dtype=synth.BF16)
+    z = lambda *s: bits(np.zeros(s, np.float32)).reshape(s)
+    head = rng.standard_normal((V, d)).astype(np.float32) * np.float32(0.02)
+    cols = np.array([0, 31, 32, 777, 1023, 1024, 2015, 2047])
+    special = np.array([0.0, -0.0, 2.0 ** -126, -2.0 ** -130, 1e30, -3e-20, 5.0, 2.0 ** -133], np.float32)
+    head[64:80, 992:1024] = special[rng.integers(0, 8, (16, 32))]  # a tile with (many) more than 128 weights outside ...
+    if not wide:
+        head[64:80, 992:1024] *= rng.random((16, 32)) < 0.15  # ... or some 60
+    head[V - 3:, cols] = special[rng.integers(0, 8, (3, 8))]
+    for r in rng.integers(0, V, 60):
+        head[r, cols[rng.integers(0, 8)]] = special[rng.integers(0, 8)]
+    head[1, cols] = 1
+    tok, la = np.zeros((V, d), np.float32), np.zeros((k, d), np.float32)
+    tok[3, cols[0]], la[np.arange(k), cols[1:]] = 1, 1
+    one = bits(np.ones(d, np.float32))
+    W = {"tok_emb": bits(tok).reshape(V, d), "lm_head": bits(head).reshape(V, d), "final_norm": one, "lookahead": bits(la).reshape(k, d),
+         "attn_norm": [one], "ffn_norm": [one], "wq": [z(128, d)], "wk": [z(128, d)], "wv": [z(128, d)], "wo": [z(d, 128)],
+         "w_gate": [z(32, d)], "w_up": [z(32, d)], "w_down": [z(d, 32)]}
+    g = binding.Pass(binding.make_config(shape, k, 1, 64, 64))
+    g.load_weights(W)
+    assert g.coded is not None
+    g.prefill(0, np.array([3], np.int32))
+    g.draft([0], 0.0, 1)
+    got = g.get_logits(0, 0)
+    g.close()
+    want = rounded(head)[:, cols].T
+    assert np.array_equal(got, want * got[:, 1:2])
+
+
+# blocks a workgroup of QKV (d 2048: 10 and 16 heads, 3072, 5120), of gate/up (F 3200, 5504, 9600, 14400), Wo and down whole on up to 256
+# strips, on more (5120), down in slices of K of the plain matrix (d 2048, F 9600)
+@pytest.mark.parametrize("d,heads,F,V,k,spread", [(2048, 10, 3200, 1008, 0, 0.002), (2048, 16, 5504, 4800, 4, 0.0), (3072, 24, 9600, 1008, 7, 0.002),
+                                                  (5120, 40, 14400, 1008, 4, 0.002), (2048, 16, 9600, 1008, 3, 0.004)])
+def test_coded_and_plain_products_agree(d, heads, F, V, k, spread):
+    """Both calls' logits on the copies and on the plain matrices.  The weights are the same, so only sums in another order and the
+    K/V rows that round the other way for it differ: 1e-4 of the logits, a fifth of what one weight in 2048 gone wrong would make."""
+    from paper_2311_13581_amd import binding
+    shape = synth.ModelShape(1, d, heads, 128, F, V, dtype=synth.BF16)
+    g = binding.Pass(binding.make_config(shape, k, 1, 128, 64), {"graph": 1})
+    g.load_weights(random_weights(shape, k, d + F, spread))
+    assert g.coded is not None
+    prompt = np.random.default_rng(1).integers(0, V, 40).astype(np.int32)
+    out = []
+    for coded in (0, 1, 1):
+        g.set_option("tune.coded", coded)
+        g.prefill(0, prompt)
+        g.draft([0], 0.0, 1)
+        d0 = g.get_logits(0, 0).copy()
+        g.verify([0], 0.0, 1)
+        out.append((d0, g.get_logits(0, 1).copy()))
+    g.close()
+    for a, b, c in zip(*out):
+        assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(a)
+        assert np.array_equal(b, c)
+
+
+def test_training_on_coded_matrices():
+    """A step of few rows (its gate/up product keeps the pre-activations): the gradient on the copies and on the plain matrices."""
+    from paper_2311_13581_amd import binding
+    shape, k = synth.ModelShape(1, 2048, 16, 128, 5504, 1024, dtype=synth.BF16), 3
+    W = random_weights(shape, k, 5, 0.002)
+    prompt, target = np.arange(50, dtype=np.int32), np.array([[5, 6, 7]], np.int32)
+    out = []
+    for coded in (0, 1):
+        g = binding.Pass(binding.make_config(shape, k, 1, 128, 64), {"tune.coded": coded})
+        g.load_weights(W)
+        g.train_begin(-1)
+        g.prefill(0, prompt)
+        loss = g.train_step([0], target, 0.01)
+        out.append((loss, g.train_read(1)))
+        g.close()
+    (l0, g0), (l1, g1) = out
+    assert abs(l0 - l1) <= 1e-5 * abs(l0) and np.linalg.norm(g0 - g1) <= 1e-4 * np.linalg.norm(g0)
+
+
+def test_workspace_of_the_copies():
+    """What pass_coded_begin refuses, and that loading weights again ends the use of the old copies (captured graphs too)."""
+    import torch
+    from paper_2311_13581_amd import binding
+    shape, k = synth.ModelShape(1, 2048, 2, 128, 2048, 1008, dtype=synth.BF16), 2
+    g = binding.Pass(binding.make_config(shape, k, 1, 128, 64), {"graph": 1})
+    assert g.lib.pass_coded_bytes(g.h) == 0 and g.lib.pass_coded_begin(g.h, None, 0) == -2  # no weights yet
+    prompt = np.arange(20, dtype=np.int32)
+
+    def logits():
+        g.prefill(0, prompt)
+        res = []
+        for _ in range(3):
+            g.draft([0], 0.0, 1)
+            g.verify([0], 0.0, 1)
+            res.append(g.get_logits(0, 1).copy())
+        return res
+
+    g.load_weights(random_weights(shape, k, 1))
+    n = g.lib.pass_coded_bytes(g.h)
+    ws = torch.empty(n + 512, dtype=torch.uint8, device="cuda")
+    base = (ws.data_ptr() + 255) & ~255
+    for p, b in ((0, n), (base + 64, n), (base, n - 1)):
+        assert g.lib.pass_coded_begin(g.h, C.c_void_p(p), b) == -1
+    first = logits()
+    g.load_weights(random_weights(shape, k, 2))
+    second = logits()
+    g.set_option("tune.coded", 0)
+    plain = logits()
+    g.close()
+    assert all(np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(b) for a, b in zip(second, plain))
+    assert not np.allclose(first[0], second[0])
+    small = binding.Pass(binding.make_config(synth.ModelShape(1, 512, 4, 128, 1184, 1008, dtype=synth.BF16), k, 1, 128, 64))
+    small.load_weights(random_weights(synth.ModelShape(1, 512, 4, 128, 1184, 1008, dtype=synth.BF16), k, 3))
+    assert small.coded is None and small.lib.pass_coded_bytes(small.h) == 0
+    assert small.lib.pass_coded_begin(small.h, C.c_void_p(base), n) == -2
+    small.close()
