@@ -303,6 +303,7 @@ __global__ __launch_bounds__(256) void assemble_mfma_kernel(Params p, const uint
   if (threadIdx.x == 0 && row_tables) {
     p.row_pos[m] = dead ? 0 : pos;
     p.row_slot[m] = dead ? -1 : slot;
+    p.row_page[m] = dead ? -1 : p.block_table[(size_t)slot * p.pages_per_seq + (pos >> p.page_shift)];
     p.row_out[m] = slot * (1 + p.k) + r;
   }
 }
@@ -335,169 +336,230 @@ struct GemmArgs {
   Coded z;                    // the matrix in its coded form, read in place of W where the kernel says so
 };
 
-// What follows the K loop, for the register and the LDS-ring form alike.  acc: this wavefront's sums over its k-tiles;
-// red: [WAVES] areas of `red_stride` 16-byte words, one of each wavefront's own, for the partial tiles of MB row groups; strip0: first strip
-// of the workgroup.
+// What follows the K loop, for the register and the LDS-ring form alike.  All that the epilogue reads from memory is requested
+// together and early (the register form: behind the first trip's requests; the ring form: behind the last tile): with one workgroup a
+// compute unit nothing else hides the trips.  One after the other they took, after the K loop, 1.9 us of the QKV product's 15.5 at 5 rows, 1.0 of
+// gate/up's 23.8, and at 40 rows 5.3 of 27.4 and 4.7 of 36.9.
+// MB: row groups whose partial tiles the areas of LDS take at a time.
 template <int MT, int EPI, int WAVES, int NB, int NS, int MB>
-__device__ __forceinline__ void gemm_finish(const Params &p, const GemmArgs &a, floatx4 (&acc)[NS][MT], floatx4 *red, int red_stride,
-                                            float (*red_ss)[MT][8], int strip0) {
-  constexpr int kGemmWaves = WAVES;
-  constexpr bool GU = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE);
-  constexpr int PER = GU ? 2 : 1;  // strips per block
-  constexpr bool NORM = (EPI != EPI_RESID && EPI != EPI_PARTIAL);
+struct Epilogue {
+  static constexpr bool GU = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE);
+  static constexpr int PER = GU ? 2 : 1;  // strips per block
+  static constexpr bool NORM = (EPI != EPI_RESID && EPI != EPI_PARTIAL);
   static_assert(NS == NB * PER, "strips of a workgroup");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ml = lane & 15, g = lane >> 4;
-  // partial sums of h^2 (written by the producer of X) -> this wavefront's share.
-  // Lane (ml & 7) covers row mt*8 + (ml & 7); the two halves of the columns take alternate partials.
-  if constexpr (NORM) {
+  static constexpr int UNITS = (MB * NB + WAVES - 1) / WAVES;  // (row group, block) pairs of a wavefront per batch of row groups
+  // The partial sums of h^2 (written by the producer of X, [strip][kMaxRows]) in rounds.  Few rows: a value a lane and request, lane
+  // (ml & 7) has row ml & 7, the two halves of the columns and the four groups of lanes take alternate partials.  More rows: four rows a lane,
+  // 16 lanes a partial.
+  static constexpr int ASKED = NORM ? (MT == 1 ? 8 : 16) : 1;
+  static constexpr int ROUND = WAVES * 64;  // partials of a round, in either form
+  floatx4 norm[ASKED];
+  float2 cs[UNITS], sn[UNITS];  // QKV
+  int pos[UNITS], page[UNITS], out[UNITS];  // QKV; LOGITS
+  floatx4 h[UNITS];             // RESID
+  uint2 gain[UNITS];
+
+  // row and first feature of the wavefront's j-th unit of the batch that begins with row group mt0; false: there is none
+  __device__ __forceinline__ static bool unit(int j, int mt0, int strip0, int n_strips, int &mt, int &blk, int &strip) {
+    const int u = (threadIdx.x >> 6) + j * WAVES;
+    const int mb = u / NB;
+    blk = u - mb * NB;
+    mt = mt0 + mb;
+    strip = strip0 + blk * PER;
+    return u < MB * NB && mt < MT && strip < n_strips;
+  }
+  __device__ __forceinline__ void ask_norm(const Params &p, int round) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int NP = p.d / 16;
-    // requested in batches of 8 through a buffer descriptor (indices past the end read as zero):
-    // one trip to L2 per batch instead of one per partial
+    // through a buffer descriptor: indices past the end read as zero
     const __amdgpu_buffer_rsrc_t sr = __builtin_amdgcn_make_buffer_rsrc((void *)p.ssq, 0, NP * kMaxRows * 4, 0x00020000);
-    for (int mt = 0; mt < MT; ++mt) {
-      float ss = 0.f;
-      for (int i0 = wave * 8 + g * 2 + (ml >> 3); i0 < NP; i0 += kGemmWaves * 64) {
-        float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-              sr, ((i0 + u * kGemmWaves * 8) * kMaxRows + mt * 8 + (ml & 7)) * 4, 0, 0));
-#pragma unroll
-        for (int u = 0; u < 8; ++u) ss += v[u];
+    for (int u = 0; u < ASKED; ++u) {
+      if constexpr (MT == 1) {
+        const int i = round * ROUND + u * WAVES * 8 + wave * 8 + (lane >> 4) * 2 + ((lane >> 3) & 1);
+        norm[u][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sr, (i * kMaxRows + (lane & 7)) * 4, 0, 0));
+      } else {
+        const int i = round * ROUND + u * WAVES * 4 + wave * 4 + (lane >> 4), row = (lane & 15) * 4;
+        norm[u] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(sr, row < MT * 8 ? (i * kMaxRows + row) * 4 : 0x40000000, 0, 0));
       }
-      ss += __shfl_xor(ss, 8);
-      ss += __shfl_xor(ss, 16);
-      ss += __shfl_xor(ss, 32);
-      if (lane < 8) red_ss[wave][mt][lane] = ss;
     }
   }
-  // Per batch of 8-row groups (as many as the areas take): every wavefront posts its partial tiles, then the
-  // (row group, block) pairs are shared out: a wavefront reduces a pair's tiles in a fixed order, adds the lo columns to
-  // the hi columns and runs the fused epilogue.  Lanes with ml < 8 hold Y[m = mt*8 + ml][n0 + 4g .. 4g+3].
+  __device__ __forceinline__ void ask_units(const Params &p, const GemmArgs &a, int mt0, int strip0) {
+    const int lane = threadIdx.x & 63, g = lane >> 4;
 #pragma unroll
-  for (int mt0 = 0; mt0 < MT; mt0 += MB) {
-   if (mt0 > 0) __syncthreads();  // the previous batch has been read
-#pragma unroll
-   for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-      if (mt0 + mb < MT) red[(size_t)wave * red_stride + (mb * NS + s) * 64 + lane] = acc[s][mt0 + mb < MT ? mt0 + mb : 0];
-   __syncthreads();
-   for (int u = wave; u < MB * NB; u += kGemmWaves) {
-    const int mb = u / NB, blk = u - mb * NB, mt = mt0 + mb;
-    const int strip = strip0 + blk * PER;
-    if (mt >= MT || strip >= a.n_strips) continue;  // past the rows, or a block that does not exist
-    floatx4 y[PER];
-#pragma unroll
-    for (int s = 0; s < PER; ++s) {
-      y[s] = red[(mb * NS + blk * PER + s) * 64 + lane];
-#pragma unroll
-      for (int w = 1; w < kGemmWaves; ++w) y[s] += red[(size_t)w * red_stride + (mb * NS + blk * PER + s) * 64 + lane];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) y[s][r] += __shfl_xor(y[s][r], 8);
+    for (int j = 0; j < UNITS; ++j) {
+      int mt, blk, strip;
+      unit(j, mt0, strip0, a.n_strips, mt, blk, strip);
+      const int m = min(mt, MT - 1) * 8 + (lane & 7), n = min(strip, a.n_strips - 1) * 16 + 4 * g;
+      if constexpr (EPI == EPI_QKV) {
+        const int half = p.hd / 2, at = m * half + (n - n / p.hd * p.hd) / 2;  // (projections are whole heads)
+        cs[j] = *(const float2 *)(p.rope_cos + at);
+        sn[j] = *(const float2 *)(p.rope_sin + at);
+        pos[j] = p.row_pos[m];
+        page[j] = p.row_page[m];
+      } else if constexpr (EPI == EPI_LOGITS) {
+        out[j] = p.row_out[m];
+      } else if constexpr (EPI == EPI_RESID) {
+        h[j] = *(const floatx4 *)(p.h + (size_t)m * p.d + n);
+        gain[j] = *(const uint2 *)(a.gain_next + n);
+      }
     }
-    const int m = mt * 8 + (ml & 7);
-    float inv = 1.f;
-    if constexpr (NORM) {
-      float ss = 0.f;
-#pragma unroll
-      for (int w = 0; w < kGemmWaves; ++w) ss += red_ss[w][mt][ml & 7];
-      inv = 1.0f / sqrtf(ss / (float)p.d + p.eps);
-    }
-    const bool live = m < a.M && ml < 8;
+  }
+  __device__ __forceinline__ void ask(const Params &p, const GemmArgs &a, int strip0) {
+    if constexpr (NORM) ask_norm(p, 0);
+    ask_units(p, a, 0, strip0);
+  }
 
-    if constexpr (EPI == EPI_LOGITS) {
-      if (live) {
-        float *o = a.logits + (size_t)p.row_out[m] * p.V + strip * 16 + 4 * g;
-        *(floatx4 *)o = y[0] * inv;
-      }
-    } else if constexpr (GU) {
-      if (live) {
-        // strips 2b (gate) and 2b+1 (up) of the interleaved matrix both belong to features 16b..16b+15
-        int f0 = (blockIdx.x * NB + blk) * 16 + 4 * g;
-        float t[4];
+  // acc: this wavefront's sums over its k-tiles; red: [WAVES] areas of `red_stride` 16-byte words, one of each wavefront's own
+  __device__ __forceinline__ void finish(const Params &p, const GemmArgs &a, floatx4 (&acc)[NS][MT], floatx4 *red, int red_stride,
+                                         float (*red_ss)[MT * 8], int strip0) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ml = lane & 15, g = lane >> 4;
+    // Per batch of 8-row groups (as many as the areas take): every wavefront posts its partial tiles, then the
+    // (row group, block) pairs are shared out: a wavefront reduces a pair's tiles in a fixed order, adds the lo columns to
+    // the hi columns and runs the fused epilogue.  Lanes with ml < 8 hold Y[m = mt*8 + ml][n0 + 4g .. 4g+3].
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float gt = y[0][r] * inv, up = y[1][r] * inv;
-          t[r] = gt / (1.0f + __expf(-gt)) * up;
-        }
-        store_split4(p.act_x, m, p.F, f0, t);
-        if constexpr (EPI == EPI_GATEUP_SAVE) {
-          *(floatx4 *)(a.gu_save + (size_t)m * 2 * p.F + f0) = y[0] * inv;
-          *(floatx4 *)(a.gu_save + (size_t)m * 2 * p.F + p.F + f0) = y[1] * inv;
-        }
+    for (int mt0 = 0; mt0 < MT; mt0 += MB) {
+      if (mt0 > 0) {
+        __syncthreads();  // the previous batch has been read
+        ask_units(p, a, mt0, strip0);
       }
-    } else if constexpr (EPI == EPI_PARTIAL) {
-      // sums over this workgroup's slice of K; the slices are added up by resid_reduce_kernel
-      if (live)
-        *(floatx4 *)(a.partial + ((size_t)blockIdx.y * kMaxRows + m) * a.ldy + strip * 16 + 4 * g) = y[0];
-    } else if constexpr (EPI == EPI_RESID) {
-      int n = strip * 16 + 4 * g;
-      float ss = 0.f;
-      if (live) {
-        const size_t at = (size_t)m * p.d + n;
-        floatx4 hv = *(const floatx4 *)(p.h + at) + y[0];
-        *(floatx4 *)(p.h_out + at) = hv;
-        float t[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          t[r] = hv[r] * bf16_to_f32(a.gain_next[n + r]);
-          ss += hv[r] * hv[r];
-        }
-        store_split4(p.xg, m, p.d, n, t);
-      }
-      ss += __shfl_xor(ss, 16);
-      ss += __shfl_xor(ss, 32);
-      if (lane < 8) p.ssq[(size_t)strip * kMaxRows + m] = ss;  // rows >= M get 0
-    } else {  // EPI_QKV
-      if (live) {
-        int n = strip * 16 + 4 * g;       // column in [0, 3D)
-        int which = n / p.D;              // 0 q, 1 k, 2 v
-        int c = n - which * p.D;          // column inside the projection
-        int head = c / p.hd, dim = c - head * p.hd;
-        floatx4 v = y[0] * inv;
-        if (which < 2) {
-          int half = p.hd / 2;
-          const float *cs = p.rope_cos + (size_t)m * half + dim / 2;
-          const float *sn = p.rope_sin + (size_t)m * half + dim / 2;
-          float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
-          v[0] = x0 * cs[0] - x1 * sn[0];
-          v[1] = x0 * sn[0] + x1 * cs[0];
-          v[2] = x2 * cs[1] - x3 * sn[1];
-          v[3] = x2 * sn[1] + x3 * cs[1];
-        }
-        if (which == 0) {
-          *(floatx4 *)(p.qkv + (size_t)m * 3 * p.D + c) = v;
-        } else if (p.row_slot[m] >= 0) {  // a dead row (see row_is_dead) has no place in the cache
-          // the cache is bf16 storage: the one place besides the weights where values are rounded
-          uint16_t *pool = (uint16_t *)(which == 1 ? p.k_pool : p.v_pool);
-          if (p.kv_tiled) {
-            const int pos = p.row_pos[m], off = pos & (p.page_size - 1);
-            const int page = p.block_table[(size_t)p.row_slot[m] * p.pages_per_seq + (pos >> p.page_shift)];
-            pool += (((size_t)a.layer * p.n_pages + page) * p.H + head) * p.page_size * p.hd;
-            if (which == 1) {
-              uint2 pk;
-              pk.x = pack2_bf16(v[0], v[1]);
-              pk.y = pack2_bf16(v[2], v[3]);
-              *(uint2 *)(pool + k_tile(p, off, dim)) = pk;
-            } else {
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-              for (int r = 0; r < 4; ++r) pool[v_tile(p, off, dim + r)] = f32_to_bf16(v[r]);
+        for (int s = 0; s < NS; ++s)
+          if (mt0 + mb < MT) red[(size_t)wave * red_stride + (mb * NS + s) * 64 + lane] = acc[s][mt0 + mb < MT ? mt0 + mb : 0];
+      if constexpr (NORM) {
+        if (mt0 == 0) {
+          floatx4 ss = {0.f, 0.f, 0.f, 0.f};
+          for (int round = 0;;) {
+#pragma unroll
+            for (int u = 0; u < ASKED; ++u) {
+              if constexpr (MT == 1) ss[0] += norm[u][0];
+              else ss += norm[u];
             }
+            if (++round * ROUND >= p.d / 16) break;
+            ask_norm(p, round);
+          }
+          if constexpr (MT == 1) {
+            ss[0] += __shfl_xor(ss[0], 8);
+            ss[0] += __shfl_xor(ss[0], 16);
+            ss[0] += __shfl_xor(ss[0], 32);
+            if (lane < 8) red_ss[wave][lane] = ss[0];
           } else {
-            size_t off = kv_offset(p, a.layer, p.row_slot[m], p.row_pos[m], head) + dim;
-            uint2 pk;
-            pk.x = pack2_bf16(v[0], v[1]);
-            pk.y = pack2_bf16(v[2], v[3]);
-            *(uint2 *)(pool + off) = pk;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              ss[r] += __shfl_xor(ss[r], 16);
+              ss[r] += __shfl_xor(ss[r], 32);
+            }
+            if (lane < MT * 2) *(floatx4 *)&red_ss[wave][lane * 4] = ss;
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < UNITS; ++j) {
+        int mt, blk, strip;
+        if (!unit(j, mt0, strip0, a.n_strips, mt, blk, strip)) continue;  // past the rows, or a block that does not exist
+        const int mb = mt - mt0;
+        floatx4 y[PER];
+#pragma unroll
+        for (int s = 0; s < PER; ++s) {
+          y[s] = red[(mb * NS + blk * PER + s) * 64 + lane];
+#pragma unroll
+          for (int w = 1; w < WAVES; ++w) y[s] += red[(size_t)w * red_stride + (mb * NS + blk * PER + s) * 64 + lane];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) y[s][r] += __shfl_xor(y[s][r], 8);
+        }
+        const int m = mt * 8 + (ml & 7);
+        float inv = 1.f;
+        if constexpr (NORM) {
+          float ss = 0.f;
+#pragma unroll
+          for (int w = 0; w < WAVES; ++w) ss += red_ss[w][m];
+          inv = 1.0f / sqrtf(ss / (float)p.d + p.eps);
+        }
+        const bool live = m < a.M && ml < 8;
+
+        if constexpr (EPI == EPI_LOGITS) {
+          if (live) {
+            float *o = a.logits + (size_t)out[j] * p.V + strip * 16 + 4 * g;
+            *(floatx4 *)o = y[0] * inv;
+          }
+        } else if constexpr (GU) {
+          if (live) {
+            // strips 2b (gate) and 2b+1 (up) of the interleaved matrix both belong to features 16b..16b+15
+            int f0 = (blockIdx.x * NB + blk) * 16 + 4 * g;
+            float t[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              float gt = y[0][r] * inv, up = y[1][r] * inv;
+              t[r] = gt / (1.0f + __expf(-gt)) * up;
+            }
+            store_split4(p.act_x, m, p.F, f0, t);
+            if constexpr (EPI == EPI_GATEUP_SAVE) {
+              *(floatx4 *)(a.gu_save + (size_t)m * 2 * p.F + f0) = y[0] * inv;
+              *(floatx4 *)(a.gu_save + (size_t)m * 2 * p.F + p.F + f0) = y[1] * inv;
+            }
+          }
+        } else if constexpr (EPI == EPI_PARTIAL) {
+          // sums over this workgroup's slice of K; the slices are added up by resid_reduce_kernel
+          if (live)
+            *(floatx4 *)(a.partial + ((size_t)blockIdx.y * kMaxRows + m) * a.ldy + strip * 16 + 4 * g) = y[0];
+        } else if constexpr (EPI == EPI_RESID) {
+          int n = strip * 16 + 4 * g;
+          float ss = 0.f;
+          if (live) {
+            floatx4 hv = h[j] + y[0];
+            *(floatx4 *)(p.h_out + (size_t)m * p.d + n) = hv;
+            const uint32_t gw[2] = {gain[j].x, gain[j].y};
+            float t[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              t[r] = hv[r] * __uint_as_float(r & 1 ? gw[r >> 1] & 0xffff0000u : gw[r >> 1] << 16);
+              ss += hv[r] * hv[r];
+            }
+            store_split4(p.xg, m, p.d, n, t);
+          }
+          ss += __shfl_xor(ss, 16);
+          ss += __shfl_xor(ss, 32);
+          if (lane < 8) p.ssq[(size_t)strip * kMaxRows + m] = ss;  // rows >= M get 0
+        } else {  // EPI_QKV
+          if (live) {
+            int n = strip * 16 + 4 * g;       // column in [0, 3D)
+            int which = n / p.D;              // 0 q, 1 k, 2 v
+            int c = n - which * p.D;          // column inside the projection
+            int head = c / p.hd, dim = c - head * p.hd;
+            floatx4 v = y[0] * inv;
+            if (which < 2) {
+              float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
+              v[0] = x0 * cs[j].x - x1 * sn[j].x;
+              v[1] = x0 * sn[j].x + x1 * cs[j].x;
+              v[2] = x2 * cs[j].y - x3 * sn[j].y;
+              v[3] = x2 * sn[j].y + x3 * cs[j].y;
+            }
+            if (which == 0) {
+              *(floatx4 *)(p.qkv + (size_t)m * 3 * p.D + c) = v;
+            } else if (page[j] >= 0) {  // a dead row (see row_is_dead) has no place in the cache
+              // the cache is bf16 storage: the one place besides the weights where values are rounded
+              const int off = pos[j] & (p.page_size - 1);
+              uint16_t *pool = (uint16_t *)(which == 1 ? p.k_pool : p.v_pool) + (((size_t)a.layer * p.n_pages + page[j]) * p.H + head) * p.page_size * p.hd;
+              if (p.kv_tiled && which == 2) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) pool[v_tile(p, off, dim + r)] = f32_to_bf16(v[r]);
+              } else {
+                uint2 pk;
+                pk.x = pack2_bf16(v[0], v[1]);
+                pk.y = pack2_bf16(v[2], v[3]);
+                *(uint2 *)(pool + (p.kv_tiled ? k_tile(p, off, dim) : (size_t)off * p.hd + dim)) = pk;
+              }
+            }
           }
         }
       }
     }
-   }
   }
-}
+};
 
 // Calls of up to 8 rows: one MFMA column block, operands through registers.  A workgroup owns NB output blocks (a block is
 // one strip of 16 features, or the gate strip and the up strip of 16 FFN features) and its wavefronts share K: wavefront w
@@ -519,7 +581,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
   constexpr int NA = few_rows_chains<EPI, WAVES>();
   constexpr int G = NA > U ? NA / U : 1;  // trips until an accumulator's turn comes again
   __shared__ floatx4 red[WAVES * NS * 64];
-  __shared__ float red_ss[WAVES][1][8];
+  __shared__ float red_ss[WAVES][8];
+  Epilogue<1, EPI, WAVES, NB, NS, 1> epilogue;
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ml = lane & 15;  // MFMA column = pseudo-row
@@ -598,6 +661,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
       fix[s] = *(const u32x2 *)(a.z.fix + (size_t)min(strip0 + s, a.n_strips - 1) * fix_stride(KT) + fix_index(KT, kt));
     __builtin_amdgcn_sched_barrier(0);
   }
+  epilogue.ask(p, a, strip0);
+  __builtin_amdgcn_sched_barrier(0);
   for (; t + STEP < trips; t += STEP) {  // (all of these are full)
 #pragma unroll
     for (int g = 0; g < STEP; ++g) {
@@ -630,7 +695,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
 #pragma unroll
     for (int c = 1; c < NA; ++c) sum[s][0] += acc[c][s];
   }
-  gemm_finish<1, EPI, WAVES, NB, NS, 1>(p, a, sum, red, NS * 64, red_ss, strip0);
+  epilogue.finish(p, a, sum, red, NS * 64, red_ss, strip0);
 }
 
 // Calls with more than 8 rows (and slices of K of any call): the same product with both operands in LDS rings.  Such a call pulls two to three times
@@ -652,7 +717,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
   constexpr int PER = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;
   constexpr int NS = NB * PER, T = NS + MT, D = ring_stages(WAVES, T);
   __shared__ u32x4 ring[WAVES * D * T * 64];
-  __shared__ float red_ss[WAVES][MT][8];
+  __shared__ __align__(16) float red_ss[WAVES][MT * 8];
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KT = a.K >> 5;                                        // k-tiles of the whole K (strip stride)
@@ -759,7 +824,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
       for (int mt = 0; mt < MT; ++mt) acc[s][mt] = floatx4{sum[s][mt][0], sum[s][mt][1], sum[s][mt][2], sum[s][mt][3]};
   }
   constexpr int MB = D * T / NS < MT ? D * T / NS : MT;  // row groups whose partial tiles fit a wavefront's ring
-  gemm_finish<MT, EPI, WAVES, NB, NS, MB>(p, a, acc, (floatx4 *)ring, D * T * 64, red_ss, strip0);
+  Epilogue<MT, EPI, WAVES, NB, NS, MB> epilogue;
+  epilogue.ask(p, a, strip0);
+  epilogue.finish(p, a, acc, (floatx4 *)ring, D * T * 64, red_ss, strip0);
 }
 
 // Launch shape of the decode-sized GEMMs: GemmTuning (a member of the context, so two contexts

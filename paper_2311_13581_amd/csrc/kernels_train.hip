@@ -111,6 +111,7 @@ __global__ __launch_bounds__(256) void assemble_train_mfma_kernel(Params p, cons
   if (threadIdx.x == 0) {
     p.row_pos[m] = pos;
     p.row_slot[m] = slot;
+    p.row_page[m] = p.block_table[(size_t)slot * p.pages_per_seq + (pos >> p.page_shift)];
     p.row_out[m] = m;
   }
 }

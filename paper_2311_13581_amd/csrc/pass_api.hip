@@ -207,7 +207,7 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   P.draft_logits = A.take<float>(S * (1 + c.k) * V);
   P.verify_logits = A.take<float>(S * (1 + c.k) * V);
   P.step_slots = A.take<int32_t>(M);
-  P.row_pos = A.take<int32_t>(M); P.row_slot = A.take<int32_t>(M); P.row_out = A.take<int32_t>(M);
+  P.row_pos = A.take<int32_t>(M); P.row_slot = A.take<int32_t>(M); P.row_out = A.take<int32_t>(M); P.row_page = A.take<int32_t>(M);
   P.rope_cos = A.take<float>(M * c.head_dim / 2); P.rope_sin = A.take<float>(M * c.head_dim / 2);
   P.rope_theta = A.take<double>(c.head_dim / 2);
   P.h = P.h_out = A.take<float>(M * d); P.xn = A.take<float>(M * d); P.qkv = A.take<float>(M * 3 * D);
@@ -828,6 +828,7 @@ int pass_create(const pass_config *cfg, void *hip_stream, void *device_arena, si
   // row tables: entries past a call's row count are never meant to be read, but start in bounds
   launch_fill_i32(c->P.row_pos, 0, kMaxRows, c->stream);
   launch_fill_i32(c->P.row_slot, 0, kMaxRows, c->stream);
+  launch_fill_i32(c->P.row_page, -1, kMaxRows, c->stream);
   launch_fill_i32(c->P.row_out, 0, kMaxRows, c->stream);
   // rotary frequencies theta_i = base^(-2i/hd), in double (the angle pos * theta_i is formed in double too)
   std::vector<double> theta(cfg->head_dim / 2);

@@ -112,6 +112,7 @@ struct Params {
   int32_t *step_slots;   // [B]
   int32_t *prefill_ids;  // [R]
   int32_t *row_pos, *row_slot, *row_out;  // [M]
+  int32_t *row_page;                      // [M] matrix-core path: the K/V page of the row's position, -1: a dead row
   float *rope_cos, *rope_sin;             // [M][hd/2]
   double *rope_theta;                     // [hd/2] base^(-2i/hd), filled at create
   // workspaces
