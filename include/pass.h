@@ -113,9 +113,9 @@ int pass_create(const pass_config *cfg, void *hip_stream, void *device_arena, si
  * pointers are host memory; 1: device memory.  The caller may free its tensors afterwards. */
 int pass_load_weights(pass_ctx *ctx, const pass_weights *w, int on_device);
 
-/* Optional, after pass_load_weights: copies of the model's large matrices in 12 bits a weight, without loss, for the
- * calls of up to 8 rows, which are bound by the bytes of their weights and take 10 to 25 % less time on them.  The plain
- * matrices stay where they are: prompts and larger calls are multiplied with those.  What a call multiplies is bit for bit the same
+/* Optional, after pass_load_weights: copies of the model's large matrices in 12 bits a weight, without loss, for calls of up to
+ * 48 rows, which are bound by the bytes of their weights and take 5 to 25 % less time on them.  The plain matrices stay where
+ * they are: prompts, larger calls and products that gain nothing are multiplied with those.  What a call multiplies is bit for bit the same
  * weight; its sums may be taken in another order.
  *   pass_coded_bytes   device bytes pass_coded_begin needs, about three quarters of the matrices (0: no context, no weights, the
  *                      generic path, or a model so small that nothing is gained)
@@ -245,7 +245,8 @@ int pass_run_iterations(pass_ctx *ctx, const int32_t *slots, int n_slots, int n_
  *   pass_train_bytes   device bytes pass_train_begin needs for this context, after pass_load_weights
  *                      (0: no context, no weights, or k = 0)
  *   pass_train_begin   device_workspace: caller's device memory (256-byte aligned, kept alive while
- *                      training); the embeddings start from the embedding of init_token (the paper:
+ *                      training; after pass_coded_begin and with pass_coded_bytes more than needed, the transposes are coded as
+ *                      well); the embeddings start from the embedding of init_token (the paper:
  *                      [UNK]) or, with init_token < 0, from the model's own look-ahead tensor;
  *                      AdamW's moments and step count start at zero; pass_load_weights ends the set-up
  *   pass_train_step    slots: host, n_slots prefilled slots, (1+k) * n_slots <= PASS_MAX_ROWS, at most

@@ -245,22 +245,29 @@ class Pass:
         self._check(self.lib.pass_load_weights(self.h, C.byref(w), int(on_device)))
         self._code_weights()
 
+    def _room(self, nbytes):
+        """Whether a tensor of that size leaves an eighth of the card's memory free."""
+        cuda = self._torch.cuda
+        free, total = cuda.mem_get_info()
+        return nbytes + total // 8 <= free + cuda.memory_reserved() - cuda.memory_allocated()
+
+    def _workspace(self, nbytes):
+        """A tensor of that size and the 256-byte aligned address in it that is the library's."""
+        ws = self._torch.empty(nbytes + 256, dtype=self._torch.uint8, device="cuda")
+        self._torch.cuda.synchronize()
+        return ws, C.c_void_p((ws.data_ptr() + 255) & ~255)
+
     def _code_weights(self):
-        """The 12-bit copies for the small calls, where that leaves an eighth of the card's memory free (without them those calls
-        read the plain matrices)."""
-        torch = self._torch
+        """The 12-bit copies for decode-sized calls, where there is room (without them those calls read the plain matrices)."""
         self.coded = None
         nbytes = self.lib.pass_coded_bytes(self.h)
-        free, total = torch.cuda.mem_get_info()
-        free += torch.cuda.memory_reserved() - torch.cuda.memory_allocated()
-        if nbytes == 0 or nbytes + total // 8 > free:
+        if nbytes == 0 or not self._room(nbytes):
             return
         try:
-            ws = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
-        except torch.OutOfMemoryError:  # free, but not in one piece
+            ws, base = self._workspace(nbytes)
+        except self._torch.OutOfMemoryError:  # free, but not in one piece
             return
-        torch.cuda.synchronize()
-        self._check(self.lib.pass_coded_begin(self.h, C.c_void_p((ws.data_ptr() + 255) & ~255), nbytes))
+        self._check(self.lib.pass_coded_begin(self.h, base, nbytes))
         self.coded = ws
 
     def prefill(self, slot: int, prompt, seq_id: int = 0):
@@ -351,10 +358,17 @@ class Pass:
         nbytes = self.lib.pass_train_bytes(self.h)
         if nbytes == 0:
             raise PassError(-1, "no look-ahead embeddings to train")
-        self.train_ws = self._torch.empty(nbytes + 256, dtype=self._torch.uint8, device="cuda")
-        self._torch.cuda.synchronize()
-        base = (self.train_ws.data_ptr() + 255) & ~255
-        self._check(self.lib.pass_train_begin(self.h, C.c_void_p(base), nbytes, init_token))
+        ws = None
+        extra = self.lib.pass_coded_bytes(self.h) if self.coded is not None else 0
+        if extra and self._room(nbytes + extra):  # room for 12-bit copies of the transposes too
+            try:
+                ws, base = self._workspace(nbytes + extra)
+            except self._torch.OutOfMemoryError:
+                pass
+        if ws is None:
+            ws, base = self._workspace(nbytes)
+        self.train_ws = ws
+        self._check(self.lib.pass_train_begin(self.h, base, ws.numel() - 256, init_token))
 
     def train_step(self, slots, targets, lr: float, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01) -> float:
         s = np.ascontiguousarray(slots, dtype=np.int32)

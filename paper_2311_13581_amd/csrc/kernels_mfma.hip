@@ -710,13 +710,19 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
 // 108.7 -> 78.2.  Bound by the unit's vector memory path all the same: its returns are in order, so a row out of L2 waits
 // for the weights requested before it.
 constexpr int kRingWaves = 4;  // (eight wavefronts with two stages each: 3 to 5 % slower in every product)
-constexpr int ring_stages(int waves, int tiles) { return waves * tiles * 3 <= 156 ? 3 : (waves * tiles * 2 <= 156 ? 2 : 1); }
+constexpr int kRingFixTiles = 64;  // k-tiles a wavefront of a product on coded weights may have: their fix words wait in LDS
+constexpr int ring_stages(int waves, int stage) { return waves * stage * 3 <= 156 * 1024 ? 3 : (waves * stage * 2 <= 156 * 1024 ? 2 : 1); }
+// on coded weights two where a stage is large (three: 1 to 4 % slower), more where two would hold too little
+constexpr int coded_ring_stages(int stage) { return stage >= 5 * 1024 ? 2 : (stage >= 4 * 1024 ? 3 : 4); }
 
-template <int MT, int EPI, int WAVES, int NB>
+template <int MT, int EPI, int WAVES, int NB, bool Z>
 __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArgs a) {
   constexpr int PER = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;
-  constexpr int NS = NB * PER, T = NS + MT, D = ring_stages(WAVES, T);
-  __shared__ u32x4 ring[WAVES * D * T * 64];
+  constexpr int NS = NB * PER, T = NS + MT;
+  constexpr int TILE = Z ? kCodedTile : 1024, STAGE = NS * TILE + MT * 1024;  // bytes
+  constexpr int D = Z ? coded_ring_stages(STAGE) : ring_stages(WAVES, STAGE);
+  __shared__ u32x4 ring[WAVES * D * STAGE / 16];
+  __shared__ uint32_t fixes[Z ? WAVES : 1][Z ? NS : 1][Z ? 2 * kRingFixTiles : 1];  // fix words of the wavefront's k-tiles
   __shared__ __align__(16) float red_ss[WAVES][MT * 8];
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -727,12 +733,14 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
 
   // strips past the end repeat the last one (in bounds; their results are dropped).  Rows >= M of the last group hold
   // whatever the buffer holds: a column of the product depends on its own row only, and those columns are dropped.
-  const u32x4 *wp[NS], *xp[MT];
+  const char *wp[NS];
+  const u32x4 *xp[MT];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) wp[s] = a.W + ((size_t)min(strip0 + s, a.n_strips - 1) * KT + kbase + wave) * 64 + lane;
+  for (int s = 0; s < NS; ++s) 
+    wp[s] = (const char *)(Z ? a.z.tiles : a.W) + ((size_t)min(strip0 + s, a.n_strips - 1) * KT + kbase + wave) * TILE + min(lane, TILE / 16 - 1) * 16;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) xp[mt] = (const u32x4 *)a.X + ((size_t)mt * KT + kbase + wave) * 64 + lane;
-  u32x4 *mine = ring + wave * (D * T * 64);
+  char *mine = (char *)ring + wave * (D * STAGE);
 
   // The sums lose as little as with eight wavefronts or more sharing K: either two accumulators per tile, one of the
   // wavefront's even and one of its odd k-tiles, or, where the registers do not hold those, a product of one k-tile at a
@@ -754,33 +762,71 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
 
   // this wavefront's k-tiles: wave, wave + WAVES, ...  (the workgroup walks its strips front to back)
   const int n = (KTl - wave + WAVES - 1) / WAVES;
-  auto issue = [&](int i, u32x4 *st) __attribute__((always_inline)) {
-    const size_t off = (size_t)i * WAVES * 64;
+  auto issue = [&](int i, char *st) __attribute__((always_inline)) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) copy_to_lds<false>(xp[mt] + off, st + (NS + mt) * 64);
+    for (int mt = 0; mt < MT; ++mt) copy_to_lds<false>(xp[mt] + (size_t)i * WAVES * 64, st + NS * TILE + mt * 1024);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) copy_to_lds<true>(wp[s] + off, st + s * 64);
+    for (int s = 0; s < NS; ++s) {
+      if (!Z || lane < kCodedTile / 16) copy_to_lds<true>(wp[s] + (size_t)i * WAVES * TILE, st + s * TILE);
+    }
   };
+  if constexpr (Z) {  // the run of n fix words of every strip, ahead of the first stage
+    const int f0 = fix_index(KT, kbase + wave);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const uint32_t *fp = (const uint32_t *)(a.z.fix + (size_t)min(strip0 + s, a.n_strips - 1) * fix_stride(KT) + f0);
+#pragma unroll
+      for (int h = 0; h < 2 * kRingFixTiles; h += 64)
+        if (h < 2 * n) copy1_to_lds(fp + min(h + lane, 2 * n - 1), &fixes[wave][s][h]);
+    }
+  }
 #pragma unroll
   for (int d = 0; d < D; ++d)
-    if (d < n) issue(d, mine + d * T * 64);
+    if (d < n) issue(d, mine + d * STAGE);
   int at = 0;
+  uint32_t marks = 0;
   auto tile = [&](int i, auto &into) __attribute__((always_inline)) {
-    u32x4 *st = mine + at * T * 64;
+    char *st = mine + at * STAGE;
     const int left = n - 1 - i;  // stages requested after this one: min(left, D - 1)
     if (left >= D - 1) wait_copies<(D - 1) * T>();
+    else if (D > 3 && left == 2) wait_copies<(D > 3 ? 2 * T : 0)>();
     else if (D > 2 && left == 1) wait_copies<(D > 2 ? T : 0)>();
     else wait_copies<0>();
     u32x4 av[NS], bv[MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) bv[mt] = st[(NS + mt) * 64 + lane];
+    for (int mt = 0; mt < MT; ++mt) bv[mt] = ((const u32x4 *)(st + NS * TILE + mt * 1024))[lane];
+    typename LaneTile<Z>::T cv[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) av[s] = st[s * 64 + lane];
+    for (int s = 0; s < NS; ++s) {
+      if constexpr (Z) {
+        cv[s] = *(const u32x3 *)(st + s * TILE + lane * 12);
+      } else {
+        cv[s] = ((const u32x4 *)(st + s * TILE))[lane];
+      }
+    }
     if (i + D < n) {
       wait_lds_reads();  // the stage has been read: it can be filled again
       issue(i + D, st);
     }
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (Z) {
+      if (i == 0) {  // the fix words came ahead of the first stage: lane j learns which strips of the wavefront's j-th k-tile have any
+#pragma unroll
+        for (int s = 0; s < NS; ++s) marks |= (fixes[wave][s][2 * min(lane, n - 1)] ? 1u : 0u) << s;
+      }
+#pragma unroll
+      for (int s = 0; s < NS; ++s) av[s] = decode_tile(cv[s], a.z.lut0, a.z.lut1);
+      const uint32_t mark = (uint32_t)__builtin_amdgcn_readlane((int)marks, i);
+      if (__builtin_expect(mark != 0, 0)) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+          if (mark >> s & 1)
+            fix_tile(av[s], __builtin_amdgcn_readfirstlane(fixes[wave][s][2 * i]), __builtin_amdgcn_readfirstlane(fixes[wave][s][2 * i + 1]), a.z.more, lane);
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) av[s] = cv[s];
+    }
     auto product = [&](int s, int mt, floatx4 c) __attribute__((always_inline)) {
       return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[s]), __builtin_bit_cast(bf16x8, bv[mt]), c, 0, 0, 0);
     };
@@ -823,10 +869,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) acc[s][mt] = floatx4{sum[s][mt][0], sum[s][mt][1], sum[s][mt][2], sum[s][mt][3]};
   }
-  constexpr int MB = D * T / NS < MT ? D * T / NS : MT;  // row groups whose partial tiles fit a wavefront's ring
+  constexpr int MB = D * STAGE / (NS * 1024) < MT ? D * STAGE / (NS * 1024) : MT;  // row groups whose partial tiles fit a wavefront's ring
   Epilogue<MT, EPI, WAVES, NB, NS, MB> epilogue;
   epilogue.ask(p, a, strip0);
-  epilogue.finish(p, a, acc, (floatx4 *)ring, D * T * 64, red_ss, strip0);
+  epilogue.finish(p, a, acc, (floatx4 *)ring, D * STAGE / 16, red_ss, strip0);
 }
 
 // Launch shape of the decode-sized GEMMs: GemmTuning (a member of the context, so two contexts
@@ -834,7 +880,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
 GemmTuning::GemmTuning()
     : waves{0, 0, 0, 0, 0},        // QKV, Wo, gate/up, LM head, down; 0 = by the count of blocks (few_rows_shape)
       unroll{1, 1, 1, 1, 1},
-      big_blocks{0, 0, 0, 0, 0},   // 0 = by the count of blocks (ring_blocks)
+      big_blocks{0, 0, 0, 0, 0},   // 0 = by the count of blocks (ring_shape)
       split_ks(-1) {}              // -1 = by the rows (launch_resid_split)
 
 int GemmTuning::set(int kind, int w, int u) {
@@ -891,6 +937,9 @@ static FewShape few_rows_shape(int epi, int n) {
       return n <= 256 ? FewShape{8, 4, 1} : FewShape{16, 1, 2};
   }
 }
+// Whether a product of the ring form gains by coded weights.  Small ones only wait longer for their first tile (Wo d 2048 at 16 rows
+// 6.5 us, coded 7.1; QKV 8.2 and 8.7; but Wo d 4096 12.6 and 10.5).
+static bool coded_pays(int n_strips, int K) { return (int64_t)n_strips * 16 * K >= 1 << 24; }
 // Slices of K of Wo and down in calls of up to 8 rows, and strips per workgroup; 1 = whole K.  Fewer strips than units leave
 // units idle, 257 to 511 strips give some of them two: then the product is bound by those, and slices over all of them pay for
 // the kernel that adds their sums.  In us, fitted to d 1024 .. 5120 (K up to 3.5 d): a unit takes 0.033 us per KB of weights and 0.010
@@ -908,8 +957,9 @@ static int few_rows_slices(int n, int K, int d, int F, bool coded, int &nb_best)
     if ((KT + kts - 1) / kts != ks || kts < 8) continue;
     if ((size_t)ks * d > (size_t)2 * F) continue;  // the slices' sums borrow the generic path's gate/up workspace
     for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
-      const float unit = ((n + nb - 1) / nb * ks + 255) / 256 * (nb * 0.033f + 0.010f) * kts;
-      const float us = 5.2f + std::max(unit, (float)n * K * 32 / 6.9e6f);
+      const float rounds = ((n + nb - 1) / nb * ks + 255) / 256;
+      const float us = coded && coded_pays(n, K) ? 5.2f + std::max(rounds * (nb * 0.027f + 0.0125f) * kts, (float)n * K * 24 / 6.9e6f)
+                                                 : 5.2f + std::max(rounds * (nb * 0.033f + 0.010f) * kts, (float)n * K * 32 / 6.9e6f);
       if (us < best) { best = us; ks_best = ks; nb_best = nb; }
     }
   }
@@ -990,14 +1040,20 @@ static void launch_few(const Params &p, const GemmArgs &a, int n_blocks, FewShap
 
 // Blocks a workgroup of the ring form may own: its sums (of the 512 registers that one wavefront per SIMD has) and two
 // stages of its ring must fit.
+constexpr int kRingCodedGroups = 6;  // row groups up to which the ring form takes coded weights
 constexpr bool ring_fits(int strips, int mt) { return strips * mt <= 64 && kRingWaves * 2 * (strips + mt) <= 156; }
 
 template <int MT, int EPI>
-static void launch_rows_mt(const Params &p, const GemmArgs &a, dim3 grid, int nb, hipStream_t s) {
+static void launch_rows_mt(const Params &p, const GemmArgs &a, dim3 grid, int nb, bool coded, hipStream_t s) {
   constexpr int PER = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;
   auto go = [&](auto B) {
     constexpr int NB = decltype(B)::value;
-    if constexpr (ring_fits(NB * PER, MT)) gemm_rows_kernel<MT, EPI, kRingWaves, NB><<<grid, kRingWaves * 64, 0, s>>>(p, a);
+    if constexpr (ring_fits(NB * PER, MT)) {
+      if constexpr (MT <= kRingCodedGroups && NB * PER * MT <= 30) {
+        if (coded) return gemm_rows_kernel<MT, EPI, kRingWaves, NB, true><<<grid, kRingWaves * 64, 0, s>>>(p, a);
+      }
+      gemm_rows_kernel<MT, EPI, kRingWaves, NB, false><<<grid, kRingWaves * 64, 0, s>>>(p, a);
+    }
   };
   switch (nb) {
     case 1: go(nb_c<1>{}); break;
@@ -1009,31 +1065,45 @@ static void launch_rows_mt(const Params &p, const GemmArgs &a, dim3 grid, int nb
     default: go(nb_c<8>{}); break;
   }
 }
-// Blocks per workgroup (1 .. 6 or 8).  A workgroup pulls all M rows whatever it owns, and a compute unit holds one: the
-// product takes (rounds of 256 workgroups) x (operand tiles per k-tile).  `want` > 0 asks for a number.
-static int ring_blocks(int want, int n_blocks, int per, int mt, int slices) {
-  int best = 1, best_cost = INT_MAX;
-  for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
-    if (!ring_fits(nb * per, mt)) continue;
-    const int cost = want ? std::abs(nb - want) : (((n_blocks + nb - 1) / nb * slices + 255) / 256) * (nb * per + mt);
-    if (cost < best_cost) { best_cost = cost; best = nb; }
-  }
+// Blocks per workgroup (1 .. 6 or 8), and whether the product reads coded weights.  A workgroup pulls all M rows whatever it owns, and a
+// compute unit holds one: the product takes (rounds of 256 workgroups) x (operand tiles per k-tile).  Products added step by step (sums
+// past 30 tiles) cost a quarter more, and with the decoding beside them too much.  On coded weights a strip is three quarters of a tile, and
+// a second round costs a quarter more unless two workgroups fit a unit's LDS (gate/up an eighth).  `want` > 0 asks for a number.
+// Measured with and without the copies, us: 40 rows, d 4096, QKV 26.0 and 23.8, gate/up (688 blocks) 36.1 and 33.7, Wo 15.4 and 14.7, down
+// 25.1 and 23.6 (with the kernel that adds the slices), LM head (V 32000) 50.8 and 49.1; 16 rows 19.2 and 17.1, 30.7 and 25.6, 12.6 and
+// 10.5, 19.3 and 18.2, 46.4 and 35.7; d 5120, 24 rows, 860 blocks 47.8 and 42.5; 48 rows, d 4096, QKV 28.3 and 26.3.
+struct RingShape { int nb; bool coded; };
+static RingShape ring_shape(int want, int n_blocks, int per, int mt, int slices, bool coded) {
+  RingShape best{1, false};
+  float best_cost = 1e30f;
+  for (int z = 0; z <= (coded ? 1 : 0); ++z)
+    for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
+      const int ns = nb * per, rounds = ((n_blocks + nb - 1) / nb * slices + 255) / 256;
+      if (!ring_fits(ns, mt) || (z && ns * mt > 30)) continue;
+      float cost = rounds * ((z ? 0.75f : 1.0f) * ns + mt);
+      if (ns * mt > 30) cost *= 1.28f;
+      if (z && rounds > 1) cost *= 8 * (0.75f * ns + mt) + 2 * ns > 79 ? 1.25f : per == 2 ? 1.12f : 1.0f;
+      if (want) cost = (float)std::abs(nb - want) + (coded && !z ? 0.5f : 0.0f);
+      if (cost < best_cost) { best_cost = cost; best = RingShape{nb, z != 0}; }
+    }
   return best;
 }
 template <int EPI>
 static void launch_rows(const Params &p, const GemmArgs &a, int n_blocks, int want, int slices, hipStream_t s) {
   constexpr int PER = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;
-  const int mt = (a.M + 7) / 8, nb = ring_blocks(want, n_blocks, PER, mt, slices);
+  const int mt = (a.M + 7) / 8;
+  const bool coded = a.z.tiles && mt <= kRingCodedGroups && coded_pays(a.n_strips, a.K) && (EPI == EPI_PARTIAL ? a.kt_split : a.K >> 5) <= kRingFixTiles * kRingWaves;
+  const auto [nb, z] = ring_shape(want, n_blocks, PER, mt, slices, coded);
   const dim3 grid((n_blocks + nb - 1) / nb, slices);
   switch (mt) {
-    case 1: if constexpr (EPI == EPI_PARTIAL) launch_rows_mt<1, EPI>(p, a, grid, nb, s); break;
-    case 2: launch_rows_mt<2, EPI>(p, a, grid, nb, s); break;
-    case 3: launch_rows_mt<3, EPI>(p, a, grid, nb, s); break;
-    case 4: launch_rows_mt<4, EPI>(p, a, grid, nb, s); break;
-    case 5: launch_rows_mt<5, EPI>(p, a, grid, nb, s); break;
-    case 6: launch_rows_mt<6, EPI>(p, a, grid, nb, s); break;
-    case 7: launch_rows_mt<7, EPI>(p, a, grid, nb, s); break;
-    default: launch_rows_mt<8, EPI>(p, a, grid, nb, s); break;
+    case 1: if constexpr (EPI == EPI_PARTIAL) launch_rows_mt<1, EPI>(p, a, grid, nb, z, s); break;
+    case 2: launch_rows_mt<2, EPI>(p, a, grid, nb, z, s); break;
+    case 3: launch_rows_mt<3, EPI>(p, a, grid, nb, z, s); break;
+    case 4: launch_rows_mt<4, EPI>(p, a, grid, nb, z, s); break;
+    case 5: launch_rows_mt<5, EPI>(p, a, grid, nb, z, s); break;
+    case 6: launch_rows_mt<6, EPI>(p, a, grid, nb, z, s); break;
+    case 7: launch_rows_mt<7, EPI>(p, a, grid, nb, z, s); break;
+    default: launch_rows_mt<8, EPI>(p, a, grid, nb, z, s); break;
   }
 }
 

@@ -19,6 +19,11 @@ __device__ __forceinline__ void copy_to_lds(const void *src, void *dst) {
   else
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "memory", "m0");
 }
+// 64 x 4 bytes to 256 bytes of LDS
+__device__ __forceinline__ void copy1_to_lds(const void *src, void *dst) {
+  const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(off) : "memory", "m0");
+}
 // until no more than the wavefront's youngest N copies are in flight
 template <int N>
 __device__ __forceinline__ void wait_copies() {

@@ -61,6 +61,7 @@ struct TrainWs {
   // and the (hi, lo) tiles of the gradient that is the next product's input [2 * kMaxRows * max(V, 2F, 3D, d)]
   void *lm_head_t = nullptr;
   std::vector<LayerW> layers_t;  // wqkv, wo, wgu, wdown: the transposes; the norm gains are unused
+  std::vector<Coded> coded;      // their coded copies, in the order of pass_ctx::coded, or empty
   uint16_t *x = nullptr;
   float *row_loss;                                   // [kMaxRows]
   int32_t *targets;                                  // [kMaxRows] target token of a row, -1 = no loss
@@ -266,16 +267,18 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
 
 // The coded copies in the caller's workspace.  counts: what the coding counts, [matrices][128] exponents, then [matrices][2] of the
 // overflow lists.
-size_t carve_coded(const pass_config &c, char *base, std::vector<Coded> *out, uint32_t **counts) {
+// transposed: of the transposes that training multiplies with (in calls of more than 8 rows, which gain on matrices of 2^24 weights or more).
+size_t carve_coded(const pass_config &c, bool transposed, char *base, std::vector<Coded> *out, uint32_t **counts) {
   Arena A{base, 0};
   const size_t d = c.d_model, D = (size_t)c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
   std::vector<Coded> coded;
   bool any = false;
   auto add = [&](size_t N, size_t K) {
     Coded z{};
+    if (transposed) std::swap(N, K);
     // small products are bound by their start (d 1024: QKV 4.4 us on plain tiles and 4.6 on coded ones, gate/up of 448 strips 5.0
     // and 5.2; but LM heads of 500 and 1000 strips 5.1 and 4.9, 7.6 and 6.8; d 2048, 63 strips 4.7 and 4.6)
-    if (K >= 2048 || N * K >= (size_t)8000 * 1024) {
+    if (transposed ? N * K >= 1 << 24 : K >= 2048 || N * K >= (size_t)8000 * 1024) {
       any = z.wanted = true;
       z.tiles = A.take<char>(coded_tile_bytes(N, K));
       z.fix = A.take<uint2>(coded_fix_words(N, K));
@@ -415,14 +418,17 @@ Matrix matrix(const pass_ctx *c, const void *tiles, int which) {
 
 // The coded copies of all matrices: a table each, then the tiles.  A matrix that its table suits badly (the overflow list does not
 // take what lies outside: every tile of it would wait for its fixes) is left without.
-int code_weights(pass_ctx *c, std::vector<Coded> &coded, uint32_t *counts) {
+int code_weights(pass_ctx *c, std::vector<Coded> &coded, uint32_t *counts, const void *lm_head, const std::vector<LayerW> &layers,
+                 bool transposed) {
   const size_t n = coded.size(), d = c->P.d, D = c->P.D, F = c->P.F, V = c->P.V;
   struct Src { const void *p; size_t N, K; };
-  std::vector<Src> src{{c->lm_head, V, d}};
-  for (const LayerW &l : c->layers) {
+  std::vector<Src> src{{lm_head, V, d}};
+  for (const LayerW &l : layers) {
     src.push_back({l.wqkv, 3 * D, d}); src.push_back({l.wo, d, D});
     src.push_back({l.wgu, 2 * F, d}); src.push_back({l.wdown, d, F});
   }
+  if (transposed)
+    for (Src &x : src) std::swap(x.N, x.K);
   uint32_t *used = counts + n * 128;
   launch_fill_i32((int32_t *)counts, 0, n * 130, c->stream);
   for (size_t i = 0; i < n; ++i)
@@ -922,7 +928,9 @@ int pass_load_weights(pass_ctx *c, const pass_weights *w, int on_device) {
 }
 
 size_t pass_coded_bytes(pass_ctx *c) {
-  return c && c->weights_loaded && c->use_mfma ? carve_coded(c->cfg, nullptr, nullptr, nullptr) : 0;
+  if (!c || !c->weights_loaded || !c->use_mfma) return 0;
+  const size_t plain = carve_coded(c->cfg, false, nullptr, nullptr, nullptr), transposed = carve_coded(c->cfg, true, nullptr, nullptr, nullptr);
+  return plain ? std::max(plain, transposed) : 0;
 }
 
 int pass_coded_begin(pass_ctx *c, void *device_workspace, size_t bytes) {
@@ -937,8 +945,8 @@ int pass_coded_begin(pass_ctx *c, void *device_workspace, size_t bytes) {
   c->coded.clear();
   std::vector<Coded> coded;
   uint32_t *counts;
-  carve_coded(c->cfg, (char *)device_workspace, &coded, &counts);
-  const int rc = code_weights(c, coded, counts);
+  carve_coded(c->cfg, false, (char *)device_workspace, &coded, &counts);
+  const int rc = code_weights(c, coded, counts, c->lm_head, c->layers, false);
   if (rc == PASS_OK) c->coded = coded;
   return rc;
 }
@@ -1504,6 +1512,13 @@ int pass_train_begin(pass_ctx *c, void *device_workspace, size_t bytes, int32_t 
       launch_transpose_packed(w.wdown, t.wdown, d, F, c->stream);
     }
     HIP_TRY(c, hipGetLastError());
+    const size_t need = carve_train(c->cfg, true, nullptr, nullptr);
+    if (!c->coded.empty() && bytes - need >= pass_coded_bytes(c)) {
+      uint32_t *counts;
+      carve_coded(c->cfg, true, (char *)device_workspace + need, &c->train.coded, &counts);
+      const int rc = code_weights(c, c->train.coded, counts, c->train.lm_head_t, c->train.layers_t, true);
+      if (rc) return rc;
+    }
   }
   if (!c->train_loss_host) HIP_TRY(c, hipHostMalloc((void **)&c->train_loss_host, sizeof(float) * kMaxRows, hipHostMallocDefault));
   launch_lookahead_init(c->cfg.dtype, c->tok_emb, c->lookahead, init_token, c->cfg.k, c->P.d, c->train.master, c->train.m1,
@@ -1575,20 +1590,23 @@ int pass_train_step(pass_ctx *c, const int32_t *slots, int n_slots, const int32_
     // ---- backward: every dx = W^T dy is a matrix-core product with the packed transpose; its input travels as
     // (hi, lo) tiles (T.x), its output as slices over the contraction (T.part) that the consumer adds up ----
     const size_t rows = kMaxRows;
+    auto transposed = [&](const void *tiles, int which) {
+      return Matrix{tiles, c->opt_coded && !T.coded.empty() && T.coded[which].on ? T.coded[which] : Coded{}};
+    };
     launch_ce_grad(T.logits, T.targets, loss_scale, T.row_loss, M, P.V, (float2 *)P.row_parts, T.x, s);
-    int KS = launch_gemm_plain(P, Matrix{T.lm_head_t, {}}, T.x, M, (int)d, (int)V, T.part, s);
+    int KS = launch_gemm_plain(P, transposed(T.lm_head_t, 0), T.x, M, (int)d, (int)V, T.part, s);
     launch_rmsnorm_bwd(P, dt, T.save_hl, c->final_norm, T.part, KS, rows * d, T.dh, M, 0, T.x, s);
     for (int l = P.L - 1; l >= 0; --l) {
       const LayerW &w = c->layers[l], &t = T.layers_t[l];
-      KS = launch_gemm_plain(P, Matrix{t.wdown, {}}, T.x, M, (int)F, (int)d, T.part, s);
+      KS = launch_gemm_plain(P, transposed(t.wdown, 4 + 4 * l), T.x, M, (int)F, (int)d, T.part, s);
       launch_swiglu_bwd_tiles(P, T.save_gu + (size_t)l * kMaxRows * 2 * F, T.part, KS, rows * F, T.x, M, s);
-      KS = launch_gemm_plain(P, Matrix{t.wgu, {}}, T.x, M, (int)d, (int)(2 * F), T.part, s);
+      KS = launch_gemm_plain(P, transposed(t.wgu, 3 + 4 * l), T.x, M, (int)d, (int)(2 * F), T.part, s);
       launch_rmsnorm_bwd(P, dt, T.save_h1 + (size_t)l * kMaxRows * d, w.ffn_norm, T.part, KS, rows * d, T.dh, M, 1, T.x, s);
-      KS = launch_gemm_plain(P, Matrix{t.wo, {}}, T.x, M, (int)D, (int)d, T.part, s);
+      KS = launch_gemm_plain(P, transposed(t.wo, 2 + 4 * l), T.x, M, (int)D, (int)d, T.part, s);
       launch_attn_bwd(P, dt, l, n_slots, R, max_keys, T.save_qkv + (size_t)l * kMaxRows * 3 * D, (int)(3 * D), nullptr,
                       (const uint16_t *)(T.save_attn + (size_t)l * kMaxRows * D), T.save_lse + (size_t)l * kMaxRows * H, T.part, KS,
                       rows * D, T.dq_part, T.dqkv, T.x, s);
-      KS = launch_gemm_plain(P, Matrix{t.wqkv, {}}, T.x, M, (int)d, (int)(3 * D), T.part, s);
+      KS = launch_gemm_plain(P, transposed(t.wqkv, 1 + 4 * l), T.x, M, (int)d, (int)(3 * D), T.part, s);
       launch_rmsnorm_bwd(P, dt, T.save_h0 + (size_t)l * kMaxRows * d, w.attn_norm, T.part, KS, rows * d, T.dh, M, 1, T.x, s);
     }
   } else {

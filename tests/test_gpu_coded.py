@@ -36,39 +36,42 @@ def random_weights(shape, k, seed, spread=0.0):
     return W
 
 
-# strips: one, two, three and four a workgroup of the LM head, the last workgroup with fewer; the last: exponents all over, no copy
-@pytest.mark.parametrize("V,wide", [(2000, False), (6416, False), (10000, False), (15984, False), (2000, True)])
-def test_what_is_read_back(V, wide):
+# strips: one, two, three and four a workgroup of the LM head, the last workgroup with fewer; exponents all over, no copy; several slots:
+# 16, 24 and 40 rows through rings of LDS stages
+@pytest.mark.parametrize("d,V,slots,wide", [(2048, 2000, 1, False), (2048, 6416, 1, False), (2048, 10000, 1, False), (2048, 15984, 1, False), (2048, 2000, 1, True),
+                                            (4096, 4112, 2, False), (2080, 8208, 3, False), (4096, 12016, 5, False)])
+def test_what_is_read_back(d, V, slots, wide):
     """Rows that are one-hot make a logit a weight of the LM head times the row's norm, which one weight of 1 gives."""
     from paper_2311_13581_amd import binding
-    d, k, rng = 2048, 7, np.random.default_rng(V)
+    k, rng = 7, np.random.default_rng(V)
     shape = synth.ModelShape(1, d, 1, 128, 32, V, dtype=synth.BF16)
     z = lambda *s: bits(np.zeros(s, np.float32)).reshape(s)
     head = rng.standard_normal((V, d)).astype(np.float32) * np.float32(0.02)
-    cols = np.array([0, 31, 32, 777, 1023, 1024, 2015, 2047])
+    cols = np.array([31, 32, 777, 1023, 1024, 2015, d - 1, 0, 1, 1025, 64, 2047])[:7 + slots]  # of the look-ahead rows, of the slots' tokens
     special = np.array([0.0, -0.0, 2.0 ** -126, -2.0 ** -130, 1e30, -3e-20, 5.0, 2.0 ** -133], np.float32)
     head[64:80, 992:1024] = special[rng.integers(0, 8, (16, 32))]  # a tile with (many) more than 128 weights outside ...
     if not wide:
         head[64:80, 992:1024] *= rng.random((16, 32)) < 0.15  # ... or some 60
-    head[V - 3:, cols] = special[rng.integers(0, 8, (3, 8))]
+    head[V - 3:, cols] = special[rng.integers(0, 8, (3, len(cols)))]
     for r in rng.integers(0, V, 60):
-        head[r, cols[rng.integers(0, 8)]] = special[rng.integers(0, 8)]
+        head[r, cols[rng.integers(0, len(cols))]] = special[rng.integers(0, 8)]
     head[1, cols] = 1
     tok, la = np.zeros((V, d), np.float32), np.zeros((k, d), np.float32)
-    tok[3, cols[0]], la[np.arange(k), cols[1:]] = 1, 1
+    tok[3 + np.arange(slots), cols[7:]], la[np.arange(k), cols[:7]] = 1, 1
     one = bits(np.ones(d, np.float32))
     W = {"tok_emb": bits(tok).reshape(V, d), "lm_head": bits(head).reshape(V, d), "final_norm": one, "lookahead": bits(la).reshape(k, d),
          "attn_norm": [one], "ffn_norm": [one], "wq": [z(128, d)], "wk": [z(128, d)], "wv": [z(128, d)], "wo": [z(d, 128)],
          "w_gate": [z(32, d)], "w_up": [z(32, d)], "w_down": [z(d, 32)]}
-    g = binding.Pass(binding.make_config(shape, k, 1, 64, 64))
+    g = binding.Pass(binding.make_config(shape, k, slots, 64, 64))
     g.load_weights(W)
     assert g.coded is not None
-    g.prefill(0, np.array([3], np.int32))
-    g.draft([0], 0.0, 1)
-    got = g.get_logits(0, 0)
+    for s in range(slots):
+        g.prefill(s, np.array([3 + s], np.int32))
+    g.draft(list(range(slots)), 0.0, 1)
+    for s in range(slots):
+        got, want = g.get_logits(s, 0), rounded(head)[:, np.append(cols[7 + s], cols[:7])].T
+        assert np.array_equal(got, want * got[:, 1:2])
     g.close()
-    want = rounded(head)[:, cols].T
-    assert np.array_equal(got, want * got[:, 1:2])
 
 
 # blocks a workgroup of QKV (d 2048: 10 and 16 heads, 3072, 5120), of gate/up (F 3200, 5504, 9600, 14400), Wo and down whole on up to 256
@@ -98,23 +101,50 @@ def test_coded_and_plain_products_agree(d, heads, F, V, k, spread):
         assert np.array_equal(b, c)
 
 
-def test_training_on_coded_matrices():
-    """A step of few rows (its gate/up product keeps the pre-activations): the gradient on the copies and on the plain matrices."""
+# 16, 24, 40 and 48 rows: two to eight strips a workgroup, whole and in slices of K, and (d 5120, 32 rows and more) gate/up on the plain matrix
+@pytest.mark.parametrize("d,heads,F,V", [(4096, 32, 11008, 8000), (5120, 40, 13760, 4160), (4096, 32, 9632, 33008)])
+def test_coded_and_plain_products_agree_in_batches(d, heads, F, V):
     from paper_2311_13581_amd import binding
-    shape, k = synth.ModelShape(1, 2048, 16, 128, 5504, 1024, dtype=synth.BF16), 3
+    shape, slots = synth.ModelShape(1, d, heads, 128, F, V, dtype=synth.BF16), list(range(8))
+    g = binding.Pass(binding.make_config(shape, 5, 8, 128, 64))
+    g.load_weights(random_weights(shape, 5, d + F, 0.002))
+    for rows in (1, 2, 4, 5):
+        g.set_option("lookahead_rows", rows)
+        out = []
+        for coded in (0, 1):
+            g.set_option("tune.coded", coded)
+            for s in slots:
+                g.prefill(s, np.arange(20 + s, dtype=np.int32))
+            g.draft(slots, 0.0, 1)
+            out.append(np.stack([g.get_logits(s, 0)[:1 + rows] for s in slots]))
+            g.verify(slots, 0.0, 1)  # (the number of rows changes between iterations only)
+        assert np.linalg.norm(out[0] - out[1]) <= 1e-4 * np.linalg.norm(out[0]), rows
+    g.close()
+
+
+# one slot: four rows through the register form, its gate/up product keeping the pre-activations; eight: 32 rows and coded transposes
+@pytest.mark.parametrize("d,heads,F,slots", [(2048, 16, 5504, 1), (4096, 32, 4416, 8)])
+def test_training_on_coded_matrices(d, heads, F, slots):
+    """The gradient of a step on the copies and on the plain matrices."""
+    from paper_2311_13581_amd import binding
+    shape, k = synth.ModelShape(1, d, heads, 128, F, 4096, dtype=synth.BF16), 3
     W = random_weights(shape, k, 5, 0.002)
-    prompt, target = np.arange(50, dtype=np.int32), np.array([[5, 6, 7]], np.int32)
+    target = np.arange(3 * slots, dtype=np.int32).reshape(slots, 3)
+    g = binding.Pass(binding.make_config(shape, k, slots, 128, 64))
+    g.load_weights(W)
     out = []
     for coded in (0, 1):
-        g = binding.Pass(binding.make_config(shape, k, 1, 128, 64), {"tune.coded": coded})
-        g.load_weights(W)
+        g.set_option("tune.coded", coded)
         g.train_begin(-1)
-        g.prefill(0, prompt)
-        loss = g.train_step([0], target, 0.01)
+        for s in range(slots):
+            g.prefill(s, np.arange(30 + s, dtype=np.int32))
+        loss = g.train_step(list(range(slots)), target, 0.01)
         out.append((loss, g.train_read(1)))
-        g.close()
+        g.load_weights(W)
+    assert g.train_ws.numel() > g.lib.pass_train_bytes(g.h) + g.lib.pass_coded_bytes(g.h)
+    g.close()
     (l0, g0), (l1, g1) = out
-    assert abs(l0 - l1) <= 1e-5 * abs(l0) and np.linalg.norm(g0 - g1) <= 1e-4 * np.linalg.norm(g0)
+    assert abs(l0 - l1) <= 1e-5 * abs(l0) and np.linalg.norm(g0 - g1) <= 2e-4 * np.linalg.norm(g0)
 
 
 def test_workspace_of_the_copies():
