@@ -73,9 +73,9 @@ template <int DPL> struct RawChunk<bf16_t, DPL> { uint32_t v[DPL / 2]; };
 // kernel would give them (a merge of one triple multiplies by one), and no merge kernel runs.
 __device__ __forceinline__ void store_attn_split(const Params &p, int m, int head_dim_index, float o) {
   const uint16_t hi = f32_to_bf16(o);
-  const size_t xi = xs_index(m, p.D, head_dim_index);
+  const size_t xi = xs_index(m, p.D, head_dim_index, p.xr);
   p.attn_x[xi] = hi;
-  p.attn_x[xi + kXsLoOffset] = f32_to_bf16(o - bf16_to_f32(hi));
+  p.attn_x[xi + kXsLo * p.xr] = f32_to_bf16(o - bf16_to_f32(hi));
 }
 
 // RQ: rows carried in registers (rows of a group, rounded up to 4 or 8: a row's arithmetic does not depend on it)
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   }
   if (direct) {
     const float t[4] = {v[0] / l_n, v[1] / l_n, v[2] / l_n, v[3] / l_n};
-    store_split4(p.attn_x, m0 + r, p.D, head * HD + dim, t);
+    store_split4(p.attn_x, m0 + r, p.D, head * HD + dim, t, p.xr);
     return;
   }
   const size_t pi = (((size_t)(m0 + r) * p.H + head) * kMaxSplits + split);
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(Params p, int R, int 
 #pragma unroll
   for (int e = 0; e < 4; ++e) o[e] = dead ? 0.f : v[e] / l_n;
   if (OUT == 1)  // (hi, lo) pairs in the tiled activation layout of the matrix-core GEMMs
-    store_split4(p.attn_x, m, p.D, head * HD + dim, o);
+    store_split4(p.attn_x, m, p.D, head * HD + dim, o, p.xr);
   else
     *(f32x4_t *)(p.attn + (size_t)m * p.D + head * HD + dim) = f32x4_t{o[0], o[1], o[2], o[3]};
 }

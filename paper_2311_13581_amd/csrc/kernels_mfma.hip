@@ -87,7 +87,7 @@ void launch_pack_tiles(const uint16_t *src, uint16_t *dst, int N, int K, int str
 // of those per tile stand in a fix word beside it (place and bits); a tile with more is read in its plain form.  What a
 // product multiplies is bit for bit the plain weight.
 // Measured at 5 rows (7B shapes, us, plain -> coded): QKV 17.6 -> 14.6, gate/up 29.0 -> 23.0, LM head 41.2 -> 31.4, Wo
-// 8.1 -> 7.4, down 17.4 -> 16.1.
+// 8.1 -> 7.4, down 17.4 -> 16.1 (beside activation tiles with room for 8 rows; xs_index has what tiles of 5 give).
 // ---------------------------------------------------------------------------------------------
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3), aligned(4)));
 constexpr int kCodedTile = 768;  // bytes
@@ -281,9 +281,9 @@ __global__ __launch_bounds__(256) void assemble_mfma_kernel(Params p, const uint
     hi.y = split2_bf16(x[2], x[3], true); lo.y = split2_bf16(x[2], x[3], false);
     hi.z = split2_bf16(x[4], x[5], true); lo.z = split2_bf16(x[4], x[5], false);
     hi.w = split2_bf16(x[6], x[7], true); lo.w = split2_bf16(x[6], x[7], false);
-    uint16_t *xh = p.xg + xs_index(m, p.d, c0);
+    uint16_t *xh = p.xg + xs_index(m, p.d, c0, p.xr);
     *(uint4 *)xh = hi;
-    *(uint4 *)(xh + kXsLoOffset) = lo;
+    *(uint4 *)(xh + kXsLo * p.xr) = lo;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
   }
@@ -496,7 +496,7 @@ struct Epilogue {
               float gt = y[0][r] * inv, up = y[1][r] * inv;
               t[r] = gt / (1.0f + __expf(-gt)) * up;
             }
-            store_split4(p.act_x, m, p.F, f0, t);
+            store_split4(p.act_x, m, p.F, f0, t, p.xr);
             if constexpr (EPI == EPI_GATEUP_SAVE) {
               *(floatx4 *)(a.gu_save + (size_t)m * 2 * p.F + f0) = y[0] * inv;
               *(floatx4 *)(a.gu_save + (size_t)m * 2 * p.F + p.F + f0) = y[1] * inv;
@@ -519,7 +519,7 @@ struct Epilogue {
               t[r] = hv[r] * __uint_as_float(r & 1 ? gw[r >> 1] & 0xffff0000u : gw[r >> 1] << 16);
               ss += hv[r] * hv[r];
             }
-            store_split4(p.xg, m, p.d, n, t);
+            store_split4(p.xg, m, p.d, n, t, p.xr);
           }
           ss += __shfl_xor(ss, 16);
           ss += __shfl_xor(ss, 32);
@@ -561,6 +561,9 @@ struct Epilogue {
   }
 };
 
+// byte offset of a lane's 16 bytes in a k-tile of a group of rows that has room for xr of them
+__device__ __forceinline__ int x_lane(int lane, int xr) { return ((lane >> 4) * 2 * xr + (lane & 7) + (lane >> 3 & 1) * xr) * 16; }
+
 // Calls of up to 8 rows: one MFMA column block, operands through registers.  A workgroup owns NB output blocks (a block is
 // one strip of 16 features, or the gate strip and the up strip of 16 FFN features) and its wavefronts share K: wavefront w
 // takes k-tiles w, w + WAVES, ..., U of them a trip, and requests a trip while it computes the one before.  The last trip may
@@ -599,7 +602,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
   // offset and the hardware returns zeros without touching memory.  All loads are unconditional instructions, so
   // outstanding requests are counted exactly and a trip can wait for its operands while the next trip's stay in flight.
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, 16 * a.K * 2, 0x00020000);
-  const int xoff = (ml & 7) < a.M ? lane * 16 : 0x40000000;  // byte offset of this lane's 16 bytes in k-tile 0
+  const int xtile = p.xr * 128;  // bytes of a k-tile of the rows
+  const int xoff = (ml & 7) < a.M ? x_lane(lane, p.xr) : 0x40000000;  // byte offset of this lane's 16 bytes in k-tile 0
   typedef typename LaneTile<Z>::T Tile;
   const char *wp[NS];  // strips past the end repeat the last one (in bounds; their results are dropped)
 #pragma unroll
@@ -612,7 +616,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_mfma_kernel(Params p, GemmArg
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int kt = min(wave + (trip * U + u) * WAVES, KT - 1);
-      bv[buf][u] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff, kt * 1024, 0);
+      bv[buf][u] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff, kt * xtile, 0);
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         if constexpr (Z) av[buf][u][s] = __builtin_nontemporal_load((const u32x3 *)(wp[s] + ((size_t)kt * 64 + lane) * 12));
@@ -740,6 +744,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
     wp[s] = (const char *)(Z ? a.z.tiles : a.W) + ((size_t)min(strip0 + s, a.n_strips - 1) * KT + kbase + wave) * TILE + min(lane, TILE / 16 - 1) * 16;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) xp[mt] = (const u32x4 *)a.X + ((size_t)mt * KT + kbase + wave) * 64 + lane;
+  const int xr = MT == 1 ? p.xr : 8;  // (one group: the rows that are not there have no place in memory, theirs in LDS holds anything)
+  const char *x1 = (const char *)a.X + (size_t)(kbase + wave) * (xr * 128) + x_lane(lane, xr);
   char *mine = (char *)ring + wave * (D * STAGE);
 
   // The sums lose as little as with eight wavefronts or more sharing K: either two accumulators per tile, one of the
@@ -764,7 +770,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_rows_kernel(Params p, GemmArg
   const int n = (KTl - wave + WAVES - 1) / WAVES;
   auto issue = [&](int i, char *st) __attribute__((always_inline)) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) copy_to_lds<false>(xp[mt] + (size_t)i * WAVES * 64, st + NS * TILE + mt * 1024);
+    for (int mt = 0; mt < MT; ++mt) {
+      if constexpr (MT > 1) copy_to_lds<false>(xp[mt] + (size_t)i * WAVES * 64, st + NS * TILE + mt * 1024);
+      else if ((lane & 7) < xr) copy_to_lds<false>(x1 + (size_t)i * WAVES * (xr * 128), st + NS * TILE);
+    }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       if (!Z || lane < kCodedTile / 16) copy_to_lds<true>(wp[s] + (size_t)i * WAVES * TILE, st + s * TILE);
@@ -969,7 +978,8 @@ static int few_rows_slices(int n, int K, int d, int F, bool coded, int &nb_best)
 // three quarters of a tile per strip and the activation tile.  Residual products as above.  (Measured against the plain tiles in
 // their best shape, us: QKV d 2048 7.2 and 7.3, 4096 14.9 and 17.7, 5120 21.1 and 25.8; gate/up d 2048, 344 blocks, two a workgroup
 // 9.3 and 9.9, 4096, 688, three 23.8 and 29.1, 5120, 860, four 35.1 and 43.5, 1120, three 49.9 and 59.6; LM head V 32000, four, d 1024 10.3
-// and 12.3, 4096 31.7 and 41.4, V 24000, two, 26.2 and 31.8; Wo d 4096 7.5 and 8.1, 5120 11.9 and 12.6; down K 11008 16.7 and 17.5.)
+// and 12.3, 4096 31.7 and 41.4, V 24000, two, 26.2 and 31.8; Wo d 4096 6.9 and 8.1, 5120 11.9 and 12.6; down K 11008 15.3 and
+// 17.5: their four k-tiles a trip take 2 % less than two.)
 static int coded_blocks(int n, int per) {
   int best = 1;
   auto cost = [&](int nb) { return ((n + nb - 1) / nb + 255) / 256 * (3 * per * nb + 4); };
@@ -986,7 +996,7 @@ static void launch_coded(const Params &p, const GemmArgs &a, int n_blocks, hipSt
     gemm_mfma_kernel<EPI, w, u, nb, true><<<(n_blocks + nb - 1) / nb, w * 64, 0, s>>>(p, a);
   };
   if constexpr (EPI == EPI_RESID) {
-    if (n_blocks <= 256) go(nb_c<8>{}, nb_c<2>{}, nb_c<1>{});
+    if (n_blocks <= 256) go(nb_c<8>{}, nb_c<4>{}, nb_c<1>{});
     else go(nb_c<16>{}, nb_c<1>{}, nb_c<2>{});
   } else {
     constexpr int U = EPI == EPI_QKV ? 2 : 1;  // k-tiles a trip where a workgroup has two or three blocks
@@ -1153,7 +1163,7 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(Params p, const float
       t[r] = hv[r] * bf16_to_f32(gain_next[n + r]);
       ss += hv[r] * hv[r];
     }
-    store_split4(p.xg, m, p.d, n, t);
+    store_split4(p.xg, m, p.d, n, t, p.xr);
   }
   ss += __shfl_xor(ss, 1);
   ss += __shfl_xor(ss, 2);

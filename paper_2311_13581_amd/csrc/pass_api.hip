@@ -186,7 +186,7 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   Params P;
   memset(&P, 0, sizeof P);
   P.L = c.n_layers; P.d = c.d_model; P.H = c.n_heads; P.hd = c.head_dim; P.D = (int)D; P.F = c.d_ffn; P.V = c.vocab;
-  P.k = c.k; P.k_act = c.k; P.la_token = -1; P.max_slots = c.max_slots; P.max_seq_len = c.max_seq_len; P.page_size = c.page_size;
+  P.k = c.k; P.k_act = c.k; P.la_token = -1; P.xr = 8; P.max_slots = c.max_slots; P.max_seq_len = c.max_seq_len; P.page_size = c.page_size;
   P.page_shift = __builtin_ctz(c.page_size); P.n_pages = np; P.pages_per_seq = pps;
   P.gen_cap = c.max_seq_len + kMaxK + 2;
   P.eps = c.rms_eps; P.rope_base = c.rope_base;
@@ -454,6 +454,7 @@ int run_step(pass_ctx *c, int mode, int B, int R, float *logits_base, int max_ke
   Params P = c->P;
   P.prefill_ids = const_cast<int32_t *>(prefill_ids);
   const int dt = c->cfg.dtype, M = B * R;
+  P.xr = std::min(M, 8);
   if (c->static_scratch) {  // same layout as in the arena: [M][H][kMaxSplits] accumulators, then maxima, then sums
     float *base = (float *)g_scratch_ptr[c->device];
     const size_t triples = (size_t)M * P.H * kMaxSplits;

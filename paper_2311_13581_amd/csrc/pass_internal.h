@@ -91,6 +91,7 @@ struct Params {
   int gen_cap;
   int kv_tiled;  // pages hold K as [head][hd / 8][page_size][8] and V as [head][page_size / 8][hd][8] (matrix-core attention: sixteen
                  //   lanes that read neighbouring keys, or dimensions, read whole lines) instead of [head][page_size][hd]
+  int xr;        // matrix-core path: rows that a group of the (hi, lo) activation tiles has room for (xs_index); 8, a decode call's M if fewer
   float eps, rope_base;
   // per-slot state (device), indexed by slot
   int32_t *kv_len, *pending, *first, *drafts /*[slot][kMaxK]*/, *n_gen, *n_acc, *frozen, *gen_limit;
@@ -238,21 +239,26 @@ void launch_gemm_resid(const Params &p, const GemmTuning &tn, const Matrix &W, c
 void launch_gemm_gateup(const Params &p, const GemmTuning &tn, const Matrix &W, int M, hipStream_t s);
 // (hi, lo) activation buffers of the matrix-core path, K features per row, tiled like the MFMA B
 // operand: [m / 8][K / 32][64 lanes][8 features]; lane = (k / 8 % 4) * 16 + m % 8 for the hi half,
-// 8 lanes further for the lo half.  Element index of the hi half of feature k of row m:
-__device__ __forceinline__ size_t xs_index(int m, int K, int k) {
-  return ((((size_t)(m >> 3) * (K >> 5) + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (m & 7)) << 3) + (k & 7);
+// 8 lanes further for the lo half.  The one group of a decode call of fewer than 8 rows has no room for the rows that are not there
+// (xr, Params::xr: rows that a group has room for; a tile is [k / 8 % 4][hi, lo][xr][8]): a workgroup that owns few strips takes in as many
+// cache lines of activations as of weights, and these come in whole lines whatever rows they hold.
+// Measured at 5 rows (tiles of 8 rows -> of 5): down 16.6 -> 15.3 us, Wo 7.4 -> 6.9, LM head 31.2 -> 30.9; 1 row 16.4 -> 14.6 and 7.3 -> 6.7.
+// Element index of the hi half of feature k of row m:
+__device__ __forceinline__ size_t xs_index(int m, int K, int k, int xr = 8) {
+  return ((((size_t)(m >> 3) * (K >> 5) + (k >> 5)) * 4 + ((k >> 3) & 3)) * (2 * xr) + (m & 7)) * 8 + (k & 7);
 }
-constexpr int kXsLoOffset = 64;  // elements from a hi half to its lo half
+constexpr int kXsLo = 8;         // elements from a hi half to its lo half: kXsLo * xr
+constexpr int kXsLoOffset = 64;  // the same where a group has 8 rows
 // (hi, lo) of four consecutive features k .. k+3 of row m: x = hi + lo up to 2^-17 relative
-__device__ __forceinline__ void store_split4(uint16_t *xs, int m, int K, int k, const float (&v)[4]) {
+__device__ __forceinline__ void store_split4(uint16_t *xs, int m, int K, int k, const float (&v)[4], int xr = 8) {
   uint2 ph, pl;
   ph.x = pack2_bf16(v[0], v[1]);
   ph.y = pack2_bf16(v[2], v[3]);
   pl.x = pack2_bf16(v[0] - __uint_as_float(ph.x << 16), v[1] - __uint_as_float(ph.x & 0xffff0000u));
   pl.y = pack2_bf16(v[2] - __uint_as_float(ph.y << 16), v[3] - __uint_as_float(ph.y & 0xffff0000u));
-  uint16_t *hp = xs + xs_index(m, K, k);
+  uint16_t *hp = xs + xs_index(m, K, k, xr);
   *(uint2 *)hp = ph;
-  *(uint2 *)(hp + kXsLoOffset) = pl;
+  *(uint2 *)(hp + kXsLo * xr) = pl;
 }
 
 // Tiled prompt pass (bf16 models on the matrix-core path with a tiled cache): up to `rows`

@@ -122,6 +122,34 @@ def test_coded_and_plain_products_agree_in_batches(d, heads, F, V):
     g.close()
 
 
+# calls of 1 to 8 rows, whose activation tiles have room for just those: both register forms, and slices of K through rings of LDS stages
+@pytest.mark.parametrize("coded,slices", [(1, 0), (0, 0), (1, 3), (0, 2)])
+@pytest.mark.parametrize("d,heads,F", [(2048, 16, 3200), (5120, 40, 8224)])
+def test_few_rows_agree_with_a_batch(d, heads, F, coded, slices):
+    """A slot's logits in a call of its own and in one of eight slots, of 8 to 64 rows: only sums in another order differ.  1e-4 as above,
+    which holds for one layer: a K/V element rounds the other way with the chance of the sums' difference over its last place, 3e-7 / 4e-3, and
+    is 4e-3 off then, 3e-5 of the row; in a second layer, whose input differs by that much, ten times as much."""
+    from paper_2311_13581_amd import binding
+    shape, slots = synth.ModelShape(1, d, heads, 128, F, 1008, dtype=synth.BF16), list(range(8))
+    g = binding.Pass(binding.make_config(shape, 7, 8, 128, 64))
+    g.load_weights(random_weights(shape, 7, d + F, 0.002))
+    g.set_option("tune.coded", coded)
+    g.set_option("tune.gemm_cfg", 2000000 + slices)
+    for ahead in range(8):
+        g.set_option("lookahead_rows", ahead)
+        out = []
+        for of in (slots, [ahead]):
+            for s in of:
+                g.prefill(s, np.arange(1, 3 + s, dtype=np.int32), seq_id=s)  # (prompts of 1 to 8 rows)
+            g.draft(of, 0.0, 1)
+            a = g.get_logits(ahead, 0)[:1 + ahead].copy()
+            g.verify(of, 0.0, 1)
+            out.append((a, g.get_logits(ahead, 1)[:1 + ahead].copy()))
+        for a, b in zip(*out):
+            assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(a), ahead
+    g.close()
+
+
 # one slot: four rows through the register form, its gate/up product keeping the pre-activations; eight: 32 rows and coded transposes
 @pytest.mark.parametrize("d,heads,F,slots", [(2048, 16, 5504, 1), (4096, 32, 4416, 8)])
 def test_training_on_coded_matrices(d, heads, F, slots):
