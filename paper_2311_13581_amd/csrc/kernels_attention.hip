@@ -238,15 +238,22 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 template <int I> struct yes_c { static constexpr int value = I; };
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void attn_split_mfma_kernel(Params p, int layer, int R, int direct) {
+// MORE: splits may hold several steps.  Where none does, no plan is looked up and the requests for V wait for the query rows, whose registers they
+// take: 123 registers and four workgroups a unit instead of 144 and three (us, before -> now: 520 keys 6.15 -> 5.9, 2100 keys of one row 9.0 -> 8.9,
+// of seven 10.7 -> 10.4, batch of eight 28.5 -> 28.3; five runs of whole cases 0.3 to 1 % faster).
+template <bool MORE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MORE ? 3 : 4, MORE ? 3 : 4))) void attn_split_mfma_kernel(Params p, int layer, int R, int direct) {
   constexpr int HD = 128, RQ = kAttnRowsPerGroup;
   __shared__ float s_m[4][RQ], s_l[4][RQ];
   __shared__ __align__(16) float s_acc[4][RQ][HD];
 
   const int split = blockIdx.x, head = blockIdx.y, grp_id = blockIdx.z;
-  const int groups_per_slot = (R + RQ - 1) / RQ;
-  const int b = grp_id / groups_per_slot;
-  const int r0 = (grp_id % groups_per_slot) * RQ;
+  int b = grp_id, r0 = 0;
+  if (R > RQ) {
+    const int groups_per_slot = (R + RQ - 1) / RQ;
+    b = grp_id / groups_per_slot;
+    r0 = (grp_id % groups_per_slot) * RQ;
+  }
   const int nr = min(RQ, R - r0);
   const int m0 = b * R + r0;
   // Requests that depend on each other come in three rounds and no more: (slot, position), then
@@ -256,8 +263,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const int slot = p.row_slot[m0];
   const int pos0 = p.row_pos[m0];
   const int n_keys = pos0 + nr;
-  int n_splits, chunk;
-  split_plan_mfma(n_keys, p.H, n_splits, chunk);
+  int n_splits = (n_keys + 127) / 128, chunk = 128;
+  if (MORE) split_plan_mfma(n_keys, p.H, n_splits, chunk);
   if (slot < 0 || split >= n_splits) {
     if (direct && slot < 0)
       for (int e = threadIdx.x; e < nr * HD; e += 256) store_attn_split(p, m0 + e / HD, head * HD + e % HD, 0.f);
@@ -310,8 +317,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     // in this split asks for the split's first keys, which exist, and skips the loop)
     const int at = base < k_hi ? base : k_lo, page = page_of(at);
     request_k(at, page);
-    request_v(at, page);
-    __builtin_amdgcn_sched_barrier(0);  // all sixteen leave before anything is computed
+    if (MORE) request_v(at, page);
+    __builtin_amdgcn_sched_barrier(0);  // these leave before anything is computed
     const float sc_q = live ? scale : 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -320,6 +327,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         qf[j][2 * h] = split2_bf16(raw[j][h][0] * sc_q, raw[j][h][1] * sc_q, ml < 8);
         qf[j][2 * h + 1] = split2_bf16(raw[j][h][2] * sc_q, raw[j][h][3] * sc_q, ml < 8);
       }
+    if (!MORE) {  // V's registers are those that the query rows came in, which are halved here (left alone, the compiler does it behind V)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(qf[j]));
+      __builtin_amdgcn_sched_barrier(0);
+      request_v(at, page);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 
   f32x4_t o[8];
@@ -348,15 +362,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     // lane (column ml, g) now holds the scores of keys base + 8g + 4t + r; add the lo-half column
     float s[8];
     float m_blk = -INFINITY;
+    const int last = row < nr ? min(k_hi - 1, pos0 + row) - base - 8 * g : -1;  // the last of the lane's keys that its row sees
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float v = sc[t][r];
         v += dpp_move<0x128>(v);  // row_ror 8: column ml <-> ml + 8
-        const int key = base + 8 * g + 4 * t + r;
-        const bool ok = (row < nr) && (key < k_hi) && (key <= pos0 + row);
-        v = ok ? v : -INFINITY;
+        v = 4 * t + r <= last ? v : -INFINITY;
         s[4 * t + r] = v;
         m_blk = fmaxf(m_blk, v);
       }
@@ -364,10 +377,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     m_blk = fmaxf(m_blk, __shfl_xor(m_blk, 32));
     const float m_new = kFirst ? m_blk : fmaxf(m_run, m_blk);
     const float alpha = kFirst || m_run == -INFINITY ? 0.f : __expf(m_run - m_new);
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // (a row without keys here: e^(-inf - 0) = 0)
     float pv[8], psum = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      pv[i] = (s[i] == -INFINITY) ? 0.f : __expf(s[i] - m_new);
+      pv[i] = __expf(s[i] - m_ref);
       psum += pv[i];
     }
     l_run = kFirst ? psum : l_run * alpha + psum;
@@ -385,10 +399,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       base += 128;
     }
   };
-  if (base + 128 < k_hi) {
-    step(yes_c<1>{}, yes_c<1>{});
-    while (base + 128 < k_hi) step(yes_c<0>{}, yes_c<1>{});
-    step(yes_c<0>{}, yes_c<0>{});
+  if (MORE && base + 128 < k_hi) {
+    if constexpr (MORE) {
+      step(yes_c<1>{}, yes_c<1>{});
+      while (base + 128 < k_hi) step(yes_c<0>{}, yes_c<1>{});
+      step(yes_c<0>{}, yes_c<0>{});
+    }
   } else if (base < k_hi) {
     step(yes_c<1>{}, yes_c<0>{});
   } else {  // no keys of this split for this wavefront
@@ -556,7 +572,11 @@ void launch_attention(const Params &p, int dtype, int layer, int B, int R, int n
     if (!direct) launch_combine<decltype(HD)::value>(p, B * R * p.H, R, n_splits, out_split, mfma_plan, s);
   };
   if (p.kv_tiled) {  // bf16, head_dim 128, page_size % 32 == 0: matrix-core kernel (its rows leave as (hi, lo) tiles)
-    attn_split_mfma_kernel<<<grid, 256, 0, s>>>(p, layer, R, direct);
+    // while every length up to the caller's bound is cut into single steps, a launch has as many splits as the longest has steps; at the
+    // most steps that can be, or beyond, it has that many or more
+    const bool one_step = n_splits < std::min(kMaxSplits, kAttnResident / p.H);
+    if (one_step) attn_split_mfma_kernel<false><<<grid, 256, 0, s>>>(p, layer, R, direct);
+    else attn_split_mfma_kernel<true><<<grid, 256, 0, s>>>(p, layer, R, direct);
     merge(hd_c<128>{}, 1);
     return;
   }

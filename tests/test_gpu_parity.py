@@ -517,6 +517,26 @@ def test_attention_with_one_split(path, plen):
     g.close()
 
 
+# 96 heads: up to 896 keys in splits of one step, in the kernel for those; 1024 in the general one, in eight; more in splits of two steps
+# (k = 8: groups of eight rows and of one)
+@pytest.mark.parametrize("k,plen", [(4, 60), (4, 880), (4, 889), (4, 893), (4, 1014), (4, 1021), (8, 880), (8, 1100)])
+def test_attention_on_either_side_of_one_step(k, plen):
+    """Logits with the matrix-core attention and with the vector kernel, which differ by the (hi, lo) pairs of queries and probabilities
+    (2^-17 each) and the order of the sums: 5e-5."""
+    shape = synth.ModelShape(1, 256, 96, 128, 512, 1008, dtype=synth.BF16)
+    W = synth.make_weights(shape, 7, k, 6.0)
+    prompt = np.random.default_rng(plen).integers(0, 1008, plen).astype(np.int32)
+    out = []
+    for attn in (0, 1):
+        g = _gpu(shape, W, k, max_slots=2, max_seq_len=1280, page_size=64, options={"attention": attn, "prefill_tiled": 0})
+        for s in (0, 1):
+            g.prefill(s, prompt[:plen - 300 * s] if plen > 300 else prompt, seq_id=s)
+        g.draft([0, 1], 0.0, 1)
+        out.append(np.stack([g.get_logits(s, 0) for s in (0, 1)]))
+        g.close()
+    assert np.linalg.norm(out[0] - out[1]) <= 5e-5 * np.linalg.norm(out[0])
+
+
 @pytest.mark.parametrize("w", [TINY, TINY_BF16, MFMA_HD128], ids=["fp32", "bf16", "hd128"])
 @pytest.mark.parametrize("plen", [125, 180, 186, 193])
 def test_generic_attention_with_two_to_four_splits(w, plen):
