@@ -120,11 +120,15 @@ int pass_load_weights(pass_ctx *ctx, const pass_weights *w, int on_device);
  *   pass_coded_bytes   device bytes pass_coded_begin needs, about three quarters of the matrices (0: no context, no weights, the
  *                      generic path, or a model so small that nothing is gained)
  *   pass_coded_begin   device_workspace: caller's device memory, 256-byte aligned, kept alive until pass_destroy or the
- *                      next pass_load_weights, which ends the use of the copies.  A matrix whose exponents spread too far for the code
- *                      is left without a copy.
- * Errors: PASS_ESTATE (no weights, or pass_coded_bytes is 0), PASS_EINVAL (workspace), PASS_EDEVICE. */
+ *                      next pass_load_weights, which ends the use of the copies.  Weights outside the sixteen octaves that
+ *                      the code takes stand beside it and cost time: a matrix of which more than one in 1300 lies outside, or that has
+ *                      many in one place (a row of zeros among others, say), is multiplied in its plain form.
+ *   pass_coded_use     1: a call of that many rows reads the copy of the matrix, 0: the plain one.  matrix: 0 the LM head, then wq | wk | wv,
+ *                      wo, w_gate | w_up and w_down of every layer; as many again: their transposes, which training multiplies with
+ * Errors: PASS_ESTATE (no weights, or pass_coded_bytes is 0), PASS_EINVAL (workspace, matrix, rows), PASS_EDEVICE. */
 size_t pass_coded_bytes(pass_ctx *ctx);
 int pass_coded_begin(pass_ctx *ctx, void *device_workspace, size_t bytes);
+int pass_coded_use(pass_ctx *ctx, int matrix, int rows);
 
 /* Start a sequence in `slot` (frees what the slot held).  prompt: host, n >= 1 token ids.
  * Computes K/V of prompt[0..n-2]; prompt[n-1] becomes the pending token, so the first

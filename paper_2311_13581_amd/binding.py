@@ -17,7 +17,7 @@ LIB_PATH = os.path.join(_HERE, "libpass_hip.so")
 PASS_F32, PASS_BF16 = 0, 1
 MAX_K, MAX_ROWS = 15, 64
 
-SYMBOLS = ["pass_arena_bytes", "pass_create", "pass_load_weights", "pass_coded_bytes", "pass_coded_begin", "pass_prefill", "pass_prefill_batch", "pass_release",
+SYMBOLS = ["pass_arena_bytes", "pass_create", "pass_load_weights", "pass_coded_bytes", "pass_coded_begin", "pass_coded_use", "pass_prefill", "pass_prefill_batch", "pass_release",
            "pass_draft", "pass_draft_static", "pass_verify", "pass_generate", "pass_sps_iteration", "pass_run_iterations", "pass_kernel_time", "pass_plain_read", "pass_rng_uniforms", "pass_get_logits", "pass_seq_len",
            "pass_train_bytes", "pass_train_begin", "pass_train_step", "pass_train_read", "pass_train_resume", "pass_set_option", "pass_attention_plan", "pass_prefill_plan", "pass_get_tokens", "pass_time_step", "pass_last_error", "pass_destroy"]
 
@@ -85,6 +85,7 @@ def load_library():
     L.pass_coded_bytes.restype = C.c_size_t
     L.pass_coded_bytes.argtypes = [C.c_void_p]
     L.pass_coded_begin.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t]
+    L.pass_coded_use.argtypes = [C.c_void_p, C.c_int, C.c_int]
     L.pass_prefill.argtypes = [C.c_void_p, C.c_int, C.c_uint32, ip, C.c_int]
     L.pass_prefill_batch.argtypes = [C.c_void_p, ip, C.POINTER(C.c_uint32), ip, ip, C.c_int]
     L.pass_release.argtypes = [C.c_void_p, C.c_int]
@@ -269,6 +270,12 @@ class Pass:
             return
         self._check(self.lib.pass_coded_begin(self.h, base, nbytes))
         self.coded = ws
+
+    def coded_use(self, matrix: int, rows: int) -> bool:
+        """Whether a call of that many rows reads the 12-bit copy of a matrix (pass_coded_use)."""
+        rc = self.lib.pass_coded_use(self.h, matrix, rows)
+        self._check(min(rc, 0))
+        return bool(rc)
 
     def prefill(self, slot: int, prompt, seq_id: int = 0):
         p = np.ascontiguousarray(prompt, dtype=np.int32)

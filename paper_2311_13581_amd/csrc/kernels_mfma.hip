@@ -156,8 +156,9 @@ void launch_exponents(const void *src, size_t weights, uint32_t *hist, hipStream
 }
 
 // Packed tiles -> coded tiles and fix words, a wavefront per four tiles.  counts[0]: entries of the overflow list taken so far, counts[1]:
-// set where the copy does not hold the matrix (the list is full, or a tile has more than kFixMost weights outside the table).
-__device__ __forceinline__ void code_tile(const uint4 v, const Coded &z, size_t tile, uint2 *words, uint32_t *counts, int lane) {
+// set where the copy does not hold the matrix (the list is full, or a tile has more than kFixMost weights outside the table).  load: what
+// the tile's strip has outside in the k-tiles that go with this one.
+__device__ __forceinline__ void code_tile(const uint4 v, const Coded &z, size_t tile, uint2 *words, uint32_t *load, uint32_t *counts, int lane) {
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
   const uint32_t first = z.lut0 & 255, base = (z.lut0 >> 8 & 255) - 1;  // the table: `first`, then a run from base + 1 (coded_table)
   uint32_t c[3] = {0, 0, 0};
@@ -178,6 +179,7 @@ __device__ __forceinline__ void code_tile(const uint4 v, const Coded &z, size_t 
     if (lane == 0) *words = make_uint2(0, 0);
     return;
   }
+  if (lane == 0) atomicAdd(load, (uint32_t)n);
   uint32_t at = 0;
   if (n > 2) {
     if (lane == 0) at = atomicAdd(&counts[0], (uint32_t)n - 1);
@@ -210,12 +212,28 @@ __global__ __launch_bounds__(256) void code_tiles_kernel(const uint4 *src, Coded
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const size_t tile = tile0 + i, strip = tile / KT;
-    if (tile < tiles) code_tile(v[i], z, tile, z.fix + strip * fix_stride(KT) + fix_index(KT, (int)(tile - strip * KT)), counts, lane);
+    const int kt = (int)(tile - strip * KT);
+    if (tile < tiles) code_tile(v[i], z, tile, z.fix + strip * fix_stride(KT) + fix_index(KT, kt), z.load + strip * 4 + (kt & 3), counts, lane);
   }
 }
 void launch_code_tiles(const void *src, const Coded &z, int N, int K, uint32_t *counts, hipStream_t s) {
   const size_t tiles = (size_t)(N / 16) * (K / 32);
   code_tiles_kernel<<<(unsigned)((tiles + 15) / 16), 256, 0, s>>>((const uint4 *)src, z, K / 32, tiles, counts);
+}
+// Whether the products of up to 8 rows gain by a copy with that many weights outside its table (load: [N / 16][4], the weights of a strip
+// whose k-tiles agree modulo 4, which the same wavefronts read).  A wavefront puts them in one after the other, 0.10 to 0.14 us each,
+// while the other wavefronts of its workgroup wait at the end.
+// Over all: gate/up of d 4096, 5 rows, 29.3 us plain, with 0.04 weights of a tile outside (normally distributed ones) 24.0, 0.3 25.5, 0.55 27.1, 0.8
+// 32.4, one in every tile 33.5, two 47.7.  In one place: a tile with 32 outside 24.0 us, with 64 26.2, with 128 39.5; a strip with one
+// row of zeros (32 in every tile) 177, with two 342.  Twice what there is on average, and 12, is beyond what chance
+// does to normally distributed weights (60 to 190 in a million outside, by their scale).
+bool coded_pays_for(const uint32_t *load, int N, int K, float *outside) {
+  uint64_t all = 0;
+  uint32_t most = 0;
+  const size_t n = (size_t)N / 16 * 4;
+  for (size_t i = 0; i < n; ++i) { all += load[i]; most = std::max(most, load[i]); }
+  *outside = (float)((double)all * 512 / ((double)N * K));
+  return *outside <= 0.4f && most <= 12 + 2 * all / n;
 }
 // The table of a matrix: the eight values that leave the fewest weights outside, a run of eight or zero's and a run of seven.
 void coded_table(const uint32_t *hist, uint32_t *lut0, uint32_t *lut1) {
@@ -949,13 +967,17 @@ static FewShape few_rows_shape(int epi, int n) {
 // Whether a product of the ring form gains by coded weights.  Small ones only wait longer for their first tile (Wo d 2048 at 16 rows
 // 6.5 us, coded 7.1; QKV 8.2 and 8.7; but Wo d 4096 12.6 and 10.5).
 static bool coded_pays(int n_strips, int K) { return (int64_t)n_strips * 16 * K >= 1 << 24; }
+// What a strip costs it, a plain one being 1, with that many weights of a tile outside the table: its four wavefronts put those in one by one, and
+// beyond 0.16 of a tile the plain matrix is faster (gate/up d 4096, us, plain and coded: 16 rows 31.0, with 0.04 outside 25.8, 0.14 28.0, 0.3 33.7,
+// 0.55 42.9; 40 rows 37.0, 33.6, 36.2, 41.9, 50.9).
+static float coded_strip(float outside) { return 0.75f + 2.0f * std::max(0.0f, outside - 0.04f); }
 // Slices of K of Wo and down in calls of up to 8 rows, and strips per workgroup; 1 = whole K.  Fewer strips than units leave
 // units idle, 257 to 511 strips give some of them two: then the product is bound by those, and slices over all of them pay for
 // the kernel that adds their sums.  In us, fitted to d 1024 .. 5120 (K up to 3.5 d): a unit takes 0.033 us per KB of weights and 0.010
 // per KB of activation tile, the chip 6.9 TB/s, both kernels together 5.2.  The choice is within 9 % of the fastest there, within 6 % at
 // d 6656 and 8192; d 6144 (384 strips) stays whole where two slices of three strips would take 10 % less (one K in six 21 %).
 // d 5120, K 13760: 38.0 us whole in one strip a workgroup, 28 in two, 25.6 in slices; d 2048, K 5504: 9.4 and 8.1.
-static int few_rows_slices(int n, int K, int d, int F, bool coded, int &nb_best) {
+static int few_rows_slices(int n, int K, int d, int F, bool coded, bool slices_coded, int &nb_best) {
   const int KT = K / 32;
   float whole = n <= 256 ? 2.8f + K * (1.1e-3f + 0.7e-6f * n) : 3.0f + ((n + 1) / 2 + 255) / 256 * K * 1.97e-3f;
   if (coded) whole = n <= 256 ? 2.8f + K * (0.95e-3f + 0.9e-6f * n) : 3.0f + ((n + 1) / 2 + 255) / 256 * K * 1.73e-3f;
@@ -967,8 +989,8 @@ static int few_rows_slices(int n, int K, int d, int F, bool coded, int &nb_best)
     if ((size_t)ks * d > (size_t)2 * F) continue;  // the slices' sums borrow the generic path's gate/up workspace
     for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
       const float rounds = ((n + nb - 1) / nb * ks + 255) / 256;
-      const float us = coded && coded_pays(n, K) ? 5.2f + std::max(rounds * (nb * 0.027f + 0.0125f) * kts, (float)n * K * 24 / 6.9e6f)
-                                                 : 5.2f + std::max(rounds * (nb * 0.033f + 0.010f) * kts, (float)n * K * 32 / 6.9e6f);
+      const float us = slices_coded ? 5.2f + std::max(rounds * (nb * 0.027f + 0.0125f) * kts, (float)n * K * 24 / 6.9e6f)
+                                    : 5.2f + std::max(rounds * (nb * 0.033f + 0.010f) * kts, (float)n * K * 32 / 6.9e6f);
       if (us < best) { best = us; ks_best = ks; nb_best = nb; }
     }
   }
@@ -989,6 +1011,9 @@ static int coded_blocks(int n, int per) {
 }
 // whether a wavefront's lanes hold the fix words of all its k-tiles (64 of them) in the shapes of launch_coded
 static bool coded_fits(int epi, int n_blocks, int K) { return (K >> 5) <= 64 * (epi == EPI_RESID && n_blocks > 256 ? 16 : 8); }
+static bool few_rows_read_coded(const GemmTuning &tn, int kind, int epi, const Coded &z, int n_blocks, int K) {
+  return !tn.waves[kind] && z.tiles && coded_fits(epi, n_blocks, K);  // (a launch shape that was asked for is one of the plain form)
+}
 template <int EPI>
 static void launch_coded(const Params &p, const GemmArgs &a, int n_blocks, hipStream_t s) {
   auto go = [&](auto W, auto U, auto B) {
@@ -1079,31 +1104,37 @@ static void launch_rows_mt(const Params &p, const GemmArgs &a, dim3 grid, int nb
 // compute unit holds one: the product takes (rounds of 256 workgroups) x (operand tiles per k-tile).  Products added step by step (sums
 // past 30 tiles) cost a quarter more, and with the decoding beside them too much.  On coded weights a strip is three quarters of a tile, and
 // a second round costs a quarter more unless two workgroups fit a unit's LDS (gate/up an eighth).  `want` > 0 asks for a number.
-// Measured with and without the copies, us: 40 rows, d 4096, QKV 26.0 and 23.8, gate/up (688 blocks) 36.1 and 33.7, Wo 15.4 and 14.7, down
+// Measured without and with the copies, us: 40 rows, d 4096, QKV 26.0 and 23.8, gate/up (688 blocks) 36.1 and 33.7, Wo 15.4 and 14.7, down
 // 25.1 and 23.6 (with the kernel that adds the slices), LM head (V 32000) 50.8 and 49.1; 16 rows 19.2 and 17.1, 30.7 and 25.6, 12.6 and
 // 10.5, 19.3 and 18.2, 46.4 and 35.7; d 5120, 24 rows, 860 blocks 47.8 and 42.5; 48 rows, d 4096, QKV 28.3 and 26.3.
 struct RingShape { int nb; bool coded; };
-static RingShape ring_shape(int want, int n_blocks, int per, int mt, int slices, bool coded) {
+static RingShape ring_shape(int want, int n_blocks, int per, int mt, int slices, bool coded, float outside) {
+  const float strip = coded_strip(outside);
   RingShape best{1, false};
   float best_cost = 1e30f;
   for (int z = 0; z <= (coded ? 1 : 0); ++z)
     for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
       const int ns = nb * per, rounds = ((n_blocks + nb - 1) / nb * slices + 255) / 256;
       if (!ring_fits(ns, mt) || (z && ns * mt > 30)) continue;
-      float cost = rounds * ((z ? 0.75f : 1.0f) * ns + mt);
+      float cost = rounds * ((z ? strip : 1.0f) * ns + mt);
       if (ns * mt > 30) cost *= 1.28f;
       if (z && rounds > 1) cost *= 8 * (0.75f * ns + mt) + 2 * ns > 79 ? 1.25f : per == 2 ? 1.12f : 1.0f;
-      if (want) cost = (float)std::abs(nb - want) + (coded && !z ? 0.5f : 0.0f);
+      if (want) cost = (float)std::abs(nb - want) + (coded && z == (strip > 1) ? 0.5f : 0.0f);  // the nearest, in the cheaper form
       if (cost < best_cost) { best_cost = cost; best = RingShape{nb, z != 0}; }
     }
   return best;
+}
+// kts: k-tiles of a workgroup
+static RingShape rows_shape(const Coded &z, int M, int n_blocks, int per, int K, int kts, int want, int slices) {
+  const int mt = (M + 7) / 8;
+  const bool coded = z.tiles && mt <= kRingCodedGroups && coded_pays(n_blocks * per, K) && kts <= kRingFixTiles * kRingWaves;
+  return ring_shape(want, n_blocks, per, mt, slices, coded, z.outside);
 }
 template <int EPI>
 static void launch_rows(const Params &p, const GemmArgs &a, int n_blocks, int want, int slices, hipStream_t s) {
   constexpr int PER = (EPI == EPI_GATEUP || EPI == EPI_GATEUP_SAVE) ? 2 : 1;
   const int mt = (a.M + 7) / 8;
-  const bool coded = a.z.tiles && mt <= kRingCodedGroups && coded_pays(a.n_strips, a.K) && (EPI == EPI_PARTIAL ? a.kt_split : a.K >> 5) <= kRingFixTiles * kRingWaves;
-  const auto [nb, z] = ring_shape(want, n_blocks, PER, mt, slices, coded);
+  const auto [nb, z] = rows_shape(a.z, a.M, n_blocks, PER, a.K, EPI == EPI_PARTIAL ? a.kt_split : a.K >> 5, want, slices);
   const dim3 grid((n_blocks + nb - 1) / nb, slices);
   switch (mt) {
     case 1: if constexpr (EPI == EPI_PARTIAL) launch_rows_mt<1, EPI>(p, a, grid, nb, z, s); break;
@@ -1123,9 +1154,8 @@ static void launch_gemm_epi(const Params &p, const GemmTuning &tn, const GemmArg
   constexpr int PER = (EPI == EPI_GATEUP) ? 2 : 1;
   const int n_blocks = n_strips / PER;
   if (a.M <= 8) {
-    if (tn.waves[kind]) return launch_few<EPI>(p, a, n_blocks, FewShape{tn.waves[kind], tn.unroll[kind], 1}, s);  // a shape of the plain form
-    if (a.z.tiles && coded_fits(EPI, n_blocks, a.K)) return launch_coded<EPI>(p, a, n_blocks, s);
-    return launch_few<EPI>(p, a, n_blocks, few_rows_shape(EPI, n_blocks), s);
+    if (few_rows_read_coded(tn, kind, EPI, a.z, n_blocks, a.K)) return launch_coded<EPI>(p, a, n_blocks, s);
+    return launch_few<EPI>(p, a, n_blocks, tn.waves[kind] ? FewShape{tn.waves[kind], tn.unroll[kind], 1} : few_rows_shape(EPI, n_blocks), s);
   }
   launch_rows<EPI>(p, a, n_blocks, tn.big_blocks[kind], 1, s);
 }
@@ -1170,29 +1200,39 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(Params p, const float
   if ((threadIdx.x & 3) == 0) p.ssq[(size_t)strip * kMaxRows + m] = ss;  // rows >= M get 0
 }
 
-static bool launch_resid_split(const Params &p, const GemmTuning &tn, const GemmArgs &a0, int kind, hipStream_t s) {
-  const int n_strips = p.d / 16, KT = a0.K >> 5;
+// Slices of K of a residual product (1: whole), k-tiles of a slice, strips per workgroup (0: by cost)
+struct ResidSlices { int ks, kts, nb; };
+static ResidSlices resid_slices(const Params &p, const GemmTuning &tn, int kind, const Coded &z, int M, int K) {
+  const int n_strips = p.d / 16, KT = K >> 5;
   int KS = tn.split_ks, nb = tn.big_blocks[kind];
-  if (KS < 0 && a0.M > 8) KS = 4;
+  if (KS < 0 && M > 8) KS = 4;
   if (KS < 0 && tn.waves[kind]) KS = 1;  // a launch shape of the whole product was asked for
   if (KS < 0) {
     int best = 0;
-    KS = few_rows_slices(n_strips, a0.K, p.d, p.F, a0.z.tiles && coded_fits(EPI_RESID, n_strips, a0.K), best);
+    const bool coded = z.tiles && coded_fits(EPI_RESID, n_strips, K);
+    KS = few_rows_slices(n_strips, K, p.d, p.F, coded, coded && coded_pays(n_strips, K) && coded_strip(z.outside) <= 1, best);
     if (!nb) nb = best;
   }
-  if (KS < 2) return false;
-  GemmArgs a = a0;
+  if (KS < 2) return {1, KT, nb};
   // K need not divide evenly, the last slice holds what is left (40 rows, down of d 4096, K 9408, 294 k-tiles: 22.5 us in
   // slices of 74, 74, 74 and 72, 31.7 whole; d 5120, K 13760: 32.9 and 56.1)
-  a.kt_split = (KT + KS - 1) / KS;
-  KS = (KT + a.kt_split - 1) / a.kt_split;
-  if (KS < 2 || (size_t)KS * p.d > (size_t)2 * p.F) return false;  // the slices' sums borrow the generic path's gate/up workspace
+  const int kts = (KT + KS - 1) / KS;
+  KS = (KT + kts - 1) / kts;
+  if (KS < 2 || (size_t)KS * p.d > (size_t)2 * p.F) return {1, KT, nb};  // the slices' sums borrow the generic path's gate/up workspace
+  return {KS, kts, nb};
+}
+static bool launch_resid_split(const Params &p, const GemmTuning &tn, const GemmArgs &a0, int kind, hipStream_t s) {
+  const ResidSlices sl = resid_slices(p, tn, kind, a0.z, a0.M, a0.K);
+  if (sl.ks < 2) return false;
+  GemmArgs a = a0;
+  a.kt_split = sl.kts;
   a.partial = p.gu;
   a.ldy = p.d;
-  launch_rows<EPI_PARTIAL>(p, a, n_strips, nb, KS, s);
-  resid_reduce_kernel<<<n_strips, 256, 0, s>>>(p, a.partial, KS, a.M, a.gain_next);
+  launch_rows<EPI_PARTIAL>(p, a, p.d / 16, sl.nb, sl.ks, s);
+  resid_reduce_kernel<<<p.d / 16, 256, 0, s>>>(p, a.partial, sl.ks, a.M, a.gain_next);
   return true;
 }
+static int resid_kind(const Params &p, int K) { return K == p.F ? 4 : 1; }  // the down projection has its own shape
 
 void launch_gemm_qkv(const Params &p, const GemmTuning &tn, const Matrix &W, int layer, int M, hipStream_t s) {
   GemmArgs a{(const u32x4 *)W.tiles, p.xg, M, p.d, layer, nullptr, nullptr, 0, nullptr, 3 * p.D / 16, 0, nullptr, W.coded};
@@ -1201,8 +1241,8 @@ void launch_gemm_qkv(const Params &p, const GemmTuning &tn, const Matrix &W, int
 void launch_gemm_resid(const Params &p, const GemmTuning &tn, const Matrix &W, const uint16_t *X, int K,
                        const void *gain_next, int M, hipStream_t s) {
   GemmArgs a{(const u32x4 *)W.tiles, X, M, K, 0, (const uint16_t *)gain_next, nullptr, 0, nullptr, p.d / 16, 0, nullptr, W.coded};
-  if (launch_resid_split(p, tn, a, K == p.F ? 4 : 1, s)) return;
-  launch_gemm_epi<EPI_RESID>(p, tn, a, p.d / 16, s, K == p.F ? 4 : 1);  // the down projection has its own shape
+  if (launch_resid_split(p, tn, a, resid_kind(p, K), s)) return;
+  launch_gemm_epi<EPI_RESID>(p, tn, a, p.d / 16, s, resid_kind(p, K));
 }
 void launch_gemm_gateup(const Params &p, const GemmTuning &tn, const Matrix &W, int M, hipStream_t s) {
   GemmArgs a{(const u32x4 *)W.tiles, p.xg, M, p.d, 0, nullptr, nullptr, 0, nullptr, 2 * p.F / 16, 0, nullptr, W.coded};
@@ -1211,6 +1251,19 @@ void launch_gemm_gateup(const Params &p, const GemmTuning &tn, const Matrix &W, 
 void launch_gemm_logits(const Params &p, const GemmTuning &tn, const Matrix &W, float *logits, int M, hipStream_t s) {
   GemmArgs a{(const u32x4 *)W.tiles, p.xg, M, p.d, 0, nullptr, logits, 0, nullptr, p.V / 16, 0, nullptr, W.coded};
   launch_gemm_epi<EPI_LOGITS>(p, tn, a, p.V / 16, s);
+}
+
+bool gemm_reads_coded(const Params &p, const GemmTuning &tn, int kind, const Coded &z, int M) {
+  const bool resid = kind == 1 || kind == 4;
+  const int K = kind == 1 ? p.D : kind == 4 ? p.F : p.d, per = kind == 2 ? 2 : 1;
+  const int n_blocks = (kind == 0 ? 3 * p.D : kind == 2 ? p.F : kind == 3 ? p.V : p.d) / 16;
+  if (resid) {
+    const ResidSlices sl = resid_slices(p, tn, resid_kind(p, K), z, M, K);
+    if (sl.ks > 1) return rows_shape(z, M, n_blocks, 1, K, sl.kts, sl.nb, sl.ks).coded;
+    kind = resid_kind(p, K);
+  }
+  if (M <= 8) return few_rows_read_coded(tn, kind, resid ? EPI_RESID : EPI_QKV, z, n_blocks, K);
+  return rows_shape(z, M, n_blocks, per, K, K >> 5, tn.big_blocks[kind], 1).coded;
 }
 
 
@@ -1240,6 +1293,10 @@ int plain_gemm_slices(int N, int K) {
   }
   const int kts = (KT + best - 1) / best;
   return (KT + kts - 1) / kts;  // every slice holds something
+}
+bool gemm_plain_reads_coded(const Coded &z, int M, int N, int K) {
+  const int KT = K / 32, KS = plain_gemm_slices(N, K);
+  return rows_shape(z, M, N / 16, 1, K, (KT + KS - 1) / KS, 0, KS).coded;
 }
 int launch_gemm_plain(const Params &p, const Matrix &W, const uint16_t *X, int M, int N, int K, float *part, hipStream_t s) {
   const int KT = K / 32, KS = plain_gemm_slices(N, K);

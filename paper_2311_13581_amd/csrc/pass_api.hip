@@ -96,7 +96,7 @@ struct pass_ctx {
   std::vector<LayerW> layers;
   // matrix-core path, after pass_coded_begin: the LM head's coded copy, then wqkv, wo, wgu and wdown of every layer; else empty
   std::vector<Coded> coded;
-  bool opt_coded = true;
+  int opt_coded = 1;  // "tune.coded"
   bool weights_loaded = false;
   bool use_mfma = false;  // matrix-core path active (set by pass_load_weights)
   int opt_graph = 0, opt_path = 0, opt_attn = 0;
@@ -265,21 +265,22 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
   return (A.off + 255) & ~(size_t)255;
 }
 
-// The coded copies in the caller's workspace.  counts: what the coding counts, [matrices][128] exponents, then [matrices][2] of the
-// overflow lists.
+// The coded copies in the caller's workspace.  counts: what the coding counts, [matrices][128] exponents, [matrices][2] of the
+// overflow lists, then [strips][4] of every matrix that is coded (Coded::load).
 // transposed: of the transposes that training multiplies with (in calls of more than 8 rows, which gain on matrices of 2^24 weights or more).
 size_t carve_coded(const pass_config &c, bool transposed, char *base, std::vector<Coded> *out, uint32_t **counts) {
   Arena A{base, 0};
   const size_t d = c.d_model, D = (size_t)c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
   std::vector<Coded> coded;
-  bool any = false;
+  size_t strips = 0;
   auto add = [&](size_t N, size_t K) {
     Coded z{};
     if (transposed) std::swap(N, K);
     // small products are bound by their start (d 1024: QKV 4.4 us on plain tiles and 4.6 on coded ones, gate/up of 448 strips 5.0
     // and 5.2; but LM heads of 500 and 1000 strips 5.1 and 4.9, 7.6 and 6.8; d 2048, 63 strips 4.7 and 4.6)
     if (transposed ? N * K >= 1 << 24 : K >= 2048 || N * K >= (size_t)8000 * 1024) {
-      any = z.wanted = true;
+      z.wanted = true;
+      strips += N / 16;
       z.tiles = A.take<char>(coded_tile_bytes(N, K));
       z.fix = A.take<uint2>(coded_fix_words(N, K));
       z.more_room = (uint32_t)coded_more_words(N, K);
@@ -289,9 +290,9 @@ size_t carve_coded(const pass_config &c, bool transposed, char *base, std::vecto
   };
   add(V, d);
   for (int l = 0; l < c.n_layers; ++l) { add(3 * D, d); add(d, D); add(2 * F, d); add(d, F); }
-  uint32_t *n = A.take<uint32_t>(coded.size() * 130);
+  uint32_t *n = A.take<uint32_t>(coded.size() * 130 + strips * 4);
   if (out) { *out = coded; *counts = n; }
-  return any ? (A.off + 255) & ~(size_t)255 : 0;
+  return strips ? (A.off + 255) & ~(size_t)255 : 0;
 }
 
 size_t carve_train(const pass_config &c, bool mfma, char *base, TrainWs *out) {
@@ -411,13 +412,18 @@ int choose_splits(const pass_ctx *c, int B, int R, int max_keys) {
   return plain_splits(std::max(1, max_keys));
 }
 
-// A matrix as the decode-sized products take it.  which: 0 the LM head, 1 + 4 * layer + 0 .. 3 wqkv, wo, wgu, wdown
-Matrix matrix(const pass_ctx *c, const void *tiles, int which) {
-  return Matrix{tiles, c->opt_coded && !c->coded.empty() && c->coded[which].on ? c->coded[which] : Coded{}};
+// The copy of a matrix that its products may read (tiles null: none).  which: 0 the LM head, 1 + 4 * layer + 0 .. 3 wqkv, wo, wgu, wdown
+Coded coded_copy(const pass_ctx *c, const std::vector<Coded> &copies, int which) {
+  if (!c->opt_coded || copies.empty() || !copies[which].held || (c->opt_coded == 1 && !copies[which].pays)) return Coded{};
+  Coded z = copies[which];
+  if (c->opt_coded == 2) z.outside = 0;
+  return z;
 }
+// A matrix as the decode-sized products take it
+Matrix matrix(const pass_ctx *c, const void *tiles, int which) { return Matrix{tiles, coded_copy(c, c->coded, which)}; }
 
-// The coded copies of all matrices: a table each, then the tiles.  A matrix that its table suits badly (the overflow list does not
-// take what lies outside: every tile of it would wait for its fixes) is left without.
+// The coded copies of all matrices: a table each, then the tiles.  One that does not hold its matrix (the overflow list does not take
+// what lies outside the table) is not read, nor is one whose products would take longer (coded_pays_for).
 int code_weights(pass_ctx *c, std::vector<Coded> &coded, uint32_t *counts, const void *lm_head, const std::vector<LayerW> &layers,
                  bool transposed) {
   const size_t n = coded.size(), d = c->P.d, D = c->P.D, F = c->P.F, V = c->P.V;
@@ -429,8 +435,10 @@ int code_weights(pass_ctx *c, std::vector<Coded> &coded, uint32_t *counts, const
   }
   if (transposed)
     for (Src &x : src) std::swap(x.N, x.K);
-  uint32_t *used = counts + n * 128;
-  launch_fill_i32((int32_t *)counts, 0, n * 130, c->stream);
+  uint32_t *used = counts + n * 128, *load = used + n * 2;
+  for (size_t i = 0; i < n; ++i)
+    if (coded[i].wanted) { coded[i].load = load; load += src[i].N / 4; }
+  launch_fill_i32((int32_t *)counts, 0, load - counts, c->stream);
   for (size_t i = 0; i < n; ++i)
     if (coded[i].wanted) launch_exponents(src[i].p, src[i].N * src[i].K, counts + i * 128, c->stream);
   HIP_TRY(c, hipGetLastError());
@@ -443,9 +451,14 @@ int code_weights(pass_ctx *c, std::vector<Coded> &coded, uint32_t *counts, const
     launch_code_tiles(src[i].p, coded[i], (int)src[i].N, (int)src[i].K, used + 2 * i, c->stream);
   }
   HIP_TRY(c, hipGetLastError());
-  HIP_TRY(c, hipMemcpyAsync(host.data(), used, n * 8, hipMemcpyDeviceToHost, c->stream));
+  host.resize(load - used);
+  HIP_TRY(c, hipMemcpyAsync(host.data(), used, host.size() * 4, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  for (size_t i = 0; i < n; ++i) coded[i].on = coded[i].wanted && !host[2 * i + 1];
+  for (size_t i = 0; i < n; ++i) {
+    if (!coded[i].wanted) continue;
+    coded[i].held = !host[2 * i + 1];
+    coded[i].pays = coded_pays_for(host.data() + (coded[i].load - used), (int)src[i].N, (int)src[i].K, &coded[i].outside);
+  }
   return PASS_OK;
 }
 
@@ -950,6 +963,19 @@ int pass_coded_begin(pass_ctx *c, void *device_workspace, size_t bytes) {
   const int rc = code_weights(c, coded, counts, c->lm_head, c->layers, false);
   if (rc == PASS_OK) c->coded = coded;
   return rc;
+}
+
+int pass_coded_use(pass_ctx *c, int matrix, int rows) {
+  if (!c) return PASS_EINVAL;
+  if (!c->weights_loaded) return fail(c, PASS_ESTATE, "weights not loaded");
+  const int n = 1 + 4 * c->P.L;
+  if (matrix < 0 || matrix >= 2 * n || rows < 1 || rows > kMaxRows) return fail(c, PASS_EINVAL, "matrix %d, %d rows", matrix, rows);
+  const int which = matrix % n, kind = which ? (const int[]){0, 1, 2, 4}[(which - 1) % 4] : 3;
+  if (matrix < n) return gemm_reads_coded(c->P, c->tuning, kind, coded_copy(c, c->coded, which), rows);
+  if (!c->train.on) return 0;
+  const int d = c->P.d, D = c->P.D, F = c->P.F;
+  const int N = kind == 1 ? D : kind == 4 ? F : d, K = kind == 0 ? 3 * D : kind == 2 ? 2 * F : kind == 3 ? c->P.V : d;  // of the transpose
+  return gemm_plain_reads_coded(coded_copy(c, c->train.coded, which), rows, N, K);
 }
 
 int pass_release(pass_ctx *c, int slot) {
@@ -1591,9 +1617,7 @@ int pass_train_step(pass_ctx *c, const int32_t *slots, int n_slots, const int32_
     // ---- backward: every dx = W^T dy is a matrix-core product with the packed transpose; its input travels as
     // (hi, lo) tiles (T.x), its output as slices over the contraction (T.part) that the consumer adds up ----
     const size_t rows = kMaxRows;
-    auto transposed = [&](const void *tiles, int which) {
-      return Matrix{tiles, c->opt_coded && !T.coded.empty() && T.coded[which].on ? T.coded[which] : Coded{}};
-    };
+    auto transposed = [&](const void *tiles, int which) { return Matrix{tiles, coded_copy(c, T.coded, which)}; };
     launch_ce_grad(T.logits, T.targets, loss_scale, T.row_loss, M, P.V, (float2 *)P.row_parts, T.x, s);
     int KS = launch_gemm_plain(P, transposed(T.lm_head_t, 0), T.x, M, (int)d, (int)V, T.part, s);
     launch_rmsnorm_bwd(P, dt, T.save_hl, c->final_norm, T.part, KS, rows * d, T.dh, M, 0, T.x, s);
@@ -1743,7 +1767,8 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   //                       400 + blocks (strips of 16 output features, or gate / up pairs, per workgroup, 0..8, 0 = by cost);
   //                       2000000 + K slices of the residual GEMMs, 0..8 (0 and 1 = whole K; until it is set, 4, and by
   //                       cost for calls of up to 8 rows)
-  //   tune.coded          1 = the decode-sized products read the coded copies of the matrices that have one, 0 = the plain ones
+  //   tune.coded          1 = the decode-sized products read the coded copies of matrices that gain by it, 0 = the plain ones,
+  //                       2 = every copy that holds its matrix
   //   tune.prefill_rows   prompt rows per pass of the tiled prompt pass (a multiple of 128)
   //   tune.prefill_tile   query rows per attention workgroup of the tiled prompt pass (0, 16, 32, 128)
   //   tune.prefill_block  (1 .. 64) * 100 + row tiles of a panel of the tiled GEMMs' tile order (0 = 1024 rows)
@@ -1785,7 +1810,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
     return PASS_OK;
   }
   if (!strcmp(name, "tune.coded")) {
-    if (value < 0 || value > 1) return fail(c, PASS_EINVAL, "tune.coded: 0 or 1");
+    if (value < 0 || value > 2) return fail(c, PASS_EINVAL, "tune.coded: 0, 1 or 2");
     c->opt_coded = value;
     drop_graphs(c);  // captured launches read the one or the other
     return PASS_OK;

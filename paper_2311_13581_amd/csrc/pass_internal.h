@@ -205,7 +205,9 @@ struct Coded {
   uint32_t *more;       // [more_room]: those of tiles with more than two
   uint32_t more_room;
   uint32_t lut0, lut1;  // the table: eight values of the exponent's upper seven bits
-  bool wanted, on;      // the product is large enough to gain; the copy holds the matrix
+  uint32_t *load;       // while it is coded, [strip][4]: weights outside the table, by k-tile modulo 4
+  float outside;        // those of a tile, on average over the matrix
+  bool wanted, held, pays;  // the product is large enough to gain; the copy holds the matrix; putting in what is outside does not cost the gain
 };
 // a weight matrix of the matrix-core path as the decode-sized products take it
 struct Matrix {
@@ -217,7 +219,8 @@ inline size_t coded_fix_words(size_t N, size_t K) { return N / 16 * ((K / 32 + 3
 void launch_exponents(const void *src, size_t weights, uint32_t *hist /*[128], added to*/, hipStream_t s);
 void coded_table(const uint32_t *hist, uint32_t *lut0, uint32_t *lut1);
 inline size_t coded_more_words(size_t N, size_t K) { return std::min<size_t>(N * K / 1024, (size_t)1 << 24); }
-void launch_code_tiles(const void *src, const Coded &z, int N, int K, uint32_t *counts /*[2], zero*/, hipStream_t s);
+void launch_code_tiles(const void *src, const Coded &z, int N, int K, uint32_t *counts /*[2], zero, as is z.load*/, hipStream_t s);
+bool coded_pays_for(const uint32_t *load, int N, int K, float *outside);
 void launch_pack_tiles(const uint16_t *src, uint16_t *dst, int N, int K, int strip_off, int strip_stride,
                        hipStream_t s);
 void launch_assemble_mfma(const Params &p, const void *tok_emb, const void *lookahead, const void *gain0, int mode,
@@ -306,6 +309,9 @@ int launch_prefill_resid(const Params &p, const PrefillWs &w, const void *W, con
 void launch_prefill_gateup(const Params &p, const PrefillWs &w, const void *W, int M, hipStream_t s);
 
 void launch_gemm_logits(const Params &p, const GemmTuning &tn, const Matrix &W, float *logits, int M, hipStream_t s);
+// whether the product of that kind (GemmTuning) on a matrix with that copy reads it in a call of M rows; the same of launch_gemm_plain
+bool gemm_reads_coded(const Params &p, const GemmTuning &tn, int kind, const Coded &z, int M);
+bool gemm_plain_reads_coded(const Coded &z, int M, int N, int K);
 
 // ---- look-ahead embedding training: matrix-core pieces (kernels_mfma.hip) ----
 void launch_gemm_gateup_save(const Params &p, const Matrix &W, float *gu_save, int M, hipStream_t s);

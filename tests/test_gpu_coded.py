@@ -175,6 +175,46 @@ def test_training_on_coded_matrices(d, heads, F, slots):
     assert abs(l0 - l1) <= 1e-5 * abs(l0) and np.linalg.norm(g0 - g1) <= 2e-4 * np.linalg.norm(g0)
 
 
+def head_only(d, V, head, k=1, tok=None, la=None):
+    """A model of one layer that adds nothing: its logits are the LM head times the normalised embedding."""
+    z, one = lambda *s: bits(np.zeros(s, np.float32)).reshape(s), bits(np.ones(d, np.float32))
+    return {"tok_emb": z(V, d) if tok is None else bits(tok).reshape(V, d), "lm_head": bits(head).reshape(V, d), "final_norm": one,
+            "lookahead": z(k, d) if la is None else bits(la).reshape(k, d), "attn_norm": [one], "ffn_norm": [one], "wq": [z(128, d)],
+            "wk": [z(128, d)], "wv": [z(128, d)], "wo": [z(d, 128)], "w_gate": [z(32, d)], "w_up": [z(32, d)], "w_down": [z(d, 32)]}
+
+
+# weights outside the table (2^-24 of the others), and whether calls of 5 and of 16 rows read the copy: none but those of a normal distribution; a tile
+# with 12; with 40; a row of one strip; 0.2 and 1 of a tile all over
+@pytest.mark.parametrize("where,few,ring", [("none", True, True), ("tile 12", True, True), ("tile 40", False, False), ("row", False, False),
+                                            ("all 0.2", True, False), ("all 1", False, False)])
+def test_copies_that_would_cost_time_are_not_read(where, few, ring):
+    """A copy is read where it saves time: what lies outside its table is put in by one wavefront while the others wait."""
+    from paper_2311_13581_amd import binding
+    d, V, rng = 2048, 8208, np.random.default_rng(3)
+    head = rng.standard_normal((V, d), dtype=np.float32) * np.float32(0.02)
+    low = np.zeros((V, d), bool)
+    if where.startswith("tile"):
+        at = rng.permutation(512)[:int(where[5:])]
+        low[160 + at // 32, 992 + at % 32] = True
+    elif where == "row":
+        low[163] = True
+    elif where.startswith("all"):
+        low = rng.random((V, d), dtype=np.float32) < float(where[4:]) / 512
+    g = binding.Pass(binding.make_config(synth.ModelShape(1, d, 1, 128, 32, V, dtype=synth.BF16), 1, 8, 64, 64))
+    with pytest.raises(binding.PassError):
+        g.coded_use(0, 5)  # no weights yet
+    g.load_weights(head_only(d, V, np.where(low, head * np.float32(2.0 ** -24), head)))
+    assert (g.coded_use(0, 5), g.coded_use(0, 16)) == (few, ring)
+    g.set_option("tune.coded", 2)  # every copy that holds its matrix
+    assert g.coded_use(0, 5) and g.coded_use(0, 16)
+    g.set_option("tune.coded", 0)
+    assert not g.coded_use(0, 5) and not g.coded_use(0, 16)
+    for matrix, rows in ((-1, 5), (10, 5), (0, 0), (0, 65)):  # five matrices, and as many transposes
+        assert g.lib.pass_coded_use(g.h, matrix, rows) == -1
+    assert g.lib.pass_coded_use(g.h, 9, 5) == 0  # no training
+    g.close()
+
+
 def test_workspace_of_the_copies():
     """What pass_coded_begin refuses, and that loading weights again ends the use of the old copies (captured graphs too)."""
     import torch
