@@ -977,10 +977,13 @@ static float coded_strip(float outside) { return 0.75f + 2.0f * std::max(0.0f, o
 // per KB of activation tile, the chip 6.9 TB/s, both kernels together 5.2.  The choice is within 9 % of the fastest there, within 6 % at
 // d 6656 and 8192; d 6144 (384 strips) stays whole where two slices of three strips would take 10 % less (one K in six 21 %).
 // d 5120, K 13760: 38.0 us whole in one strip a workgroup, 28 in two, 25.6 in slices; d 2048, K 5504: 9.4 and 8.1.
+// On coded weights a strip takes 0.027 a KB and the start and end of both kernels 7.3 (5 rows, whole and in slices: d 3072, K 8192 10.8 and 13.5,
+// 10752 15.0 and 15.8; d 4096, 8192 12.3 and 16.4, 14336 18.6 and 21.6; d 5120, 5120 13.2 and 14.2, 10240 21.8 and 20.5, 13824 28.0 and 24.5;
+// d 6144, 6144 15.1 and 17.2, 16384 33.1 and 31.1; d 8192, 8192 20.2 and 24.1, 22016 55.4 and 51.0).
 static int few_rows_slices(int n, int K, int d, int F, bool coded, bool slices_coded, int &nb_best) {
   const int KT = K / 32;
   float whole = n <= 256 ? 2.8f + K * (1.1e-3f + 0.7e-6f * n) : 3.0f + ((n + 1) / 2 + 255) / 256 * K * 1.97e-3f;
-  if (coded) whole = n <= 256 ? 2.8f + K * (0.95e-3f + 0.9e-6f * n) : 3.0f + ((n + 1) / 2 + 255) / 256 * K * 1.73e-3f;
+  if (coded) whole = n <= 256 ? 2.8f + K * (0.8e-3f + 1.3e-6f * n) : 3.0f + ((n + 1) / 2 + 255) / 256 * K * 1.73e-3f;
   float best = 0.95f * whole;
   int ks_best = 1;
   for (int ks = 2; ks <= 8; ++ks) {
@@ -989,7 +992,7 @@ static int few_rows_slices(int n, int K, int d, int F, bool coded, bool slices_c
     if ((size_t)ks * d > (size_t)2 * F) continue;  // the slices' sums borrow the generic path's gate/up workspace
     for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
       const float rounds = ((n + nb - 1) / nb * ks + 255) / 256;
-      const float us = slices_coded ? 5.2f + std::max(rounds * (nb * 0.027f + 0.0125f) * kts, (float)n * K * 24 / 6.9e6f)
+      const float us = slices_coded ? 7.3f + std::max(rounds * (nb * 0.027f + 0.0125f) * kts, (float)n * K * 24 / 6.9e6f)
                                     : 5.2f + std::max(rounds * (nb * 0.033f + 0.010f) * kts, (float)n * K * 32 / 6.9e6f);
       if (us < best) { best = us; ks_best = ks; nb_best = nb; }
     }

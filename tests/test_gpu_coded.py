@@ -150,6 +150,24 @@ def test_few_rows_agree_with_a_batch(d, heads, F, coded, slices):
     g.close()
 
 
+@pytest.mark.parametrize("d,heads,F", [(3072, 24, 8192), (4096, 32, 14336)])
+def test_down_on_the_copy_stays_whole(d, heads, F):
+    """On coded weights the kernel that adds the sums of slices takes longer than slices save here: the same bits as K whole by request."""
+    from paper_2311_13581_amd import binding
+    shape = synth.ModelShape(1, d, heads, 128, F, 1008, dtype=synth.BF16)
+    g = binding.Pass(binding.make_config(shape, 4, 1, 128, 64))
+    g.load_weights(random_weights(shape, 4, F))
+    assert g.coded_use(4, 5)
+    out = []
+    for _ in range(2):
+        g.prefill(0, np.arange(9, dtype=np.int32))
+        g.draft([0], 0.0, 1)
+        out.append(g.get_logits(0, 0).copy())
+        g.set_option("tune.gemm_cfg", 2000001)
+    g.close()
+    assert np.array_equal(*out)
+
+
 # one slot: four rows through the register form, its gate/up product keeping the pre-activations; eight: 32 rows and coded transposes
 @pytest.mark.parametrize("d,heads,F,slots", [(2048, 16, 5504, 1), (4096, 32, 4416, 8)])
 def test_training_on_coded_matrices(d, heads, F, slots):
