@@ -1106,32 +1106,38 @@ static void launch_rows_mt(const Params &p, const GemmArgs &a, dim3 grid, int nb
 // Blocks per workgroup (1 .. 6 or 8), and whether the product reads coded weights.  A workgroup pulls all M rows whatever it owns, and a
 // compute unit holds one: the product takes (rounds of 256 workgroups) x (operand tiles per k-tile).  Products added step by step (sums
 // past 30 tiles) cost a quarter more, and with the decoding beside them too much.  On coded weights a strip is three quarters of a tile, and
-// a second round costs a quarter more unless two workgroups fit a unit's LDS (gate/up an eighth).  `want` > 0 asks for a number.
+// a second round costs a quarter more unless two workgroups fit a unit's LDS (gate/up an eighth).  Against a plain product added step by step, which
+// owns eight strips a workgroup, coded strips in two rounds lose that gain with K (k-tiles: of a workgroup).  `want` > 0 asks for a number.
 // Measured without and with the copies, us: 40 rows, d 4096, QKV 26.0 and 23.8, gate/up (688 blocks) 36.1 and 33.7, Wo 15.4 and 14.7, down
 // 25.1 and 23.6 (with the kernel that adds the slices), LM head (V 32000) 50.8 and 49.1; 16 rows 19.2 and 17.1, 30.7 and 25.6, 12.6 and
-// 10.5, 19.3 and 18.2, 46.4 and 35.7; d 5120, 24 rows, 860 blocks 47.8 and 42.5; 48 rows, d 4096, QKV 28.3 and 26.3.
+// 10.5, 19.3 and 18.2, 46.4 and 35.7; d 5120, 24 rows, 860 blocks 47.8 and 42.5; 48 rows, d 4096, QKV 28.3 and 26.3.  LM head, V 32000, eight strips
+// plain and four coded: 32 rows, d 1024 20.0 and 19.9, 2048 31.9 and 27.7, 3072 37.2 and 37.3, 4096 49.4 and 47.7, 5120 59.3 and 60.7, 6144 69.8 and
+// 71.4, 8192 88.7 and 92.5; 40 rows 22.2 and 21.9, 33.2 and 30.7, 40.2 and 42.0, 53.0 and 54.2, 62.5 and 67.8, 74.4 and 78.1, 94.2 and 101.5.
 struct RingShape { int nb; bool coded; };
-static RingShape ring_shape(int want, int n_blocks, int per, int mt, int slices, bool coded, float outside) {
+static RingShape ring_shape(int want, int n_blocks, int per, int mt, int slices, int kts, bool coded, float outside) {
   const float strip = coded_strip(outside);
   RingShape best{1, false};
   float best_cost = 1e30f;
-  for (int z = 0; z <= (coded ? 1 : 0); ++z)
+  float rounds_lose = 1;
+  for (int z = 0; z <= (coded ? 1 : 0); ++z) {
+    if (z && best.nb * per * mt > 30) rounds_lose = kts <= 64 ? 1.0f : kts <= 128 ? 1.05f : 1.1f;
     for (int nb : {1, 2, 3, 4, 5, 6, 8}) {
       const int ns = nb * per, rounds = ((n_blocks + nb - 1) / nb * slices + 255) / 256;
       if (!ring_fits(ns, mt) || (z && ns * mt > 30)) continue;
       float cost = rounds * ((z ? strip : 1.0f) * ns + mt);
       if (ns * mt > 30) cost *= 1.28f;
-      if (z && rounds > 1) cost *= 8 * (0.75f * ns + mt) + 2 * ns > 79 ? 1.25f : per == 2 ? 1.12f : 1.0f;
+      if (z && rounds > 1) cost *= 8 * (0.75f * ns + mt) + 2 * ns > 79 ? 1.25f : per == 2 ? 1.12f : rounds_lose;
       if (want) cost = (float)std::abs(nb - want) + (coded && z == (strip > 1) ? 0.5f : 0.0f);  // the nearest, in the cheaper form
       if (cost < best_cost) { best_cost = cost; best = RingShape{nb, z != 0}; }
     }
+  }
   return best;
 }
 // kts: k-tiles of a workgroup
 static RingShape rows_shape(const Coded &z, int M, int n_blocks, int per, int K, int kts, int want, int slices) {
   const int mt = (M + 7) / 8;
   const bool coded = z.tiles && mt <= kRingCodedGroups && coded_pays(n_blocks * per, K) && kts <= kRingFixTiles * kRingWaves;
-  return ring_shape(want, n_blocks, per, mt, slices, coded, z.outside);
+  return ring_shape(want, n_blocks, per, mt, slices, kts, coded, z.outside);
 }
 template <int EPI>
 static void launch_rows(const Params &p, const GemmArgs &a, int n_blocks, int want, int slices, hipStream_t s) {

@@ -168,6 +168,17 @@ def test_down_on_the_copy_stays_whole(d, heads, F):
     assert np.array_equal(*out)
 
 
+@pytest.mark.parametrize("d,reads", [(2048, {16: 1, 32: 1, 40: 1, 48: 0}), (4096, {16: 1, 32: 1, 40: 0, 48: 0}), (5120, {16: 1, 32: 0, 40: 0, 48: 0})])
+def test_large_heads_read_the_faster_form(d, reads):
+    """An LM head of 32000: from some width on the plain matrix, eight strips a workgroup, is faster than coded strips in two rounds."""
+    from paper_2311_13581_amd import binding
+    head = np.tile(np.random.default_rng(0).standard_normal((1000, d), dtype=np.float32), (32, 1))
+    g = binding.Pass(binding.make_config(synth.ModelShape(1, d, 1, 128, 32, 32000, dtype=synth.BF16), 1, 8, 64, 64))
+    g.load_weights(head_only(d, 32000, head))
+    assert {rows: g.coded_use(0, rows) for rows in reads} == reads
+    g.close()
+
+
 # one slot: four rows through the register form, its gate/up product keeping the pre-activations; eight: 32 rows and coded transposes
 @pytest.mark.parametrize("d,heads,F,slots", [(2048, 16, 5504, 1), (4096, 32, 4416, 8)])
 def test_training_on_coded_matrices(d, heads, F, slots):
