@@ -118,16 +118,19 @@ int pass_load_weights(pass_ctx *ctx, const pass_weights *w, int on_device);
  * they are: prompts, larger calls and products that gain nothing are multiplied with those.  What a call multiplies is bit for bit the same
  * weight; its sums may be taken in another order.
  *   pass_coded_bytes   device bytes pass_coded_begin needs, about three quarters of the matrices (0: no context, no weights, the
- *                      generic path, or a model so small that nothing is gained)
+ *                      generic path, or a model so small that nothing is gained); after pass_coded_begin without the matrices that
+ *                      it found to gain nothing, so that a caller may begin again in less
  *   pass_coded_begin   device_workspace: caller's device memory, 256-byte aligned, kept alive until pass_destroy or the
  *                      next pass_load_weights, which ends the use of the copies.  Weights outside the sixteen octaves that
  *                      the code takes stand beside it and cost time: a matrix of which more than one in 1300 lies outside, or that has
  *                      many in one place (a row of zeros among others, say), is multiplied in its plain form.
+ *   pass_coded_end     ends the use of the copies: the workspace is the caller's again, calls read the plain matrices
  *   pass_coded_use     1: a call of that many rows reads the copy of the matrix, 0: the plain one.  matrix: 0 the LM head, then wq | wk | wv,
  *                      wo, w_gate | w_up and w_down of every layer; as many again: their transposes, which training multiplies with
  * Errors: PASS_ESTATE (no weights, or pass_coded_bytes is 0), PASS_EINVAL (workspace, matrix, rows), PASS_EDEVICE. */
 size_t pass_coded_bytes(pass_ctx *ctx);
 int pass_coded_begin(pass_ctx *ctx, void *device_workspace, size_t bytes);
+int pass_coded_end(pass_ctx *ctx);
 int pass_coded_use(pass_ctx *ctx, int matrix, int rows);
 
 /* Start a sequence in `slot` (frees what the slot held).  prompt: host, n >= 1 token ids.

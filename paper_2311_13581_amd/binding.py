@@ -17,7 +17,7 @@ LIB_PATH = os.path.join(_HERE, "libpass_hip.so")
 PASS_F32, PASS_BF16 = 0, 1
 MAX_K, MAX_ROWS = 15, 64
 
-SYMBOLS = ["pass_arena_bytes", "pass_create", "pass_load_weights", "pass_coded_bytes", "pass_coded_begin", "pass_coded_use", "pass_prefill", "pass_prefill_batch", "pass_release",
+SYMBOLS = ["pass_arena_bytes", "pass_create", "pass_load_weights", "pass_coded_bytes", "pass_coded_begin", "pass_coded_end", "pass_coded_use", "pass_prefill", "pass_prefill_batch", "pass_release",
            "pass_draft", "pass_draft_static", "pass_verify", "pass_generate", "pass_sps_iteration", "pass_run_iterations", "pass_kernel_time", "pass_plain_read", "pass_rng_uniforms", "pass_get_logits", "pass_seq_len",
            "pass_train_bytes", "pass_train_begin", "pass_train_step", "pass_train_read", "pass_train_resume", "pass_set_option", "pass_attention_plan", "pass_prefill_plan", "pass_get_tokens", "pass_time_step", "pass_last_error", "pass_destroy"]
 
@@ -85,6 +85,7 @@ def load_library():
     L.pass_coded_bytes.restype = C.c_size_t
     L.pass_coded_bytes.argtypes = [C.c_void_p]
     L.pass_coded_begin.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t]
+    L.pass_coded_end.argtypes = [C.c_void_p]
     L.pass_coded_use.argtypes = [C.c_void_p, C.c_int, C.c_int]
     L.pass_prefill.argtypes = [C.c_void_p, C.c_int, C.c_uint32, ip, C.c_int]
     L.pass_prefill_batch.argtypes = [C.c_void_p, ip, C.POINTER(C.c_uint32), ip, ip, C.c_int]
@@ -162,7 +163,12 @@ class _Results:
 
 
 class Pass:
-    """One model instance on the current CUDA(HIP) device.  Methods mirror the C entry points."""
+    """One model instance on the current CUDA(HIP) device.  Methods mirror the C entry points.
+
+    Beside the arena (pass_arena_bytes) an instance keeps 12-bit copies of its large matrices for decode-sized calls, about three
+    quarters of their bytes once more, where these are no more than a quarter of what is free when the weights are loaded.  The
+    option {"tune.coded": 0} declines them (or gives them back), 1 asks for them wherever they fit; training gives them up where its own
+    workspace has no room beside them."""
 
     def __init__(self, cfg: PassConfig, options: dict | None = None):
         import torch
@@ -189,6 +195,7 @@ class Pass:
             raise PassError(rc, self.lib.pass_last_error(None).decode())
         self.h = h
         self.coded = None
+        self._coded_mode = None  # "tune.coded" if it was set
         # the logits of both calls of every slot, twice: a loop still holds an iteration's results while it reads the next one's
         self._logits = _Results((cfg.k + 1, cfg.vocab), 4 * cfg.max_slots)
         for name, val in (options or {}).items():
@@ -215,6 +222,9 @@ class Pass:
         self._check(self.lib.pass_set_option(self.h, name.encode(), int(value)))
         if name == "lookahead_rows":
             self.k_act = int(value)  # rows 1 .. k_act of drafts / logits are live, the rest padding
+        if name == "tune.coded":  # 0: no copies and no memory for them; else: copies wherever they fit
+            self._coded_mode = int(value)
+            self._code_weights()
 
     def load_weights(self, weights: dict):
         """weights: dict of numpy arrays (host) or torch CUDA tensors (device), plain layout."""
@@ -246,30 +256,44 @@ class Pass:
         self._check(self.lib.pass_load_weights(self.h, C.byref(w), int(on_device)))
         self._code_weights()
 
-    def _room(self, nbytes):
-        """Whether a tensor of that size leaves an eighth of the card's memory free."""
-        cuda = self._torch.cuda
-        free, total = cuda.mem_get_info()
-        return nbytes + total // 8 <= free + cuda.memory_reserved() - cuda.memory_allocated()
-
     def _workspace(self, nbytes):
-        """A tensor of that size and the 256-byte aligned address in it that is the library's."""
+        """A tensor of that size beside the arena and the 256-byte aligned address in it that is the library's."""
         ws = self._torch.empty(nbytes + 256, dtype=self._torch.uint8, device="cuda")
         self._torch.cuda.synchronize()
         return ws, C.c_void_p((ws.data_ptr() + 255) & ~255)
 
+    def _spare_workspace(self, nbytes, spare):
+        """The same for memory that is an extra: None where there is none, or where the `spare` bytes of it are more than a quarter of
+        what is free and copies were not asked for (the rest of the program counts on the card as it was)."""
+        cuda = self._torch.cuda
+        free = cuda.mem_get_info()[0] + cuda.memory_reserved() - cuda.memory_allocated()
+        if not self._coded_mode and 4 * spare > free - (nbytes - spare):
+            return None
+        try:
+            return self._workspace(nbytes)
+        except self._torch.OutOfMemoryError:  # not free, or not in one piece
+            return None
+
+    def _drop_copies(self):
+        self._check(self.lib.pass_coded_end(self.h))
+        self.coded = None
+
     def _code_weights(self):
         """The 12-bit copies for decode-sized calls, where there is room (without them those calls read the plain matrices)."""
-        self.coded = None
+        self._drop_copies()
         nbytes = self.lib.pass_coded_bytes(self.h)
-        if nbytes == 0 or not self._room(nbytes):
-            return
-        try:
-            ws, base = self._workspace(nbytes)
-        except self._torch.OutOfMemoryError:  # free, but not in one piece
-            return
-        self._check(self.lib.pass_coded_begin(self.h, base, nbytes))
-        self.coded = ws
+        while self._coded_mode != 0 and nbytes:
+            room = self._spare_workspace(nbytes, nbytes)
+            if room is None:
+                break
+            ws, base = room
+            self._check(self.lib.pass_coded_begin(self.h, base, nbytes))
+            self.coded = ws
+            need = self.lib.pass_coded_bytes(self.h)
+            if need == nbytes:
+                break
+            self._drop_copies()  # some matrices gain nothing by a copy: again, without room for theirs
+            nbytes = need
 
     def coded_use(self, matrix: int, rows: int) -> bool:
         """Whether a call of that many rows reads the 12-bit copy of a matrix (pass_coded_use)."""
@@ -365,17 +389,19 @@ class Pass:
         nbytes = self.lib.pass_train_bytes(self.h)
         if nbytes == 0:
             raise PassError(-1, "no look-ahead embeddings to train")
-        ws = None
         extra = self.lib.pass_coded_bytes(self.h) if self.coded is not None else 0
-        if extra and self._room(nbytes + extra):  # room for 12-bit copies of the transposes too
+        room = self._spare_workspace(nbytes + extra, extra) if extra else None  # with 12-bit copies of the transposes
+        if room is None:
             try:
-                ws, base = self._workspace(nbytes + extra)
+                room = self._workspace(nbytes)
             except self._torch.OutOfMemoryError:
-                pass
-        if ws is None:
-            ws, base = self._workspace(nbytes)
-        self.train_ws = ws
+                if self.coded is None:
+                    raise
+                self._drop_copies()  # training needs the room more
+                room = self._workspace(nbytes)
+        ws, base = room
         self._check(self.lib.pass_train_begin(self.h, base, ws.numel() - 256, init_token))
+        self.train_ws = ws
 
     def train_step(self, slots, targets, lr: float, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01) -> float:
         s = np.ascontiguousarray(slots, dtype=np.int32)

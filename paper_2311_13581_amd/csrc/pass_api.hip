@@ -96,6 +96,7 @@ struct pass_ctx {
   std::vector<LayerW> layers;
   // matrix-core path, after pass_coded_begin: the LM head's coded copy, then wqkv, wo, wgu and wdown of every layer; else empty
   std::vector<Coded> coded;
+  std::vector<char> uncoded;  // in the same order: matrices that pass_coded_begin found no use in a copy of
   int opt_coded = 1;  // "tune.coded"
   bool weights_loaded = false;
   bool use_mfma = false;  // matrix-core path active (set by pass_load_weights)
@@ -268,7 +269,8 @@ size_t carve(const pass_config &c, char *base, pass_ctx *ctx) {
 // The coded copies in the caller's workspace.  counts: what the coding counts, [matrices][128] exponents, [matrices][2] of the
 // overflow lists, then [strips][4] of every matrix that is coded (Coded::load).
 // transposed: of the transposes that training multiplies with (in calls of more than 8 rows, which gain on matrices of 2^24 weights or more).
-size_t carve_coded(const pass_config &c, bool transposed, char *base, std::vector<Coded> *out, uint32_t **counts) {
+// without: matrices to leave out, or empty.
+size_t carve_coded(const pass_config &c, const std::vector<char> &without, bool transposed, char *base, std::vector<Coded> *out, uint32_t **counts) {
   Arena A{base, 0};
   const size_t d = c.d_model, D = (size_t)c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
   std::vector<Coded> coded;
@@ -278,7 +280,7 @@ size_t carve_coded(const pass_config &c, bool transposed, char *base, std::vecto
     if (transposed) std::swap(N, K);
     // small products are bound by their start (d 1024: QKV 4.4 us on plain tiles and 4.6 on coded ones, gate/up of 448 strips 5.0
     // and 5.2; but LM heads of 500 and 1000 strips 5.1 and 4.9, 7.6 and 6.8; d 2048, 63 strips 4.7 and 4.6)
-    if (transposed ? N * K >= 1 << 24 : K >= 2048 || N * K >= (size_t)8000 * 1024) {
+    if ((transposed ? N * K >= 1 << 24 : K >= 2048 || N * K >= (size_t)8000 * 1024) && (without.empty() || !without[coded.size()])) {
       z.wanted = true;
       strips += N / 16;
       z.tiles = A.take<char>(coded_tile_bytes(N, K));
@@ -875,6 +877,7 @@ int pass_load_weights(pass_ctx *c, const pass_weights *w, int on_device) {
     drop_graphs(c);
     c->coded.clear();
   }
+  c->uncoded.clear();
   const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
   auto cp = [&](void *dst, const void *src, size_t elems) -> int {
     if (!src) return fail(c, PASS_EINVAL, "null weight pointer");
@@ -943,8 +946,8 @@ int pass_load_weights(pass_ctx *c, const pass_weights *w, int on_device) {
 
 size_t pass_coded_bytes(pass_ctx *c) {
   if (!c || !c->weights_loaded || !c->use_mfma) return 0;
-  const size_t plain = carve_coded(c->cfg, false, nullptr, nullptr, nullptr), transposed = carve_coded(c->cfg, true, nullptr, nullptr, nullptr);
-  return plain ? std::max(plain, transposed) : 0;
+  const size_t plain = carve_coded(c->cfg, c->uncoded, false, nullptr, nullptr, nullptr);
+  return plain ? std::max(plain, carve_coded(c->cfg, c->uncoded, true, nullptr, nullptr, nullptr)) : 0;
 }
 
 int pass_coded_begin(pass_ctx *c, void *device_workspace, size_t bytes) {
@@ -959,10 +962,22 @@ int pass_coded_begin(pass_ctx *c, void *device_workspace, size_t bytes) {
   c->coded.clear();
   std::vector<Coded> coded;
   uint32_t *counts;
-  carve_coded(c->cfg, false, (char *)device_workspace, &coded, &counts);
+  carve_coded(c->cfg, c->uncoded, false, (char *)device_workspace, &coded, &counts);
   const int rc = code_weights(c, coded, counts, c->lm_head, c->layers, false);
-  if (rc == PASS_OK) c->coded = coded;
-  return rc;
+  if (rc) return rc;
+  c->coded = coded;
+  c->uncoded.resize(coded.size());
+  for (size_t i = 0; i < coded.size(); ++i) c->uncoded[i] = c->uncoded[i] || (coded[i].wanted && !(coded[i].held && (coded[i].pays || c->opt_coded == 2)));
+  return PASS_OK;
+}
+
+int pass_coded_end(pass_ctx *c) {
+  if (!c) return PASS_EINVAL;
+  if (c->coded.empty()) return PASS_OK;
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  drop_graphs(c);
+  c->coded.clear();
+  return PASS_OK;
 }
 
 int pass_coded_use(pass_ctx *c, int matrix, int rows) {
@@ -1542,7 +1557,7 @@ int pass_train_begin(pass_ctx *c, void *device_workspace, size_t bytes, int32_t 
     const size_t need = carve_train(c->cfg, true, nullptr, nullptr);
     if (!c->coded.empty() && bytes - need >= pass_coded_bytes(c)) {
       uint32_t *counts;
-      carve_coded(c->cfg, true, (char *)device_workspace + need, &c->train.coded, &counts);
+      carve_coded(c->cfg, c->uncoded, true, (char *)device_workspace + need, &c->train.coded, &counts);
       const int rc = code_weights(c, c->train.coded, counts, c->train.lm_head_t, c->train.layers_t, true);
       if (rc) return rc;
     }
@@ -1812,6 +1827,7 @@ int pass_set_option(pass_ctx *c, const char *name, int value) {
   if (!strcmp(name, "tune.coded")) {
     if (value < 0 || value > 2) return fail(c, PASS_EINVAL, "tune.coded: 0, 1 or 2");
     c->opt_coded = value;
+    c->uncoded.clear();  // found by the former rule
     drop_graphs(c);  // captured launches read the one or the other
     return PASS_OK;
   }
