@@ -258,15 +258,15 @@ class Pass:
 
     def _workspace(self, nbytes):
         """A tensor of that size beside the arena and the 256-byte aligned address in it that is the library's."""
-        ws = self._torch.empty(nbytes + 256, dtype=self._torch.uint8, device="cuda")
-        self._torch.cuda.synchronize()
+        ws = self._torch.empty(nbytes + 256, dtype=self._torch.uint8, device=self.arena.device)
+        self._torch.cuda.synchronize(self.arena.device)
         return ws, C.c_void_p((ws.data_ptr() + 255) & ~255)
 
     def _spare_workspace(self, nbytes, spare):
         """The same for memory that is an extra: None where there is none, or where the `spare` bytes of it are more than a quarter of
         what is free and copies were not asked for (the rest of the program counts on the card as it was)."""
-        cuda = self._torch.cuda
-        free = cuda.mem_get_info()[0] + cuda.memory_reserved() - cuda.memory_allocated()
+        cuda, dev = self._torch.cuda, self.arena.device
+        free = cuda.mem_get_info(dev)[0] + cuda.memory_reserved(dev) - cuda.memory_allocated(dev)
         if not self._coded_mode and 4 * spare > free - (nbytes - spare):
             return None
         try:

@@ -26,24 +26,26 @@ class Tensor:
 
 
 class Card:
-    """torch, as far as the binding uses it for memory, on a card of a given size."""
+    """torch, as far as the binding uses it for memory, on a card (number 3, not the current one) of a given size."""
     uint8, OutOfMemoryError = None, OutOfMemory
 
     def __init__(self, total):
         self.total, self.used, self.cuda = total, 0, self
 
     def empty(self, nbytes, dtype, device):
+        assert device == 3
         if self.used + nbytes > self.total:
             raise OutOfMemory
         return Tensor(self, nbytes)
 
-    def mem_get_info(self):
+    def mem_get_info(self, dev):
+        assert dev == 3
         return self.total - self.used, self.total
 
-    def synchronize(self):
-        pass
+    def synchronize(self, dev):
+        assert dev == 3
 
-    def memory_reserved(self):
+    def memory_reserved(self, dev):
         return 0
 
     memory_allocated = memory_reserved
@@ -83,6 +85,7 @@ def context(card, lib, arena, mode=None):
     g = binding.Pass.__new__(binding.Pass)
     g._torch, g.lib, g.h, g.coded, g._coded_mode, g._logits = card, lib, 1, None, None, binding._Results((1, 1), 0)
     g.arena = Tensor(card, arena)
+    g.arena.device = 3
     if mode is not None:
         g.set_option("tune.coded", mode)
     return g
