@@ -36,42 +36,75 @@ def random_weights(shape, k, seed, spread=0.0):
     return W
 
 
-# strips: one, two, three and four a workgroup of the LM head, the last workgroup with fewer; exponents all over, no copy; several slots:
-# 16, 24 and 40 rows through rings of LDS stages
-@pytest.mark.parametrize("d,V,slots,wide", [(2048, 2000, 1, False), (2048, 6416, 1, False), (2048, 10000, 1, False), (2048, 15984, 1, False), (2048, 2000, 1, True),
-                                            (4096, 4112, 2, False), (2080, 8208, 3, False), (4096, 12016, 5, False)])
-def test_what_is_read_back(d, V, slots, wide):
-    """Rows that are one-hot make a logit a weight of the LM head times the row's norm, which one weight of 1 gives."""
+def head_only(d, V, head, k=1, tok=None, la=None):
+    """A model of one layer that adds nothing: its logits are the LM head times the normalised embedding."""
+    z, one = lambda *s: bits(np.zeros(s, np.float32)).reshape(s), bits(np.ones(d, np.float32))
+    return {"tok_emb": z(V, d) if tok is None else bits(tok).reshape(V, d), "lm_head": bits(head).reshape(V, d), "final_norm": one,
+            "lookahead": z(k, d) if la is None else bits(la).reshape(k, d), "attn_norm": [one], "ffn_norm": [one], "wq": [z(128, d)],
+            "wk": [z(128, d)], "wv": [z(128, d)], "wo": [z(d, 128)], "w_gate": [z(32, d)], "w_up": [z(32, d)], "w_down": [z(d, 32)]}
+
+
+# strips: one, two, three and four a workgroup of the LM head, the last workgroup with fewer; a tile with one weight more outside the table than a
+# copy holds; several slots: 16, 24 and 40 rows through rings of LDS stages; the most k-tiles that either form takes, and one more
+@pytest.mark.parametrize("d,V,slots,most,read", [(2048, 2000, 1, 128, True), (2048, 6416, 1, 128, True), (2048, 10000, 1, 128, True), (2048, 15984, 1, 128, True),
+                                                 (2048, 2000, 1, 129, False), (4096, 4112, 2, 128, True), (2080, 8208, 3, 128, True), (4096, 12016, 5, 128, True),
+                                                 (4096, 4112, 2, 129, False), (16384, 1040, 1, 128, True), (16416, 1040, 1, 128, False), (8192, 2064, 2, 128, True),
+                                                 (8224, 2064, 2, 128, False)])
+def test_what_is_read_back(d, V, slots, most, read):
+    """Rows that are one-hot make a logit a weight of the LM head times the row's norm, which one weight of 2^-5 gives: all 32 columns of tiles with
+    1, 2, 3, 60 and `most` weights outside the table, and columns of others."""
     from paper_2311_13581_amd import binding
     k, rng = 7, np.random.default_rng(V)
-    shape = synth.ModelShape(1, d, 1, 128, 32, V, dtype=synth.BF16)
-    z = lambda *s: bits(np.zeros(s, np.float32)).reshape(s)
     head = rng.standard_normal((V, d)).astype(np.float32) * np.float32(0.02)
-    cols = np.array([31, 32, 777, 1023, 1024, 2015, d - 1, 0, 1, 1025, 64, 2047])[:7 + slots]  # of the look-ahead rows, of the slots' tokens
+    ahead = np.array([31, 32, 777, 64, 1024, 1025, d - 1])  # columns of the look-ahead rows
+    cols = np.concatenate([np.arange(992, 1024), [0, 1, 63, d - 33, d - 32, d - 2]])  # of the prompts' tokens
     special = np.array([0.0, -0.0, 2.0 ** -126, -2.0 ** -130, 1e30, -3e-20, 5.0, 2.0 ** -133], np.float32)
-    head[64:80, 992:1024] = special[rng.integers(0, 8, (16, 32))]  # a tile with (many) more than 128 weights outside ...
-    if not wide:
-        head[64:80, 992:1024] *= rng.random((16, 32)) < 0.15  # ... or some 60
-    head[V - 3:, cols] = special[rng.integers(0, 8, (3, len(cols)))]
-    for r in rng.integers(0, V, 60):
-        head[r, cols[rng.integers(0, len(cols))]] = special[rng.integers(0, 8)]
-    head[1, cols] = 1
+    strips = V // 16
+    for strip, n in ((1, 1), (2, 2), (3, 3), (4, 60), (5, most), (strips - 2, 2), (strips - 1, 4)):
+        tile = head[16 * strip:16 * strip + 16, 992:1024]
+        tile[(np.abs(tile) < 1e-5) | (np.abs(tile) > 0.12)] = 0.01  # (what the normal distribution has outside)
+        at = rng.permutation(512)[:n]
+        tile[at // 32, at % 32] = special[rng.integers(0, 8, n)]
+    for r in rng.integers(96, V - 32, 60):  # two or so in other tiles
+        c = np.append(ahead, cols[32:])
+        head[r, c[rng.integers(0, len(c))]] = special[rng.integers(0, 8)]
+    head[0, :] = 2.0 ** -5
     tok, la = np.zeros((V, d), np.float32), np.zeros((k, d), np.float32)
-    tok[3 + np.arange(slots), cols[7:]], la[np.arange(k), cols[:7]] = 1, 1
-    one = bits(np.ones(d, np.float32))
-    W = {"tok_emb": bits(tok).reshape(V, d), "lm_head": bits(head).reshape(V, d), "final_norm": one, "lookahead": bits(la).reshape(k, d),
-         "attn_norm": [one], "ffn_norm": [one], "wq": [z(128, d)], "wk": [z(128, d)], "wv": [z(128, d)], "wo": [z(d, 128)],
-         "w_gate": [z(32, d)], "w_up": [z(32, d)], "w_down": [z(d, 32)]}
-    g = binding.Pass(binding.make_config(shape, k, slots, 64, 64))
-    g.load_weights(W)
-    assert g.coded is not None
-    for s in range(slots):
-        g.prefill(s, np.array([3 + s], np.int32))
-    g.draft(list(range(slots)), 0.0, 1)
-    for s in range(slots):
-        got, want = g.get_logits(s, 0), rounded(head)[:, np.append(cols[7 + s], cols[:7])].T
-        assert np.array_equal(got, want * got[:, 1:2])
+    tok[np.arange(len(cols)), cols], la[np.arange(k), ahead] = 1, 1
+    g = binding.Pass(binding.make_config(synth.ModelShape(1, d, 1, 128, 32, V, dtype=synth.BF16), k, slots, 64, 64), {"tune.coded": 2})
+    g.load_weights(head_only(d, V, head, k, tok, la))
+    assert g.coded_use(0, 8 * slots) == read
+    stored = rounded(head)
+    for first in range(0, len(cols), slots):
+        tokens = [min(first + s, len(cols) - 1) for s in range(slots)]
+        for s in range(slots):
+            g.prefill(s, np.array([tokens[s]], np.int32))
+        g.draft(list(range(slots)), 0.0, 1)
+        for s in range(slots):
+            got, want = g.get_logits(s, 0), stored[:, np.append(cols[tokens[s]], ahead)].T
+            assert np.array_equal(got, want * (got[:, :1] * 32)), (first, s)
     g.close()
+
+
+def test_infinities_and_nan_are_read_back():
+    """They stand outside every table: the logits of their rows are not numbers, all others the same bits."""
+    from paper_2311_13581_amd import binding
+    d, V = 2048, 2000
+    head = np.random.default_rng(5).standard_normal((V, d)).astype(np.float32) * np.float32(0.02)
+    head[70, 5], head[90, 1000], head[1999, 2047], head[1999, 3] = np.inf, np.nan, -np.inf, np.inf
+    tok = np.random.default_rng(6).standard_normal((V, d)).astype(np.float32)
+    g = binding.Pass(binding.make_config(synth.ModelShape(1, d, 1, 128, 32, V, dtype=synth.BF16), 1, 1, 64, 64))
+    g.load_weights(head_only(d, V, head, 1, tok))
+    assert g.coded_use(0, 2)
+    g.prefill(0, np.array([3], np.int32))
+    g.draft([0], 0.0, 1)
+    got = g.get_logits(0, 0)[0]
+    g.close()
+    want = rounded(tok)[3].astype(np.float64) @ rounded(np.where(np.isfinite(head), head, 0)).T.astype(np.float64)
+    want /= np.sqrt((rounded(tok)[3].astype(np.float64) ** 2).mean() + 1e-5)
+    bad = np.zeros(V, bool)
+    bad[[70, 90, 1999]] = True
+    assert not np.isfinite(got[bad]).any() and np.linalg.norm(got[~bad] - want[~bad]) <= 1e-4 * np.linalg.norm(want[~bad])
 
 
 # blocks a workgroup of QKV (d 2048: 10 and 16 heads, 3072, 5120), of gate/up (F 3200, 5504, 9600, 14400), Wo and down whole on up to 256
@@ -85,11 +118,12 @@ def test_coded_and_plain_products_agree(d, heads, F, V, k, spread):
     shape = synth.ModelShape(1, d, heads, 128, F, V, dtype=synth.BF16)
     g = binding.Pass(binding.make_config(shape, k, 1, 128, 64), {"graph": 1})
     g.load_weights(random_weights(shape, k, d + F, spread))
-    assert g.coded is not None
     prompt = np.random.default_rng(1).integers(0, V, 40).astype(np.int32)
     out = []
-    for coded in (0, 1, 1):
+    for coded in (0, 2, 2):
         g.set_option("tune.coded", coded)
+        for matrix in range(5):
+            assert g.coded_use(matrix, 1 + k) == (coded and (matrix != 2 or heads >= 16))  # (K 1280: no copy of Wo)
         g.prefill(0, prompt)
         g.draft([0], 0.0, 1)
         d0 = g.get_logits(0, 0).copy()
@@ -111,8 +145,9 @@ def test_coded_and_plain_products_agree_in_batches(d, heads, F, V):
     for rows in (1, 2, 4, 5):
         g.set_option("lookahead_rows", rows)
         out = []
-        for coded in (0, 1):
+        for coded in (0, 2):
             g.set_option("tune.coded", coded)
+            assert rows > 1 or [g.coded_use(matrix, 16) for matrix in range(5)] == 5 * [bool(coded)]
             for s in slots:
                 g.prefill(s, np.arange(20 + s, dtype=np.int32))
             g.draft(slots, 0.0, 1)
@@ -133,8 +168,9 @@ def test_few_rows_agree_with_a_batch(d, heads, F, coded, slices):
     shape, slots = synth.ModelShape(1, d, heads, 128, F, 1008, dtype=synth.BF16), list(range(8))
     g = binding.Pass(binding.make_config(shape, 7, 8, 128, 64))
     g.load_weights(random_weights(shape, 7, d + F, 0.002))
-    g.set_option("tune.coded", coded)
+    g.set_option("tune.coded", 2 * coded)
     g.set_option("tune.gemm_cfg", 2000000 + slices)
+    assert g.coded_use(3, 5) == coded
     for ahead in range(8):
         g.set_option("lookahead_rows", ahead)
         out = []
@@ -190,9 +226,12 @@ def test_training_on_coded_matrices(d, heads, F, slots):
     g = binding.Pass(binding.make_config(shape, k, slots, 128, 64))
     g.load_weights(W)
     out = []
-    for coded in (0, 1):
+    for coded in (0, 2):
         g.set_option("tune.coded", coded)
         g.train_begin(-1)
+        for matrix in (0, 1, 3, 4):  # forward, and the transposes of 2^24 weights or more
+            assert g.coded_use(matrix, 4 * slots) == bool(coded)
+            assert g.coded_use(5 + matrix, 4 * slots) == bool(coded and (d == 4096 or matrix == 3))
         for s in range(slots):
             g.prefill(s, np.arange(30 + s, dtype=np.int32))
         loss = g.train_step(list(range(slots)), target, 0.01)
@@ -202,14 +241,6 @@ def test_training_on_coded_matrices(d, heads, F, slots):
     g.close()
     (l0, g0), (l1, g1) = out
     assert abs(l0 - l1) <= 1e-5 * abs(l0) and np.linalg.norm(g0 - g1) <= 2e-4 * np.linalg.norm(g0)
-
-
-def head_only(d, V, head, k=1, tok=None, la=None):
-    """A model of one layer that adds nothing: its logits are the LM head times the normalised embedding."""
-    z, one = lambda *s: bits(np.zeros(s, np.float32)).reshape(s), bits(np.ones(d, np.float32))
-    return {"tok_emb": z(V, d) if tok is None else bits(tok).reshape(V, d), "lm_head": bits(head).reshape(V, d), "final_norm": one,
-            "lookahead": z(k, d) if la is None else bits(la).reshape(k, d), "attn_norm": [one], "ffn_norm": [one], "wq": [z(128, d)],
-            "wk": [z(128, d)], "wv": [z(128, d)], "wo": [z(d, 128)], "w_gate": [z(32, d)], "w_up": [z(32, d)], "w_down": [z(d, 32)]}
 
 
 # weights outside the table (2^-24 of the others), and whether calls of 5 and of 16 rows read the copy: none but those of a normal distribution; a tile
