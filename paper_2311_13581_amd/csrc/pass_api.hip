@@ -275,12 +275,19 @@ size_t carve_coded(const pass_config &c, const std::vector<char> &without, bool 
   const size_t d = c.d_model, D = (size_t)c.n_heads * c.head_dim, F = c.d_ffn, V = c.vocab;
   std::vector<Coded> coded;
   size_t strips = 0;
-  auto add = [&](size_t N, size_t K) {
+  auto add = [&](size_t N, size_t K, bool head = false) {
     Coded z{};
     if (transposed) std::swap(N, K);
-    // small products are bound by their start (d 1024: QKV 4.4 us on plain tiles and 4.6 on coded ones, gate/up of 448 strips 5.0
-    // and 5.2; but LM heads of 500 and 1000 strips 5.1 and 4.9, 7.6 and 6.8; d 2048, 63 strips 4.7 and 4.6)
-    if ((transposed ? N * K >= 1 << 24 : K >= 2048 || N * K >= (size_t)8000 * 1024) && (without.empty() || !without[coded.size()])) {
+    // Small products are bound by their start.  us that the copy adds to a product of 1, 5 and 8 rows:
+    //   K from 2048, N x K up to 3 * 2^20: Wo and down 512 x 2048 +0.31 +0.01 -0.17, 1024 x 2048 +0.18 +0.09 -0.05, 1024 x 2816 +0.21 -0.07
+    //     -0.10, 1536 x 2048 +0.14 0 -0.10, QKV 1536 x 2048 +0.40 -0.02 -0.08 (a call of 30 layers of d 1024, d_ffn 2048 653 us instead of 642)
+    //   larger ones: 1280 x 2560 -0.04 -0.30 -0.21, 1280 x 3200 -0.05 -0.13 -0.37, 2048 x 2048 0 -0.05 -0.17; and from K 3072 on narrow ones,
+    //     whose plain form is cut into slices: 512 x 3072 -1.5 -1.9 -1.4, 1024 x 3584 -2.7 -2.8 -3.0
+    //   K below 2048: QKV and gate/up 10240 x 1024 +0.04 +0.08 +0.07, 6400 x 1280 +0.20 +0.21 +0.16, 5376 x 1792 +0.24 +0.20 +0.13, 6144 x 1792 +0.21
+    //     +0.06 +0.24, 7168 x 1536 -0.03 -0.07 +0.02; 7680 x 1536 -0.13 -0.12 -0.22, 8192 x 1536 -0.28 -0.33 -0.20, 7168 x 1792 -0.28 -0.14 +0.01
+    //   the LM head: 8000 x 1024 +0.25 +0.10 +0.03, 9008 x 1024 -0.23 -0.54 -0.75, 1008 x 2048 -0.04 +0.06 -0.01
+    const bool large = head ? K >= 2048 || N * K >= 9000 << 10 : K >= 3072 || N * K >= 11 << 20 || (K >= 2048 && N * K > 3 << 20);
+    if ((transposed ? N * K >= 1 << 24 : large) && (without.empty() || !without[coded.size()])) {
       z.wanted = true;
       strips += N / 16;
       z.tiles = A.take<char>(coded_tile_bytes(N, K));
@@ -290,7 +297,7 @@ size_t carve_coded(const pass_config &c, const std::vector<char> &without, bool 
     }
     coded.push_back(z);
   };
-  add(V, d);
+  add(V, d, true);
   for (int l = 0; l < c.n_layers; ++l) { add(3 * D, d); add(d, D); add(2 * F, d); add(d, F); }
   uint32_t *n = A.take<uint32_t>(coded.size() * 130 + strips * 4);
   if (out) { *out = coded; *counts = n; }

@@ -275,6 +275,21 @@ def test_copies_that_would_cost_time_are_not_read(where, few, ring):
     g.close()
 
 
+# small products are not coded: of QKV, Wo, gate/up and down those of up to 3 * 2^20 weights (K from 2048) or 11 * 2^20 (shorter K), but narrow ones
+# of a long K are; LM heads of a short K from 9000 * 1024 on
+@pytest.mark.parametrize("d,heads,F,V,reads", [(1024, 16, 2560, 8016, [0, 0, 0, 0, 0]), (1024, 8, 3072, 9008, [1, 0, 0, 0, 1]), (1536, 16, 4096, 1008, [0, 0, 0, 1, 1]),
+                                               (1792, 14, 2048, 1008, [0, 0, 0, 0, 1]), (2048, 4, 2048, 1008, [1, 0, 0, 1, 1])])
+def test_small_products_read_the_plain_matrix(d, heads, F, V, reads):
+    from paper_2311_13581_amd import binding
+    shape = synth.ModelShape(1, d, heads, 128, F, V, dtype=synth.BF16)
+    g = binding.Pass(binding.make_config(shape, 1, 1, 64, 64))
+    g.load_weights(random_weights(shape, 1, F))
+    for rows in (1, 8):
+        assert [g.coded_use(matrix, rows) for matrix in range(5)] == reads
+    assert (g.lib.pass_coded_bytes(g.h) > 0) == (g.coded is not None) == any(reads)
+    g.close()
+
+
 def test_workspace_of_the_copies():
     """What pass_coded_begin refuses, and that loading weights again ends the use of the old copies (captured graphs too)."""
     import torch
