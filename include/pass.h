@@ -114,14 +114,14 @@ int pass_create(const pass_config *cfg, void *hip_stream, void *device_arena, si
 int pass_load_weights(pass_ctx *ctx, const pass_weights *w, int on_device);
 
 /* Optional, after pass_load_weights: copies of the model's large matrices in 12 bits a weight, without loss, for calls of up to
- * 48 rows, which are bound by the bytes of their weights and take 5 to 25 % less time on them.  The plain matrices stay where
+ * 48 rows, which are bound by the bytes of their weights: a product takes 3 to 25 % less time on them.  The plain matrices stay where
  * they are: prompts, larger calls and products that gain nothing are multiplied with those.  What a call multiplies is bit for bit the same
  * weight; its sums may be taken in another order.
  *   pass_coded_bytes   device bytes pass_coded_begin needs, about three quarters of the matrices (0: no context, no weights, the
  *                      generic path, or a model so small that nothing is gained); after pass_coded_begin without the matrices that
  *                      it found to gain nothing, so that a caller may begin again in less
- *   pass_coded_begin   device_workspace: caller's device memory, 256-byte aligned, kept alive until pass_destroy or the
- *                      next pass_load_weights, which ends the use of the copies.  Weights outside the sixteen octaves that
+ *   pass_coded_begin   device_workspace: caller's device memory, 256-byte aligned, kept alive until pass_coded_end,
+ *                      pass_destroy or the next pass_load_weights, which ends the use of the copies.  Weights outside the sixteen octaves that
  *                      the code takes stand beside it and cost time: a matrix of which more than one in 1300 lies outside, or that has
  *                      many in one place (a row of zeros among others, say), is multiplied in its plain form.
  *   pass_coded_end     ends the use of the copies: the workspace is the caller's again, calls read the plain matrices

@@ -20,9 +20,10 @@
 // MFMA and one activation load per weight tile, and nothing but the weights and the K/V cache is
 // ever rounded to 8 bits of mantissa (the paper's bfloat16 is read as the storage format of the
 // model, Training details).  Activation buffers are laid out for that, in tiles like the weights:
-// [group of 8 rows][K/32][64 lanes][8], lane (k/8 % 4) * 16 + c holds 8 consecutive features of
-// pseudo-row c (c < 8: hi of row c, c >= 8: lo of row c - 8), so a wavefront fetches its B operand
-// of a k-tile as 1 KB of whole cache lines.
+// [group of 8 rows][K/32][4][hi, lo][xr][8]: eight consecutive features (k/8 % 4 of the k-tile) of
+// the hi halves of xr rows, then of their lo halves.  xr is 8, where a wavefront fetches its B operand
+// of a k-tile as 1 KB of whole cache lines in lane order, and the call's rows if these are fewer
+// (Params::xr, xs_index).
 //
 // Fused epilogues:
 //   QKV     : RMSNorm scale, rotary embedding, q (fp32) to the workspace, K/V rows (bf16) into
@@ -341,7 +342,7 @@ template <int I> struct nb_c { static constexpr int value = I; };
 
 struct GemmArgs {
   const u32x4 *W;             // packed weight tiles
-  const uint16_t *X;          // activation rows as (hi, lo) tiles [ceil(M/8)][K/32][64 lanes][8]
+  const uint16_t *X;          // activation rows as (hi, lo) tiles [ceil(M/8)][K/32][4][hi, lo][p.xr][8]
   int M, K;
   int layer;
   const uint16_t *gain_next;  // RESID: gain of the norm that follows
@@ -587,8 +588,9 @@ __device__ __forceinline__ int x_lane(int lane, int xr) { return ((lane >> 4) * 
 // takes k-tiles w, w + WAVES, ..., U of them a trip, and requests a trip while it computes the one before.  The last trip may
 // hold k-tiles past the end: those are requested too (clamped), so that nothing is waited for one by one, and not computed.
 // Bound by how evenly the weights are spread over the compute units: a unit takes in about 30 GB/s of weights and the
-// activation tile that goes with NB strips costs a third of a weight tile whatever rows it holds (1 or 8 rows: the same
-// time), the chip 6.9 TB/s.  Which NB, WAVES and U that asks for: few_rows_shape.
+// activation tile of 8 rows that goes with NB strips costs a third of a weight tile (one with room for fewer rows
+// less, by its lines: down on coded weights, d 4096, one strip a workgroup, 16.6 -> 15.3 us at 5 rows and 16.4 -> 14.6 at 1; with several
+// strips a workgroup 1 to 2 %), the chip 6.9 TB/s.  Which NB, WAVES and U that asks for: few_rows_shape.
 // The sums of a strip have WAVES x NA accumulators, at least 4 for QKV and gate/up and 16 for the other products (fewer
 // would round more often).
 template <int EPI, int WAVES>
@@ -1109,7 +1111,7 @@ static void launch_rows_mt(const Params &p, const GemmArgs &a, dim3 grid, int nb
 // a second round costs a quarter more unless two workgroups fit a unit's LDS (gate/up an eighth).  Against a plain product added step by step, which
 // owns eight strips a workgroup, coded strips in two rounds lose that gain with K (k-tiles: of a workgroup).  `want` > 0 asks for a number.
 // Measured without and with the copies, us: 40 rows, d 4096, QKV 26.0 and 23.8, gate/up (688 blocks) 36.1 and 33.7, Wo 15.4 and 14.7, down
-// 25.1 and 23.6 (with the kernel that adds the slices), LM head (V 32000) 50.8 and 49.1; 16 rows 19.2 and 17.1, 30.7 and 25.6, 12.6 and
+// 25.1 and 23.6 (with the kernel that adds the slices); 16 rows 19.2 and 17.1, 30.7 and 25.6, 12.6 and
 // 10.5, 19.3 and 18.2, 46.4 and 35.7; d 5120, 24 rows, 860 blocks 47.8 and 42.5; 48 rows, d 4096, QKV 28.3 and 26.3.  LM head, V 32000, eight strips
 // plain and four coded: 32 rows, d 1024 20.0 and 19.9, 2048 31.9 and 27.7, 3072 37.2 and 37.3, 4096 49.4 and 47.7, 5120 59.3 and 60.7, 6144 69.8 and
 // 71.4, 8192 88.7 and 92.5; 40 rows 22.2 and 21.9, 33.2 and 30.7, 40.2 and 42.0, 53.0 and 54.2, 62.5 and 67.8, 74.4 and 78.1, 94.2 and 101.5.
